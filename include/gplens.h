@@ -193,6 +193,17 @@ int gpl_gauss_product(const gpl_gauss* g, int nt, const float* tx, const float* 
                       int ns, const float* sx, const float* sy, const float* sz, const float* sw, int nrhs,
                       const float* V, int ldv, float* Y, int ldy, float beta, hipStream_t stream);
 
+/* The same product with a workspace, which large products use to sort both sides
+ * along a Hilbert curve and leave out the pairs whose Gaussian is exactly zero
+ * in FP32 (the result equals the all-pairs product up to FP32 summation order).
+ * gpl_gauss_product_workspace is 0 where the all-pairs product is used; with
+ * ws = NULL this is gpl_gauss_product. */
+size_t gpl_gauss_product_workspace(int nt, int ns, int nrhs);
+int gpl_gauss_product_ws(const gpl_gauss* g, int nt, const float* tx, const float* ty, const float* tz,
+                         const float* tw, int ns, const float* sx, const float* sy, const float* sz, const float* sw,
+                         int nrhs, const float* V, int ldv, float* Y, int ldy, float beta, void* ws, size_t ws_bytes,
+                         hipStream_t stream);
+
 /* Adjoint of one column of gpl_gauss_product for sources without shape
  * covariances: with F = sum_i U_i Y_i, Y = the product of V (one column, ns),
  * accumulates (+=, FP32, device) the gradients gtx/gty (nt, nullable pair) of

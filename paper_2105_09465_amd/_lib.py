@@ -115,6 +115,9 @@ SIGNATURES = {
     "gpl_posterior_variance": (_I, [_I, _I, _P, _I, _P, _I, _D, _P, _P]),
     "gpl_gauss_product": (_I, [C.POINTER(gpl_gauss), _I, _P, _P, _P, _P, _I, _P, _P, _P, _P, _I, _P, _I, _P, _I,
                                C.c_float, _P]),
+    "gpl_gauss_product_workspace": (_Z, [_I, _I, _I]),
+    "gpl_gauss_product_ws": (_I, [C.POINTER(gpl_gauss), _I, _P, _P, _P, _P, _I, _P, _P, _P, _P, _I, _P, _I, _P, _I,
+                                  C.c_float, _P, _Z, _P]),
     "gpl_gauss_matrix": (_I, [C.POINTER(gpl_gauss), _I, _P, _P, _P, _P, _I, _P, _P, _P, _P, _P, _I, _P]),
     "gpl_pixel_shapes": (_I, [C.POINTER(gpl_grid), _P, _P, _P, _P]),
     "gpl_gauss_product_backward": (_I, [C.POINTER(gpl_gauss), _I, _P, _P, _P, _P, _I, _P, _P, _P, _P, _P, _P, _P, _P,

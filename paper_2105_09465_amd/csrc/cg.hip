@@ -473,6 +473,11 @@ static int apply_A_into(const gpl_problem* prob, const Taps& taps, const MvmCtx&
 
 using namespace gpl;
 
+// The product's part of the workspace, by the kind of kernel.
+static size_t apply_A_product_bytes(const gpl_problem* prob, int N, int nrhs, int prec) {
+  return prob->kernel.kind == 1 ? windowed_workspace(N, nrhs) : mvm_workspace(N, nrhs, prec);
+}
+
 extern "C" size_t gpl_apply_A_workspace(const gpl_problem* prob, int nrhs, int prec) {
   if (prob == nullptr || nrhs <= 0) return 0;
   const int N = prob->grid.n * prob->grid.ss * prob->grid.n * prob->grid.ss;
@@ -480,7 +485,7 @@ extern "C" size_t gpl_apply_A_workspace(const gpl_problem* prob, int nrhs, int p
   const int ldf = round_up(N, 64);
   s.take<float>((size_t)ldf * nrhs);
   s.take<float>((size_t)ldf * nrhs);
-  s.take<char>(mvm_workspace(N, nrhs, prec));
+  s.take<char>(apply_A_product_bytes(prob, N, nrhs, prec));
   return s.used;
 }
 
@@ -498,7 +503,7 @@ extern "C" int gpl_apply_A(const gpl_problem* prob, int nrhs, const float* X, in
   const int ldf = round_up(N, 64);
   float* T1 = c.take<float>((size_t)ldf * nrhs);
   float* T2 = c.take<float>((size_t)ldf * nrhs);
-  const size_t mb = mvm_workspace(N, nrhs, prec);
+  const size_t mb = apply_A_product_bytes(prob, N, nrhs, prec);
   char* mws = c.take<char>(mb);
   if (!c.ok()) return check_ws(nullptr, 0, 1);
   if (prob->kernel.kind == 1) {  // windowed kernel: B^T, the Gaussian product with pixel shapes, B

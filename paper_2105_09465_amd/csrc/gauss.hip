@@ -15,6 +15,7 @@
 #include <cmath>
 
 #include "common.hpp"
+#include "gauss_tiles.hpp"
 #include "internal.hpp"
 
 namespace gpl {
@@ -468,10 +469,14 @@ int pixel_shapes_launch(int M, const float* px, const float* py, float* z, hipSt
 
 using namespace gpl;
 
-extern "C" int gpl_gauss_product(const gpl_gauss* g, int nt, const float* tx, const float* ty, const float* tz,
-                                 const float* tw, int ns, const float* sx, const float* sy, const float* sz,
-                                 const float* sw, int nrhs, const float* V, int ldv, float* Y, int ldy, float beta,
-                                 hipStream_t stream) {
+extern "C" size_t gpl_gauss_product_workspace(int nt, int ns, int nrhs) {
+  return gauss_pair_workspace(nt, ns, false, nrhs);
+}
+
+extern "C" int gpl_gauss_product_ws(const gpl_gauss* g, int nt, const float* tx, const float* ty, const float* tz,
+                                    const float* tw, int ns, const float* sx, const float* sy, const float* sz,
+                                    const float* sw, int nrhs, const float* V, int ldv, float* Y, int ldy, float beta,
+                                    void* ws, size_t ws_bytes, hipStream_t stream) {
   GPL_REQUIRE(g != nullptr, "gauss parameters are NULL");
   GPL_REQUIRE(g->base_var > 0 && std::isfinite(g->base_var) && std::isfinite(g->norm), "base_var must be > 0");
   GPL_REQUIRE(nt >= 0 && ns >= 0 && nrhs >= 0, "negative size");
@@ -481,7 +486,16 @@ extern "C" int gpl_gauss_product(const gpl_gauss* g, int nt, const float* tx, co
   GPL_REQUIRE(ldv >= ns && ldy >= nt, "ldv=%d (>= %d) / ldy=%d (>= %d)", ldv, ns, ldy, nt);
   GPL_REQUIRE(V != Y, "V and Y must not overlap");
   const GSide T{tx, ty, tz, tw, nt}, S{sx, sy, sz, sw, ns};
+  if (ws != nullptr && gauss_pair_sorted(nt, ns))
+    return gauss_pair_product(T, S, g->base_var, g->norm, nrhs, V, ldv, Y, ldy, beta, ws, ws_bytes, stream);
   return gauss_product_launch(T, S, g->base_var, g->norm, nrhs, V, ldv, Y, ldy, beta, stream);
+}
+
+extern "C" int gpl_gauss_product(const gpl_gauss* g, int nt, const float* tx, const float* ty, const float* tz,
+                                 const float* tw, int ns, const float* sx, const float* sy, const float* sz,
+                                 const float* sw, int nrhs, const float* V, int ldv, float* Y, int ldy, float beta,
+                                 hipStream_t stream) {
+  return gpl_gauss_product_ws(g, nt, tx, ty, tz, tw, ns, sx, sy, sz, sw, nrhs, V, ldv, Y, ldy, beta, nullptr, 0, stream);
 }
 
 extern "C" int gpl_gauss_matrix(const gpl_gauss* g, int nt, const float* tx, const float* ty, const float* tz,

@@ -1,0 +1,724 @@
+// Gaussian products over sorted points with the pairs that are exactly zero left
+// out. The sums are those of the dense products of gauss.hip,
+//   sum_j ws_j |C_ij|^{-1/2} exp(-d^T C_ij^{-1} d / 2) V_j  (and their moments in C^{-1} d),
+// C_ij = Zt_i + Zs_j + base I, for the transmission matrix of Sec. 3.4 (eq.
+// "transmission"), the windowed kernel of Sec. 3.2 (eq. "covariance") and the
+// variational step built on them.
+//
+// Both sides are taken along a Hilbert curve of their positions (plan_sort). A
+// pair of boxes with gap g has d^T C^{-1} d >= g^2 / lambda for every pair in
+// it, lambda the largest eigenvalue of C there (base plus the largest
+// eigenvalues of the shapes of both boxes). v_exp_f32 returns zero below an
+// argument of -126.5, so a 16-target x 32-source pair of boxes with
+// (log2(e)/2) g^2 / lambda >= 127 holds exact zeros only and is not evaluated:
+// the sum over the rest is the sum over all pairs up to its order. A chunk with
+// a non-finite position, shape, weight or column value, or a shape whose
+// covariance is not positive definite, is never left out.
+//
+// Work: a workgroup of four waves takes 64 targets and every kslices-th chunk of
+// 32 sources (strided, since the live chunks of a tile lie together along the
+// curve), lists its live chunks with the mask of the four 16-target subtiles that
+// see each, and deals them to the waves in turn. A lane holds one target of each
+// subtile and 8 of the chunk's sources. Partial sums go to part[slice][sum][target]
+// and are added in slice order by a second kernel: a fixed order, so results do
+// not vary between runs. Slices keep the tiles whose shapes reach far (next to
+// the lens centre one sees every chunk) from being the launch's tail.
+//
+// Bound by FP32 issue (8 to 19 VALU instructions and one exp a pair). At 40,000
+// traced points, shapes on one side: l = 0.01 evaluates 4% of the pairs, 45 us, and
+// l = 0.04 10%, 88 us, with three sums; the all-pairs kernels take 636 us for one
+// sum and 678 us for three.
+#include <algorithm>
+#include <cmath>
+
+#include "common.hpp"
+#include "gauss_tiles.hpp"
+#include "internal.hpp"
+#include "tileplan.hpp"
+
+namespace gpl {
+
+constexpr int kTWaves = 4;                     // waves per workgroup
+constexpr int kTBatch = 4;                     // box tests of a lane in flight
+constexpr int kTList = kTWaves * kTBatch * 64; // chunks tested per round
+constexpr float kZeroArg = 127.f;              // exp2(-kZeroArg) is exactly zero, with margin for rounding
+
+// Pairs from which a product of points in the caller's order is sorted first: the
+// all-pairs kernel takes some 0.4 us a million pairs, the sorts of both sides and
+// the three launches after them 100 us and more.
+constexpr long long kSortedPairs = 1LL << 25;
+constexpr int kEntryShift = 28;                // list entries: chunk below, subtile mask above
+constexpr uint32_t kEntryChunk = (1u << kEntryShift) - 1u;
+
+static_assert(kRowTile == 64 && kSubTile == 16 && kChunk == 32, "the lane layout below");
+
+__device__ __forceinline__ float finite_or_inf(float v) { return v < INFINITY ? v : INFINITY; }  // NaN -> inf
+
+// Upper bound of the largest eigenvalue of the shape (zxx, zxy, zyy); infinite
+// when the shape with the covariance base_min added is not positive definite.
+__device__ __forceinline__ float shape_reach(float zxx, float zxy, float zyy, float base_min) {
+  const float cxx = zxx + base_min, cyy = zyy + base_min;
+  if (!(cxx > 0.f && cyy > 0.f && cxx * cyy > zxy * zxy)) return INFINITY;
+  const float h = 0.5f * (zxx - zyy);
+  return finite_or_inf(fmaxf(0.f, (0.5f * (zxx + zyy) + sqrtf(h * h + zxy * zxy)) * 1.00001f));
+}
+
+// Source side in sorted order: columns ws_j V_j (times |C_j|^{-1/2} when the
+// shapes are the sources' alone), the forms or shapes, and per chunk the reach
+// of its shapes. Thread j handles sorted source j < npad; the padding has zero
+// columns.
+template <int MODE>
+__global__ __launch_bounds__(256) void gauss_prep_kernel(GSorted S, const float* __restrict__ z,
+                                                         const float* __restrict__ w, const float* __restrict__ V,
+                                                         int ldv, int nc, float base, float* __restrict__ wv,
+                                                         float* __restrict__ form, float* __restrict__ reach) {
+  const int j = blockIdx.x * 256 + threadIdx.x;
+  const int npad = S.nch * kChunk;
+  if (j >= npad) return;  // whole waves: npad is a multiple of 64
+  const bool live = j < S.n;
+  const int jj = live ? S.perm[j] : 0;
+  float scale = live ? (w ? w[jj] : 1.f) : 0.f, lam = 0.f;
+  if (MODE == kShapesSource || MODE == kShapesBoth) {
+    const float zxx = live && z ? z[jj] : 0.f, zxy = live && z ? z[S.n + jj] : 0.f,
+                zyy = live && z ? z[2 * (size_t)S.n + jj] : 0.f;
+    if (MODE == kShapesSource) {
+      const Form f = gauss_form(zxx + base, zxy, zyy + base);
+      form[j] = f.xx;
+      form[npad + j] = f.xy;
+      form[2 * npad + j] = f.yy;
+      scale *= f.rdet;
+      lam = shape_reach(zxx, zxy, zyy, base);
+    } else {
+      form[j] = zxx;
+      form[npad + j] = zxy;
+      form[2 * npad + j] = zyy;
+      lam = shape_reach(zxx, zxy, zyy, 0.5f * base);
+    }
+  }
+  for (int c = 0; c < nc; ++c) {
+    const float v = live ? scale * V[(size_t)c * ldv + jj] : 0.f;
+    wv[(size_t)c * npad + j] = v;
+    if (!isfinite(v)) lam = INFINITY;
+  }
+  for (int off = 16; off > 0; off >>= 1) lam = fmaxf(lam, __shfl_xor(lam, off, 32));
+  if ((j & (kChunk - 1)) == 0) reach[j / kChunk] = lam;
+}
+
+// Sums held per target: NC columns, or (MOM) the sum and its first moments in
+// the scaled C^{-1} d.
+template <bool MOM, int NC>
+constexpr int kSums = MOM ? 3 : NC;
+
+template <int MODE, bool MOM, int NC>
+__global__ __launch_bounds__(64 * kTWaves) void gauss_tiles_kernel(GSorted T, const float* __restrict__ tz, GSorted S,
+                                                                   const float* __restrict__ wv,
+                                                                   const float* __restrict__ form,
+                                                                   const float* __restrict__ reach, float base,
+                                                                   float* __restrict__ part) {
+  constexpr int K = kSums<MOM, NC>;
+  __shared__ uint32_t list[kTList];
+  __shared__ int cnt_s[kTWaves * kTBatch];
+  __shared__ float red[kTWaves][K][kRowTile];
+  const int tid = threadIdx.x, lane = tid & 63, wvi = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ri = lane & 15, g = lane >> 4;
+  const int tile = blockIdx.x, slice = blockIdx.y, nslices = gridDim.y;
+  const int npt = T.nch * kChunk, nps = S.nch * kChunk;
+  // this lane's target of each subtile, and the subtiles' boxes and reaches
+  float xi[kSubsPerTile], yi[kSubsPerTile];
+  Form F[kSubsPerTile];  // the target's form (shapes of the targets alone) or its shape (both sides)
+  float4 sb[kSubsPerTile];
+  float lam[kSubsPerTile];
+#pragma unroll
+  for (int t = 0; t < kSubsPerTile; ++t) {
+    const int i = tile * kRowTile + t * kSubTile + ri;
+    xi[t] = T.x[i];
+    yi[t] = T.y[i];
+    sb[t] = T.sbox[tile * kSubsPerTile + t];
+    lam[t] = base;
+    F[t] = Form{0.f, 0.f, 0.f, 1.f};
+    if (MODE == kShapesTarget || MODE == kShapesBoth) {
+      const int ii = T.perm[min(i, T.n - 1)];
+      const float zxx = tz[ii], zxy = tz[T.n + ii], zyy = tz[2 * (size_t)T.n + ii];
+      float l = shape_reach(zxx, zxy, zyy, MODE == kShapesTarget ? base : 0.5f * base);
+      for (int off = 8; off > 0; off >>= 1) l = fmaxf(l, __shfl_xor(l, off, 16));
+      lam[t] += l;
+      F[t] = MODE == kShapesTarget ? gauss_form(zxx + base, zxy, zyy + base) : Form{zxx + base, zxy, zyy + base, 1.f};
+    }
+  }
+  const float iso = kFormScale / base;
+  float acc[kSubsPerTile][K];
+#pragma unroll
+  for (int t = 0; t < kSubsPerTile; ++t)
+#pragma unroll
+    for (int k = 0; k < K; ++k) acc[t][k] = 0.f;
+
+  const int mine = cdiv(S.nch - slice, nslices);  // chunks slice, slice + nslices, ...
+  for (int k0 = 0; k0 < mine; k0 += kTList) {
+    // the live chunks of this round, in order
+    uint32_t e[kTBatch];
+    float4 q[kTBatch];
+    float ls[kTBatch];
+#pragma unroll
+    for (int u = 0; u < kTBatch; ++u) {
+      const int k = k0 + (wvi * kTBatch + u) * 64 + lane;
+      const int c = min(slice + k * nslices, S.nch - 1);
+      e[u] = (uint32_t)c;
+      q[u] = S.cbox[c];
+      ls[u] = reach[c];
+    }
+    unsigned long long bal[kTBatch];
+#pragma unroll
+    for (int u = 0; u < kTBatch; ++u) {
+      const int k = k0 + (wvi * kTBatch + u) * 64 + lane;
+      uint32_t mask = 0u;
+#pragma unroll
+      for (int t = 0; t < kSubsPerTile; ++t) {
+        const float gx = fmaxf(0.f, fmaxf(q[u].x - sb[t].y, sb[t].x - q[u].y));
+        const float gy = fmaxf(0.f, fmaxf(q[u].z - sb[t].w, sb[t].z - q[u].w));
+        const bool zero = -kFormScale * fmaf(gx, gx, gy * gy) >= kZeroArg * (lam[t] + ls[u]);
+        mask |= (zero ? 0u : 1u) << t;
+      }
+      if (k >= mine) mask = 0u;
+      e[u] |= mask << kEntryShift;
+      bal[u] = __ballot(mask != 0u);
+      if (lane == 0) cnt_s[wvi * kTBatch + u] = __popcll(bal[u]);
+    }
+    __syncthreads();
+    int total = 0, before[kTBatch];
+#pragma unroll
+    for (int b = 0; b < kTWaves * kTBatch; ++b) {
+      const int u = b - wvi * kTBatch;
+#pragma unroll
+      for (int uu = 0; uu < kTBatch; ++uu)
+        if (u == uu) before[uu] = total;
+      total += cnt_s[b];
+    }
+#pragma unroll
+    for (int u = 0; u < kTBatch; ++u)
+      if (e[u] >> kEntryShift) list[before[u] + __popcll(bal[u] & ((1ull << lane) - 1ull))] = e[u];
+    __syncthreads();
+    for (int p = wvi; p < total; p += kTWaves) {
+      const uint32_t ent = (uint32_t)__builtin_amdgcn_readfirstlane((int)list[p]);
+      const int j0 = (int)(ent & kEntryChunk) * kChunk + g * 8;
+      float xj[8], yj[8], wj[NC][8], fxx[8], fxy[8], fyy[8];
+      auto load8 = [](float(&d)[8], const float* s) {
+        const float4 a = *reinterpret_cast<const float4*>(s), b = *reinterpret_cast<const float4*>(s + 4);
+        d[0] = a.x, d[1] = a.y, d[2] = a.z, d[3] = a.w, d[4] = b.x, d[5] = b.y, d[6] = b.z, d[7] = b.w;
+      };
+      load8(xj, S.x + j0);
+      load8(yj, S.y + j0);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) load8(wj[c], wv + (size_t)c * nps + j0);
+      if (MODE == kShapesSource || MODE == kShapesBoth) {
+        load8(fxx, form + j0);
+        load8(fxy, form + nps + j0);
+        load8(fyy, form + 2 * nps + j0);
+      }
+#pragma unroll
+      for (int t = 0; t < kSubsPerTile; ++t) {
+        if (!((ent >> (kEntryShift + t)) & 1u)) continue;
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+          const float dx = xi[t] - xj[v], dy = yi[t] - yj[v];
+          float val, ux = 0.f, uy = 0.f;
+          if (MODE == kShapesNone) {
+            val = exp2_fast(iso * fmaf(dx, dx, dy * dy));
+          } else if (MODE == kShapesBoth) {
+            const float cxx = F[t].xx + fxx[v], cxy = F[t].xy + fxy[v], cyy = F[t].yy + fyy[v];
+            const float det = fmaf(cxx, cyy, -cxy * cxy);
+            const float qd = fmaf(cyy * dx, dx, fmaf(-2.f * cxy * dx, dy, cxx * dy * dy));
+            const float rd = rsqrtf(det);
+            val = rd * exp2_fast(kFormScale * (qd * (rd * rd)));
+          } else {
+            const float a = MODE == kShapesTarget ? F[t].xx : fxx[v], b = MODE == kShapesTarget ? F[t].xy : fxy[v],
+                        d = MODE == kShapesTarget ? F[t].yy : fyy[v];
+            ux = fmaf(a, dx, b * dy);
+            uy = fmaf(b, dx, d * dy);
+            val = exp2_fast(fmaf(dx, ux, dy * uy));
+          }
+          if (MOM) {
+            const float gv = val * wj[0][v];
+            acc[t][0] += gv;
+            acc[t][1 % K] = fmaf(gv, ux, acc[t][1 % K]);
+            acc[t][2 % K] = fmaf(gv, uy, acc[t][2 % K]);
+          } else {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) acc[t][c] = fmaf(val, wj[c][v], acc[t][c]);
+          }
+        }
+      }
+    }
+    __syncthreads();  // the list is rebuilt by the next round
+  }
+  // the four lanes of a target, then the four waves, in a fixed order
+#pragma unroll
+  for (int t = 0; t < kSubsPerTile; ++t)
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      float v = acc[t][k];
+      v += __shfl_xor(v, 16, 64);
+      v += __shfl_xor(v, 32, 64);
+      if (g == 0) red[wvi][k][t * kSubTile + ri] = v;
+    }
+  __syncthreads();
+  for (int o = tid; o < K * kRowTile; o += 64 * kTWaves) {
+    const int k = o / kRowTile, r = o % kRowTile;
+    float v = red[0][k][r];
+#pragma unroll
+    for (int w = 1; w < kTWaves; ++w) v += red[w][k][r];
+    part[((size_t)slice * K + k) * npt + tile * kRowTile + r] = v;
+  }
+}
+
+// Y[c][i] = norm wt_i |C_i|^{-1/2} sum + beta Y[c][i] (the determinant when the
+// shapes are the targets' alone).
+template <int MODE>
+__global__ __launch_bounds__(256) void gauss_finish_kernel(GSorted T, const float* __restrict__ tz,
+                                                           const float* __restrict__ tw, float base, float norm,
+                                                           const float* __restrict__ part, int nslices, int K,
+                                                           float* Y, int ldy, float beta) {
+  const int i = blockIdx.x * 256 + threadIdx.x, c = blockIdx.y;
+  if (i >= T.n) return;
+  const int ii = T.perm[i];
+  float f = norm * (tw ? tw[ii] : 1.f);
+  if (MODE == kShapesTarget)
+    f *= gauss_form(tz[ii] + base, tz[T.n + ii], tz[2 * (size_t)T.n + ii] + base).rdet;
+  if (MODE == kShapesNone) f *= rsqrtf(base * base);
+  const float s = f * fold_slices(part, nslices, K, T.nch * kChunk, c, i);
+  float* y = Y + (size_t)c * ldy + ii;
+  *y = beta != 0.f ? s + beta * *y : s;
+}
+
+// About 4096 workgroups, at most 32 slices (each adds its partial sums to the second kernel).
+static int tile_slices(const GSorted& T, const GSorted& S) {
+  return std::max(1, std::min({32, 4096 / cdiv(T.n, kRowTile), S.nch}));
+}
+
+// Columns a kernel holds for nc columns: the next of 1, 2, 4 and 8.
+static int held_columns(int nc) { return nc > 4 ? 8 : nc > 2 ? 4 : nc; }
+
+template <class C>
+static void carve_tiles(C& cv, const GSorted& T, const GSorted& S, int cols, GTileBufs& b) {
+  const size_t nps = (size_t)S.nch * kChunk, npt = (size_t)T.nch * kChunk;
+  const int held = held_columns(cols);
+  b.wv = cv.template take<float>(held * nps);
+  b.form = cv.template take<float>(3 * nps);
+  b.reach = cv.template take<float>(S.nch);
+  b.part = cv.template take<float>((size_t)tile_slices(T, S) * std::max(held, 3) * npt);
+}
+
+static GSorted sorted_sizes(int n) {
+  GSorted s{};
+  s.n = n;
+  s.nch = cdiv(n, kRowTile) * kChunksPerTile;
+  return s;
+}
+
+GSorted sorted_view(const TilePlan& p) { return GSorted{p.xs, p.ys, p.perm, p.cbox, p.sbox, p.n, p.nch}; }
+
+size_t gauss_tiles_scratch(int nt, int ns, int cols) {
+  Sizer s;
+  GTileBufs b;
+  carve_tiles(s, sorted_sizes(nt), sorted_sizes(ns), cols, b);
+  return s.used;
+}
+
+int gauss_tiles_carve(int nt, int ns, int cols, void* ws, size_t ws_bytes, GTileBufs& b) {
+  GPL_TRY(check_ws(ws, ws_bytes, gauss_tiles_scratch(nt, ns, cols)));
+  Carver cv(ws, ws_bytes);
+  carve_tiles(cv, sorted_sizes(nt), sorted_sizes(ns), cols, b);
+  return cv.ok() ? GPL_OK : check_ws(nullptr, 0, 1);
+}
+
+template <int MODE>
+static int prep_launch(const GSorted& S, const float* z, const float* w, const float* V, int ldv, int nc, float base,
+                       const GTileBufs& b, hipStream_t stream) {
+  hipLaunchKernelGGL(gauss_prep_kernel<MODE>, dim3(cdiv(S.nch * kChunk, 256)), dim3(256), 0, stream, S, z, w, V, ldv,
+                     nc, base, b.wv, b.form, b.reach);
+  GPL_LAUNCH_CHECK();
+  return GPL_OK;
+}
+
+template <int MODE, bool MOM, int NC>
+static int tiles_launch(const GSorted& T, const float* tz, const GSorted& S, float base, const GTileBufs& b,
+                        int nslices, hipStream_t stream) {
+  hipLaunchKernelGGL((gauss_tiles_kernel<MODE, MOM, NC>), dim3(cdiv(T.n, kRowTile), nslices), dim3(64 * kTWaves), 0,
+                     stream, T, tz, S, b.wv, b.form, b.reach, base, b.part);
+  GPL_LAUNCH_CHECK();
+  return GPL_OK;
+}
+
+template <int MODE>
+static int product_cols(const GSorted& T, const float* tz, const float* tw, const GSorted& S, const float* sz,
+                        const float* sw, float base, float norm, int nrhs, const float* V, int ldv, float* Y, int ldy,
+                        float beta, const GTileBufs& b, hipStream_t stream) {
+  const int ns = tile_slices(T, S);
+  for (int c0 = 0; c0 < nrhs;) {
+    const int nc = std::min(8, nrhs - c0);
+    const int held = held_columns(nc);  // those past nc hold anything and are not stored
+    GPL_TRY(prep_launch<MODE>(S, sz, sw, V + (size_t)c0 * ldv, ldv, nc, base, b, stream));
+    switch (held) {
+      case 1: GPL_TRY((tiles_launch<MODE, false, 1>(T, tz, S, base, b, ns, stream))); break;
+      case 2: GPL_TRY((tiles_launch<MODE, false, 2>(T, tz, S, base, b, ns, stream))); break;
+      case 4: GPL_TRY((tiles_launch<MODE, false, 4>(T, tz, S, base, b, ns, stream))); break;
+      default: GPL_TRY((tiles_launch<MODE, false, 8>(T, tz, S, base, b, ns, stream))); break;
+    }
+    hipLaunchKernelGGL(gauss_finish_kernel<MODE>, dim3(cdiv(T.n, 256), nc), dim3(256), 0, stream, T, tz, tw, base,
+                       norm, b.part, ns, held, Y + (size_t)c0 * ldy, ldy, beta);
+    GPL_LAUNCH_CHECK();
+    c0 += nc;
+  }
+  return GPL_OK;
+}
+
+int gauss_tiles_product(const GSorted& T, const float* tz, const float* tw, const GSorted& S, const float* sz,
+                        const float* sw, double base, double norm, int nrhs, const float* V, int ldv, float* Y,
+                        int ldy, float beta, const GTileBufs& b, hipStream_t stream) {
+  const float fb = (float)base, fn = (float)norm;
+  if (tz && sz)
+    return product_cols<kShapesBoth>(T, tz, tw, S, sz, sw, fb, fn, nrhs, V, ldv, Y, ldy, beta, b, stream);
+  if (tz) return product_cols<kShapesTarget>(T, tz, tw, S, sz, sw, fb, fn, nrhs, V, ldv, Y, ldy, beta, b, stream);
+  if (sz) return product_cols<kShapesSource>(T, tz, tw, S, sz, sw, fb, fn, nrhs, V, ldv, Y, ldy, beta, b, stream);
+  return product_cols<kShapesNone>(T, tz, tw, S, sz, sw, fb, fn, nrhs, V, ldv, Y, ldy, beta, b, stream);
+}
+
+int gauss_tiles_sums(const GSorted& T, const GSorted& S, const float* sz, double base, const float* V,
+                     const GTileBufs& b, int* nslices, hipStream_t stream) {
+  const float fb = (float)base;
+  const int ns = *nslices = tile_slices(T, S);
+  if (sz) {
+    GPL_TRY(prep_launch<kShapesSource>(S, sz, nullptr, V, 0, 1, fb, b, stream));
+    return tiles_launch<kShapesSource, true, 1>(T, nullptr, S, fb, b, ns, stream);
+  }
+  GPL_TRY(prep_launch<kShapesNone>(S, sz, nullptr, V, 0, 1, fb, b, stream));
+  return tiles_launch<kShapesNone, false, 1>(T, nullptr, S, fb, b, ns, stream);
+}
+
+// ---- one column, sources in the caller's order
+//
+// The transmission T y of the variational step with the sums its adjoint towards
+// the targets needs. The targets are sorted, the sources stay in the caller's
+// order, and the sum over them has the order of the dense kernel: eight shares of
+// whole 64-point steps, each added up source by source, then the shares in order.
+// Chunks of 16 consecutive sources whose terms are exact zeros are left out, so
+// the flux keeps the dense product's bits. (The log-likelihood is a sum of squares
+// of small differences of these fluxes in FP64: another order of the sum moves it
+// by some 1e-9, within its own error but visible.)
+//
+// A wave takes 16 targets and one share: lane 4 t + q forms the terms of target t
+// and source q of every four, and the sum goes round the four lanes of a target,
+// each adding its own term (DPP moves within the quad).
+// Several images of one source region fall into one share (a band of image rows),
+// so the longest waves see all of their share: with 64 targets a wave these took
+// 430 us at l = 0.04 of a launch whose work is worth 150. For the same reason each
+// wave is a workgroup of its own, and a second kernel adds the shares: waves that
+// wait for the longest share of their targets keep others from being started.
+// Bound by issue, about 27 VALU instructions and one exp for 64 pairs: 71 us at
+// l = 0.01 and 200 us at 0.04 (40,000 points); the all-pairs product took 580 us and
+// its adjoint towards the targets, formed here with it, another 767 us.
+//
+// Targets whose shapes reach far (next to the lens centre) would have their
+// neighbours evaluate every source too. Those with a shape beyond kFarReach base
+// are listed and taken by workgroups of their own, the sources dealt to the
+// threads and the sums folded in a tree (fewer than one target in a hundred, so
+// the order of their sums does not matter to the likelihood).
+
+constexpr int kOChunk = 8;     // consecutive sources of a box
+constexpr int kOTargets = 16;  // targets of a wave, four lanes each
+constexpr int kOWaves = 8;    // shares of the sources, one wave each
+constexpr float kFarReach = 8.f;
+constexpr int kFarBlocks = 2048;  // waves that take the listed targets in turn
+static_assert(64 % kOChunk == 0 && kOChunk % 4 == 0 && kOTargets == kSubTile, "whole chunks and quads");
+
+static __host__ __device__ int ordered_share(int n) { return cdiv(cdiv(n, 64), kOWaves) * (64 / kOChunk); }
+
+// Source j: (x, y, weight, column value), zeros past n, and the box of its chunk,
+// infinite when one of them is not finite in it. Sorted target j: listed in far
+// when its shape reaches far (the order of the list does not enter any result).
+__global__ __launch_bounds__(256) void ordered_prep_kernel(int n, const float* __restrict__ x,
+                                                           const float* __restrict__ y, const float* __restrict__ w,
+                                                           const float* __restrict__ V, float4* __restrict__ src,
+                                                           float4* __restrict__ box, GSorted T,
+                                                           const float* __restrict__ tz, float base, int* far_count,
+                                                           int* __restrict__ far) {
+  const int j = blockIdx.x * 256 + threadIdx.x, npad = round_up(n, kOChunk);
+  if (tz && j < T.n) {
+    const int jj = T.perm[j];
+    if (shape_reach(tz[jj], tz[T.n + jj], tz[2 * (size_t)T.n + jj], base) > kFarReach * base)
+      far[atomicAdd(far_count, 1)] = j;
+  }
+  float4 q = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
+  if (j < n) {
+    const float4 s = make_float4(x[j], y[j], w[j], V[j]);
+    src[j] = s;
+    const bool ok = isfinite(s.x) && isfinite(s.y) && isfinite(s.z) && isfinite(s.w);
+    q = ok ? make_float4(s.x, s.x, s.y, s.y) : make_float4(-INFINITY, INFINITY, -INFINITY, INFINITY);
+  } else if (j < npad) {
+    src[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  for (int off = kOChunk / 2; off > 0; off >>= 1) {
+    q.x = fminf(q.x, __shfl_xor(q.x, off, kOChunk));
+    q.y = fmaxf(q.y, __shfl_xor(q.y, off, kOChunk));
+    q.z = fminf(q.z, __shfl_xor(q.z, off, kOChunk));
+    q.w = fmaxf(q.w, __shfl_xor(q.w, off, kOChunk));
+  }
+  if (j < npad && (j & (kOChunk - 1)) == 0) box[j / kOChunk] = q;
+}
+
+// One target of the ordered product: its form, and the terms of one source.
+template <bool kShapes>
+struct OrderedTarget {
+  static constexpr int K = kShapes ? 6 : 3;
+  float x, y, ixx, ixy, iyy, rdet;
+  float acc[K];
+  __device__ __forceinline__ void init(float xi, float yi, float txx, float txy, float tyy, float base) {
+    x = xi;
+    y = yi;
+    const float cxx = txx + base, cxy = txy, cyy = tyy + base;
+    const float det = fmaf(cxx, cyy, -cxy * cxy), idet = 1.f / det;
+    ixx = cyy * idet;
+    ixy = -cxy * idet;
+    iyy = cxx * idet;
+    rdet = rsqrtf(det);
+#pragma unroll
+    for (int k = 0; k < K; ++k) acc[k] = 0.f;
+  }
+  // the weighted Gaussian of source s, its moments added
+  __device__ __forceinline__ float term(const float4& s) {
+    const float dx = x - s.x, dy = y - s.y;
+    const float ux = kShapes ? fmaf(ixx, dx, ixy * dy) : ixx * dx;
+    const float uy = kShapes ? fmaf(ixy, dx, iyy * dy) : iyy * dy;
+    const float val = s.z * exp2_fast(kFormScale * fmaf(dx, ux, dy * uy));
+    const float gv = val * s.w;
+    const float gx = gv * ux, gy = gv * uy;
+    acc[1] += gx;
+    acc[2] += gy;
+    if (kShapes) {
+      acc[3 % K] = fmaf(gx, ux, acc[3 % K]);
+      acc[4 % K] = fmaf(gx, uy, acc[4 % K]);
+      acc[5 % K] = fmaf(gy, uy, acc[5 % K]);
+    }
+    return val;
+  }
+  __device__ __forceinline__ void store(float norm, float beta, int first_pos, int first_shape, int ii, int n, float* f,
+                                        float* tg) const {
+    const float c = norm * rdet, h = 0.5f * c;
+    f[ii] = beta != 0.f ? c * acc[0] + beta * f[ii] : c * acc[0];
+    const float v[5] = {-c * acc[1], -c * acc[2], h * (acc[3 % K] - ixx * acc[0]), h * (acc[4 % K] - ixy * acc[0]),
+                        h * (acc[5 % K] - iyy * acc[0])};
+#pragma unroll
+    for (int k = 0; k < (kShapes ? 5 : 2); ++k) {
+      float* t = tg + (size_t)k * n + ii;
+      *t = (k < 2 ? first_pos : first_shape) ? v[k] : *t + v[k];
+    }
+  }
+};
+
+// Each four lanes: the value of the lane before (lane 0 takes lane 3's).
+__device__ __forceinline__ float quad_next(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x93, 0xf, 0xf, true));
+}
+
+// Workgroup (wave) b < 8 tiles: share b / tiles of the sources for the 16 sorted
+// targets of tile b % tiles (a share's waves go round the XCDs: the shares that
+// hold the images are several times the work of the others). The rest (with
+// shapes): wave q takes eighth q % 8 of the sources of listed target q / 8.
+template <bool kShapes>
+__global__ __launch_bounds__(64) void gauss_ordered_kernel(GSorted T, int tiles, const float* __restrict__ tz, int ns,
+                                                           const float4* __restrict__ src,
+                                                           const float4* __restrict__ box, float base,
+                                                           const int* __restrict__ far_count,
+                                                           const int* __restrict__ far, float* __restrict__ part) {
+  using Target = OrderedTarget<kShapes>;
+  constexpr int K = Target::K;
+  const int lane = threadIdx.x, wv = blockIdx.x / tiles, tile = blockIdx.x % tiles, npt = T.nch * kChunk;
+  const int quad = lane & 3;
+  Target t;
+  if (kShapes && wv >= kOWaves) {
+    const int cnt = *far_count * kOWaves, first = tiles * kOWaves;
+    for (int q = blockIdx.x - first; q < cnt; q += kFarBlocks) {
+      const int i = far[q / kOWaves], ii = T.perm[i], w = q % kOWaves;
+      t.init(T.x[i], T.y[i], tz[ii], tz[T.n + ii], tz[2 * (size_t)T.n + ii], base);
+      for (int j = w * 64 + lane; j < ns; j += 64 * kOWaves) {
+        const float4 s = src[j];
+        t.acc[0] = fmaf(t.term(s), s.w, t.acc[0]);
+      }
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const float v = warp_sum(t.acc[k]);
+        if (lane == 0) part[((size_t)w * K + k) * npt + i] = v;
+      }
+    }
+    return;
+  }
+  const int i = tile * kOTargets + (lane >> 2);
+  bool live = i < T.n;
+  const int ii = T.perm[min(i, T.n - 1)];
+  float txx = 0.f, txy = 0.f, tyy = 0.f, lam = 0.f;
+  if (kShapes) {
+    txx = tz[ii];
+    txy = tz[T.n + ii];
+    tyy = tz[2 * (size_t)T.n + ii];
+    lam = shape_reach(txx, txy, tyy, base);
+    if (lam > kFarReach * base) {  // listed
+      lam = 0.f;
+      live = false;
+    }
+    for (int off = 32; off > 2; off >>= 1) lam = fmaxf(lam, __shfl_xor(lam, off, 64));
+  }
+  t.init(T.x[i], T.y[i], txx, txy, tyy, base);
+  const float4 rb = T.sbox[tile];
+  const float limit = kZeroArg * (base + lam);
+  const int nch = cdiv(ns, kOChunk), share = ordered_share(ns);
+  const int cend = min(nch, (wv + 1) * share);
+  for (int c0 = wv * share; c0 < cend; c0 += 64) {
+    const float4 q = box[min(c0 + lane, nch - 1)];
+    const float gx = fmaxf(0.f, fmaxf(q.x - rb.y, rb.x - q.y));
+    const float gy = fmaxf(0.f, fmaxf(q.z - rb.w, rb.z - q.w));
+    const bool zero = -kFormScale * fmaf(gx, gx, gy * gy) >= limit;
+    unsigned long long m = __ballot(c0 + lane < cend && !zero);
+    while (m != 0ull) {
+      const int j0 = (c0 + __ffsll((long long)m) - 1) * kOChunk;
+      m &= m - 1ull;
+      float4 s[kOChunk / 4];
+#pragma unroll
+      for (int v = 0; v < kOChunk / 4; ++v) s[v] = src[j0 + 4 * v + quad];
+#pragma unroll
+      for (int v = 0; v < kOChunk / 4; ++v) {
+        // the sum so far is lane 0's: it takes its term, lane 1 the next, ...
+        const float val = t.term(s[v]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) t.acc[0] = quad_next(fmaf(val, s[v].w, t.acc[0]));
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 1; k < K; ++k) {  // the moments of the four lanes (the sum itself is in lane 0)
+    t.acc[k] += __shfl_xor(t.acc[k], 1, 64);
+    t.acc[k] += __shfl_xor(t.acc[k], 2, 64);
+  }
+  if (quad != 0 || !live) return;
+#pragma unroll
+  for (int k = 0; k < K; ++k) part[((size_t)wv * K + k) * npt + i] = t.acc[k];
+}
+
+// f = norm |C|^{-1/2} sum + beta f over the shares in order, and the adjoint
+// towards the targets per unit of dF/df: tg (+)= -sum G C^{-1} d for the positions
+// and, with shapes, sum G (C^{-1} d d^T C^{-1} - C^{-1}) / 2 for the shapes (xx, xy, yy),
+// with the same factor; first_pos, first_shape: overwrite instead of adding.
+template <bool kShapes>
+__global__ __launch_bounds__(256) void ordered_finish_kernel(GSorted T, const float* __restrict__ tz, float base,
+                                                             float norm, float beta, const float* __restrict__ part,
+                                                             int first_pos, int first_shape, float* f, float* tg) {
+  using Target = OrderedTarget<kShapes>;
+  constexpr int K = Target::K;
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= T.n) return;
+  const int ii = T.perm[i], npt = T.nch * kChunk;
+  Target t;
+  t.init(T.x[i], T.y[i], kShapes ? tz[ii] : 0.f, kShapes ? tz[T.n + ii] : 0.f, kShapes ? tz[2 * (size_t)T.n + ii] : 0.f,
+         base);
+  float v[kOWaves][K];
+#pragma unroll
+  for (int w = 0; w < kOWaves; ++w)
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[w][k] = part[((size_t)w * K + k) * npt + i];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    t.acc[k] = v[0][k];
+#pragma unroll
+    for (int w = 1; w < kOWaves; ++w) t.acc[k] += v[w][k];
+  }
+  t.store(norm, beta, first_pos, first_shape, ii, T.n, f, tg);
+}
+
+struct OrderedBufs {
+  float4 *src, *box;
+  int* far;
+  float* part;
+};
+template <class C>
+static void carve_ordered(C& cv, int nt, int ns, OrderedBufs& b) {
+  b.src = cv.template take<float4>(round_up(ns, kOChunk));
+  b.box = cv.template take<float4>(cdiv(ns, kOChunk));
+  b.far = cv.template take<int>(nt);
+  b.part = cv.template take<float>((size_t)kOWaves * 6 * round_up(nt, kRowTile));
+}
+
+size_t gauss_ordered_scratch(int nt, int ns) {
+  Sizer s;
+  OrderedBufs b;
+  carve_ordered(s, nt, ns, b);
+  return s.used;
+}
+
+template <bool kShapes>
+static int ordered_run(const GSorted& T, const float* tz, int ns, float base, float norm, float beta, int first_pos,
+                       int first_shape, float* f, float* tg, int* far_count, const OrderedBufs& b,
+                       hipStream_t stream) {
+  const int tiles = cdiv(T.n, kOTargets);
+  hipLaunchKernelGGL(gauss_ordered_kernel<kShapes>, dim3(tiles * kOWaves + (kShapes ? kFarBlocks : 0)), dim3(64), 0,
+                     stream, T, tiles, tz, ns, b.src, b.box, base, far_count, b.far, b.part);
+  GPL_LAUNCH_CHECK();
+  hipLaunchKernelGGL(ordered_finish_kernel<kShapes>, dim3(cdiv(T.n, 256)), dim3(256), 0, stream, T, tz, base, norm,
+                     beta, b.part, first_pos, first_shape, f, tg);
+  GPL_LAUNCH_CHECK();
+  return GPL_OK;
+}
+
+int gauss_ordered_launch(const GSorted& T, const float* tz, const GSide& S, double base, double norm, const float* V,
+                         float beta, int first_pos, int first_shape, float* f, float* tg, int* far_count,
+                         void* scratch, size_t bytes, hipStream_t stream) {
+  Carver cv(scratch, bytes);
+  OrderedBufs b;
+  carve_ordered(cv, T.n, S.n, b);
+  if (!cv.ok()) return check_ws(nullptr, 0, 1);
+  hipLaunchKernelGGL(ordered_prep_kernel, dim3(cdiv(std::max(round_up(S.n, kOChunk), tz ? T.n : 0), 256)), dim3(256), 0,
+                     stream, S.n, S.x, S.y, S.w, V, b.src, b.box, T, tz, (float)base, far_count, b.far);
+  GPL_LAUNCH_CHECK();
+  if (tz)
+    return ordered_run<true>(T, tz, S.n, (float)base, (float)norm, beta, first_pos, first_shape, f, tg, far_count, b,
+                             stream);
+  return ordered_run<false>(T, tz, S.n, (float)base, (float)norm, beta, first_pos, first_shape, f, tg, far_count, b,
+                            stream);
+}
+
+template <class C>
+static void carve_pair(C& cv, int nt, int ns, bool same, int cols, TilePlan& pt, TilePlan& ps, char*& rest,
+                       size_t& bytes) {
+  sort_carve(cv, nt, pt);
+  if (!same) sort_carve(cv, ns, ps);
+  bytes = gauss_tiles_scratch(nt, ns, cols);
+  rest = cv.template take<char>(bytes);
+}
+
+bool gauss_pair_sorted(int nt, int ns) { return (long long)nt * ns >= kSortedPairs; }
+
+size_t gauss_pair_workspace(int nt, int ns, bool same, int nrhs) {
+  if (nt <= 0 || ns <= 0 || nrhs <= 0 || !gauss_pair_sorted(nt, ns)) return 0;
+  Sizer s;
+  TilePlan pt, ps;
+  char* rest;
+  size_t bytes;
+  carve_pair(s, nt, ns, same, std::min(nrhs, 8), pt, ps, rest, bytes);
+  return s.used;
+}
+
+int gauss_pair_product(const GSide& T, const GSide& S, double base, double norm, int nrhs, const float* V, int ldv,
+                       float* Y, int ldy, float beta, void* ws, size_t ws_bytes, hipStream_t stream) {
+  const bool same = T.n == S.n && T.x == S.x && T.y == S.y;  // one set of points: one sort
+  Carver cv(ws, ws_bytes);
+  TilePlan pt, ps;
+  char* rest;
+  size_t bytes;
+  carve_pair(cv, T.n, S.n, same, std::min(nrhs, 8), pt, ps, rest, bytes);
+  if (!cv.ok()) return check_ws(ws, ws_bytes, gauss_pair_workspace(T.n, S.n, same, nrhs));
+  GTileBufs b;
+  GPL_TRY(gauss_tiles_carve(T.n, S.n, std::min(nrhs, 8), rest, bytes, b));
+  GPL_TRY(plan_sort(pt, T.n, T.x, T.y, stream));
+  if (!same) GPL_TRY(plan_sort(ps, S.n, S.x, S.y, stream));
+  return gauss_tiles_product(sorted_view(pt), T.z, T.w, sorted_view(same ? pt : ps), S.z, S.w, base, norm, nrhs, V,
+                             ldv, Y, ldy, beta, b, stream);
+}
+
+}  // namespace gpl

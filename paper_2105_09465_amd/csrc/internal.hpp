@@ -165,9 +165,9 @@ int gauss_backward_launch(const GSide& T, const GSide& S, double base_var, doubl
                           float* gtx, float* gty, float* gtz, float* gsx, float* gsy, float* gsw, hipStream_t stream);
 int pixel_shapes_backward_launch(int M, const float* px, const float* py, const float* gz, float* gab, float* gpx,
                                  float* gpy, hipStream_t stream);
-size_t knn_workspace(int n);
-int knn_index_launch(int n, const float* qx, const float* qy, int k, float* rho, float* rk, int* nn, void* ws,
-                     size_t ws_bytes, hipStream_t stream);
+// Distance rk to (and caller index nn of) the k-th closest other point, and the
+// density rho (each nullable), for points sorted by plan_sort.
+int knn_sorted_launch(const TilePlan& p, int k, float* rho, float* rk, int* nn, hipStream_t stream);
 int knn_weight_backward_launch(int n, const float* qx, const float* qy, const float* rk, const int* nn,
                                const float* w, const float* gw, double* gq, float* gpx, float* gpy,
                                hipStream_t stream);
@@ -177,6 +177,7 @@ int raytrace_dev_launch(const gpl_grid* grid, const double* lens, float* px, flo
 int raytrace_dev_backward_launch(const gpl_grid* grid, const double* lens, const float* gpx, const float* gpy,
                                  double* g_lens, double* scratch_partial, hipStream_t stream);
 int check_kernel_any(const gpl_kernel* k);  // RBF or windowed (kind 1)
+size_t windowed_workspace(int n, int nrhs);
 int windowed_mvm(const gpl_kernel* kern, const gpl_grid* grid, int n, const float* px, const float* py, int nrhs,
                  const float* V, int ldv, float* Y, int ldy, float beta, void* ws, size_t ws_bytes,
                  hipStream_t stream);

@@ -157,19 +157,23 @@ __global__ __launch_bounds__(64 * kKnnWaves) void knn_sorted_kernel(int n, int n
   if (nn) nn[me] = kth == kKnnNone ? -1 : (int)(unsigned)kth;  // -1: fewer than k comparable points
 }
 
-size_t knn_workspace(int n) { return plan_workspace(n); }
-
-int knn_index_launch(int n, const float* qx, const float* qy, int k, float* rho, float* rk, int* nn, void* ws,
-                     size_t ws_bytes, hipStream_t stream) {
-  GPL_REQUIRE(k >= 1 && k <= kKnnMaxK && n > k, "k=%d must be in [1, %d] and below n=%d", k, kKnnMaxK, n);
-  GPL_TRY(check_ws(ws, ws_bytes, knn_workspace(n)));
-  Carver cv(ws, ws_bytes);
+static size_t knn_workspace(int n) {
+  Sizer s;
   TilePlan p;
-  plan_carve(cv, n, p);
-  GPL_REQUIRE(cv.ok(), "workspace too small for the point sort");
-  GPL_TRY(plan_sort(p, n, qx, qy, stream));
-  hipLaunchKernelGGL(knn_sorted_kernel, dim3(cdiv(n, kKnnWaves)), dim3(64 * kKnnWaves), 0, stream, n, p.nch, p.xs, p.ys,
-                     p.perm, p.cbox, k, rho, rk, nn);
+  sort_carve(s, n, p);
+  return s.used;
+}
+
+static int check_knn(int n, int k) {
+  GPL_REQUIRE(k >= 1 && k <= kKnnMaxK && n > k, "k=%d must be in [1, %d] and below n=%d", k, kKnnMaxK, n);
+  GPL_REQUIRE(n <= kMaxPlanChunks * kChunk, "n=%d exceeds the limit of %d points", n, kMaxPlanChunks * kChunk);
+  return GPL_OK;
+}
+
+int knn_sorted_launch(const TilePlan& p, int k, float* rho, float* rk, int* nn, hipStream_t stream) {
+  GPL_TRY(check_knn(p.n, k));
+  hipLaunchKernelGGL(knn_sorted_kernel, dim3(cdiv(p.n, kKnnWaves)), dim3(64 * kKnnWaves), 0, stream, p.n, p.nch, p.xs,
+                     p.ys, p.perm, p.cbox, k, rho, rk, nn);
   GPL_LAUNCH_CHECK();
   return GPL_OK;
 }
@@ -183,5 +187,12 @@ extern "C" size_t gpl_knn_density_workspace(int n) { return n <= 0 ? 0 : knn_wor
 extern "C" int gpl_knn_density(int n, const float* qx, const float* qy, int k, float* rho, void* ws, size_t ws_bytes,
                                hipStream_t stream) {
   GPL_REQUIRE(qx && qy && rho, "NULL argument");
-  return knn_index_launch(n, qx, qy, k, rho, nullptr, nullptr, ws, ws_bytes, stream);
+  GPL_TRY(check_knn(n, k));
+  GPL_TRY(check_ws(ws, ws_bytes, knn_workspace(n)));
+  Carver cv(ws, ws_bytes);
+  TilePlan p;
+  sort_carve(cv, n, p);
+  if (!cv.ok()) return check_ws(nullptr, 0, 1);
+  GPL_TRY(plan_sort(p, n, qx, qy, stream));
+  return knn_sorted_launch(p, k, rho, nullptr, nullptr, stream);
 }

@@ -11,6 +11,7 @@
 #include <cmath>
 
 #include "common.hpp"
+#include "gauss_tiles.hpp"
 #include "internal.hpp"
 #include "mvm_mfma.hpp"
 
@@ -110,9 +111,18 @@ int check_kernel(const gpl_kernel* k) {
 
 using namespace gpl;
 
-extern "C" size_t gpl_gp_kernel_mvm_workspace(int n, int nrhs, int prec) { return mvm_workspace(n, nrhs, prec); }
+extern "C" size_t gpl_gp_kernel_mvm_workspace(int n, int nrhs, int prec) {  // either kind of kernel
+  const size_t rbf = mvm_workspace(n, nrhs, prec);
+  return prec == GPL_PREC_FP32 ? std::max(rbf, windowed_workspace(n, nrhs)) : rbf;
+}
 
 namespace gpl {
+
+// The pixel shapes, and the buffers of the sorted product.
+size_t windowed_workspace(int n, int nrhs) {
+  if (n <= 0 || nrhs <= 0) return 0;
+  return align_up((size_t)3 * n * sizeof(float)) + gauss_pair_workspace(n, n, true, nrhs);
+}
 
 // The windowed kernel (kind 1) as a Gaussian product over the grid's points
 // with their pixel shapes, Z staged at the start of the workspace.
@@ -126,6 +136,11 @@ int windowed_mvm(const gpl_kernel* kern, const gpl_grid* grid, int n, const floa
   GPL_TRY(pixel_shapes_launch(grid->n * grid->ss, px, py, z, stream));
   const double l2 = kern->lengthscale * kern->lengthscale;
   const GSide side{px, py, z, nullptr, n};
+  // the sorted product where it is the faster one and the workspace holds it
+  const size_t used = align_up((size_t)3 * n * sizeof(float));
+  if (gauss_pair_sorted(n, n) && ws_bytes >= windowed_workspace(n, nrhs))
+    return gauss_pair_product(side, side, l2, kern->amplitude * kern->amplitude * l2, nrhs, V, ldv, Y, ldy, beta,
+                              static_cast<char*>(ws) + used, ws_bytes - used, stream);
   return gauss_product_launch(side, side, l2, kern->amplitude * kern->amplitude * l2, nrhs, V, ldv, Y, ldy, beta,
                               stream);
 }

@@ -469,7 +469,6 @@ static int compute_units() {
 
 int plan_sort(TilePlan& p, int n, const float* px, const float* py, hipStream_t stream) {
   GPL_REQUIRE(n >= 1, "plan needs at least one point");
-  GPL_REQUIRE(p.nch <= kMaxPlanChunks, "n=%d exceeds the product's limit of %d points", n, kMaxPlanChunks * kChunk);
   int* perm = const_cast<int*>(p.perm);
   int* irank = const_cast<int*>(p.irank);
   const int nsb = sort_blocks(n);
@@ -514,6 +513,7 @@ int plan_build(TilePlan& p, int n, const float* px, const float* py, const gpl_g
     const int m = grid->n * grid->ss;
     GPL_REQUIRE(m > 0 && (long)m * m == n, "grid does not match n=%d", n);
   }
+  GPL_REQUIRE(p.nch <= kMaxPlanChunks, "n=%d exceeds the product's limit of %d points", n, kMaxPlanChunks * kChunk);
   p.wround = 4 * compute_units();
   GPL_TRY(plan_sort(p, n, px, py, stream));
   hipLaunchKernelGGL(plan_scaled_kernel, dim3(cdiv(p.npad, 256)), dim3(256), 0, stream, p.npad, p.xs, p.ys, p.cbox, s2,

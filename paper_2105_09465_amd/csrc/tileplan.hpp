@@ -189,6 +189,27 @@ void plan_carve(C& cv, int n, TilePlan& p) {
   p.shist = cv.template take<int>((size_t)kSortDigits * sort_blocks(n));
 }
 
+// The buffers of the sort alone (plan_sort): points, boxes and scratch.
+template <class C>
+void sort_carve(C& cv, int n, TilePlan& p) {
+  p = TilePlan{};
+  p.n = n;
+  p.nrt = cdiv(n, kRowTile);
+  p.nch = kChunksPerTile * p.nrt;
+  p.npad = p.nrt * kRowTile;
+  p.perm = cv.template take<int>((size_t)p.npad);
+  p.irank = cv.template take<int>((size_t)p.npad);
+  p.xs = cv.template take<float>((size_t)p.npad);
+  p.ys = cv.template take<float>((size_t)p.npad);
+  p.xc = cv.template take<float>((size_t)p.npad);
+  p.yc = cv.template take<float>((size_t)p.npad);
+  p.cbox = cv.template take<float4>((size_t)p.nch);
+  p.sbox = cv.template take<float4>((size_t)p.nrt * kSubsPerTile);
+  p.total = cv.template take<int>(1);
+  p.sval = cv.template take<int>((size_t)p.npad);
+  p.shist = cv.template take<int>((size_t)kSortDigits * sort_blocks(n));
+}
+
 // Build the plan on `stream`. The points are sorted along the Hilbert curve of
 // their positions (ties in caller order, so the plan depends only on the
 // points). `grid` (nullable) is checked against n: with one, the points are its

@@ -8,7 +8,8 @@
 // A_j = sqrt(2 pi l_k^2) w_j with w_j = rho_j^{-1/2} = r_j sqrt(pi / k) (r_j the
 // distance to the k-th closest other inducing point). Image-plane layers: q = p,
 // Zt = the pixel shapes; the source-plane layer: q = a fixed grid, Zt = 0. All
-// products are the Gaussian products of gauss.hip (every pair in FP32).
+// products are the Gaussian products of gauss_tiles.hip over the points sorted
+// once per step (every pair that is not exactly zero in FP32).
 //
 // Step: the lens sample theta (device FP64), the source samples y (FP32),
 // ray tracing from the device-held theta, pixel shapes, k-NN weights, the
@@ -17,9 +18,17 @@
 // transmission product, the pixel shapes and the k-NN weights, and dE/dtheta
 // by the ray-tracing adjoint. A final one-thread kernel folds the FP64 sums
 // into the ELBO pieces and the gradient of the small FP64 parameter block.
+//
+// Each layer takes two passes over its pairs, not four. The adjoint of T_k y
+// towards the targets is g_f[i] times sums over j of the same terms as the
+// product itself (G_ij A_j y_j times 1, C_i^{-1} d and its products), so the
+// forward pass forms them too; the adjoint towards the inducing points is y_j
+// times sums over i of the terms of T_k^T g_f (G_ij g_f[i] times 1 and C_i^{-1} d),
+// formed together with it.
 #include <cmath>
 
 #include "common.hpp"
+#include "gauss_tiles.hpp"
 #include "internal.hpp"
 
 namespace gpl {
@@ -101,10 +110,13 @@ struct Bump {
 
 struct VBufs {
   double *lens, *g_lens, *g_src, *sums, *gq, *rt_partial, *se_partial;
-  void* knn_ws;
-  size_t knn_bytes;
+  TilePlan sort_p, sort_g;  // the traced points and the source-plane grid along the curve
+  char* tiles;
+  size_t tiles_bytes;
   float *px, *py, *Z, *f, *resid, *g_f, *gpx, *gpy, *gZ, *gw, *gab, *r, *w, *w_sp, *r_sp, *y;
+  float* tg;  // [5][N] adjoint towards the targets per unit of g_f: dx, dy, shape xx, xy, yy
   int *nn, *nn_sp;
+  int* far_count;  // [kVMaxLayers] targets of each layer whose shapes reach far
 };
 
 static size_t vigp_carve(const VLayout& L, void* ws, VBufs& b) {
@@ -135,8 +147,15 @@ static size_t vigp_carve(const VLayout& L, void* ws, VBufs& b) {
   b.r_sp = B.take<float>(G);
   b.nn_sp = B.take<int>(G);
   b.y = B.take<float>(L.ne32 ? L.ne32 : 1);
-  b.knn_bytes = knn_workspace(std::max(L.nip > 0 ? L.N : 0, L.sp >= 0 ? L.G : 0));
-  b.knn_ws = B.take<char>(std::max<size_t>(b.knn_bytes, 1));
+  b.tg = B.take<float>(5 * N);
+  b.far_count = B.take<int>(kVMaxLayers);
+  sort_carve(B, L.N, b.sort_p);
+  b.tiles_bytes = L.nip > 0 ? std::max(gauss_tiles_scratch(L.N, L.N, 1), gauss_ordered_scratch(L.N, L.N)) : 0;
+  if (L.sp >= 0) {
+    sort_carve(B, L.G, b.sort_g);
+    b.tiles_bytes = std::max({b.tiles_bytes, gauss_tiles_scratch(L.G, L.N, 1), gauss_ordered_scratch(L.N, L.G)});
+  }
+  b.tiles = B.take<char>(b.tiles_bytes);
   return B.used;
 }
 
@@ -164,9 +183,10 @@ __global__ __launch_bounds__(256) void vigp_sums_kernel(VSeg seg, double* sums) 
 }
 
 // theta = m_l + L_l e_l (L_l: strictly lower part of raw, exp of its diagonal),
-// with the fixed slope in position 3 of the 8-vector.
+// with the fixed slope in position 3 of the 8-vector. Also clears the layers' counts.
 __global__ void vigp_lens_sample_kernel(const double* __restrict__ P64, const double* __restrict__ e_l, double slope,
-                                        double* lens) {
+                                        double* lens, int* far_count) {
+  if (threadIdx.x < kVMaxLayers) far_count[threadIdx.x] = 0;
   if (threadIdx.x != 0) return;
   const int free_idx[7] = {0, 1, 2, 4, 5, 6, 7};
   for (int a = 0; a < 7; ++a) {
@@ -210,20 +230,56 @@ __global__ void vigp_copy_kernel(int n, const float* __restrict__ a, float* b) {
   if (j < n) b[j] = a[j];
 }
 
-// Per-parameter gradients of one layer, from t = T^T g_f held in gmean:
-// g_y = t - y / alpha^2 (alpha = exp(log_amp)); dE/dm = g_y,
-// dE/dlog s = s g_y e + 1, dE/dC[:, b] = g_y e_l[b] (source-plane layer).
-__global__ void vigp_layer_grad_kernel(int n, const float* __restrict__ y, const double* __restrict__ log_amp,
-                                       const float* __restrict__ logs, const float* __restrict__ e,
-                                       const double* __restrict__ e_l, float* gmean, float* glogs, float* gcross) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
+// End of a layer's transposed pass, thread j a sorted inducing point with
+// weight w_j: t_j = (T^T g_f)_j = norm w_j sum, and the parameter gradients
+// g_y = t - y / alpha^2 (alpha = exp(log_amp)); dE/dm = g_y, dE/dlog s = s g_y e + 1,
+// dE/dC[:, b] = g_y e_l[b] (source-plane layer). Image-plane layers (kPos) add the
+// adjoint towards the inducing points: norm y_j w_j sum G C^{-1} (t - q) to
+// their positions (the sums hold kFormScale C^{-1} (q - t)) and norm y_j sum G to
+// their weights.
+template <bool kPos>
+__global__ __launch_bounds__(256) void vigp_adjoint_kernel(GSorted T, const float* __restrict__ w, float norm,
+                                                           const float* __restrict__ part, int nslices,
+                                                           const float* __restrict__ y,
+                                                           const double* __restrict__ log_amp,
+                                                           const float* __restrict__ logs,
+                                                           const float* __restrict__ e,
+                                                           const double* __restrict__ e_l, float* gmean,
+                                                           float* glogs, float* gcross, float* gpx, float* gpy,
+                                                           float* gw) {
+  const int i = blockIdx.x * 256 + threadIdx.x, n = T.n;
+  if (i >= n) return;
+  constexpr int K = kPos ? 3 : 1;
+  const int j = T.perm[i], npt = T.nch * kChunk;
+  float s[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) s[k] = fold_slices(part, nslices, K, npt, k, i);
+  const float yj = y[j], wj = w[j];
   const float ia2 = (float)exp(-2.0 * log_amp[0]);
-  const float g = gmean[j] - y[j] * ia2;
+  const float g = norm * wj * s[0] - yj * ia2;
   gmean[j] = g;
   glogs[j] = fmaf(expf(logs[j]) * g, e[j], 1.f);
   if (gcross)
     for (int b = 0; b < 7; ++b) gcross[(size_t)b * n + j] = g * (float)e_l[b];
+  if (kPos) {
+    const float c = -norm * yj * wj / kFormScale;
+    gpx[j] += c * s[1 % K];
+    gpy[j] += c * s[2 % K];
+    gw[j] += norm * yj * s[0];
+  }
+}
+
+// The targets' side of dE/dp and dE/dZ: g_f times the sums of the forward passes.
+__global__ void vigp_target_kernel(int N, int shapes, const float* __restrict__ g_f, const float* __restrict__ tg,
+                                   float* gpx, float* gpy, float* gZ) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= N) return;
+  const float g = g_f[i];
+  gpx[i] += g * tg[i];
+  gpy[i] += g * tg[N + i];
+  if (shapes)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) gZ[(size_t)k * N + i] = g * tg[(size_t)(2 + k) * N + i];
 }
 
 struct VFinal {
@@ -342,12 +398,12 @@ extern "C" int gpl_vigp_elbo(const gpl_vigp_model* model, const gpl_grid* grid, 
   GPL_TRY(check_ws(ws, ws_bytes, need));
   vigp_carve(L, ws, b);
   const int N = L.N;
-  const size_t N3 = 3 * (size_t)N;
   const double kk = model->knn_k;
   const float wscale = (float)std::sqrt(M_PI / kk);
 
   // ---- samples
-  hipLaunchKernelGGL(vigp_lens_sample_kernel, dim3(1), dim3(64), 0, stream, P64, e64, model->slope, b.lens);
+  hipLaunchKernelGGL(vigp_lens_sample_kernel, dim3(1), dim3(64), 0, stream, P64, e64, model->slope, b.lens,
+                     b.far_count);
   GPL_LAUNCH_CHECK();
   float* y[kVMaxLayers];
   for (int k = 0; k < L.nl; ++k) {
@@ -360,27 +416,32 @@ extern "C" int gpl_vigp_elbo(const gpl_vigp_model* model, const gpl_grid* grid, 
   // ---- forward
   GPL_TRY(raytrace_dev_launch(grid, b.lens, b.px, b.py, stream));
   GPL_TRY(pixel_shapes_launch(L.M, b.px, b.py, b.Z, stream));
+  GPL_TRY(plan_sort(b.sort_p, N, b.px, b.py, stream));
   if (L.nip > 0) {
-    GPL_TRY(knn_index_launch(N, b.px, b.py, model->knn_k, nullptr, b.r, b.nn, b.knn_ws, b.knn_bytes, stream));
+    GPL_TRY(knn_sorted_launch(b.sort_p, model->knn_k, nullptr, b.r, b.nn, stream));
     hipLaunchKernelGGL(vigp_knn_weight_kernel, blocks_for(N), dim3(256), 0, stream, N, b.r, wscale, b.w);
     GPL_LAUNCH_CHECK();
   }
   if (L.sp >= 0) {
-    GPL_TRY(knn_index_launch(G, gx, gy, model->knn_k, nullptr, b.r_sp, b.nn_sp, b.knn_ws, b.knn_bytes, stream));
+    GPL_TRY(plan_sort(b.sort_g, G, gx, gy, stream));
+    GPL_TRY(knn_sorted_launch(b.sort_g, model->knn_k, nullptr, b.r_sp, b.nn_sp, stream));
     hipLaunchKernelGGL(vigp_knn_weight_kernel, blocks_for(G), dim3(256), 0, stream, G, b.r_sp, wscale, b.w_sp);
     GPL_LAUNCH_CHECK();
   }
   GPL_TRY(gpl_sersic_eval(src, N, b.px, b.py, b.f, stream));
-  const GSide Pz{b.px, b.py, b.Z, nullptr, N}, P0{b.px, b.py, nullptr, nullptr, N};
-  const GSide Qip{b.px, b.py, nullptr, b.w, N}, Qsp{gx, gy, nullptr, b.w_sp, G};
+  const GSorted P = sorted_view(b.sort_p), Q = sorted_view(b.sort_g);
   double norm[kVMaxLayers], base[kVMaxLayers];
+  int first_pos = 1, first_shape = 1;
   for (int k = 0; k < L.nl; ++k) {
     const double ell = model->lengthscale[k];
     base[k] = 0.5 * ell * ell;
     norm[k] = std::sqrt(2.0 * M_PI * ell * ell) / (2.0 * M_PI);
     const bool sp = k == L.sp;
-    GPL_TRY(gauss_product_launch(sp ? P0 : Pz, sp ? Qsp : Qip, base[k], norm[k], 1, y[k], L.n[k], b.f, N, 1.f,
-                                 stream));
+    const GSide S = sp ? GSide{gx, gy, nullptr, b.w_sp, G} : GSide{b.px, b.py, nullptr, b.w, N};
+    GPL_TRY(gauss_ordered_launch(P, sp ? nullptr : b.Z, S, base[k], norm[k], y[k], 1.f, first_pos, first_shape, b.f,
+                                 b.tg, b.far_count + k, b.tiles, b.tiles_bytes, stream));
+    first_pos = 0;
+    if (!sp) first_shape = 0;
   }
   hipLaunchKernelGGL(vigp_copy_kernel, blocks_for(L.npix), dim3(256), 0, stream, L.npix, d, b.resid);
   GPL_LAUNCH_CHECK();
@@ -388,33 +449,37 @@ extern "C" int gpl_vigp_elbo(const gpl_vigp_model* model, const gpl_grid* grid, 
   // ---- backward
   GPL_TRY(gpl_psf_conv(grid, psf, 1, b.resid, L.npix, b.g_f, N, (float)(1.0 / (noise_sigma * noise_sigma)), 0.f, 1,
                        stream));  // g_f = B^T r / sigma^2
-  for (int k = 0; k < L.nl; ++k) {
-    const bool sp = k == L.sp;
-    // T_k^T g_f: targets are the inducing points (weights A), sources the traced points
-    const GSide Tq = sp ? GSide{gx, gy, nullptr, b.w_sp, G} : GSide{b.px, b.py, nullptr, b.w, N};
-    const GSide Sp = sp ? P0 : Pz;
-    float* gmean = G32 + L.mean[k];
-    GPL_TRY(gauss_product_launch(Tq, Sp, base[k], norm[k], 1, b.g_f, N, gmean, L.n[k], 0.f, stream));
-    hipLaunchKernelGGL(vigp_layer_grad_kernel, blocks_for(L.n[k]), dim3(256), 0, stream, L.n[k], y[k], P64 + 56 + k,
-                       P32 + L.logs[k], e32 + L.e[k], e64, gmean, G32 + L.logs[k], sp ? G32 + L.cross : nullptr);
-    GPL_LAUNCH_CHECK();
-  }
   // dE/dp
   hipLaunchKernelGGL(vigp_fill_kernel, blocks_for(N), dim3(256), 0, stream, (size_t)N, b.gpx, 0.f);
   hipLaunchKernelGGL(vigp_fill_kernel, blocks_for(N), dim3(256), 0, stream, (size_t)N, b.gpy, 0.f);
-  hipLaunchKernelGGL(vigp_fill_kernel, blocks_for(N3), dim3(256), 0, stream, N3, b.gZ, 0.f);
   hipLaunchKernelGGL(vigp_fill_kernel, blocks_for(N), dim3(256), 0, stream, (size_t)N, b.gw, 0.f);
   hipLaunchKernelGGL(vigp_fill_double_kernel, blocks_for(2 * (size_t)N), dim3(256), 0, stream, 2 * (size_t)N, b.gq);
   GPL_LAUNCH_CHECK();
   GPL_TRY(gpl_sersic_backward(src, N, b.px, b.py, b.g_f, b.gpx, b.gpy, b.g_src, b.se_partial,
                               gpl_sersic_backward_workspace(N), stream));
+  hipLaunchKernelGGL(vigp_target_kernel, blocks_for(N), dim3(256), 0, stream, N, L.nip > 0 ? 1 : 0, b.g_f, b.tg, b.gpx,
+                     b.gpy, b.gZ);
+  GPL_LAUNCH_CHECK();
+  GTileBufs tb;
+  int ns = 0;
   for (int k = 0; k < L.nl; ++k) {
-    if (k == L.sp)
-      GPL_TRY(gauss_backward_launch(P0, Qsp, base[k], norm[k], y[k], b.g_f, b.gpx, b.gpy, nullptr, nullptr, nullptr,
-                                    nullptr, stream));
-    else
-      GPL_TRY(gauss_backward_launch(Pz, Qip, base[k], norm[k], y[k], b.g_f, b.gpx, b.gpy, b.gZ, b.gpx, b.gpy, b.gw,
-                                    stream));
+    // T_k^T g_f: targets are the inducing points (weights A), sources the traced points
+    float* gmean = G32 + L.mean[k];
+    if (k == L.sp) {
+      GPL_TRY(gauss_tiles_carve(G, N, 1, b.tiles, b.tiles_bytes, tb));
+      GPL_TRY(gauss_tiles_sums(Q, P, nullptr, base[k], b.g_f, tb, &ns, stream));
+      const float bk = (float)base[k];
+      hipLaunchKernelGGL(vigp_adjoint_kernel<false>, blocks_for(G), dim3(256), 0, stream, Q, b.w_sp,
+                         (float)norm[k] / std::sqrt(bk * bk), tb.part, ns, y[k], P64 + 56 + k, P32 + L.logs[k],
+                         e32 + L.e[k], e64, gmean, G32 + L.logs[k], G32 + L.cross, nullptr, nullptr, nullptr);
+    } else {
+      GPL_TRY(gauss_tiles_carve(N, N, 1, b.tiles, b.tiles_bytes, tb));
+      GPL_TRY(gauss_tiles_sums(P, P, b.Z, base[k], b.g_f, tb, &ns, stream));
+      hipLaunchKernelGGL(vigp_adjoint_kernel<true>, blocks_for(N), dim3(256), 0, stream, P, b.w, (float)norm[k], tb.part,
+                         ns, y[k], P64 + 56 + k, P32 + L.logs[k], e32 + L.e[k], e64, gmean, G32 + L.logs[k], nullptr,
+                         b.gpx, b.gpy, b.gw);
+    }
+    GPL_LAUNCH_CHECK();
   }
   if (L.nip > 0) {
     GPL_TRY(pixel_shapes_backward_launch(L.M, b.px, b.py, b.gZ, b.gab, b.gpx, b.gpy, stream));
@@ -424,7 +489,7 @@ extern "C" int gpl_vigp_elbo(const gpl_vigp_model* model, const gpl_grid* grid, 
   GPL_TRY(raytrace_dev_backward_launch(grid, b.lens, b.gpx, b.gpy, b.g_lens, b.rt_partial, stream));
   // ---- scalars
   VSeg seg{};
-  int ns = 0;
+  ns = 0;
   seg.a[ns] = b.resid;
   seg.n[ns] = L.npix;
   seg.square[ns++] = 1;

@@ -139,8 +139,9 @@ def gauss_product(base_var, norm, tx, ty, sx, sy, V, tz=None, tw=None, sz=None, 
     for z, n in ((tz, nt), (sz, ns)):
         if z is not None and (tuple(z.shape) != (3, n) or not z.is_contiguous()):
             raise ValueError("shape covariances must be contiguous (3, n) tensors")
-    _lib.call("gpl_gauss_product", C.byref(g), nt, _ptr(tx), _ptr(ty), _ptr(tz), _ptr(tw), ns, _ptr(sx), _ptr(sy),
-              _ptr(sz), _ptr(sw), V2.shape[0], _ptr(V2), ldv, _ptr(out2), ldy, float(beta), _stream())
+    ws, wsb = workspace(_lib.lib.gpl_gauss_product_workspace(nt, ns, V2.shape[0]), V.device)
+    _lib.call("gpl_gauss_product_ws", C.byref(g), nt, _ptr(tx), _ptr(ty), _ptr(tz), _ptr(tw), ns, _ptr(sx), _ptr(sy),
+              _ptr(sz), _ptr(sw), V2.shape[0], _ptr(V2), ldv, _ptr(out2), ldy, float(beta), _wsptr(ws), wsb, _stream())
     return out[0] if (squeeze and out.dim() == 2) else out
 
 
