@@ -521,7 +521,7 @@ extern "C" int gpl_apply_A(const gpl_problem* prob, int nrhs, const float* X, in
   }
   MvmCtx mv;
   GPL_TRY(mvm_prepare(mv, prob->kernel.lengthscale, prob->kernel.amplitude, N, prob->px, prob->py, &prob->grid, nrhs,
-                      prec, mws, mb, stream));
+                      prec, false, mws, mb, stream));
   return apply_A_into(prob, taps, mv, nrhs, X, ldx, T1, T2, ldf, Y, ldy, nullptr, CgGate{}, stream);
 }
 
@@ -556,7 +556,7 @@ extern "C" int gpl_cg_solve(const gpl_problem* prob, int nrhs, const float* Bm, 
   if (check_every > 0) GPL_TRY(poll_slots(poll));
   MvmCtx mv;  // the points stay fixed for the whole solve: one tile plan
   GPL_TRY(mvm_prepare(mv, prob->kernel.lengthscale, prob->kernel.amplitude, N, prob->px, prob->py, &prob->grid, nrhs,
-                      prec, b.mvm_ws, b.mvm_ws_bytes, stream));
+                      prec, true, b.mvm_ws, b.mvm_ws_bytes, stream));
   const RhsOut rhs_out{prec, nrhs, mv.bufs.ncp, mv.bufs.Vh, mv.bufs.Vl, mv.bufs.Vp, mv.bufs.inv_scale, b.pmax, b.nb_upd,
                        mv.plan.irank};
   const float sigma2 = (float)(prob->noise_sigma * prob->noise_sigma);

@@ -36,7 +36,8 @@ size_t mvm_workspace(int n, int nrhs, int prec) {
 }
 
 int mvm_prepare(MvmCtx& m, double lengthscale, double amplitude, int n, const float* px, const float* py,
-                const gpl_grid* grid, int nrhs, int prec, void* ws, size_t ws_bytes, hipStream_t stream) {
+                const gpl_grid* grid, int nrhs, int prec, bool zero_rhs, void* ws, size_t ws_bytes,
+                hipStream_t stream) {
   GPL_TRY(check_ws(ws, ws_bytes, mvm_workspace(n, nrhs, prec)));
   Carver cv(ws, ws_bytes);
   void* scratch;
@@ -48,7 +49,7 @@ int mvm_prepare(MvmCtx& m, double lengthscale, double amplitude, int n, const fl
   m.nrhs_max = nrhs;
   m.s2 = (float)kernel_scale2(lengthscale);
   m.amp2 = (float)(amplitude * amplitude);
-  GPL_TRY(mfma_zero_rhs(m.bufs, prec, stream));
+  if (zero_rhs) GPL_TRY(mfma_zero_rhs(m.bufs, prec, stream));
   return plan_build(m.plan, n, px, py, grid, m.s2, plan_threshold(prec), plan_lo_threshold(prec), stream);
 }
 
@@ -68,7 +69,7 @@ int mvm_launch(double lengthscale, double amplitude, int n, const float* px, con
                int nrhs, const float* V, int ldv, float* Y, int ldy, float beta, int prec, void* ws, size_t ws_bytes,
                CgGate gate, hipStream_t stream) {
   MvmCtx m;
-  GPL_TRY(mvm_prepare(m, lengthscale, amplitude, n, px, py, grid, nrhs, prec, ws, ws_bytes, stream));
+  GPL_TRY(mvm_prepare(m, lengthscale, amplitude, n, px, py, grid, nrhs, prec, false, ws, ws_bytes, stream));
   return mvm_run(m, nrhs, V, ldv, Y, ldy, beta, gate, stream);
 }
 

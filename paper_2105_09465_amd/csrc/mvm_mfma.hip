@@ -83,27 +83,27 @@ __device__ __forceinline__ float gather_rhs(int j, int c, int n, int nrhs, const
   return V[(size_t)c * ldv + (perm ? perm[j] : j)];
 }
 
-// V' = V * 2^e_c split into FP16 hi (nearest) and lo, in sorted order;
-// inv_scale[c] = 2^-e_c / 2^11 folds both scales for the output.
-__device__ __forceinline__ void split_rhs_body(int bx, int slot, int n, int nrhs, const float* __restrict__ V,
-                                               int ldv, const int* perm, const unsigned* colmax, _Float16* Vh,
-                                               _Float16* Vl, int ldh, int ncp, float* inv_scale) {
-  const int j = bx * blockDim.x + threadIdx.x;
-  if (j >= ldh) return;
-  // slot `slot` of the buffers: column `slot`, or in a packed last block one
-  // FP16 part (lo in odd slots) of column b0 + (slot - b0) / 2
+// Column of slot `slot` of the buffers: column `slot`, or in a packed last block
+// (one FP16 part a slot, lo in odd ones) column b0 + (slot - b0) / 2.
+__device__ __forceinline__ int slot_column(int slot, int nrhs, bool& packed) {
   const int b0 = packed_block_start(nrhs);
-  const bool packed = last_block_packed(nrhs) && slot >= b0;
-  const int c = packed ? b0 + (slot - b0) / 2 : slot;
-  int e = 0;
-  if (c < nrhs) {
-    unsigned mb = 0u;
-    for (int b = 0; b < kColmaxBlocks; ++b) mb = max(mb, colmax[c * kColmaxBlocks + b]);
-    const float mx = __uint_as_float(mb);
-    // mx * 2^e in [2^13, 2^14); e is capped so that 2^e stays a finite float
-    // (a column below 2^-113 then scales to less than 2^13, still normal in FP16)
-    if (mx > 0.f && isfinite(mx)) e = min(14 - ilogbf(mx) - 1, 126);
-  }
+  packed = last_block_packed(nrhs) && slot >= b0;
+  return packed ? b0 + (slot - b0) / 2 : slot;
+}
+
+// Exponent e of a column with the largest magnitude mx: mx 2^e in [2^13, 2^14); e
+// is capped so that 2^e stays a finite float (a column below 2^-113 then scales
+// to less than 2^13, still normal in FP16).
+__device__ __forceinline__ int column_exponent(float mx) {
+  return mx > 0.f && isfinite(mx) ? min(14 - ilogbf(mx) - 1, 126) : 0;
+}
+
+// V' = V * 2^e_c split into FP16 hi (nearest) and lo, in sorted order, position j
+// of one slot; inv_scale[c] = 2^-e_c / 2^11 folds both scales for the output.
+__device__ __forceinline__ void split_rhs_at(int j, int slot, int c, bool packed, int e, int n, int nrhs,
+                                             const float* __restrict__ V, int ldv, const int* perm, _Float16* Vh,
+                                             _Float16* Vl, int ncp, float* inv_scale) {
+  const int b0 = packed_block_start(nrhs);
   const float scale = ldexpf(1.f, e);
   if (j == 0 && c < ncp && (!packed || ((slot - b0) & 1) == 0)) inv_scale[c] = ldexpf(1.f, -e) / kKScale;
   const float v = gather_rhs(j, c, n, nrhs, perm, V, ldv) * scale;
@@ -121,7 +121,40 @@ __global__ void split_rhs_kernel(int n, int nrhs, const float* __restrict__ V, i
                                  const unsigned* colmax, _Float16* Vh, _Float16* Vl, int ldh, int ncp, float* inv_scale,
                                  CgGate gate) {
   if (gate.skip_all()) return;
-  split_rhs_body(blockIdx.x, blockIdx.y, n, nrhs, V, ldv, perm, colmax, Vh, Vl, ldh, ncp, inv_scale);
+  const int j = blockIdx.x * blockDim.x + threadIdx.x, slot = blockIdx.y;
+  if (j >= ldh) return;
+  bool packed;
+  const int c = slot_column(slot, nrhs, packed);
+  int e = 0;
+  if (c < nrhs) {
+    unsigned mb = 0u;
+    for (int b = 0; b < kColmaxBlocks; ++b) mb = max(mb, colmax[c * kColmaxBlocks + b]);
+    e = column_exponent(__uint_as_float(mb));
+  }
+  split_rhs_at(j, slot, c, packed, e, n, nrhs, V, ldv, perm, Vh, Vl, ncp, inv_scale);
+}
+
+// Both steps for a small product, one workgroup per slot (the column maximum is
+// formed by every workgroup that needs it): a launch less where launches are
+// what counts.
+constexpr int kSmallRhs = 4096;
+__global__ __launch_bounds__(1024) void small_rhs_kernel(int n, int nrhs, const float* __restrict__ V, int ldv,
+                                                         const int* perm, _Float16* Vh, _Float16* Vl, int ldh, int ncp,
+                                                         float* inv_scale, CgGate gate) {
+  __shared__ float red[16];
+  if (gate.skip_all()) return;
+  bool packed;
+  const int slot = blockIdx.x, c = slot_column(slot, nrhs, packed);
+  float m = 0.f;
+  if (c < nrhs)
+    for (int i = threadIdx.x; i < n; i += 1024) m = fmaxf(m, fabsf(V[(size_t)c * ldv + i]));
+  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  for (int k = 0; k < 16; ++k) m = fmaxf(m, red[k]);
+  const int e = c < nrhs ? column_exponent(m) : 0;
+  for (int j = threadIdx.x; j < ldh; j += 1024)
+    split_rhs_at(j, slot, c, packed, e, n, nrhs, V, ldv, perm, Vh, Vl, ncp, inv_scale);
 }
 
 // FP32 form: the RHS block in sorted order, zero padded.
@@ -619,7 +652,10 @@ int mfma_zero_rhs(const ProdBufs& b, int prec, hipStream_t stream) {
 int mfma_prep_rhs(const TilePlan& P, const ProdBufs& b, int prec, int nrhs, const float* V, int ldv, CgGate gate,
                   hipStream_t stream) {
   const int n = P.n;
-  if (prec == GPL_PREC_F16X3) {
+  if (prec == GPL_PREC_F16X3 && n <= kSmallRhs) {
+    hipLaunchKernelGGL(small_rhs_kernel, dim3(b.ncp), dim3(1024), 0, stream, n, nrhs, V, ldv, P.perm, b.Vh, b.Vl, b.ldh,
+                       b.ncp, b.inv_scale, gate);
+  } else if (prec == GPL_PREC_F16X3) {
     hipLaunchKernelGGL(colmax_kernel, dim3(kColmaxBlocks, nrhs), dim3(256), 0, stream, n, V, ldv, b.colmax, gate);
     GPL_LAUNCH_CHECK();
     hipLaunchKernelGGL(split_rhs_kernel, dim3(cdiv(b.ldh, 256), b.ncp), dim3(256), 0, stream, n, nrhs, V, ldv, P.perm,

@@ -1109,7 +1109,7 @@ extern "C" int gpl_pchol(const gpl_problem* prob, int k, int prec, double* L, in
   GPL_TRY(blas_handle(&h2, s2, b.blas2, kBlasScratch, 1));
   MvmCtx mv;
   GPL_TRY(mvm_prepare(mv, prob->kernel.lengthscale, prob->kernel.amplitude, N, prob->px, prob->py, &prob->grid,
-                      kPcBlock, prec, b.mvm_ws, b.mvm_bytes, stream));
+                      kPcBlock, prec, true, b.mvm_ws, b.mvm_bytes, stream));
   const float s2s = (float)kernel_scale2(prob->kernel.lengthscale);
   const double amp2 = prob->kernel.amplitude * prob->kernel.amplitude;
   const double sig2 = prob->noise_sigma * prob->noise_sigma;
@@ -1277,7 +1277,7 @@ extern "C" int gpl_pcg_solve(const gpl_problem* prob, int k, const double* L, in
   if (check_every > 0) GPL_TRY(pcg_poll(poll));
   MvmCtx mv;
   GPL_TRY(mvm_prepare(mv, prob->kernel.lengthscale, prob->kernel.amplitude, N, prob->px, prob->py, &prob->grid, nrhs,
-                      prec, b.mvm_ws, b.mvm_bytes, stream));
+                      prec, true, b.mvm_ws, b.mvm_bytes, stream));
   const RhsOut rhs_out{prec, nrhs, mv.bufs.ncp, mv.bufs.Vh, mv.bufs.Vl, mv.bufs.Vp, mv.bufs.inv_scale, b.pmax, b.nb,
                        mv.plan.irank};
   const float sigma2 = (float)(prob->noise_sigma * prob->noise_sigma);

@@ -1,6 +1,13 @@
 // Construction of the tile plan of the kernel product (see tileplan.hpp): sorted
 // points, chunk bounding boxes, and per row tile the list of chunks within the
 // exact-zero cutoff of the kernel (Sec. 3.1, eq. "grbf").
+//
+// A plan is built for every product that is not part of a solve, so its launches
+// count as much as the product itself: every kernel of it is bound by latency.
+// Nine launches (one up to kSmallPoints points) instead of twenty-two: two sort
+// passes of 12 bits in which each workgroup folds all workgroups' digit counts
+// itself (no scan launches between), boxes and scaled coordinates in one kernel,
+// and the split over the waves in two.
 #include <cmath>
 #include <utility>
 
@@ -18,56 +25,61 @@ size_t plan_workspace(int n) {
 
 // ---- point order: Hilbert keys, then a stable LSD radix sort ----
 
-// Extent of the finite points (one workgroup): (xmin, ymin, side of the square
-// from there that holds them all, 0).
-__global__ __launch_bounds__(1024) void plan_extent_kernel(int n, const float* __restrict__ px,
-                                                           const float* __restrict__ py, float4* ext) {
-  __shared__ float red[4][16];
-  float x0 = INFINITY, x1 = -INFINITY, y0 = INFINITY, y1 = -INFINITY;
-  // 8 points per thread and round, their loads issued together (an index past n
-  // reads point 0 and is not used)
-  constexpr int kU = 8;
-  for (int i0 = threadIdx.x; i0 < n; i0 += kU * blockDim.x) {
+// Four-way extent (xmin, xmax, ymin, ymax) over the lanes of a wave.
+__device__ __forceinline__ float4 wave_extent(float4 e) {
+  for (int off = 32; off > 0; off >>= 1) {
+    e.x = fminf(e.x, __shfl_xor(e.x, off, 64));
+    e.y = fmaxf(e.y, __shfl_xor(e.y, off, 64));
+    e.z = fminf(e.z, __shfl_xor(e.z, off, 64));
+    e.w = fmaxf(e.w, __shfl_xor(e.w, off, 64));
+  }
+  return e;
+}
+__device__ __forceinline__ float4 join_extent(const float4& a, const float4& b) {
+  return make_float4(fminf(a.x, b.x), fmaxf(a.y, b.y), fminf(a.z, b.z), fmaxf(a.w, b.w));
+}
+constexpr float kInf = INFINITY;
+
+// Extent of the finite points among first, first + step, ... below n for this
+// thread; 4 points a round, their loads issued together (an index past n reads
+// point 0 and is not used).
+__device__ __forceinline__ float4 thread_extent(int n, const float* __restrict__ px, const float* __restrict__ py,
+                                                int first, int step) {
+  float4 e = make_float4(kInf, -kInf, kInf, -kInf);
+  constexpr int kU = 4;
+  for (int i0 = first; i0 < n; i0 += kU * step) {
     float x[kU], y[kU];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const int i = i0 + u * blockDim.x;
-      x[u] = px[i < n ? i : 0];
-      y[u] = py[i < n ? i : 0];
+      const int i = i0 + u * step < n && i0 + u * step >= 0 ? i0 + u * step : 0;
+      x[u] = px[i];
+      y[u] = py[i];
     }
 #pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      if (i0 + u * (int)blockDim.x >= n || !(isfinite(x[u]) && isfinite(y[u]))) continue;
-      x0 = fminf(x0, x[u]);
-      x1 = fmaxf(x1, x[u]);
-      y0 = fminf(y0, y[u]);
-      y1 = fmaxf(y1, y[u]);
-    }
+    for (int u = 0; u < kU; ++u)
+      if (i0 + u * step < n && isfinite(x[u]) && isfinite(y[u]))
+        e = join_extent(e, make_float4(x[u], x[u], y[u], y[u]));
   }
-  for (int off = 32; off > 0; off >>= 1) {
-    x0 = fminf(x0, __shfl_xor(x0, off, 64));
-    x1 = fmaxf(x1, __shfl_xor(x1, off, 64));
-    y0 = fminf(y0, __shfl_xor(y0, off, 64));
-    y1 = fmaxf(y1, __shfl_xor(y1, off, 64));
-  }
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
-    red[0][w] = x0;
-    red[1][w] = x1;
-    red[2][w] = y0;
-    red[3][w] = y1;
-  }
+  return e;
+}
+
+// (xmin, ymin, side of the square from there that holds every finite point, 0).
+__device__ __forceinline__ float4 extent_square(const float4& e) {
+  if (!(e.x <= e.y)) return make_float4(0.f, 0.f, 0.f, 0.f);  // no finite point
+  return make_float4(e.x, e.z, fmaxf(e.y - e.x, e.w - e.z), 0.f);
+}
+
+// Partial extents, one per workgroup (at most 64: the key kernel folds them).
+__global__ __launch_bounds__(kSortThreads) void plan_extent_kernel(int n, const float* __restrict__ px,
+                                                                   const float* __restrict__ py, float4* part) {
+  __shared__ float4 red[kSortThreads / 64];
+  float4 e = wave_extent(thread_extent(n, px, py, blockIdx.x * kSortThreads + threadIdx.x,
+                                       (int)gridDim.x * kSortThreads));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = e;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int k = 1; k < (int)(blockDim.x >> 6); ++k) {
-      x0 = fminf(x0, red[0][k]);
-      x1 = fmaxf(x1, red[1][k]);
-      y0 = fminf(y0, red[2][k]);
-      y1 = fmaxf(y1, red[3][k]);
-    }
-    if (!(x0 <= x1)) *ext = make_float4(0.f, 0.f, 0.f, 0.f);  // no finite point
-    else *ext = make_float4(x0, y0, fmaxf(x1 - x0, y1 - y0), 0.f);
-  }
+  if (threadIdx.x != 0) return;
+  for (int k = 1; k < kSortThreads / 64; ++k) e = join_extent(e, red[k]);
+  part[blockIdx.x] = e;
 }
 
 // Index of cell (x, y) along the Hilbert curve of a 2^kHilbertBits square grid:
@@ -93,200 +105,295 @@ __device__ __forceinline__ uint32_t hilbert_index(uint32_t x, uint32_t y) {
   return d;
 }
 
-// Sort key of every point: its Hilbert index on the grid over the extent; a
-// point with a non-finite coordinate takes the last key.
-__global__ void plan_keys_kernel(int n, const float* __restrict__ px, const float* __restrict__ py,
-                                 const float4* __restrict__ ext, uint32_t* __restrict__ key) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float4 e = *ext;
-  const float x = px[i], y = py[i];
+// Sort key of a point: its Hilbert index on the grid over the extent; a point
+// with a non-finite coordinate takes the last key.
+__device__ __forceinline__ uint32_t point_key(float x, float y, const float4& e) {
   constexpr float kMaxCell = (float)((1u << kHilbertBits) - 1);
-  uint32_t k = (1u << (2 * kHilbertBits)) - 1;
-  if (isfinite(x) && isfinite(y)) {
-    const float sc = e.z > 0.f ? (float)(1u << kHilbertBits) / e.z : 0.f;
-    const float qx = fminf(fmaxf((x - e.x) * sc, 0.f), kMaxCell);
-    const float qy = fminf(fmaxf((y - e.y) * sc, 0.f), kMaxCell);
-    k = hilbert_index((uint32_t)qx, (uint32_t)qy);
-  }
-  key[i] = k;
+  if (!(isfinite(x) && isfinite(y))) return (1u << (2 * kHilbertBits)) - 1;
+  const float sc = e.z > 0.f ? (float)(1u << kHilbertBits) / e.z : 0.f;
+  const float qx = fminf(fmaxf((x - e.x) * sc, 0.f), kMaxCell);
+  const float qy = fminf(fmaxf((y - e.y) * sc, 0.f), kMaxCell);
+  return hilbert_index((uint32_t)qx, (uint32_t)qy);
+}
+__device__ __forceinline__ int key_digit(uint32_t k, int pass) {
+  return (int)((k >> (kSortBits * pass)) & (kSortDigits - 1));
 }
 
-// Digit counts of one radix pass: hist[d nsb + b] = points of sort block b with
-// digit d.
-__global__ __launch_bounds__(kSortBlock) void sort_count_kernel(int n, int nsb, int shift,
-                                                                const uint32_t* __restrict__ key,
-                                                                int* __restrict__ hist) {
+// The digit counts of a workgroup's items, h in LDS: cleared, counted by the
+// caller between the two calls, then written as one row of hist.
+__device__ __forceinline__ void clear_counts(int* h) {
+  for (int d = threadIdx.x; d < kSortDigits; d += kSortThreads) h[d] = 0;
+  __syncthreads();
+}
+__device__ __forceinline__ void store_counts(const int* h, int* __restrict__ row) {
+  __syncthreads();
+  for (int d = threadIdx.x; d < kSortDigits; d += kSortThreads) row[d] = h[d];
+}
+
+// Keys of every point and the counts of their low digit: workgroup b takes the
+// items [b span, (b + 1) span).
+__global__ __launch_bounds__(kSortThreads) void plan_keys_kernel(int n, int span, const float* __restrict__ px,
+                                                                 const float* __restrict__ py,
+                                                                 const float4* __restrict__ part, int nparts,
+                                                                 uint32_t* __restrict__ key, int* __restrict__ hist) {
   __shared__ int h[kSortDigits];
-  for (int d = threadIdx.x; d < kSortDigits; d += kSortBlock) h[d] = 0;
-  __syncthreads();
-  const int e = blockIdx.x * kSortBlock + threadIdx.x;
-  if (e < n) atomicAdd(&h[(key[e] >> shift) & (kSortDigits - 1)], 1);
-  __syncthreads();
-  for (int d = threadIdx.x; d < kSortDigits; d += kSortBlock) hist[d * nsb + blockIdx.x] = h[d];
+  __shared__ float4 ext;
+  if (threadIdx.x < 64) {
+    const float4 e = wave_extent(part[min((int)threadIdx.x, nparts - 1)]);
+    if (threadIdx.x == 0) ext = extent_square(e);
+  }
+  clear_counts(h);
+  const float4 e = ext;
+  const int end = min(n, ((int)blockIdx.x + 1) * span);
+  for (int i = blockIdx.x * span + threadIdx.x; i < end; i += kSortThreads) {
+    const uint32_t k = point_key(px[i], py[i], e);
+    key[i] = k;
+    atomicAdd(&h[key_digit(k, 0)], 1);
+  }
+  store_counts(h, hist + (size_t)blockIdx.x * kSortDigits);
 }
 
-// Stable scatter of one radix pass. hist holds the exclusive scan of the counts
-// (digit-major), i.e. the first output position of each (digit, block). A
-// point's position adds the points of its block before it with the same digit:
-// those in earlier waves (per-wave digit counts in LDS) and those in lower lanes
-// of its own wave (the lanes that agree with it on all 8 digit bits, from 8
-// ballots). vin = nullptr stands for the identity.
-__global__ __launch_bounds__(kSortBlock) void sort_scatter_kernel(int n, int nsb, int shift,
-                                                                  const uint32_t* __restrict__ kin,
-                                                                  const int* __restrict__ vin,
-                                                                  const int* __restrict__ hist,
-                                                                  uint32_t* __restrict__ kout,
-                                                                  int* __restrict__ vout) {
-  constexpr int kWaves = kSortBlock / 64;
-  __shared__ int wc[kWaves][kSortDigits];
-  for (int i = threadIdx.x; i < kWaves * kSortDigits; i += kSortBlock) (&wc[0][0])[i] = 0;
+// Counts of a later digit, the items in the order of the pass before.
+__global__ __launch_bounds__(kSortThreads) void sort_count_kernel(int n, int span, int pass,
+                                                                  const uint32_t* __restrict__ key,
+                                                                  int* __restrict__ hist) {
+  __shared__ int h[kSortDigits];
+  clear_counts(h);
+  const int end = min(n, ((int)blockIdx.x + 1) * span);
+  for (int i = blockIdx.x * span + threadIdx.x; i < end; i += kSortThreads) atomicAdd(&h[key_digit(key[i], pass)], 1);
+  store_counts(h, hist + (size_t)blockIdx.x * kSortDigits);
+}
+
+// Exclusive prefix of one int per thread of the workgroup; ws: a wave's sums.
+__device__ __forceinline__ int block_exclusive(int v, int* ws) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int e = blockIdx.x * kSortBlock + threadIdx.x;
-  const bool valid = e < n;
-  const uint32_t k = valid ? kin[e] : 0u;
-  const int v = valid ? (vin ? vin[e] : e) : 0;
-  const int d = (int)((k >> shift) & (kSortDigits - 1));
+  int x = v;
+  for (int off = 1; off < 64; off <<= 1) {
+    const int y = __shfl_up(x, off, 64);
+    if (lane >= off) x += y;
+  }
+  if (lane == 63) ws[w] = x;
+  __syncthreads();
+  int before = 0;
+  for (int k = 0; k < w; ++k) before += ws[k];
+  return before + x - v;
+}
+
+// Stable ranking of one item per thread: the items of waves 0, 1, ... in turn,
+// those of a wave by lane. pos[d] (LDS) is the next free position of digit d.
+// The lanes that hold the same digit find each other by ballots; the first of
+// them takes positions for all. Returns the item's position (valid items only).
+__device__ __forceinline__ int rank_items(int d, bool valid, int* pos) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   unsigned long long m = __ballot(valid);
 #pragma unroll
-  for (int b = 0; b < 8; ++b) {
+  for (int b = 0; b < kSortBits; ++b) {
     const bool bit = (d >> b) & 1;
     const unsigned long long bb = __ballot(bit);
     m &= bit ? bb : ~bb;
   }
-  const int lower = __popcll(m & ((1ull << lane) - 1ull));
-  __syncthreads();  // counts cleared
-  if (valid && lower == 0) wc[w][d] = __popcll(m);
-  __syncthreads();
-  if (!valid) return;
-  int r = hist[d * nsb + blockIdx.x] + lower;
-  for (int q = 0; q < w; ++q) r += wc[q][d];
-  kout[r] = k;
-  vout[r] = v;
+  const int lower = __popcll(m & ((1ull << lane) - 1ull)), first = valid ? __ffsll((long long)m) - 1 : 0;
+  int p = 0;
+  for (int k = 0; k < kSortThreads / 64; ++k) {
+    if (k == w && valid && lower == 0) p = atomicAdd(&pos[d], __popcll(m));
+    __syncthreads();
+  }
+  return __shfl(p, first, 64) + lower;
 }
 
-// Sorted coordinates and both directions of the permutation: thread r handles
-// sorted position r < n (caller index sorted[r]) and padding position r in
-// [n, npad).
-__global__ void plan_points_kernel(int n, int npad, const float* __restrict__ px, const float* __restrict__ py,
-                                   const int* sorted, int* perm, int* __restrict__ irank, float* __restrict__ xs,
-                                   float* __restrict__ ys) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= npad) return;
-  if (r >= n) {
+// Stable scatter of one pass. Every workgroup folds the counts of all workgroups
+// (hist, one row each) into the first position of each digit for its own items:
+// the digits below, and the items of the digit in the workgroups before. The
+// last pass writes the sorted points instead of keys.
+template <bool kLast>
+__global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(int n, int span, int pass,
+                                                                    const uint32_t* __restrict__ kin,
+                                                                    const int* __restrict__ vin,
+                                                                    const int* __restrict__ hist,
+                                                                    uint32_t* __restrict__ kout,
+                                                                    int* __restrict__ vout,
+                                                                    const float* __restrict__ px,
+                                                                    const float* __restrict__ py,
+                                                                    int* __restrict__ irank, float* __restrict__ xs,
+                                                                    float* __restrict__ ys) {
+  __shared__ __attribute__((aligned(16))) int pos[kSortDigits];
+  __shared__ int wsum[kSortThreads / 64];
+  constexpr int kPer = kSortDigits / kSortThreads;  // digits of a thread
+  static_assert(kPer == 4, "one int4 of every row per thread");
+  const int nb = gridDim.x, blk = blockIdx.x;
+  const int4* row = reinterpret_cast<const int4*>(hist) + threadIdx.x;
+  int4 before = make_int4(0, 0, 0, 0), all = before;
+  for (int b0 = 0; b0 < nb; b0 += 8) {
+    int4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = row[(size_t)min(b0 + u, nb - 1) * kSortThreads];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (b0 + u >= nb) continue;
+      all.x += v[u].x, all.y += v[u].y, all.z += v[u].z, all.w += v[u].w;
+      if (b0 + u < blk) before.x += v[u].x, before.y += v[u].y, before.z += v[u].z, before.w += v[u].w;
+    }
+  }
+  const int base = block_exclusive(all.x + all.y + all.z + all.w, wsum);
+  const int p1 = base + all.x, p2 = p1 + all.y, p3 = p2 + all.z;
+  *reinterpret_cast<int4*>(&pos[kPer * threadIdx.x]) =
+      make_int4(base + before.x, p1 + before.y, p2 + before.z, p3 + before.w);
+  __syncthreads();
+  const int end = min(n, (blk + 1) * span);
+  for (int i0 = blk * span; i0 < end; i0 += kSortThreads) {
+    const int i = i0 + threadIdx.x;
+    const bool valid = i < end;
+    const uint32_t k = valid ? kin[i] : 0u;
+    const int v = valid ? (vin ? vin[i] : i) : 0;
+    const int r = rank_items(key_digit(k, pass), valid, pos);
+    if (!valid) continue;
+    if (kLast) {
+      vout[r] = v;
+      irank[v] = r;
+      xs[r] = px[v];
+      ys[r] = py[v];
+    } else {
+      kout[r] = k;
+      vout[r] = v;
+    }
+  }
+}
+
+// Boxes of one 64-point tile by a wave, lane = sorted point (x, y, live or
+// padding): of every 16-point subtile and 32-point chunk, and (kScaled) the block
+// centre and the scaled, block-centred coordinates (TilePlan::xc, yc, cen). A
+// non-finite coordinate gives an infinite box (never dropped), no valid point an
+// empty one (always dropped). The centre is the middle of the block's box, scaled
+// and rounded to a multiple of 2^-12 (a float); xc = sqrt(s2) x - centre is formed
+// in FP64 and rounded once.
+template <bool kScaled>
+__device__ __forceinline__ void tile_boxes(int tile, float x, float y, bool live, float s2, float4* cbox, float4* sbox,
+                                           float* __restrict__ xc, float* __restrict__ yc, float2* __restrict__ cen) {
+  const int lane = threadIdx.x & 63;
+  const unsigned long long bad = __ballot(live && !(isfinite(x) && isfinite(y)));
+  float4 e = live && isfinite(x) && isfinite(y) ? make_float4(x, x, y, y) : make_float4(kInf, -kInf, kInf, -kInf);
+  for (int off = kSubTile / 2; off > 0; off >>= 1) {
+    e.x = fminf(e.x, __shfl_xor(e.x, off, 64));
+    e.y = fmaxf(e.y, __shfl_xor(e.y, off, 64));
+    e.z = fminf(e.z, __shfl_xor(e.z, off, 64));
+    e.w = fmaxf(e.w, __shfl_xor(e.w, off, 64));
+  }
+  if ((bad >> (lane & ~(kSubTile - 1))) & ((1ull << kSubTile) - 1ull)) e = make_float4(-kInf, kInf, -kInf, kInf);
+  if (lane % kSubTile == 0) sbox[tile * kSubsPerTile + lane / kSubTile] = e;
+  static_assert(kChunk == 2 * kSubTile && kRowTile == 2 * kChunk, "pairs of boxes");
+  auto pair = [](const float4& a, int off) {
+    return join_extent(a, make_float4(__shfl_xor(a.x, off, 64), __shfl_xor(a.y, off, 64), __shfl_xor(a.z, off, 64),
+                                      __shfl_xor(a.w, off, 64)));
+  };
+  e = pair(e, kSubTile);
+  if (lane % kChunk == 0) cbox[tile * kChunksPerTile + lane / kChunk] = e;
+  if (kScaled) {
+    e = pair(e, kChunk);
+    const double sg = sqrt((double)s2);
+    const double mx = 0.5 * ((double)e.x + (double)e.y), my = 0.5 * ((double)e.z + (double)e.w);
+    const float cx = isfinite(mx) ? (float)(rint(mx * sg * 4096.0) / 4096.0) : 0.f;
+    const float cy = isfinite(my) ? (float)(rint(my * sg * 4096.0) / 4096.0) : 0.f;
+    const int r = tile * kRowTile + lane;
+    xc[r] = (float)((double)(live ? x : 0.f) * sg - (double)cx);
+    yc[r] = (float)((double)(live ? y : 0.f) * sg - (double)cy);
+    if (lane == 0) cen[tile] = make_float2(cx, cy);
+  }
+}
+
+template <bool kScaled>
+__global__ __launch_bounds__(256) void plan_tiles_kernel(int n, int nrt, float s2, int* perm, float* __restrict__ xs,
+                                                         float* __restrict__ ys, float4* cbox, float4* sbox,
+                                                         float* __restrict__ xc, float* __restrict__ yc,
+                                                         float2* __restrict__ cen) {
+  const int tile = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (tile >= nrt) return;
+  const int r = tile * kRowTile + (threadIdx.x & 63);
+  const bool live = r < n;
+  const float x = live ? xs[r] : 0.f, y = live ? ys[r] : 0.f;
+  if (!live) {
     xs[r] = 0.f;
     ys[r] = 0.f;
     perm[r] = -1;
-    return;
   }
-  const int i = sorted[r];
-  if ((unsigned)i >= (unsigned)n) {  // not a permutation: leave a hole, never an out-of-range write
-    xs[r] = ys[r] = NAN;
-    perm[r] = -1;
-    return;
+  tile_boxes<kScaled>(tile, x, y, live, s2, cbox, sbox, xc, yc, cen);
+}
+
+// ---- lists of live chunks ----
+
+// Subtile masks of one (row tile, chunk) pair: bit t when subtile t sees the
+// chunk, bit 4 + t when that pair also needs the lo part; 0 when none does.
+__device__ __forceinline__ unsigned pair_mask(const float4 (&sb)[kSubsPerTile], const float4& rb, const float4& q,
+                                              float s2, float threshold, float lo_threshold) {
+  unsigned mask = 0u;
+  if (boxes_live(rb, q, s2, threshold)) {
+#pragma unroll
+    for (int t = 0; t < kSubsPerTile; ++t) {
+      mask |= (boxes_live(sb[t], q, s2, threshold) ? 1u : 0u) << t;
+      mask |= (boxes_live(sb[t], q, s2, lo_threshold) ? 1u : 0u) << (4 + t);
+    }
   }
-  perm[r] = i;
-  irank[i] = r;
-  xs[r] = px[i];
-  ys[r] = py[i];
+  return (mask & 0xfu) != 0u ? mask : 0u;
+}
+__device__ __forceinline__ float4 row_box(const float4* __restrict__ cbox, int r) {
+  float4 rb = cbox[kChunksPerTile * r];
+#pragma unroll
+  for (int t = 1; t < kChunksPerTile; ++t) rb = join_extent(rb, cbox[kChunksPerTile * r + t]);
+  return rb;
 }
 
-// Scaled, block-centred coordinates (TilePlan::xc, yc, cen): thread r handles
-// sorted position r. The block centre is the middle of the block's box, scaled
-// and rounded to a multiple of 2^-12 (a float), and xc = sqrt(s2) x - centre is
-// formed in FP64 and rounded once.
-__global__ void plan_scaled_kernel(int npad, const float* __restrict__ xs, const float* __restrict__ ys,
-                                   const float4* __restrict__ cbox, float s2, float* __restrict__ xc,
-                                   float* __restrict__ yc, float2* __restrict__ cen) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= npad) return;
-  const int b = r / kRowTile;
-  const double sg = sqrt((double)s2);
-  const float4 u = cbox[kChunksPerTile * b], v = cbox[kChunksPerTile * b + 1];
-  const double mx = 0.5 * ((double)fminf(u.x, v.x) + (double)fmaxf(u.y, v.y));
-  const double my = 0.5 * ((double)fminf(u.z, v.z) + (double)fmaxf(u.w, v.w));
-  const float cx = isfinite(mx) ? (float)(rint(mx * sg * 4096.0) / 4096.0) : 0.f;
-  const float cy = isfinite(my) ? (float)(rint(my * sg * 4096.0) / 4096.0) : 0.f;
-  xc[r] = (float)((double)xs[r] * sg - (double)cx);
-  yc[r] = (float)((double)ys[r] * sg - (double)cy);
-  if (r == b * kRowTile) cen[b] = make_float2(cx, cy);
-}
-
-// Bounding box of the valid points in [j0, j1); a non-finite coordinate gives
-// an infinite box (never dropped), no valid point an empty one (always dropped).
-__device__ __forceinline__ float4 point_box(const float* __restrict__ xs, const float* __restrict__ ys, int j0,
-                                            int j1) {
-  float x0 = INFINITY, x1 = -INFINITY, y0 = INFINITY, y1 = -INFINITY;
-  bool bad = false;
-  for (int j = j0; j < j1; ++j) {
-    const float x = xs[j], y = ys[j];
-    bad |= !(isfinite(x) && isfinite(y));
-    x0 = fminf(x0, x);
-    x1 = fmaxf(x1, x);
-    y0 = fminf(y0, y);
-    y1 = fmaxf(y1, y);
-  }
-  return bad ? make_float4(-INFINITY, INFINITY, -INFINITY, INFINITY) : make_float4(x0, x1, y0, y1);
-}
-
-// Boxes of each chunk of 32 sorted points and of its two 16-point subtiles.
-__global__ void plan_boxes_kernel(int n, int nch, const float* __restrict__ xs, const float* __restrict__ ys,
-                                  float4* cbox, float4* sbox) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= nch) return;
-  const int j0 = c * kChunk, jm = min(n, j0 + kSubTile), j1 = min(n, j0 + kChunk);
-  const float4 a = point_box(xs, ys, j0, jm), b = point_box(xs, ys, jm, j1);
-  sbox[2 * c] = a;
-  sbox[2 * c + 1] = b;
-  cbox[c] = make_float4(fminf(a.x, b.x), fmaxf(a.y, b.y), fminf(a.z, b.z), fmaxf(a.w, b.w));
-}
-
-// One wave per row tile: ascending list of live chunks by ballot compaction,
-// each entry with the mask of the subtiles that see the chunk and the mask of
-// those that also need the lo part (gap below lo_threshold).
-__global__ __launch_bounds__(64) void plan_lists_kernel(int nrt, int nch, const float4* __restrict__ cbox,
-                                                        const float4* __restrict__ sbox, float s2, float threshold,
-                                                        float lo_threshold, int* count, uint32_t* list, int* roww) {
-  const int r = blockIdx.x;
-  if (r >= nrt) return;
-  const int lane = threadIdx.x;
+// One workgroup of four waves per row tile: the ascending list of its live
+// chunks, 1024 chunks a round (four box loads of a lane in flight), compacted by
+// ballots; the row tile's cost.
+constexpr int kListBatch = 4;
+__global__ __launch_bounds__(256) void plan_lists_kernel(int nch, const float4* __restrict__ cbox,
+                                                         const float4* __restrict__ sbox, float s2, float threshold,
+                                                         float lo_threshold, int* count, uint32_t* list, int* roww) {
+  __shared__ int cnt_s[4 * kListBatch];
+  __shared__ int cost_s[4];
+  const int r = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   float4 sb[kSubsPerTile];
 #pragma unroll
   for (int t = 0; t < kSubsPerTile; ++t) sb[t] = sbox[kSubsPerTile * r + t];
-  float4 rb = cbox[kChunksPerTile * r];
-#pragma unroll
-  for (int t = 1; t < kChunksPerTile; ++t) {
-    const float4 c = cbox[kChunksPerTile * r + t];
-    rb = make_float4(fminf(rb.x, c.x), fmaxf(rb.y, c.y), fminf(rb.z, c.z), fmaxf(rb.w, c.w));
-  }
+  const float4 rb = row_box(cbox, r);
   uint32_t* out = list + (size_t)r * nch;
   int base = 0, cost = 0;
-  for (int c0 = 0; c0 < nch; c0 += 64) {
-    const int c = c0 + lane;
-    unsigned mask = 0u;
-    if (c < nch) {
-      const float4 q = cbox[c];
-      if (boxes_live(rb, q, s2, threshold)) {
+  for (int c0 = 0; c0 < nch; c0 += 4 * kListBatch * 64) {
+    float4 q[kListBatch];
+    unsigned mask[kListBatch];
+    unsigned long long bal[kListBatch];
 #pragma unroll
-        for (int t = 0; t < kSubsPerTile; ++t) {
-          mask |= (boxes_live(sb[t], q, s2, threshold) ? 1u : 0u) << t;
-          mask |= (boxes_live(sb[t], q, s2, lo_threshold) ? 1u : 0u) << (4 + t);
-        }
+    for (int u = 0; u < kListBatch; ++u) q[u] = cbox[min(c0 + (wv * kListBatch + u) * 64 + lane, nch - 1)];
+#pragma unroll
+    for (int u = 0; u < kListBatch; ++u) {
+      const int c = c0 + (wv * kListBatch + u) * 64 + lane;
+      mask[u] = c < nch ? pair_mask(sb, rb, q[u], s2, threshold, lo_threshold) : 0u;
+      bal[u] = __ballot(mask[u] != 0u);
+      if (lane == 0) cnt_s[wv * kListBatch + u] = __popcll(bal[u]);
+    }
+    __syncthreads();
+    int before[kListBatch];
+#pragma unroll
+    for (int b = 0; b < 4 * kListBatch; ++b) {
+#pragma unroll
+      for (int u = 0; u < kListBatch; ++u)
+        if (b == wv * kListBatch + u) before[u] = base;
+      base += cnt_s[b];
+    }
+#pragma unroll
+    for (int u = 0; u < kListBatch; ++u)
+      if (mask[u]) {
+        const uint32_t e = (uint32_t)(c0 + (wv * kListBatch + u) * 64 + lane) | (mask[u] << 16);
+        out[before[u] + __popcll(bal[u] & ((1ull << lane) - 1ull))] = e;
+        cost += unit_cost(e);
       }
-    }
-    const bool live = (mask & 0xfu) != 0u;
-    const unsigned long long bal = __ballot(live);
-    const uint32_t e = (uint32_t)c | (mask << 16);
-    if (live) {
-      out[base + __popcll(bal & ((1ull << lane) - 1ull))] = e;
-      cost += unit_cost(e);
-    }
-    base += __popcll(bal);
+    __syncthreads();  // cnt_s is rewritten by the next round
   }
-  for (int off = 32; off > 0; off >>= 1) cost += __shfl_xor(cost, off, 64);
-  if (lane == 0) {
+  cost = warp_sum(cost);
+  if (lane == 0) cost_s[wv] = cost;
+  __syncthreads();
+  if (threadIdx.x == 0) {
     count[r] = base;
-    roww[r] = kCostRowTile + cost;
+    roww[r] = kCostRowTile + cost_s[0] + cost_s[1] + cost_s[2] + cost_s[3];
   }
 }
 
@@ -365,6 +472,25 @@ __device__ __forceinline__ int wave_of_unit(int u, const int* wunit, int nw) {
   return lo;
 }
 
+// Units of a row tile's list L (cnt of them) whose cost before them, the row
+// tile's own included, is below rem: by one wave, 64 units at a time.
+__device__ __forceinline__ int units_before(const uint32_t* L, int cnt, long long rem, int lane) {
+  long long before = kCostRowTile;  // cost up to the current group of 64 units
+  int k = 0;
+  for (int k0 = 0; k0 < cnt && before < rem; k0 += 64) {
+    const int kk = k0 + lane;
+    const int c = kk < cnt ? unit_cost(L[kk]) : 0;
+    int x = c;  // inclusive prefix within the group
+    for (int off = 1; off < 64; off <<= 1) {
+      const int y = __shfl_up(x, off, 64);
+      if (lane >= off) x += y;
+    }
+    k += __popcll(__ballot(kk < cnt && before + (x - c) < rem));
+    before += __shfl(x, 63, 64);
+  }
+  return k;
+}
+
 // First unit of each wave b in [0, nw]: the first unit whose exclusive cost
 // prefix reaches the wave's target, wtot x (round weight of the waves below b)
 // / (that of all nw waves). A row tile's own cost counts before its first unit.
@@ -381,22 +507,8 @@ __global__ __launch_bounds__(256) void plan_wunit_kernel(int nrt, int nch, int n
     const int mid = (lo + hi + 1) >> 1;
     if (rowwoff[mid] <= t) lo = mid; else hi = mid - 1;
   }
-  const int r = lo, cnt = count[r];
-  const long long rem = t - rowwoff[r];
-  const uint32_t* L = list + (size_t)r * nch;
-  long long before = kCostRowTile;  // cost of the row tile up to the current group of 64 units
-  int k = 0;
-  for (int k0 = 0; k0 < cnt && before < rem; k0 += 64) {
-    const int kk = k0 + lane;
-    const int c = kk < cnt ? unit_cost(L[kk]) : 0;
-    int x = c;  // inclusive prefix within the group
-    for (int off = 1; off < 64; off <<= 1) {
-      const int y = __shfl_up(x, off, 64);
-      if (lane >= off) x += y;
-    }
-    k += __popcll(__ballot(kk < cnt && before + (x - c) < rem));
-    before += __shfl(x, 63, 64);
-  }
+  const int r = lo;
+  const int k = units_before(list + (size_t)r * nch, count[r], t - rowwoff[r], lane);
   if (lane == 0) wunit[b] = unit_off[r] + k;
 }
 
@@ -454,6 +566,292 @@ __global__ void plan_wdesc_kernel(int nw, const int* wunit, const int* unit_off,
   wrest[w] = u1 - (off + ke);
 }
 
+// ---- the same split with fewer launches, for up to kFoldRows row tiles ----
+
+constexpr int kFoldRows = 4096;
+
+// Exclusive prefixes of the row tiles' unit counts and costs, off and woff (LDS,
+// nrt <= kFoldRows), by a workgroup of NT threads; returns the total cost.
+template <int NT>
+__device__ __forceinline__ long long fold_rows(int nrt, const int* __restrict__ count, const int* __restrict__ roww,
+                                               int* off, long long* woff) {
+  __shared__ int cs[NT / 64];
+  __shared__ long long ws[NT / 64];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  for (int r = tid; r < nrt; r += NT) {
+    off[r] = count[r];
+    woff[r] = roww[r];
+  }
+  __syncthreads();
+  const int per = cdiv(nrt, NT), r0 = min(tid * per, nrt), r1 = min(r0 + per, nrt);
+  int c = 0;
+  long long v = 0;
+  for (int r = r0; r < r1; ++r) {
+    c += off[r];
+    v += woff[r];
+  }
+  int xc = c;
+  long long xv = v;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int yc = __shfl_up(xc, o, 64);
+    const long long yv = __shfl_up(xv, o, 64);
+    if (lane >= o) {
+      xc += yc;
+      xv += yv;
+    }
+  }
+  if (lane == 63) {
+    cs[w] = xc;
+    ws[w] = xv;
+  }
+  __syncthreads();
+  xc -= c;
+  xv -= v;
+  long long total = 0;
+  for (int k = 0; k < NT / 64; ++k) {
+    if (k < w) {
+      xc += cs[k];
+      xv += ws[k];
+    }
+    total += ws[k];
+  }
+  for (int r = r0; r < r1; ++r) {
+    const int cr = off[r];
+    const long long vr = woff[r];
+    off[r] = xc;
+    woff[r] = xv;
+    xc += cr;
+    xv += vr;
+  }
+  __syncthreads();
+  return total;
+}
+
+// Largest index k in [0, n) with v[k] <= u (v ascending, v[0] <= u).
+template <class T>
+__device__ __forceinline__ int last_at_most(const T* v, int n, T u) {
+  int lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (v[mid] <= u) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
+// plan_wunit_kernel with the prefixes of the row tiles formed by every workgroup
+// itself; the first one writes unit_off.
+__global__ __launch_bounds__(256) void plan_wunit_fold_kernel(int nrt, int nch, int nw, int wround, const int* count,
+                                                              const uint32_t* __restrict__ list, const int* roww,
+                                                              int* unit_off, int* wunit) {
+  __shared__ int off[kFoldRows];
+  __shared__ long long woff[kFoldRows];
+  const long long wtot = fold_rows<256>(nrt, count, roww, off, woff);
+  if (blockIdx.x == 0)
+    for (int r = threadIdx.x; r < nrt; r += 256) unit_off[r] = off[r];
+  const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (b > nw) return;
+  const long long t = wtot * wave_weight_below(b, wround) / wave_weight_below(nw, wround);
+  const int r = last_at_most(woff, nrt, t), cnt = count[r];
+  const int k = units_before(list + (size_t)r * nch, cnt, t - woff[r], lane);
+  if (lane == 0) wunit[b] = off[r] + k;
+}
+
+// Ranges and partial slots of all waves, and the slots of every row tile, by one
+// workgroup of 1024 threads: off (first unit of each row tile), wunit, wrow and
+// wslot in LDS (wrow and wslot written here), count in LDS or global memory.
+__device__ __forceinline__ void finish_waves(int nrt, int nw, const int* off, const int* count, const int* wunit,
+                                             int* wrow, int* wslot, int2* __restrict__ rslot,
+                                             int4* __restrict__ wdesc, int* __restrict__ wrest) {
+  __shared__ int ws[1024 / 64];
+  const int tid = threadIdx.x;
+  for (int w = tid; w < nw; w += 1024) {
+    const int u0 = wunit[w], u1 = wunit[w + 1];
+    int r0 = -1, rows = 0;
+    if (u0 < u1) {
+      r0 = last_at_most(off, nrt, u0);
+      rows = last_at_most(off, nrt, u1 - 1) - r0 + 1;
+    }
+    wrow[w] = r0;
+    wslot[w] = rows;
+  }
+  __syncthreads();
+  const int per = cdiv(nw, 1024), w0 = min(tid * per, nw), w1 = min(w0 + per, nw);
+  int sum = 0;
+  for (int w = w0; w < w1; ++w) sum += wslot[w];
+  int run = block_exclusive(sum, ws);
+  for (int w = w0; w < w1; ++w) {
+    const int v = wslot[w];
+    wslot[w] = run;
+    run += v;
+  }
+  __syncthreads();
+  for (int r = tid; r < nrt; r += 1024) {
+    const int a = off[r], c = count[r];
+    int2 sl = make_int2(0, 0);
+    if (c > 0) {
+      const int wf = last_at_most(wunit, nw, a), wl = last_at_most(wunit, nw, a + c - 1);
+      const int s0 = wslot[wf] + (r - wrow[wf]), s1 = wslot[wl] + (r - wrow[wl]);
+      sl = make_int2(s0, s1 - s0 + 1);
+    }
+    rslot[r] = sl;
+  }
+  for (int w = tid; w < nw; w += 1024) {
+    const int u0 = wunit[w], u1 = wunit[w + 1], r = wrow[w];
+    int4 dsc = make_int4(-1, wslot[w], 0, 0);
+    int rest = 0;
+    if (u0 < u1 && r >= 0) {
+      const int o = off[r], ke = min(u1, o + count[r]) - o;
+      dsc = make_int4(r, wslot[w], u0 - o, ke);
+      rest = u1 - (o + ke);
+    }
+    wdesc[w] = dsc;
+    wrest[w] = rest;
+  }
+}
+
+__global__ __launch_bounds__(1024) void plan_finish_kernel(int nrt, int nw, const int* __restrict__ unit_off,
+                                                           const int* __restrict__ count,
+                                                           const int* __restrict__ wunit_g, int2* __restrict__ rslot,
+                                                           int4* __restrict__ wdesc, int* __restrict__ wrest) {
+  __shared__ int off[kFoldRows];
+  __shared__ int wunit[kMaxPlanWaves + 1], wrow[kMaxPlanWaves], wslot[kMaxPlanWaves];
+  for (int r = threadIdx.x; r < nrt; r += 1024) off[r] = unit_off[r];
+  for (int w = threadIdx.x; w <= nw; w += 1024) wunit[w] = wunit_g[w];
+  __syncthreads();
+  finish_waves(nrt, nw, off, count, wunit, wrow, wslot, rslot, wdesc, wrest);
+}
+
+// ---- small point sets: the whole plan by one workgroup ----
+
+// Up to kSmallPoints points a launch costs more than its work: one workgroup of
+// 1024 threads keeps the keys, the order and the split in LDS and writes the plan
+// (or, without kPlan, the sorted points and boxes).
+constexpr int kSmallPoints = 4096;
+constexpr int kSmallTiles = kSmallPoints / kRowTile, kSmallChunks = kSmallTiles * kChunksPerTile;
+static_assert(kSortThreads == 1024, "one workgroup size for the sort and the small plan");
+
+template <bool kPlan>
+__global__ __launch_bounds__(kSortThreads) void plan_small_kernel(int n, const float* __restrict__ px,
+                                                                  const float* __restrict__ py, TilePlan P, int* perm,
+                                                                  int* irank, float s2, float threshold,
+                                                                  float lo_threshold) {
+  __shared__ union {
+    struct {
+      uint32_t key[kSmallPoints];
+      int pos[kSortDigits];
+    } sort;
+    struct {
+      unsigned short cost[kSmallTiles][kSmallChunks];  // cost of a row tile before each of its units
+      int wunit[8 * kSmallTiles + 1], wrow[8 * kSmallTiles], wslot[8 * kSmallTiles];
+      int off[kSmallTiles], count[kSmallTiles], roww[kSmallTiles];
+      long long woff[kSmallTiles];
+    } plan;
+  } L;
+  __shared__ unsigned short val[2][kSmallPoints];
+  __shared__ float4 red[kSortThreads / 64];
+  __shared__ int ws[kSortThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  constexpr int kWaves = kSortThreads / 64;
+  {
+    const float4 e = wave_extent(thread_extent(n, px, py, tid, kSortThreads));
+    if (lane == 0) red[w] = e;
+    __syncthreads();
+  }
+  float4 ext = red[0];
+  for (int k = 1; k < kWaves; ++k) ext = join_extent(ext, red[k]);
+  ext = extent_square(ext);
+  for (int i = tid; i < n; i += kSortThreads) L.sort.key[i] = point_key(px[i], py[i], ext);
+  for (int pass = 0; pass < kSortPasses; ++pass) {
+    for (int d = tid; d < kSortDigits; d += kSortThreads) L.sort.pos[d] = 0;
+    __syncthreads();
+    for (int i = tid; i < n; i += kSortThreads) atomicAdd(&L.sort.pos[key_digit(L.sort.key[i], pass)], 1);
+    __syncthreads();
+    constexpr int kPer = kSortDigits / kSortThreads;
+    int c[kPer], sum = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      c[k] = L.sort.pos[kPer * tid + k];
+      sum += c[k];
+    }
+    int run = block_exclusive(sum, ws);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      L.sort.pos[kPer * tid + k] = run;
+      run += c[k];
+    }
+    __syncthreads();
+    for (int i0 = 0; i0 < n; i0 += kSortThreads) {
+      const int i = i0 + tid;
+      const bool valid = i < n;
+      const int v = valid ? (pass == 0 ? i : (int)val[(pass - 1) & 1][i]) : 0;
+      const int r = rank_items(key_digit(L.sort.key[v], pass), valid, L.sort.pos);
+      if (valid) val[pass & 1][r] = (unsigned short)v;
+    }
+    __syncthreads();
+  }
+  const unsigned short* order = val[(kSortPasses - 1) & 1];
+  for (int tile = w; tile < P.nrt; tile += kWaves) {
+    const int r = tile * kRowTile + lane;
+    const bool live = r < n;
+    const int v = live ? (int)order[r] : -1;
+    const float x = live ? px[v] : 0.f, y = live ? py[v] : 0.f;
+    perm[r] = v;
+    if (live) irank[v] = r;
+    P.xs[r] = x;
+    P.ys[r] = y;
+    tile_boxes<kPlan>(tile, x, y, live, s2, P.cbox, P.sbox, P.xc, P.yc, P.cen);
+  }
+  if (!kPlan) return;
+  __syncthreads();  // the boxes are written; the keys are not needed any more
+  for (int r = w; r < P.nrt; r += kWaves) {
+    float4 sb[kSubsPerTile];
+#pragma unroll
+    for (int t = 0; t < kSubsPerTile; ++t) sb[t] = P.sbox[kSubsPerTile * r + t];
+    const float4 rb = row_box(P.cbox, r);
+    uint32_t* out = P.list + (size_t)r * P.nch;
+    int base = 0, before = kCostRowTile;  // units so far, and the row tile's cost up to them
+    for (int c0 = 0; c0 < P.nch; c0 += 64) {
+      const int c = c0 + lane;
+      const unsigned mask = c < P.nch ? pair_mask(sb, rb, P.cbox[c], s2, threshold, lo_threshold) : 0u;
+      const unsigned long long bal = __ballot(mask != 0u);
+      const uint32_t e = (uint32_t)c | (mask << 16);
+      const int cost = mask ? unit_cost(e) : 0;
+      int x = cost;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+      }
+      if (mask) {
+        const int k = base + __popcll(bal & ((1ull << lane) - 1ull));
+        out[k] = e;
+        L.plan.cost[r][k] = (unsigned short)(before + x - cost);
+      }
+      base += __popcll(bal);
+      before += __shfl(x, 63, 64);
+    }
+    if (lane == 0) {
+      P.count[r] = L.plan.count[r] = base;
+      L.plan.roww[r] = before;
+    }
+  }
+  __syncthreads();
+  const int nrt = P.nrt, nw = P.nw;
+  const long long wtot = fold_rows<kSortThreads>(nrt, L.plan.count, L.plan.roww, L.plan.off, L.plan.woff);
+  for (int b = tid; b <= nw; b += kSortThreads) {
+    const long long t = wtot * wave_weight_below(b, P.wround) / wave_weight_below(nw, P.wround);
+    const int r = last_at_most(L.plan.woff, nrt, t);
+    const long long rem = t - L.plan.woff[r];
+    int lo = 0, hi = L.plan.count[r];  // units whose cost before them is below rem
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if ((long long)L.plan.cost[r][mid] < rem) lo = mid + 1; else hi = mid;
+    }
+    L.plan.wunit[b] = L.plan.off[r] + lo;
+  }
+  __syncthreads();
+  finish_waves(nrt, nw, L.plan.off, L.plan.count, L.plan.wunit, L.plan.wrow, L.plan.wslot, P.rslot, P.wdesc, P.wrest);
+}
+
 // Compute units of the current device (queried once per device).
 static int compute_units() {
   static int cached[64] = {};
@@ -467,44 +865,48 @@ static int compute_units() {
   return cached[dev];
 }
 
-int plan_sort(TilePlan& p, int n, const float* px, const float* py, hipStream_t stream) {
-  GPL_REQUIRE(n >= 1, "plan needs at least one point");
+// Sort of more than kSmallPoints points, and (kScaled) the scaled coordinates.
+template <bool kScaled>
+static int sort_points(TilePlan& p, int n, const float* px, const float* py, float s2, hipStream_t stream) {
   int* perm = const_cast<int*>(p.perm);
   int* irank = const_cast<int*>(p.irank);
-  const int nsb = sort_blocks(n);
-  // sort scratch in buffers that are written only after the sort: the extent in
-  // cbox[0], the keys in xc and yc, the scan totals in total
+  const int span = sort_span(n), nb = cdiv(n, span);
+  // sort scratch in buffers that are written only after the sort: the partial
+  // extents in cbox, the keys in xc and yc
   float4* ext = p.cbox;
-  hipLaunchKernelGGL(plan_extent_kernel, dim3(1), dim3(1024), 0, stream, n, px, py, ext);
+  uint32_t *k0 = reinterpret_cast<uint32_t*>(p.xc), *k1 = reinterpret_cast<uint32_t*>(p.yc);
+  hipLaunchKernelGGL(plan_extent_kernel, dim3(nb), dim3(kSortThreads), 0, stream, n, px, py, ext);
   GPL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(plan_keys_kernel, dim3(cdiv(n, 256)), dim3(256), 0, stream, n, px, py, ext,
-                     reinterpret_cast<uint32_t*>(p.xc));
+  hipLaunchKernelGGL(plan_keys_kernel, dim3(nb), dim3(kSortThreads), 0, stream, n, span, px, py, ext, nb, k0, p.shist);
   GPL_LAUNCH_CHECK();
-  // ping-pong: keys xc <-> yc, caller indices (identity) -> sval <-> perm
-  uint32_t* kin = reinterpret_cast<uint32_t*>(p.xc);
-  uint32_t* kout = reinterpret_cast<uint32_t*>(p.yc);
-  const int* vin = nullptr;
-  int* vout = p.sval;
-  for (int pass = 0; pass < kSortPasses; ++pass) {
-    hipLaunchKernelGGL(sort_count_kernel, dim3(nsb), dim3(kSortBlock), 0, stream, n, nsb, 8 * pass, kin, p.shist);
-    GPL_LAUNCH_CHECK();
-    hipLaunchKernelGGL(plan_scan_kernel<int>, dim3(1), dim3(1024), 0, stream, kSortDigits * nsb, p.shist, p.shist,
-                       p.total);
-    GPL_LAUNCH_CHECK();
-    hipLaunchKernelGGL(sort_scatter_kernel, dim3(nsb), dim3(kSortBlock), 0, stream, n, nsb, 8 * pass, kin, vin,
-                       p.shist, kout, vout);
-    GPL_LAUNCH_CHECK();
-    std::swap(kin, kout);
-    vin = vout;
-    vout = vout == p.sval ? perm : p.sval;
-  }
-  hipLaunchKernelGGL(plan_points_kernel, dim3(cdiv(p.npad, 256)), dim3(256), 0, stream, n, p.npad, px, py, vin, perm,
-                     irank, p.xs, p.ys);
+  static_assert(kSortPasses == 2, "a first and a last pass");
+  hipLaunchKernelGGL(sort_scatter_kernel<false>, dim3(nb), dim3(kSortThreads), 0, stream, n, span, 0, k0, nullptr,
+                     p.shist, k1, p.sval, px, py, irank, p.xs, p.ys);
   GPL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(plan_boxes_kernel, dim3(cdiv(p.nch, 256)), dim3(256), 0, stream, n, p.nch, p.xs, p.ys, p.cbox,
-                     p.sbox);
+  hipLaunchKernelGGL(sort_count_kernel, dim3(nb), dim3(kSortThreads), 0, stream, n, span, 1, k1, p.shist);
+  GPL_LAUNCH_CHECK();
+  hipLaunchKernelGGL(sort_scatter_kernel<true>, dim3(nb), dim3(kSortThreads), 0, stream, n, span, 1, k1, p.sval,
+                     p.shist, nullptr, perm, px, py, irank, p.xs, p.ys);
+  GPL_LAUNCH_CHECK();
+  hipLaunchKernelGGL(plan_tiles_kernel<kScaled>, dim3(cdiv(p.nrt, 4)), dim3(256), 0, stream, n, p.nrt, s2, perm, p.xs,
+                     p.ys, p.cbox, p.sbox, p.xc, p.yc, p.cen);
   GPL_LAUNCH_CHECK();
   return GPL_OK;
+}
+
+template <bool kPlan>
+static int small_plan(TilePlan& p, int n, const float* px, const float* py, float s2, float threshold,
+                      float lo_threshold, hipStream_t stream) {
+  hipLaunchKernelGGL(plan_small_kernel<kPlan>, dim3(1), dim3(kSortThreads), 0, stream, n, px, py, p,
+                     const_cast<int*>(p.perm), const_cast<int*>(p.irank), s2, threshold, lo_threshold);
+  GPL_LAUNCH_CHECK();
+  return GPL_OK;
+}
+
+int plan_sort(TilePlan& p, int n, const float* px, const float* py, hipStream_t stream) {
+  GPL_REQUIRE(n >= 1, "plan needs at least one point");
+  if (n <= kSmallPoints) return small_plan<false>(p, n, px, py, 1.f, 0.f, 0.f, stream);
+  return sort_points<false>(p, n, px, py, 1.f, stream);
 }
 
 int plan_build(TilePlan& p, int n, const float* px, const float* py, const gpl_grid* grid, float s2, float threshold,
@@ -513,15 +915,23 @@ int plan_build(TilePlan& p, int n, const float* px, const float* py, const gpl_g
     const int m = grid->n * grid->ss;
     GPL_REQUIRE(m > 0 && (long)m * m == n, "grid does not match n=%d", n);
   }
+  GPL_REQUIRE(n >= 1, "plan needs at least one point");
   GPL_REQUIRE(p.nch <= kMaxPlanChunks, "n=%d exceeds the product's limit of %d points", n, kMaxPlanChunks * kChunk);
   p.wround = 4 * compute_units();
-  GPL_TRY(plan_sort(p, n, px, py, stream));
-  hipLaunchKernelGGL(plan_scaled_kernel, dim3(cdiv(p.npad, 256)), dim3(256), 0, stream, p.npad, p.xs, p.ys, p.cbox, s2,
-                     p.xc, p.yc, p.cen);
+  if (n <= kSmallPoints) return small_plan<true>(p, n, px, py, s2, threshold, lo_threshold, stream);
+  GPL_TRY(sort_points<true>(p, n, px, py, s2, stream));
+  hipLaunchKernelGGL(plan_lists_kernel, dim3(p.nrt), dim3(256), 0, stream, p.nch, p.cbox, p.sbox, s2, threshold,
+                     lo_threshold, p.count, p.list, p.roww);
   GPL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(plan_lists_kernel, dim3(p.nrt), dim3(64), 0, stream, p.nrt, p.nch, p.cbox, p.sbox, s2,
-                     threshold, lo_threshold, p.count, p.list, p.roww);
-  GPL_LAUNCH_CHECK();
+  if (p.nrt <= kFoldRows) {
+    hipLaunchKernelGGL(plan_wunit_fold_kernel, dim3(cdiv(p.nw + 1, 4)), dim3(256), 0, stream, p.nrt, p.nch, p.nw,
+                       p.wround, p.count, p.list, p.roww, p.unit_off, p.wunit);
+    GPL_LAUNCH_CHECK();
+    hipLaunchKernelGGL(plan_finish_kernel, dim3(1), dim3(1024), 0, stream, p.nrt, p.nw, p.unit_off, p.count, p.wunit,
+                       p.rslot, p.wdesc, p.wrest);
+    GPL_LAUNCH_CHECK();
+    return GPL_OK;
+  }
   hipLaunchKernelGGL(plan_scan_kernel<int>, dim3(1), dim3(1024), 0, stream, p.nrt, p.count, p.unit_off, p.total);
   GPL_LAUNCH_CHECK();
   hipLaunchKernelGGL(plan_scan_kernel<long long>, dim3(1), dim3(1024), 0, stream, p.nrt, p.roww, p.rowwoff, p.wtot);

@@ -111,16 +111,23 @@ struct TilePlan {
   // scratch of the sort that orders the points (used while the plan is built;
   // its Hilbert keys and extent live in xc, yc and cbox, written after the sort)
   int* sval;                // [npad] caller indices, ping-pong partner of perm
-  int* shist;               // [kSortDigits nsb] digit counts per sort block, then their offsets
+  int* shist;               // [sort blocks][kSortDigits] digit counts
 };
 
 // Sort of the points: Hilbert index of 12 bits per axis over the square that
-// holds every finite point, radix-sorted 8 bits a pass in blocks of 256 points.
+// holds every finite point, radix-sorted 12 bits a pass. A workgroup takes `span`
+// points, whole rounds of kSortThreads; at most 64 workgroups, since each of them
+// folds the counts of all.
 constexpr int kHilbertBits = 12;
-constexpr int kSortBlock = 256;
-constexpr int kSortDigits = 256;
-constexpr int kSortPasses = (2 * kHilbertBits + 7) / 8;
-__host__ __device__ inline int sort_blocks(int n) { return (n + kSortBlock - 1) / kSortBlock; }
+constexpr int kSortThreads = 1024;
+constexpr int kSortBits = 12;
+constexpr int kSortDigits = 1 << kSortBits;
+constexpr int kSortPasses = (2 * kHilbertBits + kSortBits - 1) / kSortBits;
+__host__ __device__ inline int sort_span(int n) {
+  const int per = (n + 63) / 64;
+  return (per + kSortThreads - 1) / kSortThreads * kSortThreads;
+}
+__host__ __device__ inline int sort_blocks(int n) { return (n + sort_span(n) - 1) / sort_span(n); }
 
 // Waves of a product launch for n points, and partial slots it may write.
 __host__ __device__ inline int plan_waves(int n) {
