@@ -100,13 +100,12 @@ __device__ __forceinline__ int column_exponent(float mx) {
 
 // V' = V * 2^e_c split into FP16 hi (nearest) and lo, in sorted order, position j
 // of one slot; inv_scale[c] = 2^-e_c / 2^11 folds both scales for the output.
-__device__ __forceinline__ void split_rhs_at(int j, int slot, int c, bool packed, int e, int n, int nrhs,
-                                             const float* __restrict__ V, int ldv, const int* perm, _Float16* Vh,
-                                             _Float16* Vl, int ncp, float* inv_scale) {
+__device__ __forceinline__ void split_rhs_at(int j, int slot, int c, bool packed, int e, int nrhs, float value,
+                                             _Float16* Vh, _Float16* Vl, int ncp, float* inv_scale) {
   const int b0 = packed_block_start(nrhs);
   const float scale = ldexpf(1.f, e);
   if (j == 0 && c < ncp && (!packed || ((slot - b0) & 1) == 0)) inv_scale[c] = ldexpf(1.f, -e) / kKScale;
-  const float v = gather_rhs(j, c, n, nrhs, perm, V, ldv) * scale;
+  const float v = value * scale;
   const _Float16 h = (_Float16)v;
   const _Float16 l = (_Float16)(v - (float)h);
   if (packed) {
@@ -117,21 +116,37 @@ __device__ __forceinline__ void split_rhs_at(int j, int slot, int c, bool packed
   }
 }
 
-__global__ void split_rhs_kernel(int n, int nrhs, const float* __restrict__ V, int ldv, const int* perm,
-                                 const unsigned* colmax, _Float16* Vh, _Float16* Vl, int ldh, int ncp, float* inv_scale,
-                                 CgGate gate) {
+// kSplitSlots slots a workgroup, a thread one sorted position of all of them: their
+// gathers are in flight together. Wave w folds the partial maxima of slot w.
+constexpr int kSplitSlots = 4;
+static_assert(kColmaxBlocks <= 64, "a wave folds a column's partial maxima");
+__global__ __launch_bounds__(256) void split_rhs_kernel(int n, int nrhs, const float* __restrict__ V, int ldv,
+                                                        const int* perm, const unsigned* colmax, _Float16* Vh,
+                                                        _Float16* Vl, int ldh, int ncp, float* inv_scale,
+                                                        CgGate gate) {
+  __shared__ int se[kSplitSlots];
   if (gate.skip_all()) return;
-  const int j = blockIdx.x * blockDim.x + threadIdx.x, slot = blockIdx.y;
-  if (j >= ldh) return;
-  bool packed;
-  const int c = slot_column(slot, nrhs, packed);
-  int e = 0;
-  if (c < nrhs) {
-    unsigned mb = 0u;
-    for (int b = 0; b < kColmaxBlocks; ++b) mb = max(mb, colmax[c * kColmaxBlocks + b]);
-    e = column_exponent(__uint_as_float(mb));
+  const int j = blockIdx.x * 256 + threadIdx.x, slot0 = blockIdx.y * kSplitSlots, lane = threadIdx.x & 63;
+  bool packed[kSplitSlots];
+  int c[kSplitSlots];
+  float v[kSplitSlots];
+#pragma unroll
+  for (int k = 0; k < kSplitSlots; ++k) {
+    c[k] = slot_column(slot0 + k, nrhs, packed[k]);
+    v[k] = j < ldh ? gather_rhs(j, c[k], n, nrhs, perm, V, ldv) : 0.f;
   }
-  split_rhs_at(j, slot, c, packed, e, n, nrhs, V, ldv, perm, Vh, Vl, ncp, inv_scale);
+  {
+    bool pk;
+    const int w = threadIdx.x >> 6, cw = slot_column(slot0 + w, nrhs, pk);
+    unsigned mb = cw < nrhs && lane < kColmaxBlocks ? colmax[cw * kColmaxBlocks + lane] : 0u;
+    for (int off = 32; off > 0; off >>= 1) mb = max(mb, (unsigned)__shfl_xor((int)mb, off, 64));
+    if (lane == 0) se[w] = cw < nrhs ? column_exponent(__uint_as_float(mb)) : 0;
+  }
+  __syncthreads();
+  if (j >= ldh) return;
+#pragma unroll
+  for (int k = 0; k < kSplitSlots; ++k)
+    split_rhs_at(j, slot0 + k, c[k], packed[k], se[k], nrhs, v[k], Vh, Vl, ncp, inv_scale);
 }
 
 // Both steps for a small product, one workgroup per slot (the column maximum is
@@ -154,7 +169,7 @@ __global__ __launch_bounds__(1024) void small_rhs_kernel(int n, int nrhs, const 
   for (int k = 0; k < 16; ++k) m = fmaxf(m, red[k]);
   const int e = c < nrhs ? column_exponent(m) : 0;
   for (int j = threadIdx.x; j < ldh; j += 1024)
-    split_rhs_at(j, slot, c, packed, e, n, nrhs, V, ldv, perm, Vh, Vl, ncp, inv_scale);
+    split_rhs_at(j, slot, c, packed, e, nrhs, gather_rhs(j, c, n, nrhs, perm, V, ldv), Vh, Vl, ncp, inv_scale);
 }
 
 // FP32 form: the RHS block in sorted order, zero padded.
@@ -658,7 +673,7 @@ int mfma_prep_rhs(const TilePlan& P, const ProdBufs& b, int prec, int nrhs, cons
   } else if (prec == GPL_PREC_F16X3) {
     hipLaunchKernelGGL(colmax_kernel, dim3(kColmaxBlocks, nrhs), dim3(256), 0, stream, n, V, ldv, b.colmax, gate);
     GPL_LAUNCH_CHECK();
-    hipLaunchKernelGGL(split_rhs_kernel, dim3(cdiv(b.ldh, 256), b.ncp), dim3(256), 0, stream, n, nrhs, V, ldv, P.perm,
+    hipLaunchKernelGGL(split_rhs_kernel, dim3(cdiv(b.ldh, 256), b.ncp / kSplitSlots), dim3(256), 0, stream, n, nrhs, V, ldv, P.perm,
                        b.colmax, b.Vh, b.Vl, b.ldh, b.ncp, b.inv_scale, gate);
   } else {
     hipLaunchKernelGGL(pack_rhs_kernel, dim3(cdiv(b.ldh, 256), b.ncp), dim3(256), 0, stream, n, nrhs, V, ldv, P.perm,

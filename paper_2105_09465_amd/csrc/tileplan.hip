@@ -125,9 +125,9 @@ __device__ __forceinline__ void clear_counts(int* h) {
   for (int d = threadIdx.x; d < kSortDigits; d += kSortThreads) h[d] = 0;
   __syncthreads();
 }
-__device__ __forceinline__ void store_counts(const int* h, int* __restrict__ row) {
+__device__ __forceinline__ void store_counts(const int* h, SortCount* __restrict__ row) {
   __syncthreads();
-  for (int d = threadIdx.x; d < kSortDigits; d += kSortThreads) row[d] = h[d];
+  for (int d = threadIdx.x; d < kSortDigits; d += kSortThreads) row[d] = (SortCount)h[d];
 }
 
 // Keys of every point and the counts of their low digit: workgroup b takes the
@@ -135,7 +135,8 @@ __device__ __forceinline__ void store_counts(const int* h, int* __restrict__ row
 __global__ __launch_bounds__(kSortThreads) void plan_keys_kernel(int n, int span, const float* __restrict__ px,
                                                                  const float* __restrict__ py,
                                                                  const float4* __restrict__ part, int nparts,
-                                                                 uint32_t* __restrict__ key, int* __restrict__ hist) {
+                                                                 uint32_t* __restrict__ key,
+                                                                 SortCount* __restrict__ hist) {
   __shared__ int h[kSortDigits];
   __shared__ float4 ext;
   if (threadIdx.x < 64) {
@@ -156,7 +157,7 @@ __global__ __launch_bounds__(kSortThreads) void plan_keys_kernel(int n, int span
 // Counts of a later digit, the items in the order of the pass before.
 __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(int n, int span, int pass,
                                                                   const uint32_t* __restrict__ key,
-                                                                  int* __restrict__ hist) {
+                                                                  SortCount* __restrict__ hist) {
   __shared__ int h[kSortDigits];
   clear_counts(h);
   const int end = min(n, ((int)blockIdx.x + 1) * span);
@@ -182,8 +183,9 @@ __device__ __forceinline__ int block_exclusive(int v, int* ws) {
 // Stable ranking of one item per thread: the items of waves 0, 1, ... in turn,
 // those of a wave by lane. pos[d] (LDS) is the next free position of digit d.
 // The lanes that hold the same digit find each other by ballots; the first of
-// them takes positions for all. Returns the item's position (valid items only).
-__device__ __forceinline__ int rank_items(int d, bool valid, int* pos) {
+// them takes positions for all. `waves`: the waves that hold valid items (the same
+// in every thread). Returns the item's position (valid items only).
+__device__ __forceinline__ int rank_items(int d, bool valid, int waves, int* pos) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   unsigned long long m = __ballot(valid);
 #pragma unroll
@@ -194,11 +196,28 @@ __device__ __forceinline__ int rank_items(int d, bool valid, int* pos) {
   }
   const int lower = __popcll(m & ((1ull << lane) - 1ull)), first = valid ? __ffsll((long long)m) - 1 : 0;
   int p = 0;
-  for (int k = 0; k < kSortThreads / 64; ++k) {
+  for (int k = 0; k < waves; ++k) {
     if (k == w && valid && lower == 0) p = atomicAdd(&pos[d], __popcll(m));
     __syncthreads();
   }
   return __shfl(p, first, 64) + lower;
+}
+
+// Counts of this thread's four digits over the rows [lo, hi) of hist, 16 rows a
+// round loaded together.
+__device__ __forceinline__ int4 fold_counts(const SortCount* __restrict__ hist, int lo, int hi) {
+  constexpr int kFold = 16;
+  const ushort4* row = reinterpret_cast<const ushort4*>(hist) + threadIdx.x;
+  int4 sum = make_int4(0, 0, 0, 0);
+  for (int b0 = lo; b0 < hi; b0 += kFold) {
+    ushort4 v[kFold];
+#pragma unroll
+    for (int u = 0; u < kFold; ++u) v[u] = row[(size_t)min(b0 + u, hi - 1) * (kSortDigits / 4)];
+#pragma unroll
+    for (int u = 0; u < kFold; ++u)
+      if (b0 + u < hi) sum.x += v[u].x, sum.y += v[u].y, sum.z += v[u].z, sum.w += v[u].w;
+  }
+  return sum;
 }
 
 // Stable scatter of one pass. Every workgroup folds the counts of all workgroups
@@ -209,7 +228,7 @@ template <bool kLast>
 __global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(int n, int span, int pass,
                                                                     const uint32_t* __restrict__ kin,
                                                                     const int* __restrict__ vin,
-                                                                    const int* __restrict__ hist,
+                                                                    const SortCount* __restrict__ hist,
                                                                     uint32_t* __restrict__ kout,
                                                                     int* __restrict__ vout,
                                                                     const float* __restrict__ px,
@@ -219,42 +238,45 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(int n, int s
   __shared__ __attribute__((aligned(16))) int pos[kSortDigits];
   __shared__ int wsum[kSortThreads / 64];
   constexpr int kPer = kSortDigits / kSortThreads;  // digits of a thread
-  static_assert(kPer == 4, "one int4 of every row per thread");
+  static_assert(kPer == 4, "one ushort4 of every row per thread");
   const int nb = gridDim.x, blk = blockIdx.x;
-  const int4* row = reinterpret_cast<const int4*>(hist) + threadIdx.x;
-  int4 before = make_int4(0, 0, 0, 0), all = before;
-  for (int b0 = 0; b0 < nb; b0 += 8) {
-    int4 v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = row[(size_t)min(b0 + u, nb - 1) * kSortThreads];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      if (b0 + u >= nb) continue;
-      all.x += v[u].x, all.y += v[u].y, all.z += v[u].z, all.w += v[u].w;
-      if (b0 + u < blk) before.x += v[u].x, before.y += v[u].y, before.z += v[u].z, before.w += v[u].w;
-    }
-  }
+  const int end = min(n, (blk + 1) * span);
+  // an item's key and index, and in the last pass its point: loaded ahead of the
+  // work they do not depend on (past the end the first item of all, not used)
+  uint32_t k;
+  int v;
+  auto load = [&](int i) {
+    const int ic = i < end ? i : 0;
+    k = kin[ic];
+    v = vin ? vin[ic] : ic;
+  };
+  load(blk * span + threadIdx.x);
+  const int4 before = fold_counts(hist, 0, blk), after = fold_counts(hist, blk, nb);
+  const int4 all = make_int4(before.x + after.x, before.y + after.y, before.z + after.z, before.w + after.w);
   const int base = block_exclusive(all.x + all.y + all.z + all.w, wsum);
   const int p1 = base + all.x, p2 = p1 + all.y, p3 = p2 + all.z;
   *reinterpret_cast<int4*>(&pos[kPer * threadIdx.x]) =
       make_int4(base + before.x, p1 + before.y, p2 + before.z, p3 + before.w);
   __syncthreads();
-  const int end = min(n, (blk + 1) * span);
   for (int i0 = blk * span; i0 < end; i0 += kSortThreads) {
-    const int i = i0 + threadIdx.x;
-    const bool valid = i < end;
-    const uint32_t k = valid ? kin[i] : 0u;
-    const int v = valid ? (vin ? vin[i] : i) : 0;
-    const int r = rank_items(key_digit(k, pass), valid, pos);
-    if (!valid) continue;
+    const bool valid = i0 + (int)threadIdx.x < end;
+    const uint32_t kk = k;
+    const int vv = v;
+    float x, y;
     if (kLast) {
-      vout[r] = v;
-      irank[v] = r;
-      xs[r] = px[v];
-      ys[r] = py[v];
+      x = px[vv];
+      y = py[vv];
+    }
+    load(i0 + kSortThreads + threadIdx.x);  // the next round's
+    const int r = rank_items(key_digit(kk, pass), valid, min(kSortThreads / 64, cdiv(end - i0, 64)), pos);
+    if (!valid) continue;
+    vout[r] = vv;
+    if (kLast) {
+      irank[vv] = r;
+      xs[r] = x;
+      ys[r] = y;
     } else {
-      kout[r] = k;
-      vout[r] = v;
+      kout[r] = kk;
     }
   }
 }
@@ -334,7 +356,7 @@ __device__ __forceinline__ unsigned pair_mask(const float4 (&sb)[kSubsPerTile], 
   }
   return (mask & 0xfu) != 0u ? mask : 0u;
 }
-__device__ __forceinline__ float4 row_box(const float4* __restrict__ cbox, int r) {
+__device__ __forceinline__ float4 row_box(const float4* cbox, int r) {
   float4 rb = cbox[kChunksPerTile * r];
 #pragma unroll
   for (int t = 1; t < kChunksPerTile; ++t) rb = join_extent(rb, cbox[kChunksPerTile * r + t]);
@@ -638,11 +660,17 @@ __device__ __forceinline__ int last_at_most(const T* v, int n, T u) {
   return lo;
 }
 
+// The row tiles of the units on both sides of a boundary at unit u: (of u - 1, of u).
+__device__ __forceinline__ int2 boundary_rows(const int* off, int nrt, int u) {
+  const int r = last_at_most(off, nrt, u);
+  return make_int2(u > 0 && off[r] == u ? last_at_most(off, nrt, u - 1) : r, r);
+}
+
 // plan_wunit_kernel with the prefixes of the row tiles formed by every workgroup
 // itself; the first one writes unit_off.
 __global__ __launch_bounds__(256) void plan_wunit_fold_kernel(int nrt, int nch, int nw, int wround, const int* count,
                                                               const uint32_t* __restrict__ list, const int* roww,
-                                                              int* unit_off, int* wunit) {
+                                                              int* unit_off, int* wunit, int2* wrows) {
   __shared__ int off[kFoldRows];
   __shared__ long long woff[kFoldRows];
   const long long wtot = fold_rows<256>(nrt, count, roww, off, woff);
@@ -652,73 +680,80 @@ __global__ __launch_bounds__(256) void plan_wunit_fold_kernel(int nrt, int nch, 
   if (b > nw) return;
   const long long t = wtot * wave_weight_below(b, wround) / wave_weight_below(nw, wround);
   const int r = last_at_most(woff, nrt, t), cnt = count[r];
-  const int k = units_before(list + (size_t)r * nch, cnt, t - woff[r], lane);
-  if (lane == 0) wunit[b] = off[r] + k;
+  const int u = off[r] + units_before(list + (size_t)r * nch, cnt, t - woff[r], lane);
+  if (lane == 0) {
+    wunit[b] = u;
+    wrows[b] = boundary_rows(off, nrt, u);
+  }
 }
 
 // Ranges and partial slots of all waves, and the slots of every row tile, by one
-// workgroup of 1024 threads: off (first unit of each row tile), wunit, wrow and
-// wslot in LDS (wrow and wslot written here), count in LDS or global memory.
-__device__ __forceinline__ void finish_waves(int nrt, int nw, const int* off, const int* count, const int* wunit,
-                                             int* wrow, int* wslot, int2* __restrict__ rslot,
+// workgroup of 1024 threads. off: first unit of each row tile; wunit, wrows: the
+// units and row tiles at the nw + 1 boundaries; wslot: scratch (LDS). A wave knows
+// where its row tiles' units start and end, so it writes the ends of their ranges
+// of slots itself (first, and one past the last, in LDS; a slot index is below
+// kMaxPlanWaves + kFoldRows); empty row tiles keep an empty range.
+static_assert(kMaxPlanWaves + kFoldRows < 65536 && kChunksPerTile * kFoldRows < 65536, "16-bit slots and counts");
+template <class Count>
+__device__ __forceinline__ void finish_waves(int nrt, int nw, const int* off, const Count* count, const int* wunit,
+                                             const int2* wrows, int* wslot, unsigned short* first,
+                                             unsigned short* past, int2* __restrict__ rslot,
                                              int4* __restrict__ wdesc, int* __restrict__ wrest) {
   __shared__ int ws[1024 / 64];
   const int tid = threadIdx.x;
-  for (int w = tid; w < nw; w += 1024) {
-    const int u0 = wunit[w], u1 = wunit[w + 1];
-    int r0 = -1, rows = 0;
-    if (u0 < u1) {
-      r0 = last_at_most(off, nrt, u0);
-      rows = last_at_most(off, nrt, u1 - 1) - r0 + 1;
-    }
-    wrow[w] = r0;
-    wslot[w] = rows;
+  for (int r = tid; r < nrt; r += 1024) {
+    first[r] = 0;
+    past[r] = 0;
   }
-  __syncthreads();
   const int per = cdiv(nw, 1024), w0 = min(tid * per, nw), w1 = min(w0 + per, nw);
   int sum = 0;
-  for (int w = w0; w < w1; ++w) sum += wslot[w];
+  for (int w = w0; w < w1; ++w) {
+    const int rows = wunit[w] < wunit[w + 1] ? wrows[w + 1].x - wrows[w].y + 1 : 0;
+    wslot[w] = rows;
+    sum += rows;
+  }
   int run = block_exclusive(sum, ws);
   for (int w = w0; w < w1; ++w) {
-    const int v = wslot[w];
+    const int rows = wslot[w];
     wslot[w] = run;
-    run += v;
+    run += rows;
   }
   __syncthreads();
-  for (int r = tid; r < nrt; r += 1024) {
-    const int a = off[r], c = count[r];
-    int2 sl = make_int2(0, 0);
-    if (c > 0) {
-      const int wf = last_at_most(wunit, nw, a), wl = last_at_most(wunit, nw, a + c - 1);
-      const int s0 = wslot[wf] + (r - wrow[wf]), s1 = wslot[wl] + (r - wrow[wl]);
-      sl = make_int2(s0, s1 - s0 + 1);
-    }
-    rslot[r] = sl;
-  }
   for (int w = tid; w < nw; w += 1024) {
-    const int u0 = wunit[w], u1 = wunit[w + 1], r = wrow[w];
-    int4 dsc = make_int4(-1, wslot[w], 0, 0);
+    const int u0 = wunit[w], u1 = wunit[w + 1], slot = wslot[w];
+    int4 dsc = make_int4(-1, slot, 0, 0);
     int rest = 0;
-    if (u0 < u1 && r >= 0) {
-      const int o = off[r], ke = min(u1, o + count[r]) - o;
-      dsc = make_int4(r, wslot[w], u0 - o, ke);
+    if (u0 < u1) {
+      const int r0 = wrows[w].y, r1 = wrows[w + 1].x;
+      for (int r = r0; r <= r1; ++r) {
+        const int c = count[r];
+        if (c <= 0) continue;  // its (unused) slot stays with the wave
+        if (u0 <= off[r]) first[r] = (unsigned short)(slot + (r - r0));
+        if (u1 >= off[r] + c) past[r] = (unsigned short)(slot + (r - r0) + 1);
+      }
+      const int o = off[r0], ke = min(u1, o + count[r0]) - o;
+      dsc = make_int4(r0, slot, u0 - o, ke);
       rest = u1 - (o + ke);
     }
     wdesc[w] = dsc;
     wrest[w] = rest;
   }
+  __syncthreads();
+  for (int r = tid; r < nrt; r += 1024) rslot[r] = make_int2(first[r], past[r] - first[r]);
 }
 
 __global__ __launch_bounds__(1024) void plan_finish_kernel(int nrt, int nw, const int* __restrict__ unit_off,
-                                                           const int* __restrict__ count,
-                                                           const int* __restrict__ wunit_g, int2* __restrict__ rslot,
+                                                           const int* __restrict__ count_g,
+                                                           const int* __restrict__ wunit,
+                                                           const int2* __restrict__ wrows, int2* __restrict__ rslot,
                                                            int4* __restrict__ wdesc, int* __restrict__ wrest) {
-  __shared__ int off[kFoldRows];
-  __shared__ int wunit[kMaxPlanWaves + 1], wrow[kMaxPlanWaves], wslot[kMaxPlanWaves];
-  for (int r = threadIdx.x; r < nrt; r += 1024) off[r] = unit_off[r];
-  for (int w = threadIdx.x; w <= nw; w += 1024) wunit[w] = wunit_g[w];
-  __syncthreads();
-  finish_waves(nrt, nw, off, count, wunit, wrow, wslot, rslot, wdesc, wrest);
+  __shared__ int off[kFoldRows], wslot[kMaxPlanWaves];
+  __shared__ unsigned short count[kFoldRows], first[kFoldRows], past[kFoldRows];
+  for (int r = threadIdx.x; r < nrt; r += 1024) {
+    off[r] = unit_off[r];
+    count[r] = (unsigned short)count_g[r];
+  }
+  finish_waves(nrt, nw, off, count, wunit, wrows, wslot, first, past, rslot, wdesc, wrest);
 }
 
 // ---- small point sets: the whole plan by one workgroup ----
@@ -742,9 +777,12 @@ __global__ __launch_bounds__(kSortThreads) void plan_small_kernel(int n, const f
     } sort;
     struct {
       unsigned short cost[kSmallTiles][kSmallChunks];  // cost of a row tile before each of its units
-      int wunit[8 * kSmallTiles + 1], wrow[8 * kSmallTiles], wslot[8 * kSmallTiles];
+      int wunit[8 * kSmallTiles + 1], wslot[8 * kSmallTiles];
+      int2 wrows[8 * kSmallTiles + 1];
       int off[kSmallTiles], count[kSmallTiles], roww[kSmallTiles];
+      unsigned short first[kSmallTiles], past[kSmallTiles];
       long long woff[kSmallTiles];
+      float4 cbox[kSmallChunks], sbox[kSmallTiles * kSubsPerTile];
     } plan;
   } L;
   __shared__ unsigned short val[2][kSmallPoints];
@@ -784,7 +822,7 @@ __global__ __launch_bounds__(kSortThreads) void plan_small_kernel(int n, const f
       const int i = i0 + tid;
       const bool valid = i < n;
       const int v = valid ? (pass == 0 ? i : (int)val[(pass - 1) & 1][i]) : 0;
-      const int r = rank_items(key_digit(L.sort.key[v], pass), valid, L.sort.pos);
+      const int r = rank_items(key_digit(L.sort.key[v], pass), valid, min(kWaves, cdiv(n - i0, 64)), L.sort.pos);
       if (valid) val[pass & 1][r] = (unsigned short)v;
     }
     __syncthreads();
@@ -799,20 +837,22 @@ __global__ __launch_bounds__(kSortThreads) void plan_small_kernel(int n, const f
     if (live) irank[v] = r;
     P.xs[r] = x;
     P.ys[r] = y;
-    tile_boxes<kPlan>(tile, x, y, live, s2, P.cbox, P.sbox, P.xc, P.yc, P.cen);
+    tile_boxes<kPlan>(tile, x, y, live, s2, L.plan.cbox, L.plan.sbox, P.xc, P.yc, P.cen);  // the keys are done with
   }
+  __syncthreads();
+  for (int c = tid; c < P.nch; c += kSortThreads) P.cbox[c] = L.plan.cbox[c];
+  for (int t = tid; t < P.nrt * kSubsPerTile; t += kSortThreads) P.sbox[t] = L.plan.sbox[t];
   if (!kPlan) return;
-  __syncthreads();  // the boxes are written; the keys are not needed any more
   for (int r = w; r < P.nrt; r += kWaves) {
     float4 sb[kSubsPerTile];
 #pragma unroll
-    for (int t = 0; t < kSubsPerTile; ++t) sb[t] = P.sbox[kSubsPerTile * r + t];
-    const float4 rb = row_box(P.cbox, r);
+    for (int t = 0; t < kSubsPerTile; ++t) sb[t] = L.plan.sbox[kSubsPerTile * r + t];
+    const float4 rb = row_box(L.plan.cbox, r);
     uint32_t* out = P.list + (size_t)r * P.nch;
     int base = 0, before = kCostRowTile;  // units so far, and the row tile's cost up to them
     for (int c0 = 0; c0 < P.nch; c0 += 64) {
       const int c = c0 + lane;
-      const unsigned mask = c < P.nch ? pair_mask(sb, rb, P.cbox[c], s2, threshold, lo_threshold) : 0u;
+      const unsigned mask = c < P.nch ? pair_mask(sb, rb, L.plan.cbox[c], s2, threshold, lo_threshold) : 0u;
       const unsigned long long bal = __ballot(mask != 0u);
       const uint32_t e = (uint32_t)c | (mask << 16);
       const int cost = mask ? unit_cost(e) : 0;
@@ -846,10 +886,13 @@ __global__ __launch_bounds__(kSortThreads) void plan_small_kernel(int n, const f
       const int mid = (lo + hi) >> 1;
       if ((long long)L.plan.cost[r][mid] < rem) lo = mid + 1; else hi = mid;
     }
-    L.plan.wunit[b] = L.plan.off[r] + lo;
+    const int u = L.plan.off[r] + lo;
+    L.plan.wunit[b] = u;
+    L.plan.wrows[b] = boundary_rows(L.plan.off, nrt, u);
   }
   __syncthreads();
-  finish_waves(nrt, nw, L.plan.off, L.plan.count, L.plan.wunit, L.plan.wrow, L.plan.wslot, P.rslot, P.wdesc, P.wrest);
+  finish_waves(nrt, nw, L.plan.off, L.plan.count, L.plan.wunit, L.plan.wrows, L.plan.wslot, L.plan.first, L.plan.past,
+               P.rslot, P.wdesc, P.wrest);
 }
 
 // Compute units of the current device (queried once per device).
@@ -875,9 +918,11 @@ static int sort_points(TilePlan& p, int n, const float* px, const float* py, flo
   // extents in cbox, the keys in xc and yc
   float4* ext = p.cbox;
   uint32_t *k0 = reinterpret_cast<uint32_t*>(p.xc), *k1 = reinterpret_cast<uint32_t*>(p.yc);
-  hipLaunchKernelGGL(plan_extent_kernel, dim3(nb), dim3(kSortThreads), 0, stream, n, px, py, ext);
+  const int parts = nb < 64 ? nb : 64;  // of the extent, one per workgroup: a wave folds them
+  hipLaunchKernelGGL(plan_extent_kernel, dim3(parts), dim3(kSortThreads), 0, stream, n, px, py, ext);
   GPL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(plan_keys_kernel, dim3(nb), dim3(kSortThreads), 0, stream, n, span, px, py, ext, nb, k0, p.shist);
+  hipLaunchKernelGGL(plan_keys_kernel, dim3(nb), dim3(kSortThreads), 0, stream, n, span, px, py, ext, parts, k0,
+                     p.shist);
   GPL_LAUNCH_CHECK();
   static_assert(kSortPasses == 2, "a first and a last pass");
   hipLaunchKernelGGL(sort_scatter_kernel<false>, dim3(nb), dim3(kSortThreads), 0, stream, n, span, 0, k0, nullptr,
@@ -925,10 +970,10 @@ int plan_build(TilePlan& p, int n, const float* px, const float* py, const gpl_g
   GPL_LAUNCH_CHECK();
   if (p.nrt <= kFoldRows) {
     hipLaunchKernelGGL(plan_wunit_fold_kernel, dim3(cdiv(p.nw + 1, 4)), dim3(256), 0, stream, p.nrt, p.nch, p.nw,
-                       p.wround, p.count, p.list, p.roww, p.unit_off, p.wunit);
+                       p.wround, p.count, p.list, p.roww, p.unit_off, p.wunit, reinterpret_cast<int2*>(p.wrow));
     GPL_LAUNCH_CHECK();
     hipLaunchKernelGGL(plan_finish_kernel, dim3(1), dim3(1024), 0, stream, p.nrt, p.nw, p.unit_off, p.count, p.wunit,
-                       p.rslot, p.wdesc, p.wrest);
+                       reinterpret_cast<int2*>(p.wrow), p.rslot, p.wdesc, p.wrest);
     GPL_LAUNCH_CHECK();
     return GPL_OK;
   }

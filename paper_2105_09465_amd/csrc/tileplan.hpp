@@ -61,6 +61,22 @@ __host__ __device__ inline int entry_chunk(uint32_t e) { return (int)(e & 0xffff
 __host__ __device__ inline unsigned entry_mask(uint32_t e) { return (e >> 16) & 0xfu; }
 __host__ __device__ inline unsigned entry_lomask(uint32_t e) { return (e >> 20) & 0xfu; }
 
+// Sort of the points: Hilbert index of 12 bits per axis over the square that
+// holds every finite point, radix-sorted 12 bits a pass. A workgroup takes `span`
+// points, whole rounds of kSortThreads; about 64 workgroups at most, since each of
+// them folds the counts of all, but no more points than its 16-bit counts hold.
+constexpr int kHilbertBits = 12;
+constexpr int kSortThreads = 1024;
+constexpr int kSortBits = 12;
+constexpr int kSortDigits = 1 << kSortBits;
+constexpr int kSortPasses = (2 * kHilbertBits + kSortBits - 1) / kSortBits;
+using SortCount = unsigned short;
+__host__ __device__ inline int sort_span(int n) {
+  const int per = cdiv(cdiv(n, 64), kSortThreads) * kSortThreads;
+  return per < 32768 ? per : 32768;
+}
+__host__ __device__ inline int sort_blocks(int n) { return (n + sort_span(n) - 1) / sort_span(n); }
+
 // The evaluated work is a sequence of units, the live (row tile, chunk) pairs in
 // row-tile order (T units in all). A product launch of nw waves gives each wave
 // a contiguous range of units; a wave writes one partial row block per row tile
@@ -99,7 +115,8 @@ struct TilePlan {
   uint32_t* list;   // [nrt][nch] entries of the live chunks of each row tile, ascending
   int* unit_off;    // [nrt] first unit of each row tile (exclusive prefix of count)
   int* total;       // [1] T
-  int* wrow;        // [nw] row tile of each wave's first unit (-1: no units)
+  int* wrow;        // [nw] row tile of each wave's first unit (-1: no units); or [nw + 1] pairs, the row
+                    // tiles of the units before and at each boundary (plan_wunit_fold_kernel)
   int* wslot;       // [nw + 1] first partial slot of each wave
   int2* rslot;      // [nrt] first partial slot of each row tile and their number
   int4* wdesc;      // [nw] per wave: first row tile, first slot, list range [kb, ke) in that row tile
@@ -111,23 +128,8 @@ struct TilePlan {
   // scratch of the sort that orders the points (used while the plan is built;
   // its Hilbert keys and extent live in xc, yc and cbox, written after the sort)
   int* sval;                // [npad] caller indices, ping-pong partner of perm
-  int* shist;               // [sort blocks][kSortDigits] digit counts
+  SortCount* shist;         // [sort blocks][kSortDigits] digit counts
 };
-
-// Sort of the points: Hilbert index of 12 bits per axis over the square that
-// holds every finite point, radix-sorted 12 bits a pass. A workgroup takes `span`
-// points, whole rounds of kSortThreads; at most 64 workgroups, since each of them
-// folds the counts of all.
-constexpr int kHilbertBits = 12;
-constexpr int kSortThreads = 1024;
-constexpr int kSortBits = 12;
-constexpr int kSortDigits = 1 << kSortBits;
-constexpr int kSortPasses = (2 * kHilbertBits + kSortBits - 1) / kSortBits;
-__host__ __device__ inline int sort_span(int n) {
-  const int per = (n + 63) / 64;
-  return (per + kSortThreads - 1) / kSortThreads * kSortThreads;
-}
-__host__ __device__ inline int sort_blocks(int n) { return (n + sort_span(n) - 1) / sort_span(n); }
 
 // Waves of a product launch for n points, and partial slots it may write.
 __host__ __device__ inline int plan_waves(int n) {
@@ -183,7 +185,7 @@ void plan_carve(C& cv, int n, TilePlan& p) {
   p.list = cv.template take<uint32_t>((size_t)p.nrt * p.nch);
   p.unit_off = cv.template take<int>((size_t)p.nrt);
   p.total = cv.template take<int>(1);
-  p.wrow = cv.template take<int>((size_t)p.nw);
+  p.wrow = cv.template take<int>(2 * ((size_t)p.nw + 1));
   p.wslot = cv.template take<int>((size_t)p.nw + 1);
   p.rslot = cv.template take<int2>((size_t)p.nrt);
   p.wdesc = cv.template take<int4>((size_t)p.nw);
@@ -193,7 +195,7 @@ void plan_carve(C& cv, int n, TilePlan& p) {
   p.rowwoff = cv.template take<long long>((size_t)p.nrt);
   p.wtot = cv.template take<long long>(1);
   p.sval = cv.template take<int>((size_t)p.npad);
-  p.shist = cv.template take<int>((size_t)kSortDigits * sort_blocks(n));
+  p.shist = cv.template take<SortCount>((size_t)kSortDigits * sort_blocks(n));
 }
 
 // The buffers of the sort alone (plan_sort): points, boxes and scratch.
@@ -214,7 +216,7 @@ void sort_carve(C& cv, int n, TilePlan& p) {
   p.sbox = cv.template take<float4>((size_t)p.nrt * kSubsPerTile);
   p.total = cv.template take<int>(1);
   p.sval = cv.template take<int>((size_t)p.npad);
-  p.shist = cv.template take<int>((size_t)kSortDigits * sort_blocks(n));
+  p.shist = cv.template take<SortCount>((size_t)kSortDigits * sort_blocks(n));
 }
 
 // Build the plan on `stream`. The points are sorted along the Hilbert curve of
