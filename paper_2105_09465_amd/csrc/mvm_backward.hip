@@ -6,16 +6,28 @@
 //   dF/dp_i  = -(1/l^2) sum_j K_ij s_ij (p_i - p_j)
 //   dF/dl    = (1/2) sum_ij K_ij s_ij |p_i - p_j|^2 / l^3
 //   dF/da    = sum_ij K_ij s_ij / a          (= 2F/a)
-// The points are taken in the order of the product's tile plan (a Hilbert
-// sort), so that runs of consecutive points are compact. Source chunks (32
-// points) whose box gap g to a row block's box gives s2 g^2 >= kSkipBackward
-// are skipped: every kernel value there is at most a^2 2^-36, so each skipped
-// term K s (p_i - p_j) is below 2^-36 of the same term at kernel value a^2 (the
-// precision form's product treats these values as zero as well).
-// Each lane owns R rows i and keeps w_c a_ic, w_c b_ic in registers; source
-// tiles of 256 points with their a_j, b_j are staged in LDS. The source range is
-// split across workgroups; per-slice position gradients and per-block FP64
-// hyperparameter sums are reduced in a fixed order by later kernels.
+// The points are taken in the order of the product's tile plan and the pairs are
+// the plan's: (16-point subtile, 32-point chunk) pairs of boxes with s2 g^2 <
+// kSkipBackward for their gap g, split over the waves by cost. Beyond that every
+// kernel value is at most a^2 2^-36, so each skipped term K s (p_i - p_j) is below
+// 2^-36 of the same term at kernel value a^2 (the product's forms treat these
+// values in the same way).
+//
+// s_ij is a contraction over the columns, P_i . Q_j with P = (w a, w b), Q = (b, a):
+// FP32 MFMA (v_mfma_f32_16x16x4_f32) with the sources j as rows and the points i as
+// columns of its result, so that a lane holds four j of one i and the sums over j
+// stay in registers. They are FP64 moments of K s about the row tile's first
+// point, sum K s (1, x_j, y_j, x_j^2 + y_j^2), from which dF/dp_i, dF/dl and dF/da of
+// a row follow at the end: one conversion and four FP64 operations a pair (the
+// differences in FP64 would take three more conversions), with nothing lost (the
+// moments cancel by the ratio of the tile's extent to the pair distance, squared
+// at most: some 1e4 of FP64's 1e16).
+//
+// Bound by VALU issue (six FP32, one exp, one conversion and four FP64
+// instructions a pair) beside 9 MFMAs for 256 pairs at 17 columns: 91 us at 40,000
+// traced points and 17 columns. The previous kernel (s_ij by FMAs from LDS-staged columns, 512-row blocks against 32-point
+// chunks) took 650-730 us for 16 columns of 40,000 points and another 260 us for
+// the seventeenth.
 #include <algorithm>
 #include <cmath>
 
@@ -25,221 +37,226 @@
 
 namespace gpl {
 
-constexpr int kBJ = 256;              // points per source tile (8 chunks of the plan)
-constexpr int kMaxPass = 16;          // column pairs per pass
-constexpr float kSkipBackward = kSkipF16x3;
-static_assert(kBJ % kChunk == 0, "source tiles are whole chunks");
+constexpr int kMaxPass = 18;  // column pairs per pass
+constexpr float kSkipBackward = kSkipFp32;
+constexpr int kBwdSums = 4;   // sums of a row: gx, gy (without -1/l^2), K s d^2, K s
+
+// MFMA steps of a pass of nc column pairs: step s of lane group g takes entry
+// g S + s of the 2 nc entries of P and Q (zero padded to 4 S).
+static int bwd_steps(int nc) {
+  const int s = cdiv(nc, 2);
+  return s > 8 ? 9 : s > 4 ? 8 : s > 2 ? 4 : s;
+}
+// Floats of one lane's entries in memory: a power of two or a multiple of four.
+__host__ __device__ constexpr int bwd_stride(int S) { return S > 8 ? 12 : S; }
+// Entries of sorted point j in lane group g.
+__host__ __device__ inline size_t bwd_at(int j, int g, int stride) {
+  return ((size_t)((j >> 4) * 4 + g) * 16 + (j & 15)) * stride;
+}
 
 struct WChunk {
-  float w[kMaxPass];  // weights of the (up to 16) column pairs of one pass
+  float w[kMaxPass];  // weights of the column pairs of one pass
 };
 
-struct BwdPlan {
-  int R, rows, nrb, S, jlen, ldg, nchunk;
-};
+typedef float bwd_f4 __attribute__((ext_vector_type(4)));
 
-static BwdPlan bwd_plan(int n, int npairs) {
-  BwdPlan p;
-  p.R = n >= 16384 ? 2 : 1;
-  p.rows = 256 * p.R;
-  p.nrb = cdiv(n, p.rows);
-  // about 2048 workgroups: after the cut their work varies, and many short
-  // workgroups keep the compute units filled
-  const int target = 2048;
-  const int S = std::max(1, std::min(target / p.nrb, cdiv(n, kBJ)));
-  p.jlen = round_up(cdiv(n, S), kBJ);
-  p.S = cdiv(n, p.jlen);
-  p.ldg = round_up(n, 64);
-  p.nchunk = 0;
-  for (int c0 = 0; c0 < npairs;) {
-    const int left = npairs - c0;
-    c0 += left >= 16 ? 16 : left >= 8 ? 8 : left >= 4 ? 4 : left >= 2 ? 2 : 1;
-    ++p.nchunk;
-  }
-  return p;
-}
-
-// Box of the sorted points [kBJ t, kBJ t + kBJ): the union of the plan's chunk
-// boxes (empty past the last chunk).
-__device__ __forceinline__ float4 source_tile_box(const float4* __restrict__ cbox, int nch, int t) {
-  float4 b = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
+// The S entries of one lane.
+template <int S>
+__device__ __forceinline__ void bwd_load(float (&v)[S], const float* __restrict__ p) {
+  if (S == 1) {
+    v[0] = p[0];
+  } else if (S == 2) {
+    const float2 t = *reinterpret_cast<const float2*>(p);
+    v[0] = t.x;
+    v[1 % S] = t.y;
+  } else {
 #pragma unroll
-  for (int k = 0; k < kBJ / kChunk; ++k) {
-    const int c = t * (kBJ / kChunk) + k;
-    if (c < nch) {
-      const float4 q = cbox[c];
-      b = make_float4(fminf(b.x, q.x), fmaxf(b.y, q.y), fminf(b.z, q.z), fmaxf(b.w, q.w));
+    for (int q = 0; q < S / 4; ++q) {
+      const bwd_f4 t = *reinterpret_cast<const bwd_f4*>(p + 4 * q);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[(4 * q + k) % S] = t[k];
     }
+    if (S % 4 == 1) v[S - 1] = p[S - 1];
   }
-  return b;
 }
 
-// Bit k set when chunk kBJ/kChunk t + k of source tile t is within the cutoff of
-// the row box rb (the same value in every thread of a workgroup).
-__device__ __forceinline__ unsigned source_chunks_live(const float4* __restrict__ cbox, int nch, int t,
-                                                       const float4& rb, float s2) {
-  unsigned m = 0u;
+// P and Q of the columns c0 .. c0 + nc in the plan's order, zeros past n: thread
+// (sorted point, lane group), its S entries of both, so that the lanes of a wave
+// write one run of memory.
+template <int S>
+__global__ __launch_bounds__(256) void bwd_gather_kernel(int n, int npad, int nc, int c0, const int* __restrict__ perm,
+                                                         const float* __restrict__ A, int lda,
+                                                         const float* __restrict__ Bv, int ldb, WChunk w,
+                                                         float* __restrict__ P, float* __restrict__ Q) {
+  constexpr int stride = bwd_stride(S);
+  const int o = blockIdx.x * 256 + threadIdx.x;  // (16-point group, lane group, point of the group)
+  if (o >= 4 * npad) return;
+  const int g = (o >> 4) & 3, j = (o >> 6) * 16 + (o & 15);
+  const bool live = j < n;
+  const int i = live ? perm[j] : 0;
+  float p[S], q[S];
 #pragma unroll
-  for (int k = 0; k < kBJ / kChunk; ++k) {
-    const int c = t * (kBJ / kChunk) + k;
-    if (c < nch && boxes_live(rb, cbox[c], s2, kSkipBackward)) m |= 1u << k;
+  for (int s = 0; s < S; ++s) {
+    const int k = g * S + s, c = k < 2 * S ? k : k - 2 * S;  // entries (w a, b), then (w b, a)
+    const bool ok = live && c < nc;
+    const float a = ok ? A[(size_t)(c0 + c) * lda + i] : 0.f, b = ok ? Bv[(size_t)(c0 + c) * ldb + i] : 0.f;
+    p[s] = w.w[min(c, kMaxPass - 1)] * (k < 2 * S ? a : b);
+    q[s] = k < 2 * S ? b : a;
   }
-  return m;
-}
-
-// Columns c0 .. c0 + nc of A and Bv in the plan's order: As[c][j] = A[c0 + c][perm[j]].
-__global__ void bwd_gather_kernel(int n, int nc, int c0, const int* __restrict__ perm, const float* __restrict__ A,
-                                  int lda, const float* __restrict__ Bv, int ldb, float* __restrict__ As,
-                                  float* __restrict__ Bs, int ldp) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  const int i = perm[j];
-  for (int c = 0; c < nc; ++c) {
-    As[(size_t)c * ldp + j] = A[(size_t)(c0 + c) * lda + i];
-    Bs[(size_t)c * ldp + j] = Bv[(size_t)(c0 + c) * ldb + i];
+  float *dp = P + (size_t)o * stride, *dq = Q + (size_t)o * stride;
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    dp[s] = p[s];
+    dq[s] = q[s];
   }
 }
 
-// part_g[slice][2][ldg]: position-gradient partials of the sorted rows;
-// part_h[slice][block][2]: FP64 sums of K s d^2 and K s.
-template <int NC, int R>
-__global__ __launch_bounds__(256) void mvm_bwd_kernel(int n, const float* __restrict__ xs,
-                                                      const float* __restrict__ ys, const float4* __restrict__ cbox,
-                                                      int nch, float s2, float amp2, const float* __restrict__ As,
-                                                      const float* __restrict__ Bs, int ldp, WChunk w, int jlen,
-                                                      double* __restrict__ part_g, int ldg,
-                                                      double* __restrict__ part_h) {
-  __shared__ float sx[kBJ], sy[kBJ];
-  __shared__ __attribute__((aligned(16))) float sa[kBJ * NC];
-  __shared__ __attribute__((aligned(16))) float sb[kBJ * NC];
+// One wave's share of the plan (as the product's waves): per row tile it touches,
+// part[slot][kBwdSums][64 rows].
+template <int S>
+__global__ __launch_bounds__(256, 3) void mvm_bwd_kernel(const TilePlan T, float s2, const float* __restrict__ P,
+                                                         const float* __restrict__ Q, double* __restrict__ part) {
+  const int w = plan_block(blockIdx.x, T.nw, T.wround) * kPlanWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int4 dsc = T.wdesc[w];
+  int rest = T.wrest[w];
+  if (dsc.x < 0) return;
+  constexpr int stride = bwd_stride(S);
+  const int lane = threadIdx.x & 63, ri = lane & 15, g = lane >> 4;
+  int r = dsc.x, slot = dsc.y, kb = dsc.z, ke = dsc.w;
+#pragma unroll 1
+  while (true) {
+    float xi[kSubsPerTile], yi[kSubsPerTile], pf[kSubsPerTile][S];
+#pragma unroll
+    for (int t = 0; t < kSubsPerTile; ++t) {
+      const int i = r * kRowTile + t * kSubTile + ri;
+      xi[t] = T.xs[i];
+      yi[t] = T.ys[i];
+      bwd_load<S>(pf[t], P + bwd_at(i, g, stride));
+    }
+    // (a non-finite first point must not reach the other rows through the centre)
+    const float fx = T.xs[r * kRowTile], fy = T.ys[r * kRowTile];
+    const double cx = isfinite(fx) ? (double)fx : 0.0, cy = isfinite(fy) ? (double)fy : 0.0;
+    double s0[kSubsPerTile] = {}, sx[kSubsPerTile] = {}, sy[kSubsPerTile] = {}, sr[kSubsPerTile] = {};
+    const uint32_t* lst = T.list + (size_t)r * T.nch;
+#pragma unroll 1
+    for (int k0 = kb; k0 < ke; k0 += 64) {
+      const int m = min(64, ke - k0);
+      const int vidx = lane < m ? (int)lst[k0 + lane] : 0;
+#pragma unroll 1
+      for (int q = 0; q < m; ++q) {
+        const uint32_t e = (uint32_t)__builtin_amdgcn_readlane(vidx, q);
+        const unsigned mask = entry_mask(e);
+#pragma unroll
+        for (int h = 0; h < kChunk / 16; ++h) {
+          const int j0 = entry_chunk(e) * kChunk + h * 16;
+          float qf[S];
+          bwd_load<S>(qf, Q + bwd_at(j0 + ri, g, stride));
+          const bwd_f4 xj = *reinterpret_cast<const bwd_f4*>(&T.xs[j0 + 4 * g]);
+          const bwd_f4 yj = *reinterpret_cast<const bwd_f4*>(&T.ys[j0 + 4 * g]);
+          double X[4], Y[4], R[4];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            X[v] = (double)xj[v] - cx;
+            Y[v] = (double)yj[v] - cy;
+            R[v] = fma(X[v], X[v], Y[v] * Y[v]);
+          }
+#pragma unroll
+          for (int t = 0; t < kSubsPerTile; ++t) {
+            if (!((mask >> t) & 1u)) continue;
+            bwd_f4 sd = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < S; ++s) sd = __builtin_amdgcn_mfma_f32_16x16x4f32(qf[s], pf[t][s], sd, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              const float dx = xi[t] - xj[v], dy = yi[t] - yj[v];
+              const float d2 = fmaf(dx, dx, dy * dy);
+              const double kt = (double)(exp2_fast(-(d2 * s2)) * sd[v]);
+              s0[t] += kt;
+              sx[t] = fma(kt, X[v], sx[t]);
+              sy[t] = fma(kt, Y[v], sy[t]);
+              sr[t] = fma(kt, R[v], sr[t]);
+            }
+          }
+        }
+      }
+    }
+    // over the four lane groups; lane 16 t + ri then ends row 16 t + ri
+    double m0 = 0.0, mx = 0.0, my = 0.0, mr = 0.0;
+    auto fold = [](double v) {
+      v += __shfl_xor(v, 16, 64);
+      return v + __shfl_xor(v, 32, 64);
+    };
+#pragma unroll
+    for (int t = 0; t < kSubsPerTile; ++t) {
+      const double a = fold(s0[t]), b = fold(sx[t]), c = fold(sy[t]), d = fold(sr[t]);
+      if (g == t) m0 = a, mx = b, my = c, mr = d;
+    }
+    float xo = xi[0], yo = yi[0];
+#pragma unroll
+    for (int t = 1; t < kSubsPerTile; ++t)
+      if (g == t) xo = xi[t], yo = yi[t];
+    const double x = (double)xo - cx, y = (double)yo - cy;
+    double* out = part + (size_t)slot * kBwdSums * kRowTile + lane;
+    out[0] = x * m0 - mx;
+    out[kRowTile] = y * m0 - my;
+    out[2 * kRowTile] = fma(fma(x, x, y * y), m0, mr) - 2.0 * fma(x, mx, y * my);
+    out[3 * kRowTile] = m0;
+    if (rest <= 0) break;
+    ++r;
+    ++slot;
+    kb = 0;
+    ke = min(rest, T.count[r]);
+    rest -= ke;
+  }
+}
+
+// Sums of every row over its partial slots in order (and, gacc, over the passes);
+// the last pass ends them: gpx[perm[i]] += -(a^2/l^2) sum, same for y. Per
+// workgroup, part_h = the sums of K s d^2 and K s of its rows.
+__global__ __launch_bounds__(256) void bwd_rows_kernel(const TilePlan T, const double* __restrict__ part, int first,
+                                                       int last, double scale, double* __restrict__ gacc, float* gpx,
+                                                       float* gpy, double* __restrict__ part_h) {
   __shared__ double red[4];
-  const int tid = threadIdx.x;
-  const int row0 = blockIdx.x * (256 * R);
-  const int jbeg = blockIdx.y * jlen;
-  const int jend = min(n, jbeg + jlen);
-  // the row block's box (the same value in every thread, so the tile test below
-  // takes the same branch in the whole workgroup)
-  float4 rb = source_tile_box(cbox, nch, row0 / kBJ);
+  const int j = blockIdx.x * 256 + threadIdx.x, r = j / kRowTile, row = j % kRowTile;
+  double v[kBwdSums] = {};
+  if (r < T.nrt) {
+    const int2 sl = T.rslot[r];
+    const double* p = part + (size_t)sl.x * kBwdSums * kRowTile + row;
+    for (int q0 = 0; q0 < sl.y; q0 += 4) {
+      double t[4][kBwdSums];  // past the last slot the loads repeat it and are not added
 #pragma unroll
-  for (int r = 1; r < R; ++r) {
-    const float4 q = source_tile_box(cbox, nch, row0 / kBJ + r);
-    rb = make_float4(fminf(rb.x, q.x), fmaxf(rb.y, q.y), fminf(rb.z, q.z), fmaxf(rb.w, q.w));
-  }
-  // this wave's rows: the 64-point row tiles row0/64 + w + 4r (r < R); their box
-  // (the same value in every lane) selects the chunks the wave computes
-  const int wv = tid >> 6;
-  float4 wb4 = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
+      for (int u = 0; u < 4; ++u)
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
+        for (int k = 0; k < kBwdSums; ++k) t[u][k] = p[((size_t)min(q0 + u, sl.y - 1) * kBwdSums + k) * kRowTile];
 #pragma unroll
-    for (int k = 0; k < kChunksPerTile; ++k) {
-      const int c = (row0 / kRowTile + wv + 4 * r) * kChunksPerTile + k;
-      if (c < nch) {
-        const float4 q = cbox[c];
-        wb4 = make_float4(fminf(wb4.x, q.x), fmaxf(wb4.y, q.y), fminf(wb4.z, q.z), fmaxf(wb4.w, q.w));
-      }
+      for (int u = 0; u < 4; ++u)
+        if (q0 + u < sl.y)
+#pragma unroll
+          for (int k = 0; k < kBwdSums; ++k) v[k] += t[u][k];
     }
   }
-  float xi[R], yi[R], wa[R][NC], wb[R][NC];
-  double gx[R], gy[R];       // FP64 accumulation: the gradient terms partly cancel
-  double hl = 0.0, hf = 0.0;  // per-lane sums of K s d^2 and K s
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int i = row0 + r * 256 + tid;
-    const bool ok = i < n;
-    xi[r] = ok ? xs[i] : 0.f;
-    yi[r] = ok ? ys[i] : 0.f;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      wa[r][c] = ok ? w.w[c] * As[(size_t)c * ldp + i] : 0.f;
-      wb[r][c] = ok ? w.w[c] * Bs[(size_t)c * ldp + i] : 0.f;
-    }
-    gx[r] = 0.0;
-    gy[r] = 0.0;
+  const double sl = block_sum_double(v[2], red);
+  if (threadIdx.x == 0) part_h[2 * blockIdx.x + 0] = sl;
+  const double sf = block_sum_double(v[3], red);
+  if (threadIdx.x == 0) part_h[2 * blockIdx.x + 1] = sf;
+  if (j >= T.n) return;
+  if (!first) {
+    v[0] += gacc[2 * (size_t)j];
+    v[1] += gacc[2 * (size_t)j + 1];
   }
-  for (int jt = jbeg; jt < jend; jt += kBJ) {
-    const unsigned live = source_chunks_live(cbox, nch, jt / kBJ, rb, s2);
-    if (live == 0u) continue;
-    __syncthreads();
-    const int j = jt + tid;
-    const bool ok = j < jend;
-    sx[tid] = ok ? xs[j] : 0.f;
-    sy[tid] = ok ? ys[j] : 0.f;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      sa[tid * NC + c] = ok ? As[(size_t)c * ldp + j] : 0.f;
-      sb[tid * NC + c] = ok ? Bs[(size_t)c * ldp + j] : 0.f;
-    }
-    __syncthreads();
-    const unsigned wlive = source_chunks_live(cbox, nch, jt / kBJ, wb4, s2);  // a subset of live
-    for (int g = 0; g < kBJ / kChunk; ++g) {
-      if (!((wlive >> g) & 1u)) continue;
-#pragma unroll 2
-    for (int t = g * kChunk; t < (g + 1) * kChunk; ++t) {
-      const float xj = sx[t], yj = sy[t];
-      float aj[NC], bj[NC];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        aj[c] = sa[t * NC + c];
-        bj[c] = sb[t * NC + c];
-      }
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        float s = 0.f;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) s = fmaf(wa[r][c], bj[c], fmaf(wb[r][c], aj[c], s));
-        const float dx = xi[r] - xj, dy = yi[r] - yj;
-        const float d2 = fmaf(dx, dx, dy * dy);
-        const double kt = (double)(amp2 * exp2_fast(-(d2 * s2)) * s);
-        gx[r] = fma(kt, (double)dx, gx[r]);
-        gy[r] = fma(kt, (double)dy, gy[r]);
-        hl = fma(kt, (double)d2, hl);
-        hf += kt;
-      }
-    }
-    }
+  if (last) {
+    const int dst = T.perm[j];
+    gpx[dst] += (float)(scale * v[0]);
+    gpy[dst] += (float)(scale * v[1]);
+  } else {
+    gacc[2 * (size_t)j] = v[0];
+    gacc[2 * (size_t)j + 1] = v[1];
   }
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int i = row0 + r * 256 + tid;
-    if (i < n) {
-      part_g[((size_t)blockIdx.y * 2 + 0) * ldg + i] = gx[r];
-      part_g[((size_t)blockIdx.y * 2 + 1) * ldg + i] = gy[r];  // slice partials kept in FP64
-    }
-  }
-  const size_t hb = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 2;
-  const double sl = block_sum_double(hl, red);
-  if (tid == 0) part_h[hb + 0] = sl;
-  const double sf = block_sum_double(hf, red);
-  if (tid == 0) part_h[hb + 1] = sf;
 }
 
-// gacc[k][i] (+)= sum over the slices of one pass of part_g[slice][k][i], in slice order.
-__global__ void bwd_reduce_pos_kernel(int n, int nslices, const double* __restrict__ part_g, int ldg, int first,
-                                      double* __restrict__ gacc) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  double sx = first ? 0.0 : gacc[i], sy = first ? 0.0 : gacc[ldg + i];
-  for (int k = 0; k < nslices; ++k) {
-    sx += part_g[((size_t)k * 2 + 0) * ldg + i];
-    sy += part_g[((size_t)k * 2 + 1) * ldg + i];
-  }
-  gacc[i] = sx;
-  gacc[ldg + i] = sy;
-}
-
-// gpx[perm[i]] += -(1/l^2) gacc[0][i]; same for y.
-__global__ void bwd_store_pos_kernel(int n, const int* __restrict__ perm, const double* __restrict__ gacc, int ldg,
-                                     double inv_l2, float* gpx, float* gpy) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int dst = perm[i];
-  gpx[dst] += (float)(-inv_l2 * gacc[i]);
-  gpy[dst] += (float)(-inv_l2 * gacc[ldg + i]);
-}
-
-// g_hyp[0] = (1/2) sum K s d^2 / l^3, g_hyp[1] = sum K s / a (one workgroup of
-// 256 threads, each summing a fixed stride of the blocks, then a fixed tree).
+// g_hyp[0] = (a^2/2) sum K s d^2 / l^3, g_hyp[1] = a sum K s (K without its a^2; one
+// workgroup of 256 threads, each summing a fixed stride of the blocks, then a
+// fixed tree).
 __global__ __launch_bounds__(256) void bwd_reduce_hyp_kernel(int nblocks_total, const double* part_h, double l,
                                                              double a, double* g_hyp) {
   __shared__ double red[4];
@@ -251,37 +268,40 @@ __global__ __launch_bounds__(256) void bwd_reduce_hyp_kernel(int nblocks_total, 
   sl = block_sum_double(sl, red);
   sf = block_sum_double(sf, red);
   if (threadIdx.x == 0) {
-    g_hyp[0] = 0.5 * sl / (l * l * l);
-    g_hyp[1] = sf / a;
+    g_hyp[0] = 0.5 * a * a * sl / (l * l * l);
+    g_hyp[1] = a * sf;
   }
 }
 
 struct BwdBufs {
   TilePlan plan;
-  float *As, *Bs;  // [kMaxPass][ldg] columns of one pass in the plan's order
-  double *part_g, *gacc, *part_h;
+  float *P, *Q;  // entries of one pass in the plan's order
+  double *part, *gacc, *part_h;
 };
 
+static int bwd_passes(int npairs) { return cdiv(npairs, kMaxPass); }
+
 template <class Cv>
-static void carve_bwd(Cv& cv, int n, const BwdPlan& p, BwdBufs& b) {
+static void carve_bwd(Cv& cv, int n, int npairs, BwdBufs& b) {
   plan_carve(cv, n, b.plan);
-  b.As = cv.template take<float>((size_t)kMaxPass * p.ldg);
-  b.Bs = cv.template take<float>((size_t)kMaxPass * p.ldg);
-  b.part_g = cv.template take<double>((size_t)p.S * 2 * p.ldg);
-  b.gacc = cv.template take<double>((size_t)2 * p.ldg);
-  b.part_h = cv.template take<double>((size_t)p.nchunk * p.S * p.nrb * 2);
+  const size_t entries = (size_t)b.plan.npad * 4 * bwd_stride(bwd_steps(std::min(npairs, kMaxPass)));
+  b.P = cv.template take<float>(entries);
+  b.Q = cv.template take<float>(entries);
+  b.part = cv.template take<double>((size_t)plan_slots(n) * kBwdSums * kRowTile);
+  b.gacc = cv.template take<double>(npairs > kMaxPass ? 2 * (size_t)b.plan.npad : 1);
+  b.part_h = cv.template take<double>((size_t)bwd_passes(npairs) * 2 * cdiv(b.plan.npad, 256));
 }
 
-template <int NC>
-static void launch_bwd(const BwdPlan& p, int n, const TilePlan& P, float s2, float amp2, const float* As,
-                       const float* Bs, const WChunk& w, double* part_g, double* part_h, hipStream_t stream) {
-  dim3 grid(p.nrb, p.S);
-  if (p.R == 2)
-    hipLaunchKernelGGL((mvm_bwd_kernel<NC, 2>), grid, dim3(256), 0, stream, n, P.xs, P.ys, P.cbox, P.nch, s2, amp2,
-                       As, Bs, p.ldg, w, p.jlen, part_g, p.ldg, part_h);
-  else
-    hipLaunchKernelGGL((mvm_bwd_kernel<NC, 1>), grid, dim3(256), 0, stream, n, P.xs, P.ys, P.cbox, P.nch, s2, amp2,
-                       As, Bs, p.ldg, w, p.jlen, part_g, p.ldg, part_h);
+template <int S>
+static int launch_bwd(const BwdBufs& b, float s2, int nc, int c0, const float* A, int lda, const float* Bv, int ldb,
+                      const WChunk& w, hipStream_t stream) {
+  hipLaunchKernelGGL(bwd_gather_kernel<S>, dim3(cdiv(4 * b.plan.npad, 256)), dim3(256), 0, stream, b.plan.n,
+                     b.plan.npad, nc, c0, b.plan.perm, A, lda, Bv, ldb, w, b.P, b.Q);
+  GPL_LAUNCH_CHECK();
+  hipLaunchKernelGGL(mvm_bwd_kernel<S>, dim3(b.plan.nw / kPlanWaves), dim3(256), 0, stream, b.plan, s2, b.P, b.Q,
+                     b.part);
+  GPL_LAUNCH_CHECK();
+  return GPL_OK;
 }
 
 }  // namespace gpl
@@ -290,10 +310,9 @@ using namespace gpl;
 
 extern "C" size_t gpl_gp_kernel_mvm_backward_workspace(int n, int npairs) {
   if (n <= 0 || npairs <= 0) return 0;
-  const BwdPlan p = bwd_plan(n, npairs);
   Sizer s;
   BwdBufs b;
-  carve_bwd(s, n, p, b);
+  carve_bwd(s, n, npairs, b);
   return s.used;
 }
 
@@ -308,42 +327,30 @@ extern "C" int gpl_gp_kernel_mvm_backward(const gpl_kernel* kern, int n, const f
   GPL_REQUIRE(kern->amplitude != 0.0, "amplitude must be non-zero for the amplitude gradient");
   for (int c = 0; c < npairs; ++c) GPL_REQUIRE(std::isfinite(w[c]), "weight %d is not finite", c);
   GPL_TRY(check_ws(ws, ws_bytes, gpl_gp_kernel_mvm_backward_workspace(n, npairs)));
-  const BwdPlan p = bwd_plan(n, npairs);
   Carver cv(ws, ws_bytes);
   BwdBufs b;
-  carve_bwd(cv, n, p, b);
+  carve_bwd(cv, n, npairs, b);
   if (!cv.ok()) return check_ws(nullptr, 0, 1);
   const float s2 = (float)kernel_scale2(kern->lengthscale);
-  const float amp2 = (float)(kern->amplitude * kern->amplitude);
-  GPL_TRY(plan_build(b.plan, n, px, py, nullptr, s2, kSkipFp32Exact, kSkipFp32Exact, stream));
-  int chunk = 0;
-  for (int c0 = 0; c0 < npairs; ++chunk) {
-    const int left = npairs - c0;
-    const int nc = left >= 16 ? 16 : left >= 8 ? 8 : left >= 4 ? 4 : left >= 2 ? 2 : 1;
+  GPL_TRY(plan_build(b.plan, n, px, py, nullptr, s2, kSkipBackward, kSkipBackward, stream));
+  const int npad = b.plan.npad, blocks = cdiv(npad, 256), passes = bwd_passes(npairs);
+  const double scale = -(kern->amplitude * kern->amplitude) / (kern->lengthscale * kern->lengthscale);
+  for (int pass = 0; pass < passes; ++pass) {
+    const int c0 = pass * kMaxPass, nc = std::min(kMaxPass, npairs - c0), S = bwd_steps(nc);
     WChunk wd;
     for (int c = 0; c < kMaxPass; ++c) wd.w[c] = c < nc ? (float)w[c0 + c] : 0.f;
-    hipLaunchKernelGGL(bwd_gather_kernel, dim3(cdiv(n, 256)), dim3(256), 0, stream, n, nc, c0, b.plan.perm, A, lda,
-                       Bv, ldb, b.As, b.Bs, p.ldg);
-    GPL_LAUNCH_CHECK();
-    double* ph = b.part_h + (size_t)chunk * p.S * p.nrb * 2;
-    switch (nc) {
-      case 16: launch_bwd<16>(p, n, b.plan, s2, amp2, b.As, b.Bs, wd, b.part_g, ph, stream); break;
-      case 8: launch_bwd<8>(p, n, b.plan, s2, amp2, b.As, b.Bs, wd, b.part_g, ph, stream); break;
-      case 4: launch_bwd<4>(p, n, b.plan, s2, amp2, b.As, b.Bs, wd, b.part_g, ph, stream); break;
-      case 2: launch_bwd<2>(p, n, b.plan, s2, amp2, b.As, b.Bs, wd, b.part_g, ph, stream); break;
-      default: launch_bwd<1>(p, n, b.plan, s2, amp2, b.As, b.Bs, wd, b.part_g, ph, stream); break;
+    switch (S) {
+      case 9: GPL_TRY((launch_bwd<9>(b, s2, nc, c0, A, lda, Bv, ldb, wd, stream))); break;
+      case 8: GPL_TRY((launch_bwd<8>(b, s2, nc, c0, A, lda, Bv, ldb, wd, stream))); break;
+      case 4: GPL_TRY((launch_bwd<4>(b, s2, nc, c0, A, lda, Bv, ldb, wd, stream))); break;
+      case 2: GPL_TRY((launch_bwd<2>(b, s2, nc, c0, A, lda, Bv, ldb, wd, stream))); break;
+      default: GPL_TRY((launch_bwd<1>(b, s2, nc, c0, A, lda, Bv, ldb, wd, stream))); break;
     }
+    hipLaunchKernelGGL(bwd_rows_kernel, dim3(blocks), dim3(256), 0, stream, b.plan, b.part, pass == 0 ? 1 : 0,
+                       pass + 1 == passes ? 1 : 0, scale, b.gacc, gpx, gpy, b.part_h + (size_t)pass * 2 * blocks);
     GPL_LAUNCH_CHECK();
-    hipLaunchKernelGGL(bwd_reduce_pos_kernel, dim3(cdiv(n, 256)), dim3(256), 0, stream, n, p.S, b.part_g, p.ldg,
-                       chunk == 0 ? 1 : 0, b.gacc);
-    GPL_LAUNCH_CHECK();
-    c0 += nc;
   }
-  const double inv_l2 = 1.0 / (kern->lengthscale * kern->lengthscale);
-  hipLaunchKernelGGL(bwd_store_pos_kernel, dim3(cdiv(n, 256)), dim3(256), 0, stream, n, b.plan.perm, b.gacc, p.ldg,
-                     inv_l2, gpx, gpy);
-  GPL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(bwd_reduce_hyp_kernel, dim3(1), dim3(256), 0, stream, p.nchunk * p.S * p.nrb, b.part_h,
+  hipLaunchKernelGGL(bwd_reduce_hyp_kernel, dim3(1), dim3(256), 0, stream, passes * blocks, b.part_h,
                      kern->lengthscale, kern->amplitude, g_hyp);
   GPL_LAUNCH_CHECK();
   return GPL_OK;

@@ -34,11 +34,8 @@ constexpr int kMaxPlanChunks = 65535;  // chunk indices are 16-bit
 // drops terms k_ij v_j with k_ij <= 2^-36 a^2, an error-bounded cutoff rather than
 // an exact zero: per row the dropped terms sum to at most 2^-36 a^2 sum_j |v_j|
 // (5.8e-7 a^2 max|v| at 40,000 points), and both forms evaluate the same pairs.
-// -s2 d^2 <= -152 underflows FP32 itself to zero (kept for the adjoint's plan,
-// whose own per-chunk cutoff is applied on top).
 constexpr float kSkipF16x3 = 36.f;
 constexpr float kSkipFp32 = 36.f;
-constexpr float kSkipFp32Exact = 152.f;
 // In the precision form a (subtile, chunk) pair with s2 g^2 >= kLoF16x3 has
 // every kernel value k <= 2^-20, so the lo part of its exp tile (below 2^-10 k)
 // is below 2^-30 per entry, under a 2^-20 share of the FP32 rounding of an
