@@ -17,6 +17,7 @@
 #include "common.hpp"
 #include "gauss_tiles.hpp"
 #include "internal.hpp"
+#include "pixel_axes.hpp"
 
 namespace gpl {
 
@@ -144,30 +145,10 @@ __global__ __launch_bounds__(256) void gauss_matrix_kernel(GSide T, GSide S, flo
                                           tyy + syy + base);
 }
 
-// Pixel shapes of the points of an M x M grid (row-major): a, b the half
-// differences of the neighbouring projected centres along x and y (one-sided at
-// the edges, footnote to eq. "window-kernel"), Z = (a a^T + b b^T) / (4 pi).
+// Pixel shapes of the points of an M x M grid (row-major).
 __global__ void pixel_shapes_kernel(int M, const float* __restrict__ px, const float* __restrict__ py, float* z) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  const int N = M * M;
-  if (j >= N) return;
-  const int fy = j / M, fx = j - fy * M;
-  auto diff = [&](int lo, int hi, float h) -> float2 {  // (p[hi] - p[lo]) * h
-    return make_float2((px[hi] - px[lo]) * h, (py[hi] - py[lo]) * h);
-  };
-  float2 a = make_float2(0.f, 0.f), b = make_float2(0.f, 0.f);
-  if (M > 1) {
-    if (fx == 0) a = diff(j, j + 1, 1.f);
-    else if (fx == M - 1) a = diff(j - 1, j, 1.f);
-    else a = diff(j - 1, j + 1, 0.5f);
-    if (fy == 0) b = diff(j, j + M, 1.f);
-    else if (fy == M - 1) b = diff(j - M, j, 1.f);
-    else b = diff(j - M, j + M, 0.5f);
-  }
-  const float f = (float)(1.0 / (4.0 * M_PI));
-  z[j] = f * (a.x * a.x + b.x * b.x);
-  z[N + j] = f * (a.x * a.y + b.x * b.y);
-  z[2 * N + j] = f * (a.y * a.y + b.y * b.y);
+  if (j < M * M) store_shape(pixel_axes(M, j, px, py), M * M, j, z);
 }
 
 // Adjoint of one column of the Gaussian product. With
@@ -305,90 +286,30 @@ __global__ __launch_bounds__(kGThreads) void gauss_backward_source_kernel(GSide 
   if (gsw) gsw[j] += f * aw;
 }
 
-// Adjoint of pixel_shapes: gz holds dF/dZ_j as a symmetric matrix gradient;
-// Z = (a a^T + b b^T) / (4 pi) gives dF/da = Gbar a / (2 pi), likewise for b.
-// First pass: per point, (dF/da, dF/db) into gab (4 arrays of M*M floats).
+// Adjoint of pixel_shapes. First pass: per point, (dF/da, dF/db) into gab (4
+// arrays of M*M floats).
 __global__ void pixel_axes_grad_kernel(int M, const float* __restrict__ px, const float* __restrict__ py,
                                        const float* __restrict__ gz, float* gab) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   const int N = M * M;
   if (j >= N) return;
-  const int fy = j / M, fx = j - fy * M;
-  float2 a = make_float2(0.f, 0.f), b = make_float2(0.f, 0.f);
-  if (M > 1) {
-    auto diff = [&](int lo, int hi, float h) { return make_float2((px[hi] - px[lo]) * h, (py[hi] - py[lo]) * h); };
-    if (fx == 0) a = diff(j, j + 1, 1.f);
-    else if (fx == M - 1) a = diff(j - 1, j, 1.f);
-    else a = diff(j - 1, j + 1, 0.5f);
-    if (fy == 0) b = diff(j, j + M, 1.f);
-    else if (fy == M - 1) b = diff(j - M, j, 1.f);
-    else b = diff(j - M, j + M, 0.5f);
-  }
-  const float f = (float)(1.0 / (2.0 * M_PI));
-  const float gxx = gz[j], gxy = gz[N + j], gyy = gz[2 * N + j];
-  gab[j] = f * fmaf(gxx, a.x, gxy * a.y);
-  gab[N + j] = f * fmaf(gxy, a.x, gyy * a.y);
-  gab[2 * N + j] = f * fmaf(gxx, b.x, gxy * b.y);
-  gab[3 * N + j] = f * fmaf(gxy, b.x, gyy * b.y);
+  const PixelAxes g = axes_grad(M, j, px, py, gz);
+  gab[j] = g.a.x;
+  gab[N + j] = g.a.y;
+  gab[2 * N + j] = g.b.x;
+  gab[3 * N + j] = g.b.y;
 }
 
-// d a_c / d p_m along one grid line of length M (one-sided differences at the ends).
-__device__ inline float axis_coef(int c, int m, int M) {
-  if (M == 1) return 0.f;
-  if (c == 0) return (m == 1 ? 1.f : 0.f) - (m == 0 ? 1.f : 0.f);
-  if (c == M - 1) return (m == M - 1 ? 1.f : 0.f) - (m == M - 2 ? 1.f : 0.f);
-  return (m == c + 1 ? 0.5f : 0.f) - (m == c - 1 ? 0.5f : 0.f);
-}
-
-// Second pass: gpx/gpy[m] += sum over the axes that depend on p_m (neighbours
-// c = m-1, m, m+1 along the row for a, along the column for b).
+// Second pass: gpx/gpy[m] += sum over the axes that depend on p_m.
 __global__ void pixel_axes_gather_kernel(int M, const float* __restrict__ gab, float* gpx, float* gpy) {
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
   const int N = M * M;
   if (m >= N) return;
-  const int fy = m / M, fx = m - fy * M;
-  float sx = 0.f, sy = 0.f;
-  for (int c = max(fx - 1, 0); c <= min(fx + 1, M - 1); ++c) {
-    const float w = axis_coef(c, fx, M);
-    const int j = fy * M + c;
-    sx = fmaf(w, gab[j], sx);
-    sy = fmaf(w, gab[N + j], sy);
-  }
-  for (int c = max(fy - 1, 0); c <= min(fy + 1, M - 1); ++c) {
-    const float w = axis_coef(c, fy, M);
-    const int j = c * M + fx;
-    sx = fmaf(w, gab[2 * N + j], sx);
-    sy = fmaf(w, gab[3 * N + j], sy);
-  }
-  gpx[m] += sx;
-  gpy[m] += sy;
-}
-
-// Adjoint of weights w_j = r_j sqrt(pi / k) (w = rho^{-1/2}, rho = k / (pi r^2)),
-// r_j = |q_j - q_nn(j)|: dF/dq_j += coef v, dF/dq_nn(j) -= coef v with
-// v = q_j - q_nn(j), coef = gw_j w_j / r_j^2. The neighbour's share is
-// scattered with FP64 atomic adds into gq (2n doubles: x then y).
-__global__ void knn_weight_backward_kernel(int n, const float* __restrict__ qx, const float* __restrict__ qy,
-                                           const float* __restrict__ rk, const int* __restrict__ nn,
-                                           const float* __restrict__ w, const float* __restrict__ gw, double* gq) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  const int o = nn[j];
-  const float r = rk[j];
-  if (o < 0 || !(r > 0.f)) return;
-  const double coef = (double)gw[j] * (double)w[j] / ((double)r * (double)r);
-  const double vx = coef * (double)(qx[j] - qx[o]), vy = coef * (double)(qy[j] - qy[o]);
-  atomicAdd(gq + j, vx);
-  atomicAdd(gq + n + j, vy);
-  atomicAdd(gq + o, -vx);
-  atomicAdd(gq + n + o, -vy);
-}
-
-__global__ void add_double_pairs_kernel(int n, const double* __restrict__ gq, float* gpx, float* gpy) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  gpx[j] += (float)gq[j];
-  gpy[j] += (float)gq[n + j];
+  const float2 s = axes_gather(M, m, [&](int j) {
+    return PixelAxes{make_float2(gab[j], gab[N + j]), make_float2(gab[2 * N + j], gab[3 * N + j])};
+  });
+  gpx[m] += s.x;
+  gpy[m] += s.y;
 }
 
 int gauss_backward_launch(const GSide& T, const GSide& S, double base_var, double norm, const float* V, const float* U,
@@ -418,17 +339,6 @@ int pixel_shapes_backward_launch(int M, const float* px, const float* py, const 
   hipLaunchKernelGGL(pixel_axes_grad_kernel, dim3(cdiv(N, 256)), dim3(256), 0, stream, M, px, py, gz, gab);
   GPL_LAUNCH_CHECK();
   hipLaunchKernelGGL(pixel_axes_gather_kernel, dim3(cdiv(N, 256)), dim3(256), 0, stream, M, gab, gpx, gpy);
-  GPL_LAUNCH_CHECK();
-  return GPL_OK;
-}
-
-int knn_weight_backward_launch(int n, const float* qx, const float* qy, const float* rk, const int* nn,
-                               const float* w, const float* gw, double* gq, float* gpx, float* gpy,
-                               hipStream_t stream) {
-  hipLaunchKernelGGL(knn_weight_backward_kernel, dim3(cdiv(n, 256)), dim3(256), 0, stream, n, qx, qy, rk, nn, w, gw,
-                     gq);
-  GPL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(add_double_pairs_kernel, dim3(cdiv(n, 256)), dim3(256), 0, stream, n, gq, gpx, gpy);
   GPL_LAUNCH_CHECK();
   return GPL_OK;
 }

@@ -68,10 +68,10 @@ __device__ __forceinline__ float shape_reach(float zxx, float zxy, float zyy, fl
 // of its shapes. Thread j handles sorted source j < npad; the padding has zero
 // columns.
 template <int MODE>
-__global__ __launch_bounds__(256) void gauss_prep_kernel(GSorted S, const float* __restrict__ z,
-                                                         const float* __restrict__ w, const float* __restrict__ V,
-                                                         int ldv, int nc, float base, float* __restrict__ wv,
-                                                         float* __restrict__ form, float* __restrict__ reach) {
+__device__ __forceinline__ void gauss_prep_body(const GSorted& S, const float* __restrict__ z,
+                                                const float* __restrict__ w, const float* __restrict__ V, int ldv,
+                                                int nc, float base, float* __restrict__ wv, float* __restrict__ form,
+                                                float* __restrict__ reach) {
   const int j = blockIdx.x * 256 + threadIdx.x;
   const int npad = S.nch * kChunk;
   if (j >= npad) return;  // whole waves: npad is a multiple of 64
@@ -104,24 +104,31 @@ __global__ __launch_bounds__(256) void gauss_prep_kernel(GSorted S, const float*
   if ((j & (kChunk - 1)) == 0) reach[j / kChunk] = lam;
 }
 
+template <int MODE>
+__global__ __launch_bounds__(256) void gauss_prep_kernel(GSorted S, const float* __restrict__ z,
+                                                         const float* __restrict__ w, const float* __restrict__ V,
+                                                         int ldv, int nc, float base, float* __restrict__ wv,
+                                                         float* __restrict__ form, float* __restrict__ reach) {
+  gauss_prep_body<MODE>(S, z, w, V, ldv, nc, base, wv, form, reach);
+}
+
 // Sums held per target: NC columns, or (MOM) the sum and its first moments in
 // the scaled C^{-1} d.
 template <bool MOM, int NC>
 constexpr int kSums = MOM ? 3 : NC;
 
 template <int MODE, bool MOM, int NC>
-__global__ __launch_bounds__(64 * kTWaves) void gauss_tiles_kernel(GSorted T, const float* __restrict__ tz, GSorted S,
-                                                                   const float* __restrict__ wv,
-                                                                   const float* __restrict__ form,
-                                                                   const float* __restrict__ reach, float base,
-                                                                   float* __restrict__ part) {
+__device__ __forceinline__ void gauss_tiles_body(int tile, int slice, int nslices, const GSorted& T,
+                                                 const float* __restrict__ tz, const GSorted& S,
+                                                 const float* __restrict__ wv, const float* __restrict__ form,
+                                                 const float* __restrict__ reach, float base,
+                                                 float* __restrict__ part) {
   constexpr int K = kSums<MOM, NC>;
   __shared__ uint32_t list[kTList];
   __shared__ int cnt_s[kTWaves * kTBatch];
   __shared__ float red[kTWaves][K][kRowTile];
   const int tid = threadIdx.x, lane = tid & 63, wvi = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ri = lane & 15, g = lane >> 4;
-  const int tile = blockIdx.x, slice = blockIdx.y, nslices = gridDim.y;
   const int npt = T.nch * kChunk, nps = S.nch * kChunk;
   // this lane's target of each subtile, and the subtiles' boxes and reaches
   float xi[kSubsPerTile], yi[kSubsPerTile];
@@ -270,6 +277,15 @@ __global__ __launch_bounds__(64 * kTWaves) void gauss_tiles_kernel(GSorted T, co
   }
 }
 
+template <int MODE, bool MOM, int NC>
+__global__ __launch_bounds__(64 * kTWaves) void gauss_tiles_kernel(GSorted T, const float* __restrict__ tz, GSorted S,
+                                                                   const float* __restrict__ wv,
+                                                                   const float* __restrict__ form,
+                                                                   const float* __restrict__ reach, float base,
+                                                                   float* __restrict__ part) {
+  gauss_tiles_body<MODE, MOM, NC>(blockIdx.x, blockIdx.y, gridDim.y, T, tz, S, wv, form, reach, base, part);
+}
+
 // Y[c][i] = norm wt_i |C_i|^{-1/2} sum + beta Y[c][i] (the determinant when the
 // shapes are the targets' alone).
 template <int MODE>
@@ -382,16 +398,87 @@ int gauss_tiles_product(const GSorted& T, const float* tz, const float* tw, cons
   return product_cols<kShapesNone>(T, tz, tw, S, sz, sw, fb, fn, nrhs, V, ldv, Y, ldy, beta, b, stream);
 }
 
-int gauss_tiles_sums(const GSorted& T, const GSorted& S, const float* sz, double base, const float* V,
-                     const GTileBufs& b, int* nslices, hipStream_t stream) {
-  const float fb = (float)base;
-  const int ns = *nslices = tile_slices(T, S);
-  if (sz) {
-    GPL_TRY(prep_launch<kShapesSource>(S, sz, nullptr, V, 0, 1, fb, b, stream));
-    return tiles_launch<kShapesSource, true, 1>(T, nullptr, S, fb, b, ns, stream);
+// ---- one column of several layers at once
+//
+// The layers of a source model share the points; each has its own base covariance
+// and its own targets (the traced points or the grid). Their launches are one: at a
+// thousand points each costs its launch and no more, and at 40,000 the tail of one
+// layer's launch is filled by the next layer's work (longest reach first).
+struct SumsArgs {
+  GSorted S;
+  const float *V, *sz;
+  int nl;
+  struct {
+    GSorted T;
+    int tiles, slices, shapes;
+    float base;
+    GTileBufs b;
+  } l[kGaussLayers];
+};
+
+__global__ __launch_bounds__(256) void gauss_layers_prep_kernel(SumsArgs A) {
+  const auto& L = A.l[blockIdx.y];
+  if (L.shapes)
+    gauss_prep_body<kShapesSource>(A.S, A.sz, nullptr, A.V, 0, 1, L.base, L.b.wv, L.b.form, L.b.reach);
+  else
+    gauss_prep_body<kShapesNone>(A.S, nullptr, nullptr, A.V, 0, 1, L.base, L.b.wv, L.b.form, L.b.reach);
+}
+
+__global__ __launch_bounds__(64 * kTWaves) void gauss_layers_kernel(SumsArgs A) {
+  const auto& L = A.l[blockIdx.y];
+  const int slice = blockIdx.x / L.tiles, tile = blockIdx.x - slice * L.tiles;
+  if (slice >= L.slices) return;
+  if (L.shapes)
+    gauss_tiles_body<kShapesSource, true, 1>(tile, slice, L.slices, L.T, nullptr, A.S, L.b.wv, L.b.form, L.b.reach,
+                                             L.base, L.b.part);
+  else
+    gauss_tiles_body<kShapesNone, false, 1>(tile, slice, L.slices, L.T, nullptr, A.S, L.b.wv, L.b.form, L.b.reach,
+                                            L.base, L.b.part);
+}
+
+template <class C>
+static void carve_sums(C& cv, const int* nt, int ns, int nl, GTileBufs* b) {
+  for (int k = 0; k < nl; ++k) carve_tiles(cv, sorted_sizes(nt[k]), sorted_sizes(ns), 1, b[k]);
+}
+
+size_t gauss_layers_scratch(const int* nt, int ns, int nl) {
+  Sizer s;
+  GTileBufs b[kGaussLayers];
+  carve_sums(s, nt, ns, nl, b);
+  return s.used;
+}
+
+int gauss_layers_sums(GaussLayerSums* layers, int nl, const GSorted& S, const float* sz, const float* V, void* scratch,
+                      size_t bytes, hipStream_t stream) {
+  GPL_REQUIRE(nl >= 1 && nl <= kGaussLayers, "nl=%d", nl);
+  int nt[kGaussLayers], turn[kGaussLayers];
+  GTileBufs b[kGaussLayers];
+  for (int k = 0; k < nl; ++k) {
+    nt[k] = layers[k].T.n;
+    turn[k] = k;
   }
-  GPL_TRY(prep_launch<kShapesNone>(S, sz, nullptr, V, 0, 1, fb, b, stream));
-  return tiles_launch<kShapesNone, false, 1>(T, nullptr, S, fb, b, ns, stream);
+  Carver cv(scratch, bytes);
+  carve_sums(cv, nt, S.n, nl, b);
+  if (!cv.ok()) return check_ws(nullptr, 0, 1);
+  std::stable_sort(turn, turn + nl, [&](int x, int y) { return layers[x].base > layers[y].base; });
+  SumsArgs A{};
+  A.S = S;
+  A.V = V;
+  A.sz = sz;
+  A.nl = nl;
+  int blocks = 0;
+  for (int q = 0; q < nl; ++q) {
+    GaussLayerSums& L = layers[turn[q]];
+    L.part = b[turn[q]].part;
+    L.nslices = tile_slices(L.T, S);
+    A.l[q] = {L.T, cdiv(L.T.n, kRowTile), L.nslices, L.shapes, (float)L.base, b[turn[q]]};
+    blocks = std::max(blocks, A.l[q].tiles * L.nslices);
+  }
+  hipLaunchKernelGGL(gauss_layers_prep_kernel, dim3(cdiv(S.nch * kChunk, 256), nl), dim3(256), 0, stream, A);
+  GPL_LAUNCH_CHECK();
+  hipLaunchKernelGGL(gauss_layers_kernel, dim3(blocks, nl), dim3(64 * kTWaves), 0, stream, A);
+  GPL_LAUNCH_CHECK();
+  return GPL_OK;
 }
 
 // ---- one column, sources in the caller's order
@@ -432,20 +519,40 @@ static_assert(64 % kOChunk == 0 && kOChunk % 4 == 0 && kOTargets == kSubTile, "w
 
 static __host__ __device__ int ordered_share(int n) { return cdiv(cdiv(n, 64), kOWaves) * (64 / kOChunk); }
 
-// Source j: (x, y, weight, column value), zeros past n, and the box of its chunk,
-// infinite when one of them is not finite in it. Sorted target j: listed in far
-// when its shape reaches far (the order of the list does not enter any result).
-__global__ __launch_bounds__(256) void ordered_prep_kernel(int n, const float* __restrict__ x,
-                                                           const float* __restrict__ y, const float* __restrict__ w,
-                                                           const float* __restrict__ V, float4* __restrict__ src,
-                                                           float4* __restrict__ box, GSorted T,
-                                                           const float* __restrict__ tz, float base, int* far_count,
-                                                           int* __restrict__ far) {
+struct OrderedBufs {
+  float4 *src, *box;
+  int* far;
+  float* part;
+};
+struct OrderedArgs {
+  GSorted T;
+  const float* tz;
+  int tiles, nl;
+  int turn[kGaussLayers];  // launch order of the layers
+  struct {
+    const float *x, *y, *w, *V;
+    int ns, shapes;
+    float base, norm;
+    int* far_count;
+    OrderedBufs b;
+  } l[kGaussLayers];
+};
+
+// Layer blockIdx.y. Source j: (x, y, weight, column value), zeros past n, and the
+// box of its chunk, infinite when one of them is not finite in it. Sorted target j:
+// listed in far when its shape reaches far (the order of the list does not enter
+// any result).
+__global__ __launch_bounds__(256) void ordered_prep_kernel(OrderedArgs A) {
+  const auto& L = A.l[blockIdx.y];
+  const int n = L.ns;
+  const float *__restrict__ x = L.x, *__restrict__ y = L.y, *__restrict__ w = L.w, *__restrict__ V = L.V;
+  const float* __restrict__ tz = A.tz;
+  float4 *__restrict__ src = L.b.src, *__restrict__ box = L.b.box;
   const int j = blockIdx.x * 256 + threadIdx.x, npad = round_up(n, kOChunk);
-  if (tz && j < T.n) {
-    const int jj = T.perm[j];
-    if (shape_reach(tz[jj], tz[T.n + jj], tz[2 * (size_t)T.n + jj], base) > kFarReach * base)
-      far[atomicAdd(far_count, 1)] = j;
+  if (L.shapes && j < A.T.n) {
+    const int jj = A.T.perm[j];
+    if (shape_reach(tz[jj], tz[A.T.n + jj], tz[2 * (size_t)A.T.n + jj], L.base) > kFarReach * L.base)
+      L.b.far[atomicAdd(L.far_count, 1)] = j;
   }
   float4 q = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
   if (j < n) {
@@ -500,16 +607,17 @@ struct OrderedTarget {
     }
     return val;
   }
-  __device__ __forceinline__ void store(float norm, float beta, int first_pos, int first_shape, int ii, int n, float* f,
-                                        float* tg) const {
+  // f += norm |C|^{-1/2} sum, and tg: -sum G C^{-1} d for the positions and, with
+  // shapes, sum G (C^{-1} d d^T C^{-1} - C^{-1}) / 2 (xx, xy, yy) with the same factor.
+  __device__ __forceinline__ void add(float norm, float& f, float (&tg)[5]) const {
     const float c = norm * rdet, h = 0.5f * c;
-    f[ii] = beta != 0.f ? c * acc[0] + beta * f[ii] : c * acc[0];
-    const float v[5] = {-c * acc[1], -c * acc[2], h * (acc[3 % K] - ixx * acc[0]), h * (acc[4 % K] - ixy * acc[0]),
-                        h * (acc[5 % K] - iyy * acc[0])};
-#pragma unroll
-    for (int k = 0; k < (kShapes ? 5 : 2); ++k) {
-      float* t = tg + (size_t)k * n + ii;
-      *t = (k < 2 ? first_pos : first_shape) ? v[k] : *t + v[k];
+    f = fmaf(c, acc[0], f);
+    tg[0] -= c * acc[1];
+    tg[1] -= c * acc[2];
+    if (kShapes) {
+      tg[2] += h * (acc[3 % K] - ixx * acc[0]);
+      tg[3] += h * (acc[4 % K] - ixy * acc[0]);
+      tg[4] += h * (acc[5 % K] - iyy * acc[0]);
     }
   }
 };
@@ -524,11 +632,10 @@ __device__ __forceinline__ float quad_next(float v) {
 // hold the images are several times the work of the others). The rest (with
 // shapes): wave q takes eighth q % 8 of the sources of listed target q / 8.
 template <bool kShapes>
-__global__ __launch_bounds__(64) void gauss_ordered_kernel(GSorted T, int tiles, const float* __restrict__ tz, int ns,
-                                                           const float4* __restrict__ src,
-                                                           const float4* __restrict__ box, float base,
-                                                           const int* __restrict__ far_count,
-                                                           const int* __restrict__ far, float* __restrict__ part) {
+__device__ __forceinline__ void gauss_ordered_body(const GSorted& T, int tiles, const float* __restrict__ tz, int ns,
+                                                   const float4* __restrict__ src, const float4* __restrict__ box,
+                                                   float base, const int* __restrict__ far_count,
+                                                   const int* __restrict__ far, float* __restrict__ part) {
   using Target = OrderedTarget<kShapes>;
   constexpr int K = Target::K;
   const int lane = threadIdx.x, wv = blockIdx.x / tiles, tile = blockIdx.x % tiles, npt = T.nch * kChunk;
@@ -602,19 +709,23 @@ __global__ __launch_bounds__(64) void gauss_ordered_kernel(GSorted T, int tiles,
   for (int k = 0; k < K; ++k) part[((size_t)wv * K + k) * npt + i] = t.acc[k];
 }
 
-// f = norm |C|^{-1/2} sum + beta f over the shares in order, and the adjoint
-// towards the targets per unit of dF/df: tg (+)= -sum G C^{-1} d for the positions
-// and, with shapes, sum G (C^{-1} d d^T C^{-1} - C^{-1}) / 2 for the shapes (xx, xy, yy),
-// with the same factor; first_pos, first_shape: overwrite instead of adding.
+__global__ __launch_bounds__(64) void gauss_ordered_kernel(OrderedArgs A) {
+  const auto& L = A.l[A.turn[blockIdx.y]];
+  if (L.shapes) {
+    gauss_ordered_body<true>(A.T, A.tiles, A.tz, L.ns, L.b.src, L.b.box, L.base, L.far_count, L.b.far, L.b.part);
+  } else if ((int)blockIdx.x < A.tiles * kOWaves) {
+    gauss_ordered_body<false>(A.T, A.tiles, nullptr, L.ns, L.b.src, L.b.box, L.base, nullptr, nullptr, L.b.part);
+  }
+}
+
+// One layer of the end: the shares added in order.
 template <bool kShapes>
-__global__ __launch_bounds__(256) void ordered_finish_kernel(GSorted T, const float* __restrict__ tz, float base,
-                                                             float norm, float beta, const float* __restrict__ part,
-                                                             int first_pos, int first_shape, float* f, float* tg) {
+__device__ __forceinline__ void ordered_finish(const GSorted& T, int i, int ii, const float* __restrict__ tz,
+                                               float base, float norm, const float* __restrict__ part, float& f,
+                                               float (&tg)[5]) {
   using Target = OrderedTarget<kShapes>;
   constexpr int K = Target::K;
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= T.n) return;
-  const int ii = T.perm[i], npt = T.nch * kChunk;
+  const int npt = T.nch * kChunk;
   Target t;
   t.init(T.x[i], T.y[i], kShapes ? tz[ii] : 0.f, kShapes ? tz[T.n + ii] : 0.f, kShapes ? tz[2 * (size_t)T.n + ii] : 0.f,
          base);
@@ -629,58 +740,75 @@ __global__ __launch_bounds__(256) void ordered_finish_kernel(GSorted T, const fl
 #pragma unroll
     for (int w = 1; w < kOWaves; ++w) t.acc[k] += v[w][k];
   }
-  t.store(norm, beta, first_pos, first_shape, ii, T.n, f, tg);
+  t.add(norm, f, tg);
 }
 
-struct OrderedBufs {
-  float4 *src, *box;
-  int* far;
-  float* part;
-};
+// f += the layers in their order, tg = their adjoint towards the targets.
+__global__ __launch_bounds__(256) void ordered_finish_kernel(OrderedArgs A, float* f, float* tg) {
+  const int i = blockIdx.x * 256 + threadIdx.x, n = A.T.n;
+  if (i >= n) return;
+  const int ii = A.T.perm[i];
+  float fi = f[ii], t[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int k = 0; k < A.nl; ++k) {
+    const auto& L = A.l[k];
+    if (L.shapes) ordered_finish<true>(A.T, i, ii, A.tz, L.base, L.norm, L.b.part, fi, t);
+    else ordered_finish<false>(A.T, i, ii, nullptr, L.base, L.norm, L.b.part, fi, t);
+  }
+  f[ii] = fi;
+#pragma unroll
+  for (int k = 0; k < 5; ++k) tg[(size_t)k * n + ii] = t[k];
+}
+
 template <class C>
-static void carve_ordered(C& cv, int nt, int ns, OrderedBufs& b) {
-  b.src = cv.template take<float4>(round_up(ns, kOChunk));
-  b.box = cv.template take<float4>(cdiv(ns, kOChunk));
-  b.far = cv.template take<int>(nt);
-  b.part = cv.template take<float>((size_t)kOWaves * 6 * round_up(nt, kRowTile));
+static void carve_ordered(C& cv, int nt, const int* ns, int nl, OrderedBufs* b) {
+  for (int k = 0; k < nl; ++k) {
+    b[k].src = cv.template take<float4>(round_up(ns[k], kOChunk));
+    b[k].box = cv.template take<float4>(cdiv(ns[k], kOChunk));
+    b[k].far = cv.template take<int>(nt);
+    b[k].part = cv.template take<float>((size_t)kOWaves * 6 * round_up(nt, kRowTile));
+  }
 }
 
-size_t gauss_ordered_scratch(int nt, int ns) {
+size_t gauss_ordered_scratch(int nt, const int* ns, int nl) {
   Sizer s;
-  OrderedBufs b;
-  carve_ordered(s, nt, ns, b);
+  OrderedBufs b[kGaussLayers];
+  carve_ordered(s, nt, ns, nl, b);
   return s.used;
 }
 
-template <bool kShapes>
-static int ordered_run(const GSorted& T, const float* tz, int ns, float base, float norm, float beta, int first_pos,
-                       int first_shape, float* f, float* tg, int* far_count, const OrderedBufs& b,
-                       hipStream_t stream) {
-  const int tiles = cdiv(T.n, kOTargets);
-  hipLaunchKernelGGL(gauss_ordered_kernel<kShapes>, dim3(tiles * kOWaves + (kShapes ? kFarBlocks : 0)), dim3(64), 0,
-                     stream, T, tiles, tz, ns, b.src, b.box, base, far_count, b.far, b.part);
+int gauss_ordered_launch(const GSorted& T, const float* tz, const GaussLayer* layers, int nl, float* f, float* tg,
+                         int* far_count, void* scratch, size_t bytes, hipStream_t stream) {
+  GPL_REQUIRE(nl >= 1 && nl <= kGaussLayers, "nl=%d", nl);
+  OrderedArgs A{};
+  A.T = T;
+  A.tz = tz;
+  A.tiles = cdiv(T.n, kOTargets);
+  A.nl = nl;
+  int ns[kGaussLayers], prep = 1;
+  OrderedBufs b[kGaussLayers];
+  bool shapes = false;
+  for (int k = 0; k < nl; ++k) {
+    ns[k] = layers[k].S.n;
+    A.turn[k] = k;
+    prep = std::max({prep, round_up(ns[k], kOChunk), layers[k].shapes ? T.n : 0});
+    shapes = shapes || layers[k].shapes;
+  }
+  Carver cv(scratch, bytes);
+  carve_ordered(cv, T.n, ns, nl, b);
+  if (!cv.ok()) return check_ws(nullptr, 0, 1);
+  for (int k = 0; k < nl; ++k) {
+    const GaussLayer& q = layers[k];
+    A.l[k] = {q.S.x, q.S.y, q.S.w, q.V, q.S.n, q.shapes, (float)q.base, (float)q.norm, far_count + k, b[k]};
+  }
+  std::stable_sort(A.turn, A.turn + nl, [&](int p, int q) { return layers[p].base > layers[q].base; });
+  hipLaunchKernelGGL(ordered_prep_kernel, dim3(cdiv(prep, 256), nl), dim3(256), 0, stream, A);
   GPL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(ordered_finish_kernel<kShapes>, dim3(cdiv(T.n, 256)), dim3(256), 0, stream, T, tz, base, norm,
-                     beta, b.part, first_pos, first_shape, f, tg);
+  hipLaunchKernelGGL(gauss_ordered_kernel, dim3(A.tiles * kOWaves + (shapes ? kFarBlocks : 0), nl), dim3(64), 0, stream,
+                     A);
+  GPL_LAUNCH_CHECK();
+  hipLaunchKernelGGL(ordered_finish_kernel, dim3(cdiv(T.n, 256)), dim3(256), 0, stream, A, f, tg);
   GPL_LAUNCH_CHECK();
   return GPL_OK;
-}
-
-int gauss_ordered_launch(const GSorted& T, const float* tz, const GSide& S, double base, double norm, const float* V,
-                         float beta, int first_pos, int first_shape, float* f, float* tg, int* far_count,
-                         void* scratch, size_t bytes, hipStream_t stream) {
-  Carver cv(scratch, bytes);
-  OrderedBufs b;
-  carve_ordered(cv, T.n, S.n, b);
-  if (!cv.ok()) return check_ws(nullptr, 0, 1);
-  hipLaunchKernelGGL(ordered_prep_kernel, dim3(cdiv(std::max(round_up(S.n, kOChunk), tz ? T.n : 0), 256)), dim3(256), 0,
-                     stream, S.n, S.x, S.y, S.w, V, b.src, b.box, T, tz, (float)base, far_count, b.far);
-  GPL_LAUNCH_CHECK();
-  if (tz)
-    return ordered_run<true>(T, tz, S.n, (float)base, (float)norm, beta, first_pos, first_shape, f, tg, far_count, b,
-                             stream);
-  return ordered_run<false>(T, tz, S.n, (float)base, (float)norm, beta, first_pos, first_shape, f, tg, far_count, b,
-                            stream);
 }
 
 template <class C>

@@ -3,11 +3,10 @@
 #pragma once
 
 #include "common.hpp"
+#include "internal.hpp"
 #include "tileplan.hpp"
 
 namespace gpl {
-
-struct GSide;
 
 // Which side's shapes enter the covariance C_ij (with base I always).
 constexpr int kShapesNone = 0, kShapesTarget = 1, kShapesSource = 2, kShapesBoth = 3;
@@ -62,20 +61,37 @@ int gauss_tiles_carve(int nt, int ns, int cols, void* ws, size_t ws_bytes, GTile
 int gauss_tiles_product(const GSorted& T, const float* tz, const float* tw, const GSorted& S, const float* sz,
                         const float* sw, double base, double norm, int nrhs, const float* V, int ldv, float* Y,
                         int ldy, float beta, const GTileBufs& b, hipStream_t stream);
-// Per target the partial sums over the sources of G_ij V_j u, into b.part
-// (fold_slices, *nslices slices): with source shapes sz three sums, u = 1 and both
-// components of kFormScale C_j^{-1} d, d = target - source, and G_ij = |C_j|^{-1/2}
-// exp(-d^T C_j^{-1} d / 2); without shapes one, u = 1 and G_ij = exp(-d^2 / (2 base)).
-int gauss_tiles_sums(const GSorted& T, const GSorted& S, const float* sz, double base, const float* V,
-                     const GTileBufs& b, int* nslices, hipStream_t stream);
-// One column f = T V + beta f for sources without shapes in the caller's order
-// (S.w given), targets with shapes tz (caller's order) or none, and tg, five
-// arrays of T.n floats (two without shapes): the adjoint towards the targets per
-// unit of dF/df. *far_count (device) is zero before the launch.
-size_t gauss_ordered_scratch(int nt, int ns);
-int gauss_ordered_launch(const GSorted& T, const float* tz, const GSide& S, double base, double norm, const float* V,
-                         float beta, int first_pos, int first_shape, float* f, float* tg, int* far_count,
-                         void* scratch, size_t bytes, hipStream_t stream);
+// One column of several layers over shared points, each with its own base covariance.
+constexpr int kGaussLayers = 8;
+// Per target the partial sums over the sources of G_ij V_j u, into part
+// (fold_slices, nslices slices; both set by the call): with the source shapes sz three
+// sums, u = 1 and both components of kFormScale C_j^{-1} d, d = target - source, and G_ij
+// = |C_j|^{-1/2} exp(-d^T C_j^{-1} d / 2); without (shapes 0) one, u = 1 and
+// G_ij = exp(-d^2 / (2 base)).
+struct GaussLayerSums {
+  GSorted T;
+  int shapes;
+  double base;
+  float* part;
+  int nslices;
+};
+size_t gauss_layers_scratch(const int* nt, int ns, int nl);
+int gauss_layers_sums(GaussLayerSums* layers, int nl, const GSorted& S, const float* sz, const float* V, void* scratch,
+                      size_t bytes, hipStream_t stream);
+// f += sum over the layers of T_k V_k, T_k from sources without shapes in the caller's
+// order (S.w given) to the targets T with the shapes tz (caller's order; layers with
+// shapes 0: without), and tg, five arrays of T.n floats: the adjoint towards the
+// targets per unit of dF/df (two components of the position, three of the shape).
+// far_count[k] (device) is zero before the launch.
+struct GaussLayer {
+  GSide S;
+  int shapes;
+  double base, norm;
+  const float* V;
+};
+size_t gauss_ordered_scratch(int nt, const int* ns, int nl);
+int gauss_ordered_launch(const GSorted& T, const float* tz, const GaussLayer* layers, int nl, float* f, float* tg,
+                         int* far_count, void* scratch, size_t bytes, hipStream_t stream);
 // The product from the caller's order: sorts the points in the workspace (0 bytes
 // where the dense product is the faster one, gauss_pair_sorted false).
 bool gauss_pair_sorted(int nt, int ns);

@@ -168,17 +168,27 @@ int gauss_backward_launch(const GSide& T, const GSide& S, double base_var, doubl
                           float* gtx, float* gty, float* gtz, float* gsx, float* gsy, float* gsw, hipStream_t stream);
 int pixel_shapes_backward_launch(int M, const float* px, const float* py, const float* gz, float* gab, float* gpx,
                                  float* gpy, hipStream_t stream);
-// Distance rk to (and caller index nn of) the k-th closest other point, and the
-// density rho (each nullable), for points sorted by plan_sort.
-int knn_sorted_launch(const TilePlan& p, int k, float* rho, float* rk, int* nn, hipStream_t stream);
-int knn_weight_backward_launch(int n, const float* qx, const float* qy, const float* rk, const int* nn,
-                               const float* w, const float* gw, double* gq, float* gpx, float* gpy,
-                               hipStream_t stream);
+// Distance rk to (and caller index nn of) the k-th closest other point, the
+// density rho and the weight w = scale rk (each nullable), for one or two sets of
+// points sorted by plan_sort (two: in one launch).
+struct KnnSet {
+  TilePlan plan;
+  float *rho, *rk, *w;
+  int* nn;
+};
+int knn_sorted_launch(const KnnSet* sets, int nsets, int k, float scale, hipStream_t stream);
 // Ray tracing and its adjoint with the 8 lens parameters in device memory.
-size_t raytrace_dev_backward_scratch(int N);
 int raytrace_dev_launch(const gpl_grid* grid, const double* lens, float* px, float* py, hipStream_t stream);
-int raytrace_dev_backward_launch(const gpl_grid* grid, const double* lens, const float* gpx, const float* gpy,
-                                 double* g_lens, double* scratch_partial, hipStream_t stream);
+// Per 256 points, 8 partial sums (FP64) of the gradient of the lens parameters from
+// dF/dp = gpx, gpy + gq (2 N doubles, nullable: x then y) + the adjoint of the pixel
+// shapes' gradient gz (as pixel_shapes_backward_launch; nullable) at px, py.
+struct PointGrads {
+  const float *gpx, *gpy;
+  const double* gq;
+  const float *gz, *px, *py;
+};
+int raytrace_dev_backward_launch(const gpl_grid* grid, const double* lens, const PointGrads& g, double* partial,
+                                 hipStream_t stream);
 int check_kernel_any(const gpl_kernel* k);  // RBF or windowed (kind 1)
 size_t windowed_workspace(int n, int nrhs);
 int windowed_mvm(const gpl_kernel* kern, const gpl_grid* grid, int n, const float* px, const float* py, int nrhs,

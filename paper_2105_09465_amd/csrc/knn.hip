@@ -68,15 +68,26 @@ __device__ __forceinline__ KnnKey wave_select(KnnKey a, KnnKey b, unsigned long 
 
 __device__ __forceinline__ unsigned long long low_mask(int n) { return n >= 64 ? ~0ull : (1ull << n) - 1ull; }
 
-__global__ __launch_bounds__(64 * kKnnWaves) void knn_sorted_kernel(int n, int nch, const float* __restrict__ xs,
-                                                                    const float* __restrict__ ys,
-                                                                    const int* __restrict__ perm,
-                                                                    const float4* __restrict__ cbox, int k,
-                                                                    float* rho, float* rk, int* nn) {
+// A set of sorted points and its outputs; the workgroups from `block0` on are its.
+struct KnnArgs {
+  int n, nch, block0;
+  const float *xs, *ys;
+  const int* perm;
+  const float4* cbox;
+  float *rho, *rk, *w;
+  int* nn;
+};
+
+__global__ __launch_bounds__(64 * kKnnWaves) void knn_sorted_kernel(KnnArgs first, KnnArgs second, int k, float scale) {
   __shared__ KnnKey sbuf[kKnnWaves][kKnnBuf];
+  const KnnArgs& S = (int)blockIdx.x < second.block0 ? first : second;
+  const int n = S.n, nch = S.nch;
+  const float *__restrict__ xs = S.xs, *__restrict__ ys = S.ys;
+  const int* __restrict__ perm = S.perm;
+  const float4* __restrict__ cbox = S.cbox;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int i = blockIdx.x * kKnnWaves + wv;  // sorted position of the wave's point
-  if (i >= n) return;                         // whole waves leave; no workgroup barrier below
+  const int i = ((int)blockIdx.x - S.block0) * kKnnWaves + wv;  // sorted position of the wave's point
+  if (i >= n) return;                                           // whole waves leave; no workgroup barrier below
   KnnKey* buf = sbuf[wv];
   const float xi = xs[i], yi = ys[i];
   const int me = perm[i];
@@ -152,9 +163,10 @@ __global__ __launch_bounds__(64 * kKnnWaves) void knn_sorted_kernel(int n, int n
   }
   if (lane != 0) return;
   const float d2 = __uint_as_float((unsigned)(kth >> 32));
-  if (rho) rho[me] = (float)k / ((float)M_PI * d2);
-  if (rk) rk[me] = sqrtf(d2);
-  if (nn) nn[me] = kth == kKnnNone ? -1 : (int)(unsigned)kth;  // -1: fewer than k comparable points
+  if (S.rho) S.rho[me] = (float)k / ((float)M_PI * d2);
+  if (S.rk) S.rk[me] = sqrtf(d2);
+  if (S.w) S.w[me] = scale * sqrtf(d2);
+  if (S.nn) S.nn[me] = kth == kKnnNone ? -1 : (int)(unsigned)kth;  // -1: fewer than k comparable points
 }
 
 static size_t knn_workspace(int n) {
@@ -170,10 +182,18 @@ static int check_knn(int n, int k) {
   return GPL_OK;
 }
 
-int knn_sorted_launch(const TilePlan& p, int k, float* rho, float* rk, int* nn, hipStream_t stream) {
-  GPL_TRY(check_knn(p.n, k));
-  hipLaunchKernelGGL(knn_sorted_kernel, dim3(cdiv(p.n, kKnnWaves)), dim3(64 * kKnnWaves), 0, stream, p.n, p.nch, p.xs,
-                     p.ys, p.perm, p.cbox, k, rho, rk, nn);
+int knn_sorted_launch(const KnnSet* sets, int nsets, int k, float scale, hipStream_t stream) {
+  KnnArgs a[2] = {};
+  int blocks = 0;
+  for (int q = 0; q < 2; ++q) {
+    a[q].block0 = blocks;
+    if (q >= nsets) continue;
+    const TilePlan& p = sets[q].plan;
+    GPL_TRY(check_knn(p.n, k));
+    a[q] = KnnArgs{p.n, p.nch, blocks, p.xs, p.ys, p.perm, p.cbox, sets[q].rho, sets[q].rk, sets[q].w, sets[q].nn};
+    blocks += cdiv(p.n, kKnnWaves);
+  }
+  hipLaunchKernelGGL(knn_sorted_kernel, dim3(blocks), dim3(64 * kKnnWaves), 0, stream, a[0], a[1], k, scale);
   GPL_LAUNCH_CHECK();
   return GPL_OK;
 }
@@ -194,5 +214,6 @@ extern "C" int gpl_knn_density(int n, const float* qx, const float* qy, int k, f
   sort_carve(cv, n, p);
   if (!cv.ok()) return check_ws(nullptr, 0, 1);
   GPL_TRY(plan_sort(p, n, qx, qy, stream));
-  return knn_sorted_launch(p, k, rho, nullptr, nullptr, stream);
+  const KnnSet set{p, rho, nullptr, nullptr, nullptr};
+  return knn_sorted_launch(&set, 1, k, 0.f, stream);
 }

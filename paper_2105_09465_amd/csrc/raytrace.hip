@@ -13,6 +13,7 @@
 #include "common.hpp"
 #include "dual.hpp"
 #include "internal.hpp"
+#include "pixel_axes.hpp"
 
 namespace gpl {
 
@@ -199,8 +200,9 @@ __global__ void raytrace_dev_kernel(GridF g, int N, const double* __restrict__ l
 // Adjoint: per point, dp/dtheta for (theta_E, q, phi, slope, x0, y0) by forward-mode
 // duals through sple_deflect; shear columns in closed form. Block partial sums in
 // FP64 go to `partial[block][8]`.
-__device__ inline void raytrace_backward_body(const GridF& g, int N, const gpl_lens& Lh, int nterms,
-                                              const float* gpx, const float* gpy, double* partial) {
+template <class G>  // grad(j): dF/dp of point j
+__device__ inline void raytrace_backward_body(const GridF& g, int N, const gpl_lens& Lh, int nterms, G grad,
+                                              double* partial) {
   using D6 = Dual<6>;
   __shared__ double red[4];
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
@@ -228,7 +230,8 @@ __device__ inline void raytrace_backward_body(const GridF& g, int N, const gpl_l
     L.y0 = y0;
     D6 ax, ay;
     sple_deflect<D6>(x, y, L, nterms, ax, ay);
-    const float gx = gpx[j], gy = gpy[j];
+    const float2 gp = grad(j);
+    const float gx = gp.x, gy = gp.y;
 #pragma unroll
     for (int k = 0; k < 6; ++k) acc[k] = -(double)(gx * ax.d[k] + gy * ay.d[k]);
     acc[6] = (double)(-gx * x + gy * y);  // dp/dgamma1 = (-x, y)
@@ -243,14 +246,26 @@ __device__ inline void raytrace_backward_body(const GridF& g, int N, const gpl_l
 __global__ __launch_bounds__(256) void raytrace_backward_kernel(GridF g, int N, gpl_lens Lh, int nterms,
                                                                 const float* gpx, const float* gpy,
                                                                 double* partial) {
-  raytrace_backward_body(g, N, Lh, nterms, gpx, gpy, partial);
+  raytrace_backward_body(g, N, Lh, nterms, [=](int j) { return make_float2(gpx[j], gpy[j]); }, partial);
 }
 
 __global__ __launch_bounds__(256) void raytrace_backward_dev_kernel(GridF g, int N, const double* __restrict__ lens,
-                                                                    const float* gpx, const float* gpy,
-                                                                    double* partial) {
+                                                                    PointGrads P, double* partial) {
   const gpl_lens Lh = lens_from(lens);
-  raytrace_backward_body(g, N, Lh, series_terms_dev(Lh.q), gpx, gpy, partial);
+  auto grad = [&](int j) {
+    float2 v = make_float2(P.gpx[j], P.gpy[j]);
+    if (P.gz) {
+      const float2 s = axes_gather(g.M, j, [&](int c) { return axes_grad(g.M, c, P.px, P.py, P.gz); });
+      v.x += s.x;
+      v.y += s.y;
+    }
+    if (P.gq) {
+      v.x += (float)P.gq[j];
+      v.y += (float)P.gq[N + j];
+    }
+    return v;
+  };
+  raytrace_backward_body(g, N, Lh, series_terms_dev(Lh.q), grad, partial);
 }
 
 __global__ void sum_partials_kernel(const double* partial, int nblocks, int width, double* out) {
@@ -305,8 +320,6 @@ static int scratch_address(double** out) {
   return GPL_OK;
 }
 
-size_t raytrace_dev_backward_scratch(int N) { return align_up(sizeof(double) * 8 * (size_t)cdiv(N, 256)); }
-
 int raytrace_dev_launch(const gpl_grid* grid, const double* lens, float* px, float* py, hipStream_t stream) {
   GPL_TRY(check_grid(grid));
   const GridF g = make_grid(grid);
@@ -316,15 +329,12 @@ int raytrace_dev_launch(const gpl_grid* grid, const double* lens, float* px, flo
   return GPL_OK;
 }
 
-int raytrace_dev_backward_launch(const gpl_grid* grid, const double* lens, const float* gpx, const float* gpy,
-                                 double* g_lens, double* scratch_partial, hipStream_t stream) {
+int raytrace_dev_backward_launch(const gpl_grid* grid, const double* lens, const PointGrads& P, double* partial,
+                                 hipStream_t stream) {
   GPL_TRY(check_grid(grid));
   const GridF g = make_grid(grid);
-  const int N = g.M * g.M, nb = cdiv(N, 256);
-  hipLaunchKernelGGL(raytrace_backward_dev_kernel, dim3(nb), dim3(256), 0, stream, g, N, lens, gpx, gpy,
-                     scratch_partial);
-  GPL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(64), 0, stream, scratch_partial, nb, 8, g_lens);
+  const int N = g.M * g.M;
+  hipLaunchKernelGGL(raytrace_backward_dev_kernel, dim3(cdiv(N, 256)), dim3(256), 0, stream, g, N, lens, P, partial);
   GPL_LAUNCH_CHECK();
   return GPL_OK;
 }

@@ -3,14 +3,11 @@
 #include <cmath>
 
 #include "common.hpp"
+#include "sersic.hpp"
 
 namespace gpl {
 
-struct SersicF {
-  float I_e, inv_Re, inv_n, bn_log2e, bn, xs, ys;
-};
-
-static SersicF make_sersic(const gpl_source* s) {
+SersicF make_sersic(const gpl_source* s) {
   SersicF f;
   f.I_e = (float)s->I_e;
   f.inv_Re = (float)(1.0 / s->R_e);
@@ -22,18 +19,11 @@ static SersicF make_sersic(const gpl_source* s) {
   return f;
 }
 
-static int check_source(const gpl_source* s) {
+int check_source(const gpl_source* s) {
   GPL_REQUIRE(s != nullptr, "source is NULL");
   GPL_REQUIRE(s->R_e > 0 && s->n_sersic > 0 && s->b_n > 0, "Sersic R_e, n, b_n must be > 0");
   GPL_REQUIRE(std::isfinite(s->I_e) && std::isfinite(s->xs) && std::isfinite(s->ys), "Sersic parameters must be finite");
   return GPL_OK;
-}
-
-// (r/R_e)^(1/n) via exp2(log2(.)/n); r = 0 gives exp2(-inf) = 0.
-__device__ inline float sersic_shape(const SersicF& S, float dx, float dy, float& t) {
-  const float r = sqrtf(dx * dx + dy * dy);
-  t = exp2f(log2f(r * S.inv_Re) * S.inv_n);
-  return S.I_e * exp2f(S.bn_log2e * (1.f - t));
 }
 
 __global__ void sersic_kernel(SersicF S, int n, const float* px, const float* py, float* mu) {
@@ -51,11 +41,7 @@ __global__ __launch_bounds__(256) void sersic_backward_kernel(SersicF S, int n, 
   double ax = 0.0, ay = 0.0;
   if (i < n) {
     const float dx = px[i] - S.xs, dy = py[i] - S.ys;
-    float t;
-    const float m = sersic_shape(S, dx, dy, t);
-    const float r2 = dx * dx + dy * dy;
-    // dmu/dp = -mu b_n/n (r/R_e)^(1/n) (dx, dy)/r^2; zero at r = 0 by convention
-    const float f = r2 > 0.f ? -m * S.bn * S.inv_n * t / r2 : 0.f;
+    const float f = sersic_slope(S, dx, dy);
     const float gx = gmu[i] * f * dx, gy = gmu[i] * f * dy;
     gpx[i] += gx;
     gpy[i] += gy;

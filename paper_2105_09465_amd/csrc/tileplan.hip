@@ -225,21 +225,17 @@ __device__ __forceinline__ int4 fold_counts(const SortCount* __restrict__ hist, 
 // the digits below, and the items of the digit in the workgroups before. The
 // last pass writes the sorted points instead of keys.
 template <bool kLast>
-__global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(int n, int span, int pass,
-                                                                    const uint32_t* __restrict__ kin,
-                                                                    const int* __restrict__ vin,
-                                                                    const SortCount* __restrict__ hist,
-                                                                    uint32_t* __restrict__ kout,
-                                                                    int* __restrict__ vout,
-                                                                    const float* __restrict__ px,
-                                                                    const float* __restrict__ py,
-                                                                    int* __restrict__ irank, float* __restrict__ xs,
-                                                                    float* __restrict__ ys) {
+__device__ __forceinline__ void sort_scatter_body(int nb, int n, int span, int pass, const uint32_t* __restrict__ kin,
+                                                  const int* __restrict__ vin, const SortCount* __restrict__ hist,
+                                                  uint32_t* __restrict__ kout, int* __restrict__ vout,
+                                                  const float* __restrict__ px, const float* __restrict__ py,
+                                                  int* __restrict__ irank, float* __restrict__ xs,
+                                                  float* __restrict__ ys) {
   __shared__ __attribute__((aligned(16))) int pos[kSortDigits];
   __shared__ int wsum[kSortThreads / 64];
   constexpr int kPer = kSortDigits / kSortThreads;  // digits of a thread
   static_assert(kPer == 4, "one ushort4 of every row per thread");
-  const int nb = gridDim.x, blk = blockIdx.x;
+  const int blk = blockIdx.x;
   const int end = min(n, (blk + 1) * span);
   // an item's key and index, and in the last pass its point: loaded ahead of the
   // work they do not depend on (past the end the first item of all, not used)
@@ -279,6 +275,20 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(int n, int s
       kout[r] = kk;
     }
   }
+}
+
+template <bool kLast>
+__global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(int n, int span, int pass,
+                                                                    const uint32_t* __restrict__ kin,
+                                                                    const int* __restrict__ vin,
+                                                                    const SortCount* __restrict__ hist,
+                                                                    uint32_t* __restrict__ kout,
+                                                                    int* __restrict__ vout,
+                                                                    const float* __restrict__ px,
+                                                                    const float* __restrict__ py,
+                                                                    int* __restrict__ irank, float* __restrict__ xs,
+                                                                    float* __restrict__ ys) {
+  sort_scatter_body<kLast>(gridDim.x, n, span, pass, kin, vin, hist, kout, vout, px, py, irank, xs, ys);
 }
 
 // Boxes of one 64-point tile by a wave, lane = sorted point (x, y, live or
@@ -766,10 +776,9 @@ constexpr int kSmallTiles = kSmallPoints / kRowTile, kSmallChunks = kSmallTiles 
 static_assert(kSortThreads == 1024, "one workgroup size for the sort and the small plan");
 
 template <bool kPlan>
-__global__ __launch_bounds__(kSortThreads) void plan_small_kernel(int n, const float* __restrict__ px,
-                                                                  const float* __restrict__ py, TilePlan P, int* perm,
-                                                                  int* irank, float s2, float threshold,
-                                                                  float lo_threshold) {
+__device__ __forceinline__ void plan_small_body(int n, const float* __restrict__ px, const float* __restrict__ py,
+                                                const TilePlan& P, int* perm, int* irank, float s2, float threshold,
+                                                float lo_threshold) {
   __shared__ union {
     struct {
       uint32_t key[kSmallPoints];
@@ -895,6 +904,44 @@ __global__ __launch_bounds__(kSortThreads) void plan_small_kernel(int n, const f
                P.rslot, P.wdesc, P.wrest);
 }
 
+template <bool kPlan>
+__global__ __launch_bounds__(kSortThreads) void plan_small_kernel(int n, const float* __restrict__ px,
+                                                                  const float* __restrict__ py, TilePlan P, int* perm,
+                                                                  int* irank, float s2, float threshold,
+                                                                  float lo_threshold) {
+  plan_small_body<kPlan>(n, px, py, P, perm, irank, s2, threshold, lo_threshold);
+}
+
+// A small set to be sorted beside another one.
+struct SmallSort {
+  int n;
+  const float *px, *py;
+  TilePlan plan;
+  int *perm, *irank;
+};
+static SmallSort small_sort(const TilePlan& p, int n, const float* px, const float* py) {
+  return SmallSort{n, px, py, p, const_cast<int*>(p.perm), const_cast<int*>(p.irank)};
+}
+__device__ __forceinline__ void sort_small(const SmallSort& s) {
+  plan_small_body<false>(s.n, s.px, s.py, s.plan, s.perm, s.irank, 1.f, 0.f, 0.f);
+}
+
+// Two small sets, a workgroup each.
+__global__ __launch_bounds__(kSortThreads) void sort_small_pair_kernel(SmallSort a, SmallSort b) {
+  if (blockIdx.x == 0) sort_small(a);
+  else sort_small(b);
+}
+
+// The first scatter pass of a large set, and a small set by a workgroup more: on its
+// own that workgroup takes as long as the pass (some 17 us for 1600 points).
+__global__ __launch_bounds__(kSortThreads) void sort_scatter_side_kernel(int n, int span, const uint32_t* kin,
+                                                                         const SortCount* hist, uint32_t* kout,
+                                                                         int* vout, SmallSort side) {
+  if (blockIdx.x + 1 == gridDim.x) sort_small(side);
+  else sort_scatter_body<false>(gridDim.x - 1, n, span, 0, kin, nullptr, hist, kout, vout, nullptr, nullptr, nullptr,
+                                nullptr, nullptr);
+}
+
 // Compute units of the current device (queried once per device).
 static int compute_units() {
   static int cached[64] = {};
@@ -908,9 +955,11 @@ static int compute_units() {
   return cached[dev];
 }
 
-// Sort of more than kSmallPoints points, and (kScaled) the scaled coordinates.
+// Sort of more than kSmallPoints points, and (kScaled) the scaled coordinates;
+// side (nullable): a small set sorted in the same launches.
 template <bool kScaled>
-static int sort_points(TilePlan& p, int n, const float* px, const float* py, float s2, hipStream_t stream) {
+static int sort_points(TilePlan& p, int n, const float* px, const float* py, float s2, const SmallSort* side,
+                       hipStream_t stream) {
   int* perm = const_cast<int*>(p.perm);
   int* irank = const_cast<int*>(p.irank);
   const int span = sort_span(n), nb = cdiv(n, span);
@@ -925,8 +974,12 @@ static int sort_points(TilePlan& p, int n, const float* px, const float* py, flo
                      p.shist);
   GPL_LAUNCH_CHECK();
   static_assert(kSortPasses == 2, "a first and a last pass");
-  hipLaunchKernelGGL(sort_scatter_kernel<false>, dim3(nb), dim3(kSortThreads), 0, stream, n, span, 0, k0, nullptr,
-                     p.shist, k1, p.sval, px, py, irank, p.xs, p.ys);
+  if (side)
+    hipLaunchKernelGGL(sort_scatter_side_kernel, dim3(nb + 1), dim3(kSortThreads), 0, stream, n, span, k0, p.shist, k1,
+                       p.sval, *side);
+  else
+    hipLaunchKernelGGL(sort_scatter_kernel<false>, dim3(nb), dim3(kSortThreads), 0, stream, n, span, 0, k0, nullptr,
+                       p.shist, k1, p.sval, px, py, irank, p.xs, p.ys);
   GPL_LAUNCH_CHECK();
   hipLaunchKernelGGL(sort_count_kernel, dim3(nb), dim3(kSortThreads), 0, stream, n, span, 1, k1, p.shist);
   GPL_LAUNCH_CHECK();
@@ -951,7 +1004,21 @@ static int small_plan(TilePlan& p, int n, const float* px, const float* py, floa
 int plan_sort(TilePlan& p, int n, const float* px, const float* py, hipStream_t stream) {
   GPL_REQUIRE(n >= 1, "plan needs at least one point");
   if (n <= kSmallPoints) return small_plan<false>(p, n, px, py, 1.f, 0.f, 0.f, stream);
-  return sort_points<false>(p, n, px, py, 1.f, stream);
+  return sort_points<false>(p, n, px, py, 1.f, nullptr, stream);
+}
+
+int plan_sort_pair(TilePlan& a, int na, const float* ax, const float* ay, TilePlan& b, int nb, const float* bx,
+                   const float* by, hipStream_t stream) {
+  GPL_REQUIRE(na >= 1 && nb >= 1, "plan needs at least one point");
+  if (nb > kSmallPoints) {
+    GPL_TRY(plan_sort(a, na, ax, ay, stream));
+    return plan_sort(b, nb, bx, by, stream);
+  }
+  const SmallSort side = small_sort(b, nb, bx, by);
+  if (na > kSmallPoints) return sort_points<false>(a, na, ax, ay, 1.f, &side, stream);
+  hipLaunchKernelGGL(sort_small_pair_kernel, dim3(2), dim3(kSortThreads), 0, stream, small_sort(a, na, ax, ay), side);
+  GPL_LAUNCH_CHECK();
+  return GPL_OK;
 }
 
 int plan_build(TilePlan& p, int n, const float* px, const float* py, const gpl_grid* grid, float s2, float threshold,
@@ -964,7 +1031,7 @@ int plan_build(TilePlan& p, int n, const float* px, const float* py, const gpl_g
   GPL_REQUIRE(p.nch <= kMaxPlanChunks, "n=%d exceeds the product's limit of %d points", n, kMaxPlanChunks * kChunk);
   p.wround = 4 * compute_units();
   if (n <= kSmallPoints) return small_plan<true>(p, n, px, py, s2, threshold, lo_threshold, stream);
-  GPL_TRY(sort_points<true>(p, n, px, py, s2, stream));
+  GPL_TRY(sort_points<true>(p, n, px, py, s2, nullptr, stream));
   hipLaunchKernelGGL(plan_lists_kernel, dim3(p.nrt), dim3(256), 0, stream, p.nch, p.cbox, p.sbox, s2, threshold,
                      lo_threshold, p.count, p.list, p.roww);
   GPL_LAUNCH_CHECK();

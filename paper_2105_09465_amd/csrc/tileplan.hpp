@@ -228,6 +228,9 @@ int plan_build(TilePlan& p, int n, const float* px, const float* py, const gpl_g
 // The first part of plan_build alone: the Hilbert sort (perm, irank, xs, ys)
 // and the chunk and subtile boxes.
 int plan_sort(TilePlan& p, int n, const float* px, const float* py, hipStream_t stream);
+// The sort of two sets; a small one b shares the launches of a.
+int plan_sort_pair(TilePlan& a, int na, const float* ax, const float* ay, TilePlan& b, int nb, const float* bx,
+                   const float* by, hipStream_t stream);
 
 // Relative work of a wave in the first, second and later dispatch rounds.
 constexpr int kRounds = 3;
