@@ -176,17 +176,21 @@ __device__ __forceinline__ int block_exclusive(int v, int* ws) {
   if (lane == 63) ws[w] = x;
   __syncthreads();
   int before = 0;
-  for (int k = 0; k < w; ++k) before += ws[k];
+#pragma unroll
+  for (int k = 0; k < kSortThreads / 64; ++k) before += k < w ? ws[k] : 0;
   return before + x - v;
 }
 
 // Stable ranking of one item per thread: the items of waves 0, 1, ... in turn,
-// those of a wave by lane. pos[d] (LDS) is the next free position of digit d.
-// The lanes that hold the same digit find each other by ballots; the first of
-// them takes positions for all. `waves`: the waves that hold valid items (the same
-// in every thread). Returns the item's position (valid items only).
-__device__ __forceinline__ int rank_items(int d, bool valid, int waves, int* pos) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+// those of a wave by lane. pos[d] (LDS) is the next free position of digit d, wcnt[d]
+// holds a byte per wave, the wave's items of the digit; all zero before and after. The
+// lanes that hold the same digit find each other by ballots; the first of them
+// writes the count and adds up the bytes of the waves before. (A turn of the workgroup
+// per wave, each adding to pos in its turn, took 2.0 of a scatter's 14.5 us at 40,000
+// points.) Returns the item's position (valid items only); more: another round follows.
+static_assert(kSortThreads == 16 * 64, "a byte of a uint4 per wave");
+__device__ __forceinline__ int rank_items(int d, bool valid, bool more, int* pos, uint4* wcnt) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   unsigned long long m = __ballot(valid);
 #pragma unroll
   for (int b = 0; b < kSortBits; ++b) {
@@ -195,46 +199,123 @@ __device__ __forceinline__ int rank_items(int d, bool valid, int waves, int* pos
     m &= bit ? bb : ~bb;
   }
   const int lower = __popcll(m & ((1ull << lane) - 1ull)), first = valid ? __ffsll((long long)m) - 1 : 0;
+  const bool leads = valid && lower == 0;
+  unsigned char* mine = reinterpret_cast<unsigned char*>(wcnt + d) + w;
+  if (leads) *mine = (unsigned char)__popcll(m);
+  __syncthreads();
   int p = 0;
-  for (int k = 0; k < waves; ++k) {
-    if (k == w && valid && lower == 0) p = atomicAdd(&pos[d], __popcll(m));
+  bool last = false;
+  if (leads) {
+    const uint4 c = wcnt[d];
+    const uint32_t cw[4] = {c.x, c.y, c.z, c.w};
+    uint32_t sum = 0u, after = 0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int bits = min(max(8 * (w - 4 * k), 0), 32);  // the bytes of the waves before this one
+      const uint32_t below = bits == 32 ? ~0u : (1u << bits) - 1u;
+      const uint32_t here = bits == 32 || w < 4 * k ? 0u : 0xffu << bits;
+      sum = __builtin_amdgcn_sad_u8(cw[k] & below, 0u, sum);
+      after |= cw[k] & ~(below | here);
+    }
+    p = pos[d] + (int)sum;
+    last = after == 0u;
+  }
+  const int r = __shfl(p, first, 64) + lower;
+  if (more) {
+    __syncthreads();
+    if (leads) {
+      if (last) pos[d] = p + __popcll(m);
+      *mine = 0;
+    }
     __syncthreads();
   }
-  return __shfl(p, first, 64) + lower;
+  return r;
 }
 
-// Counts of this thread's four digits over the rows [lo, hi) of hist, 16 rows a
-// round loaded together.
-__device__ __forceinline__ int4 fold_counts(const SortCount* __restrict__ hist, int lo, int hi) {
-  constexpr int kFold = 16;
-  const ushort4* row = reinterpret_cast<const ushort4*>(hist) + threadIdx.x;
-  int4 sum = make_int4(0, 0, 0, 0);
-  for (int b0 = lo; b0 < hi; b0 += kFold) {
-    ushort4 v[kFold];
+// First position of every digit for a workgroup's items, into pos: the digits below,
+// and the items of the digit in the workgroups before blk (hist: a row of counts per
+// workgroup). Bound by latency and issue, few workgroups run: so one sweep over the
+// rows, a thread taking eight digits of every other row with kFold loads in flight,
+// the counts of a round added in 16 bits (at most 65,535 items) and the rounds in 32.
+// (Four digits a thread, rows before and after in sweeps of their own, took 4.7 us of
+// a scatter's 14.5 at 40,000 points; with the ranking above the first scatter takes
+// 9.6 us instead of 14.5 and the last 12.6 instead of 16.4, at 160,000 18.0 instead of
+// 22.4 and 26.8 instead of 30.6.) tmp: 16 kSortThreads / 2 ints.
+__device__ __forceinline__ void digit_positions(const SortCount* __restrict__ hist, int blk, int nb, int span, int* pos,
+                                                int* tmp, int* ws) {
+  constexpr int kFold = 20, kHalf = kSortThreads / 2;
+  static_assert(kSortDigits == 8 * kHalf, "eight digits of a row per thread");
+  const int half = __builtin_amdgcn_readfirstlane(threadIdx.x / kHalf), g = threadIdx.x % kHalf;
+  const uint4* row = reinterpret_cast<const uint4*>(hist) + g;
+  const int per = min(kFold, 65535 / span);  // rows of a round
+  int all[8], bef[8];
 #pragma unroll
-    for (int u = 0; u < kFold; ++u) v[u] = row[(size_t)min(b0 + u, hi - 1) * (kSortDigits / 4)];
+  for (int k = 0; k < 8; ++k) all[k] = bef[k] = 0;
+  for (int b0 = half; b0 < nb; b0 += 2 * per) {
+    uint4 v[kFold];
 #pragma unroll
-    for (int u = 0; u < kFold; ++u)
-      if (b0 + u < hi) sum.x += v[u].x, sum.y += v[u].y, sum.z += v[u].z, sum.w += v[u].w;
+    for (int u = 0; u < kFold; ++u) v[u] = row[(size_t)min(b0 + 2 * u, nb - 1) * (kSortDigits / 8)];
+    uint4 a = make_uint4(0u, 0u, 0u, 0u), b = a;
+#pragma unroll
+    for (int u = 0; u < kFold; ++u) {
+      const int r = b0 + 2 * u;
+      const uint32_t live = u < per && r < nb ? ~0u : 0u, before = u < per && r < blk ? ~0u : 0u;
+      a.x += v[u].x & live, a.y += v[u].y & live, a.z += v[u].z & live, a.w += v[u].w & live;
+      b.x += v[u].x & before, b.y += v[u].y & before, b.z += v[u].z & before, b.w += v[u].w & before;
+    }
+    const uint32_t ap[4] = {a.x, a.y, a.z, a.w}, bp[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      all[2 * k] += (int)(ap[k] & 0xffffu), all[2 * k + 1] += (int)(ap[k] >> 16);
+      bef[2 * k] += (int)(bp[k] & 0xffffu), bef[2 * k + 1] += (int)(bp[k] >> 16);
+    }
   }
-  return sum;
+  if (half == 1)
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      tmp[k * kHalf + g] = all[k];
+      tmp[(8 + k) * kHalf + g] = bef[k];
+    }
+  __syncthreads();
+  int sum = 0;
+  if (half == 0)
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      all[k] += tmp[k * kHalf + g];
+      bef[k] += tmp[(8 + k) * kHalf + g];
+      sum += all[k];
+    }
+  int run = block_exclusive(sum, ws);
+  if (half == 0) {
+    int p[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      p[k] = run + bef[k];
+      run += all[k];
+    }
+    int4* out = reinterpret_cast<int4*>(pos + 8 * g);
+    out[0] = make_int4(p[0], p[1], p[2], p[3]);
+    out[1] = make_int4(p[4], p[5], p[6], p[7]);
+  }
 }
 
 // Stable scatter of one pass. Every workgroup folds the counts of all workgroups
-// (hist, one row each) into the first position of each digit for its own items:
-// the digits below, and the items of the digit in the workgroups before. The
-// last pass writes the sorted points instead of keys.
+// (hist, one row each) into the first position of each digit for its own items.
+// The last pass writes the sorted points instead of keys.
+struct ScatterLds {
+  __attribute__((aligned(16))) int pos[kSortDigits];
+  uint4 wcnt[kSortDigits];
+};
 template <bool kLast>
-__device__ __forceinline__ void sort_scatter_body(int nb, int n, int span, int pass, const uint32_t* __restrict__ kin,
+__device__ __forceinline__ void sort_scatter_body(ScatterLds& L, int nb, int n, int span, int pass, const uint32_t* __restrict__ kin,
                                                   const int* __restrict__ vin, const SortCount* __restrict__ hist,
                                                   uint32_t* __restrict__ kout, int* __restrict__ vout,
                                                   const float* __restrict__ px, const float* __restrict__ py,
                                                   int* __restrict__ irank, float* __restrict__ xs,
                                                   float* __restrict__ ys) {
-  __shared__ __attribute__((aligned(16))) int pos[kSortDigits];
   __shared__ int wsum[kSortThreads / 64];
-  constexpr int kPer = kSortDigits / kSortThreads;  // digits of a thread
-  static_assert(kPer == 4, "one ushort4 of every row per thread");
+  int* const pos = L.pos;
+  uint4* const wcnt = L.wcnt;
   const int blk = blockIdx.x;
   const int end = min(n, (blk + 1) * span);
   // an item's key and index, and in the last pass its point: loaded ahead of the
@@ -247,12 +328,9 @@ __device__ __forceinline__ void sort_scatter_body(int nb, int n, int span, int p
     v = vin ? vin[ic] : ic;
   };
   load(blk * span + threadIdx.x);
-  const int4 before = fold_counts(hist, 0, blk), after = fold_counts(hist, blk, nb);
-  const int4 all = make_int4(before.x + after.x, before.y + after.y, before.z + after.z, before.w + after.w);
-  const int base = block_exclusive(all.x + all.y + all.z + all.w, wsum);
-  const int p1 = base + all.x, p2 = p1 + all.y, p3 = p2 + all.z;
-  *reinterpret_cast<int4*>(&pos[kPer * threadIdx.x]) =
-      make_int4(base + before.x, p1 + before.y, p2 + before.z, p3 + before.w);
+  digit_positions(hist, blk, nb, span, pos, reinterpret_cast<int*>(wcnt), wsum);
+  __syncthreads();
+  for (int d = threadIdx.x; d < kSortDigits; d += kSortThreads) wcnt[d] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
   for (int i0 = blk * span; i0 < end; i0 += kSortThreads) {
     const bool valid = i0 + (int)threadIdx.x < end;
@@ -264,7 +342,7 @@ __device__ __forceinline__ void sort_scatter_body(int nb, int n, int span, int p
       y = py[vv];
     }
     load(i0 + kSortThreads + threadIdx.x);  // the next round's
-    const int r = rank_items(key_digit(kk, pass), valid, min(kSortThreads / 64, cdiv(end - i0, 64)), pos);
+    const int r = rank_items(key_digit(kk, pass), valid, i0 + kSortThreads < end, pos, wcnt);
     if (!valid) continue;
     vout[r] = vv;
     if (kLast) {
@@ -288,7 +366,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(int n, int s
                                                                     const float* __restrict__ py,
                                                                     int* __restrict__ irank, float* __restrict__ xs,
                                                                     float* __restrict__ ys) {
-  sort_scatter_body<kLast>(gridDim.x, n, span, pass, kin, vin, hist, kout, vout, px, py, irank, xs, ys);
+  __shared__ ScatterLds lds;
+  sort_scatter_body<kLast>(lds, gridDim.x, n, span, pass, kin, vin, hist, kout, vout, px, py, irank, xs, ys);
 }
 
 // Boxes of one 64-point tile by a wave, lane = sorted point (x, y, live or
@@ -775,25 +854,26 @@ constexpr int kSmallPoints = 4096;
 constexpr int kSmallTiles = kSmallPoints / kRowTile, kSmallChunks = kSmallTiles * kChunksPerTile;
 static_assert(kSortThreads == 1024, "one workgroup size for the sort and the small plan");
 
+union SmallLds {
+  struct {
+    uint32_t key[kSmallPoints];
+    ScatterLds rank;
+  } sort;
+  struct {
+    unsigned short cost[kSmallTiles][kSmallChunks];  // cost of a row tile before each of its units
+    int wunit[8 * kSmallTiles + 1], wslot[8 * kSmallTiles];
+    int2 wrows[8 * kSmallTiles + 1];
+    int off[kSmallTiles], count[kSmallTiles], roww[kSmallTiles];
+    unsigned short first[kSmallTiles], past[kSmallTiles];
+    long long woff[kSmallTiles];
+    float4 cbox[kSmallChunks], sbox[kSmallTiles * kSubsPerTile];
+  } plan;
+};
+
 template <bool kPlan>
-__device__ __forceinline__ void plan_small_body(int n, const float* __restrict__ px, const float* __restrict__ py,
-                                                const TilePlan& P, int* perm, int* irank, float s2, float threshold,
-                                                float lo_threshold) {
-  __shared__ union {
-    struct {
-      uint32_t key[kSmallPoints];
-      int pos[kSortDigits];
-    } sort;
-    struct {
-      unsigned short cost[kSmallTiles][kSmallChunks];  // cost of a row tile before each of its units
-      int wunit[8 * kSmallTiles + 1], wslot[8 * kSmallTiles];
-      int2 wrows[8 * kSmallTiles + 1];
-      int off[kSmallTiles], count[kSmallTiles], roww[kSmallTiles];
-      unsigned short first[kSmallTiles], past[kSmallTiles];
-      long long woff[kSmallTiles];
-      float4 cbox[kSmallChunks], sbox[kSmallTiles * kSubsPerTile];
-    } plan;
-  } L;
+__device__ __forceinline__ void plan_small_body(SmallLds& L, int n, const float* __restrict__ px,
+                                                const float* __restrict__ py, const TilePlan& P, int* perm, int* irank,
+                                                float s2, float threshold, float lo_threshold) {
   __shared__ unsigned short val[2][kSmallPoints];
   __shared__ float4 red[kSortThreads / 64];
   __shared__ int ws[kSortThreads / 64];
@@ -809,21 +889,24 @@ __device__ __forceinline__ void plan_small_body(int n, const float* __restrict__
   ext = extent_square(ext);
   for (int i = tid; i < n; i += kSortThreads) L.sort.key[i] = point_key(px[i], py[i], ext);
   for (int pass = 0; pass < kSortPasses; ++pass) {
-    for (int d = tid; d < kSortDigits; d += kSortThreads) L.sort.pos[d] = 0;
+    for (int d = tid; d < kSortDigits; d += kSortThreads) {
+      L.sort.rank.pos[d] = 0;
+      L.sort.rank.wcnt[d] = make_uint4(0u, 0u, 0u, 0u);
+    }
     __syncthreads();
-    for (int i = tid; i < n; i += kSortThreads) atomicAdd(&L.sort.pos[key_digit(L.sort.key[i], pass)], 1);
+    for (int i = tid; i < n; i += kSortThreads) atomicAdd(&L.sort.rank.pos[key_digit(L.sort.key[i], pass)], 1);
     __syncthreads();
     constexpr int kPer = kSortDigits / kSortThreads;
     int c[kPer], sum = 0;
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
-      c[k] = L.sort.pos[kPer * tid + k];
+      c[k] = L.sort.rank.pos[kPer * tid + k];
       sum += c[k];
     }
     int run = block_exclusive(sum, ws);
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
-      L.sort.pos[kPer * tid + k] = run;
+      L.sort.rank.pos[kPer * tid + k] = run;
       run += c[k];
     }
     __syncthreads();
@@ -831,7 +914,7 @@ __device__ __forceinline__ void plan_small_body(int n, const float* __restrict__
       const int i = i0 + tid;
       const bool valid = i < n;
       const int v = valid ? (pass == 0 ? i : (int)val[(pass - 1) & 1][i]) : 0;
-      const int r = rank_items(key_digit(L.sort.key[v], pass), valid, min(kWaves, cdiv(n - i0, 64)), L.sort.pos);
+      const int r = rank_items(key_digit(L.sort.key[v], pass), valid, i0 + kSortThreads < n, L.sort.rank.pos, L.sort.rank.wcnt);
       if (valid) val[pass & 1][r] = (unsigned short)v;
     }
     __syncthreads();
@@ -909,7 +992,8 @@ __global__ __launch_bounds__(kSortThreads) void plan_small_kernel(int n, const f
                                                                   const float* __restrict__ py, TilePlan P, int* perm,
                                                                   int* irank, float s2, float threshold,
                                                                   float lo_threshold) {
-  plan_small_body<kPlan>(n, px, py, P, perm, irank, s2, threshold, lo_threshold);
+  __shared__ SmallLds lds;
+  plan_small_body<kPlan>(lds, n, px, py, P, perm, irank, s2, threshold, lo_threshold);
 }
 
 // A small set to be sorted beside another one.
@@ -922,14 +1006,15 @@ struct SmallSort {
 static SmallSort small_sort(const TilePlan& p, int n, const float* px, const float* py) {
   return SmallSort{n, px, py, p, const_cast<int*>(p.perm), const_cast<int*>(p.irank)};
 }
-__device__ __forceinline__ void sort_small(const SmallSort& s) {
-  plan_small_body<false>(s.n, s.px, s.py, s.plan, s.perm, s.irank, 1.f, 0.f, 0.f);
+__device__ __forceinline__ void sort_small(SmallLds& lds, const SmallSort& s) {
+  plan_small_body<false>(lds, s.n, s.px, s.py, s.plan, s.perm, s.irank, 1.f, 0.f, 0.f);
 }
 
 // Two small sets, a workgroup each.
 __global__ __launch_bounds__(kSortThreads) void sort_small_pair_kernel(SmallSort a, SmallSort b) {
-  if (blockIdx.x == 0) sort_small(a);
-  else sort_small(b);
+  __shared__ SmallLds lds;
+  if (blockIdx.x == 0) sort_small(lds, a);
+  else sort_small(lds, b);
 }
 
 // The first scatter pass of a large set, and a small set by a workgroup more: on its
@@ -937,8 +1022,9 @@ __global__ __launch_bounds__(kSortThreads) void sort_small_pair_kernel(SmallSort
 __global__ __launch_bounds__(kSortThreads) void sort_scatter_side_kernel(int n, int span, const uint32_t* kin,
                                                                          const SortCount* hist, uint32_t* kout,
                                                                          int* vout, SmallSort side) {
-  if (blockIdx.x + 1 == gridDim.x) sort_small(side);
-  else sort_scatter_body<false>(gridDim.x - 1, n, span, 0, kin, nullptr, hist, kout, vout, nullptr, nullptr, nullptr,
+  __shared__ SmallLds lds;
+  if (blockIdx.x + 1 == gridDim.x) sort_small(lds, side);
+  else sort_scatter_body<false>(lds.sort.rank, gridDim.x - 1, n, span, 0, kin, nullptr, hist, kout, vout, nullptr, nullptr, nullptr,
                                 nullptr, nullptr);
 }
 
