@@ -409,12 +409,21 @@ int gpl_timing_samples(float* ms, int cap, int* count, int reset);
  * recomputed: gpx[i] += dF/dpx_i, gpy[i] += dF/dpy_i (FP32, accumulated),
  * g_hyp[0] = dF/d lengthscale, g_hyp[1] = dF/d amplitude (FP64, overwritten).
  * w is a HOST array of npairs weights. The points are sorted as for the product
- * (a tile plan is built in the workspace, so n is bounded as there), and pairs
- * whose FP32 kernel value is exactly zero are skipped. */
+ * (a tile plan is built in the workspace, so n is bounded as there), and the pairs
+ * are those of the product (kernel value above 2^-36 of a^2). */
 size_t gpl_gp_kernel_mvm_backward_workspace(int n, int npairs);
 int gpl_gp_kernel_mvm_backward(const gpl_kernel* kern, int n, const float* px, const float* py, int npairs,
                                const float* A, int lda, const float* Bv, int ldb, const double* w, float* gpx,
                                float* gpy, double* g_hyp, void* ws, size_t ws_bytes, hipStream_t stream);
+
+/* All gradients of F = sum_c g_c^T K v_c (g_c, v_c the ncols columns of G and V), as
+ * the backward pass of Y = K V with dF/dY = G: gV = K G in the precision form `prec`
+ * and, as gpl_gp_kernel_mvm_backward with unit weights, gpx, gpy and g_hyp (all
+ * overwritten). The points are sorted once for both. */
+size_t gpl_gp_kernel_mvm_vjp_workspace(int n, int ncols, int prec);
+int gpl_gp_kernel_mvm_vjp(const gpl_kernel* kern, int n, const float* px, const float* py, int ncols, const float* V,
+                          int ldv, const float* G, int ldg, float* gV, int ldgv, float* gpx, float* gpy, double* g_hyp,
+                          int prec, void* ws, size_t ws_bytes, hipStream_t stream);
 
 /* Adjoint of ray tracing: g_lens[k] = sum_i (dp_i/dtheta_k) . (gpx_i, gpy_i) for
  * theta = (theta_E, q, phi, slope, x0, y0, gamma1, gamma2) (FP64, overwritten).

@@ -106,6 +106,9 @@ SIGNATURES = {
     "gpl_gp_kernel_mvm_backward_workspace": (_Z, [_I, _I]),
     "gpl_gp_kernel_mvm_backward": (_I, [C.POINTER(gpl_kernel), _I, _P, _P, _I, _P, _I, _P, _I, C.POINTER(_D), _P, _P,
                                         _P, _P, _Z, _P]),
+    "gpl_gp_kernel_mvm_vjp_workspace": (_Z, [_I, _I, _I]),
+    "gpl_gp_kernel_mvm_vjp": (_I, [C.POINTER(gpl_kernel), _I, _P, _P, _I, _P, _I, _P, _I, _P, _I, _P, _P, _P, _I, _P,
+                                   _Z, _P]),
     "gpl_lens_raytrace_backward_workspace": (_Z, [C.POINTER(gpl_grid)]),
     "gpl_lens_raytrace_backward": (_I, [C.POINTER(gpl_grid), C.POINTER(gpl_lens), _P, _P, _P, _P, _Z, _P]),
     "gpl_lens_raytrace_backward_noalloc": (_I, [C.POINTER(gpl_grid), C.POINTER(gpl_lens), _P, _P, _P, _P]),

@@ -142,10 +142,8 @@ class KernelMVM(torch.autograd.Function):
     def backward(ctx, gY):
         px, py, V = ctx.saved_tensors
         gY = gY.contiguous()
-        gV = ops.kernel_mvm(ctx.kern, px, py, gY, prec=ctx.prec)  # K symmetric
-        gpx = torch.zeros_like(px)
-        gpy = torch.zeros_like(py)
-        _, _, ghyp = ops.kernel_mvm_backward(ctx.kern, px, py, gY, V.contiguous(), [1.0] * V.shape[0], gpx, gpy)
+        gpx, gpy, gV, ghyp = ops.kernel_mvm_vjp(ctx.kern, px.contiguous(), py.contiguous(), V.contiguous(), gY,
+                                                prec=ctx.prec)
         return gpx, gpy, gV, ghyp.to(ctx.hdtype), None
 
 

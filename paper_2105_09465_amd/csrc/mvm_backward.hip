@@ -211,11 +211,12 @@ __global__ __launch_bounds__(256, 3) void mvm_bwd_kernel(const TilePlan T, float
 }
 
 // Sums of every row over its partial slots in order (and, gacc, over the passes);
-// the last pass ends them: gpx[perm[i]] += -(a^2/l^2) sum, same for y. Per
+// the last pass ends them: gpx[perm[i]] = -(a^2/l^2) sum, added to what is there with
+// `add`, same for y. Per
 // workgroup, part_h = the sums of K s d^2 and K s of its rows.
 __global__ __launch_bounds__(256) void bwd_rows_kernel(const TilePlan T, const double* __restrict__ part, int first,
-                                                       int last, double scale, double* __restrict__ gacc, float* gpx,
-                                                       float* gpy, double* __restrict__ part_h) {
+                                                       int last, int add, double scale, double* __restrict__ gacc,
+                                                       float* gpx, float* gpy, double* __restrict__ part_h) {
   __shared__ double red[4];
   const int j = blockIdx.x * 256 + threadIdx.x, r = j / kRowTile, row = j % kRowTile;
   double v[kBwdSums] = {};
@@ -246,8 +247,9 @@ __global__ __launch_bounds__(256) void bwd_rows_kernel(const TilePlan T, const d
   }
   if (last) {
     const int dst = T.perm[j];
-    gpx[dst] += (float)(scale * v[0]);
-    gpy[dst] += (float)(scale * v[1]);
+    const float x = (float)(scale * v[0]), y = (float)(scale * v[1]);
+    gpx[dst] = add ? gpx[dst] + x : x;
+    gpy[dst] = add ? gpy[dst] + y : y;
   } else {
     gacc[2 * (size_t)j] = v[0];
     gacc[2 * (size_t)j + 1] = v[1];
@@ -274,7 +276,6 @@ __global__ __launch_bounds__(256) void bwd_reduce_hyp_kernel(int nblocks_total, 
 }
 
 struct BwdBufs {
-  TilePlan plan;
   float *P, *Q;  // entries of one pass in the plan's order
   double *part, *gacc, *part_h;
 };
@@ -283,25 +284,61 @@ static int bwd_passes(int npairs) { return cdiv(npairs, kMaxPass); }
 
 template <class Cv>
 static void carve_bwd(Cv& cv, int n, int npairs, BwdBufs& b) {
-  plan_carve(cv, n, b.plan);
-  const size_t entries = (size_t)b.plan.npad * 4 * bwd_stride(bwd_steps(std::min(npairs, kMaxPass)));
+  const int npad = cdiv(n, kRowTile) * kRowTile;
+  const size_t entries = (size_t)npad * 4 * bwd_stride(bwd_steps(std::min(npairs, kMaxPass)));
   b.P = cv.template take<float>(entries);
   b.Q = cv.template take<float>(entries);
   b.part = cv.template take<double>((size_t)plan_slots(n) * kBwdSums * kRowTile);
-  b.gacc = cv.template take<double>(npairs > kMaxPass ? 2 * (size_t)b.plan.npad : 1);
-  b.part_h = cv.template take<double>((size_t)bwd_passes(npairs) * 2 * cdiv(b.plan.npad, 256));
+  b.gacc = cv.template take<double>(npairs > kMaxPass ? 2 * (size_t)npad : 1);
+  b.part_h = cv.template take<double>((size_t)bwd_passes(npairs) * 2 * cdiv(npad, 256));
 }
 
 template <int S>
-static int launch_bwd(const BwdBufs& b, float s2, int nc, int c0, const float* A, int lda, const float* Bv, int ldb,
+static int launch_bwd(const TilePlan& plan, const BwdBufs& b, float s2, int nc, int c0, const float* A, int lda, const float* Bv, int ldb,
                       const WChunk& w, hipStream_t stream) {
-  hipLaunchKernelGGL(bwd_gather_kernel<S>, dim3(cdiv(4 * b.plan.npad, 256)), dim3(256), 0, stream, b.plan.n,
-                     b.plan.npad, nc, c0, b.plan.perm, A, lda, Bv, ldb, w, b.P, b.Q);
+  hipLaunchKernelGGL(bwd_gather_kernel<S>, dim3(cdiv(4 * plan.npad, 256)), dim3(256), 0, stream, plan.n,
+                     plan.npad, nc, c0, plan.perm, A, lda, Bv, ldb, w, b.P, b.Q);
   GPL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(mvm_bwd_kernel<S>, dim3(b.plan.nw / kPlanWaves), dim3(256), 0, stream, b.plan, s2, b.P, b.Q,
+  hipLaunchKernelGGL(mvm_bwd_kernel<S>, dim3(plan.nw / kPlanWaves), dim3(256), 0, stream, plan, s2, b.P, b.Q,
                      b.part);
   GPL_LAUNCH_CHECK();
   return GPL_OK;
+}
+
+// Gradient sums over a plan that holds every pair to be evaluated.
+static int bwd_run(const TilePlan& plan, const BwdBufs& b, const gpl_kernel* kern, int npairs, const float* A, int lda,
+                   const float* Bv, int ldb, const double* w, bool add, float* gpx, float* gpy, double* g_hyp,
+                   hipStream_t stream) {
+  const float s2 = (float)kernel_scale2(kern->lengthscale);
+  const int blocks = cdiv(plan.npad, 256), passes = bwd_passes(npairs);
+  const double scale = -(kern->amplitude * kern->amplitude) / (kern->lengthscale * kern->lengthscale);
+  for (int pass = 0; pass < passes; ++pass) {
+    const int c0 = pass * kMaxPass, nc = std::min(kMaxPass, npairs - c0), S = bwd_steps(nc);
+    WChunk wd;
+    for (int c = 0; c < kMaxPass; ++c) wd.w[c] = c >= nc ? 0.f : w ? (float)w[c0 + c] : 1.f;
+    switch (S) {
+      case 9: GPL_TRY((launch_bwd<9>(plan, b, s2, nc, c0, A, lda, Bv, ldb, wd, stream))); break;
+      case 8: GPL_TRY((launch_bwd<8>(plan, b, s2, nc, c0, A, lda, Bv, ldb, wd, stream))); break;
+      case 4: GPL_TRY((launch_bwd<4>(plan, b, s2, nc, c0, A, lda, Bv, ldb, wd, stream))); break;
+      case 2: GPL_TRY((launch_bwd<2>(plan, b, s2, nc, c0, A, lda, Bv, ldb, wd, stream))); break;
+      default: GPL_TRY((launch_bwd<1>(plan, b, s2, nc, c0, A, lda, Bv, ldb, wd, stream))); break;
+    }
+    hipLaunchKernelGGL(bwd_rows_kernel, dim3(blocks), dim3(256), 0, stream, plan, b.part, pass == 0 ? 1 : 0,
+                       pass + 1 == passes ? 1 : 0, add ? 1 : 0, scale, b.gacc, gpx, gpy,
+                       b.part_h + (size_t)pass * 2 * blocks);
+    GPL_LAUNCH_CHECK();
+  }
+  hipLaunchKernelGGL(bwd_reduce_hyp_kernel, dim3(1), dim3(256), 0, stream, passes * blocks, b.part_h,
+                     kern->lengthscale, kern->amplitude, g_hyp);
+  GPL_LAUNCH_CHECK();
+  return GPL_OK;
+}
+
+static size_t bwd_workspace(int n, int npairs) {
+  Sizer s;
+  BwdBufs b;
+  carve_bwd(s, n, npairs, b);
+  return s.used;
 }
 
 }  // namespace gpl
@@ -311,47 +348,68 @@ using namespace gpl;
 extern "C" size_t gpl_gp_kernel_mvm_backward_workspace(int n, int npairs) {
   if (n <= 0 || npairs <= 0) return 0;
   Sizer s;
+  TilePlan plan;
   BwdBufs b;
+  plan_carve(s, n, plan);
   carve_bwd(s, n, npairs, b);
   return s.used;
+}
+
+static int check_backward(const gpl_kernel* kern, int n, int npairs) {
+  GPL_TRY(check_kernel(kern));
+  GPL_REQUIRE(n >= 1 && npairs >= 1 && npairs <= 4096, "n=%d npairs=%d out of range", n, npairs);
+  GPL_REQUIRE(kern->amplitude != 0.0, "amplitude must be non-zero for the amplitude gradient");
+  return GPL_OK;
 }
 
 extern "C" int gpl_gp_kernel_mvm_backward(const gpl_kernel* kern, int n, const float* px, const float* py,
                                           int npairs, const float* A, int lda, const float* Bv, int ldb,
                                           const double* w, float* gpx, float* gpy, double* g_hyp, void* ws,
                                           size_t ws_bytes, hipStream_t stream) {
-  GPL_TRY(check_kernel(kern));
-  GPL_REQUIRE(n >= 1 && npairs >= 1 && npairs <= 4096, "n=%d npairs=%d out of range", n, npairs);
+  GPL_TRY(check_backward(kern, n, npairs));
   GPL_REQUIRE(px && py && A && Bv && w && gpx && gpy && g_hyp, "NULL argument");
   GPL_REQUIRE(lda >= n && ldb >= n, "lda/ldb must be >= n");
-  GPL_REQUIRE(kern->amplitude != 0.0, "amplitude must be non-zero for the amplitude gradient");
   for (int c = 0; c < npairs; ++c) GPL_REQUIRE(std::isfinite(w[c]), "weight %d is not finite", c);
   GPL_TRY(check_ws(ws, ws_bytes, gpl_gp_kernel_mvm_backward_workspace(n, npairs)));
   Carver cv(ws, ws_bytes);
+  TilePlan plan;
   BwdBufs b;
+  plan_carve(cv, n, plan);
   carve_bwd(cv, n, npairs, b);
   if (!cv.ok()) return check_ws(nullptr, 0, 1);
   const float s2 = (float)kernel_scale2(kern->lengthscale);
-  GPL_TRY(plan_build(b.plan, n, px, py, nullptr, s2, kSkipBackward, kSkipBackward, stream));
-  const int npad = b.plan.npad, blocks = cdiv(npad, 256), passes = bwd_passes(npairs);
-  const double scale = -(kern->amplitude * kern->amplitude) / (kern->lengthscale * kern->lengthscale);
-  for (int pass = 0; pass < passes; ++pass) {
-    const int c0 = pass * kMaxPass, nc = std::min(kMaxPass, npairs - c0), S = bwd_steps(nc);
-    WChunk wd;
-    for (int c = 0; c < kMaxPass; ++c) wd.w[c] = c < nc ? (float)w[c0 + c] : 0.f;
-    switch (S) {
-      case 9: GPL_TRY((launch_bwd<9>(b, s2, nc, c0, A, lda, Bv, ldb, wd, stream))); break;
-      case 8: GPL_TRY((launch_bwd<8>(b, s2, nc, c0, A, lda, Bv, ldb, wd, stream))); break;
-      case 4: GPL_TRY((launch_bwd<4>(b, s2, nc, c0, A, lda, Bv, ldb, wd, stream))); break;
-      case 2: GPL_TRY((launch_bwd<2>(b, s2, nc, c0, A, lda, Bv, ldb, wd, stream))); break;
-      default: GPL_TRY((launch_bwd<1>(b, s2, nc, c0, A, lda, Bv, ldb, wd, stream))); break;
-    }
-    hipLaunchKernelGGL(bwd_rows_kernel, dim3(blocks), dim3(256), 0, stream, b.plan, b.part, pass == 0 ? 1 : 0,
-                       pass + 1 == passes ? 1 : 0, scale, b.gacc, gpx, gpy, b.part_h + (size_t)pass * 2 * blocks);
-    GPL_LAUNCH_CHECK();
-  }
-  hipLaunchKernelGGL(bwd_reduce_hyp_kernel, dim3(1), dim3(256), 0, stream, passes * blocks, b.part_h,
-                     kern->lengthscale, kern->amplitude, g_hyp);
-  GPL_LAUNCH_CHECK();
-  return GPL_OK;
+  GPL_TRY(plan_build(plan, n, px, py, nullptr, s2, kSkipBackward, kSkipBackward, stream));
+  return bwd_run(plan, b, kern, npairs, A, lda, Bv, ldb, w, true, gpx, gpy, g_hyp, stream);
+}
+
+// The plan of the product serves its adjoint too: both keep the pairs below the same
+// threshold (kSkipBackward), and the precision form's mask of pairs that need the lo part
+// changes the plan's split of the work, not the pairs.
+static_assert(kSkipBackward == kSkipFp32 && kSkipBackward == kSkipF16x3, "one plan for both");
+
+extern "C" size_t gpl_gp_kernel_mvm_vjp_workspace(int n, int ncols, int prec) {
+  if (n <= 0 || ncols <= 0 || ncols > 4096) return 0;
+  return align_up(mvm_workspace(n, ncols, prec)) + bwd_workspace(n, ncols) + kAlign;
+}
+
+extern "C" int gpl_gp_kernel_mvm_vjp(const gpl_kernel* kern, int n, const float* px, const float* py, int ncols,
+                                     const float* V, int ldv, const float* G, int ldg, float* gV, int ldgv, float* gpx,
+                                     float* gpy, double* g_hyp, int prec, void* ws, size_t ws_bytes,
+                                     hipStream_t stream) {
+  GPL_TRY(check_backward(kern, n, ncols));
+  GPL_REQUIRE(prec == GPL_PREC_FP32 || prec == GPL_PREC_F16X3, "unknown precision %d", prec);
+  GPL_REQUIRE(px && py && V && G && gV && gpx && gpy && g_hyp, "NULL argument");
+  GPL_REQUIRE(ldv >= n && ldg >= n && ldgv >= n, "ldv/ldg/ldgv must be >= n");
+  GPL_REQUIRE(V != gV && G != gV, "gV must not overlap its operands");
+  GPL_TRY(check_ws(ws, ws_bytes, gpl_gp_kernel_mvm_vjp_workspace(n, ncols, prec)));
+  Carver cv(ws, ws_bytes);
+  const size_t mb = mvm_workspace(n, ncols, prec);
+  char* mws = cv.take<char>(mb);
+  BwdBufs b;
+  carve_bwd(cv, n, ncols, b);
+  if (!cv.ok()) return check_ws(nullptr, 0, 1);
+  MvmCtx m;
+  GPL_TRY(mvm_prepare(m, kern->lengthscale, kern->amplitude, n, px, py, nullptr, ncols, prec, false, mws, mb, stream));
+  GPL_TRY(mvm_run(m, ncols, G, ldg, gV, ldgv, 0.f, CgGate{}, stream));  // K is symmetric
+  return bwd_run(m.plan, b, kern, ncols, G, ldg, V, ldv, nullptr, false, gpx, gpy, g_hyp, stream);
 }

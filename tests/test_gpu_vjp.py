@@ -1,0 +1,31 @@
+"""The product's backward pass over one plan: bit for bit the product, and the
+gradients of the adjoint's own entry (same pairs and sums, split over the waves
+by another cost in the precision form, so FP64 sums in another order); errors as
+there."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("prec", ["f16x3", "fp32"])
+@pytest.mark.parametrize("n,cols", [(1, 1), (65, 17), (1600, 19), (4097, 2), (9000, 37)])
+def test_vjp(n, cols, prec):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2105_09465_amd as G
+    print("[case] vjp", n, cols, prec, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    px, py = (0.02 * n ** 0.5 * torch.rand(2, n, device="cuda", generator=g)).unbind(0)
+    V, U = (torch.randn(cols, n + 5, device="cuda", generator=g)[:, :n] for _ in range(2))  # strided columns
+    k = G.Kernel(0.04, 0.3)
+    gx, gy, gV, gh = G.ops.kernel_mvm_vjp(k, px, py, V, U, prec=prec)
+    assert torch.equal(gV, G.ops.kernel_mvm(k, px, py, U, prec=prec))
+    wx, wy, wh = G.ops.kernel_mvm_backward(k, px, py, U, V, [1.0] * cols)
+    for a, b in ((gx, wx), (gy, wy), (gh, wh)):
+        assert (a - b).abs().max() <= 1e-6 * b.abs().max()
+    with pytest.raises(Exception):
+        G.ops.kernel_mvm_vjp(G.Kernel(0.04, 0.0), px, py, V, U, prec=prec)
+    with pytest.raises(ValueError):
+        G.ops.kernel_mvm_vjp(k, px, py, V, U[:, :-1], prec=prec)
