@@ -29,3 +29,32 @@ def test_vjp(n, cols, prec):
         G.ops.kernel_mvm_vjp(G.Kernel(0.04, 0.0), px, py, V, U, prec=prec)
     with pytest.raises(ValueError):
         G.ops.kernel_mvm_vjp(k, px, py, V, U[:, :-1], prec=prec)
+
+
+def test_products_over_stale_memory():
+    """Results the caller has not given are not cleared: every entry is written."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2105_09465_amd as G
+    g = torch.Generator(device="cuda").manual_seed(3)
+    n = 700
+    px, py = torch.rand(2, n, device="cuda", generator=g).unbind(0)
+    V = torch.randn(3, n, device="cuda", generator=g)
+    grid, psf = G.Grid(n=13, ss=2, pix_scale=0.05), G.PSF(0.1)
+    img = torch.randn(2, grid.N, device="cuda", generator=g)
+    z = torch.zeros(0, device="cuda")
+
+    def run():
+        a = [G.ops.kernel_mvm(G.Kernel(0.04, 0.3), px, py, V, prec=p) for p in ("f16x3", "fp32")]
+        a += [G.ops.gauss_product(0.01, 1.0, px, py, px, py, V), G.ops.psf_conv(grid, psf, img, False),
+              G.ops.psf_conv(grid, psf, img[:, :grid.n_pix].contiguous(), True),
+              G.ops.gauss_product(0.01, 1.0, px, py, z, z, torch.zeros(3, 0, device="cuda"))]
+        return a
+    first = [t.clone() for t in run()]
+    assert (first[-1] == 0).all()
+    del g
+    for _ in range(3):
+        dirt = [torch.full_like(t, float("nan")) for t in first]
+        del dirt
+        for a, b in zip(run(), first):
+            assert torch.equal(a, b)
