@@ -455,20 +455,6 @@ static int check_problem(const gpl_problem* prob, Taps& taps, bool windowed_ok =
   return GPL_OK;
 }
 
-// One application of A to the columns of P: AP = B K B^T P + sigma^2 P, with
-// p.Ap partials when `pap` is given.
-static int apply_A_into(const gpl_problem* prob, const Taps& taps, const MvmCtx& mv, int nrhs, const float* P,
-                        int ldp, float* T1, float* T2, int ldf, float* AP, int ldap, double* pap, CgGate gate,
-                        hipStream_t stream) {
-  const int n = prob->grid.n, ss = prob->grid.ss;
-  const float s2 = (float)(prob->noise_sigma * prob->noise_sigma);
-  GPL_TRY(psf_adjoint_launch(n, ss, taps, nrhs, P, ldp, T1, ldf, 1.f, 0.f, gate, stream));
-  GPL_TRY(mvm_run(mv, nrhs, T1, ldf, T2, ldf, 0.f, gate, stream));
-  GPL_TRY(psf_forward_launch(n, ss, taps, nrhs, T2, ldf, AP, ldap, 1.f, 0.f, P, ldp, s2, pap ? P : nullptr, ldp, pap,
-                             gate, stream));
-  return GPL_OK;
-}
-
 }  // namespace gpl
 
 using namespace gpl;
@@ -519,10 +505,15 @@ extern "C" int gpl_apply_A(const gpl_problem* prob, int nrhs, const float* X, in
     return psf_forward_launch(n, ss, taps, nrhs, T2, ldf, Y, ldy, 1.f, 0.f, X, ldx, s2, nullptr, 0, nullptr,
                               CgGate{}, stream);
   }
+  // B^T X first: it is placed in the product's buffers beside the plan
+  const int n = prob->grid.n, ss = prob->grid.ss;
+  GPL_TRY(psf_adjoint_launch(n, ss, taps, nrhs, X, ldx, T1, ldf, 1.f, 0.f, CgGate{}, stream));
   MvmCtx mv;
   GPL_TRY(mvm_prepare(mv, prob->kernel.lengthscale, prob->kernel.amplitude, N, prob->px, prob->py, &prob->grid, nrhs,
-                      prec, false, mws, mb, stream));
-  return apply_A_into(prob, taps, mv, nrhs, X, ldx, T1, T2, ldf, Y, ldy, nullptr, CgGate{}, stream);
+                      prec, false, mws, mb, stream, T1, ldf));
+  GPL_TRY(mvm_run_prepared(mv, nrhs, T2, ldf, 0.f, CgGate{}, stream));
+  return psf_forward_launch(n, ss, taps, nrhs, T2, ldf, Y, ldy, 1.f, 0.f, X, ldx,
+                            (float)(prob->noise_sigma * prob->noise_sigma), nullptr, 0, nullptr, CgGate{}, stream);
 }
 
 extern "C" size_t gpl_cg_solve_workspace(const gpl_problem* prob, int nrhs, int prec) {

@@ -125,10 +125,11 @@ struct MvmCtx {
 };
 size_t mvm_workspace(int n, int nrhs, int prec);
 // zero_rhs: clear the RHS buffers (needed unless every product is an mvm_run,
-// which writes them whole, the padding included).
+// which writes them whole, the padding included). V (nullable): the columns of the
+// first product, put into the buffers beside the plan for mvm_run_prepared.
 int mvm_prepare(MvmCtx& m, double lengthscale, double amplitude, int n, const float* px, const float* py,
                 const gpl_grid* grid, int nrhs, int prec, bool zero_rhs, void* ws, size_t ws_bytes,
-                hipStream_t stream);
+                hipStream_t stream, const float* V = nullptr, int ldv = 0);
 int mvm_run(const MvmCtx& m, int nrhs, const float* V, int ldv, float* Y, int ldy, float beta, CgGate gate,
             hipStream_t stream);
 // The product from RHS buffers already written (by the fused PSF adjoint).

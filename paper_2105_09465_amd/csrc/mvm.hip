@@ -14,6 +14,7 @@
 #include "gauss_tiles.hpp"
 #include "internal.hpp"
 #include "mvm_mfma.hpp"
+#include "mvm_rhs.hpp"
 
 namespace gpl {
 
@@ -37,7 +38,7 @@ size_t mvm_workspace(int n, int nrhs, int prec) {
 
 int mvm_prepare(MvmCtx& m, double lengthscale, double amplitude, int n, const float* px, const float* py,
                 const gpl_grid* grid, int nrhs, int prec, bool zero_rhs, void* ws, size_t ws_bytes,
-                hipStream_t stream) {
+                hipStream_t stream, const float* V, int ldv) {
   GPL_TRY(check_ws(ws, ws_bytes, mvm_workspace(n, nrhs, prec)));
   Carver cv(ws, ws_bytes);
   void* scratch;
@@ -50,7 +51,11 @@ int mvm_prepare(MvmCtx& m, double lengthscale, double amplitude, int n, const fl
   m.s2 = (float)kernel_scale2(lengthscale);
   m.amp2 = (float)(amplitude * amplitude);
   if (zero_rhs) GPL_TRY(mfma_zero_rhs(m.bufs, prec, stream));
-  return plan_build(m.plan, n, px, py, grid, m.s2, plan_threshold(prec), plan_lo_threshold(prec), stream);
+  const RhsJob job{n, nrhs, ldv, prec == GPL_PREC_F16X3, V, m.plan.perm, m.bufs};
+  bool placed;
+  GPL_TRY(plan_build(m.plan, n, px, py, grid, m.s2, plan_threshold(prec), plan_lo_threshold(prec), stream,
+                     V ? &job : nullptr, &placed));
+  return V && !placed ? mfma_prep_rhs(m.plan, m.bufs, prec, nrhs, V, ldv, CgGate{}, stream) : GPL_OK;
 }
 
 int mvm_run_prepared(const MvmCtx& m, int nrhs, float* Y, int ldy, float beta, CgGate gate, hipStream_t stream) {
@@ -69,8 +74,8 @@ int mvm_launch(double lengthscale, double amplitude, int n, const float* px, con
                int nrhs, const float* V, int ldv, float* Y, int ldy, float beta, int prec, void* ws, size_t ws_bytes,
                CgGate gate, hipStream_t stream) {
   MvmCtx m;
-  GPL_TRY(mvm_prepare(m, lengthscale, amplitude, n, px, py, grid, nrhs, prec, false, ws, ws_bytes, stream));
-  return mvm_run(m, nrhs, V, ldv, Y, ldy, beta, gate, stream);
+  GPL_TRY(mvm_prepare(m, lengthscale, amplitude, n, px, py, grid, nrhs, prec, false, ws, ws_bytes, stream, V, ldv));
+  return mvm_run_prepared(m, nrhs, Y, ldy, beta, gate, stream);
 }
 
 // out[0] = listed (row tile, chunk) pairs, out[1] = listed (subtile, chunk) pairs.

@@ -35,6 +35,7 @@
 #include "common.hpp"
 #include "internal.hpp"
 #include "mvm_mfma.hpp"
+#include "mvm_rhs.hpp"
 #include "timing.hpp"
 
 namespace gpl {
@@ -45,7 +46,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kRT = kSubsPerTile;           // 16-row MFMA tiles per wave
 constexpr int kWaves = 4;                   // independent waves per workgroup
-constexpr float kKScale = 2048.f;           // 2^11 applied to the FP16 exp tile
 static constexpr int kMaxCB = 4;            // up to 64 columns per pass
 
 static_assert(kRT * 16 == kRowTile, "row tile of 16-row MFMA tiles");
@@ -54,136 +54,36 @@ static_assert(kWaves == kPlanWaves, "the plan orders workgroups of kPlanWaves wa
 
 // ---------------------------------------------------------------- RHS preparation
 
-// Column-wise max |V| in two steps without atomics: kColmaxBlocks workgroups per
-// column write partial maxima (as bit patterns of non-negative floats); the
-// split kernel folds them.
-__device__ __forceinline__ void colmax_body(int bx, int c, int n, const float* __restrict__ V, int ldv,
-                                            unsigned* partial) {
+__global__ __launch_bounds__(256) void colmax_kernel(RhsJob J, CgGate gate) {
   __shared__ float red[4];
-  float m = 0.f;
-  for (int i = bx * blockDim.x + threadIdx.x; i < n; i += kColmaxBlocks * blockDim.x)
-    m = fmaxf(m, fabsf(V[(size_t)c * ldv + i]));
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-  __syncthreads();
-  if (threadIdx.x == 0)
-    partial[c * kColmaxBlocks + bx] = __float_as_uint(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
-}
-
-__global__ __launch_bounds__(256) void colmax_kernel(int n, const float* __restrict__ V, int ldv, unsigned* partial,
-                                                     CgGate gate) {
   if (gate.skip_all()) return;
-  colmax_body(blockIdx.x, blockIdx.y, n, V, ldv, partial);
+  colmax_unit(J, blockIdx.y * kColmaxBlocks + blockIdx.x, threadIdx.x, red);
 }
 
-// Sorted position j of column c: the caller's row perm[j] (or j), zero past n
-// and for c >= nrhs.
-__device__ __forceinline__ float gather_rhs(int j, int c, int n, int nrhs, const int* perm, const float* V, int ldv) {
-  if (c >= nrhs || j >= n) return 0.f;
-  return V[(size_t)c * ldv + (perm ? perm[j] : j)];
-}
-
-// Column of slot `slot` of the buffers: column `slot`, or in a packed last block
-// (one FP16 part a slot, lo in odd ones) column b0 + (slot - b0) / 2.
-__device__ __forceinline__ int slot_column(int slot, int nrhs, bool& packed) {
-  const int b0 = packed_block_start(nrhs);
-  packed = last_block_packed(nrhs) && slot >= b0;
-  return packed ? b0 + (slot - b0) / 2 : slot;
-}
-
-// Exponent e of a column with the largest magnitude mx: mx 2^e in [2^13, 2^14); e
-// is capped so that 2^e stays a finite float (a column below 2^-113 then scales
-// to less than 2^13, still normal in FP16).
-__device__ __forceinline__ int column_exponent(float mx) {
-  return mx > 0.f && isfinite(mx) ? min(14 - ilogbf(mx) - 1, 126) : 0;
-}
-
-// V' = V * 2^e_c split into FP16 hi (nearest) and lo, in sorted order, position j
-// of one slot; inv_scale[c] = 2^-e_c / 2^11 folds both scales for the output.
-__device__ __forceinline__ void split_rhs_at(int j, int slot, int c, bool packed, int e, int nrhs, float value,
-                                             _Float16* Vh, _Float16* Vl, int ncp, float* inv_scale) {
-  const int b0 = packed_block_start(nrhs);
-  const float scale = ldexpf(1.f, e);
-  if (j == 0 && c < ncp && (!packed || ((slot - b0) & 1) == 0)) inv_scale[c] = ldexpf(1.f, -e) / kKScale;
-  const float v = value * scale;
-  const _Float16 h = (_Float16)v;
-  const _Float16 l = (_Float16)(v - (float)h);
-  if (packed) {
-    Vh[rhs_at(slot, j, ncp)] = ((slot - b0) & 1) ? l : h;
-  } else {
-    Vh[rhs_at(c, j, ncp)] = h;
-    Vl[rhs_at(c, j, ncp)] = l;
-  }
-}
-
-// kSplitSlots slots a workgroup, a thread one sorted position of all of them: their
-// gathers are in flight together. Wave w folds the partial maxima of slot w.
-constexpr int kSplitSlots = 4;
-static_assert(kColmaxBlocks <= 64, "a wave folds a column's partial maxima");
-__global__ __launch_bounds__(256) void split_rhs_kernel(int n, int nrhs, const float* __restrict__ V, int ldv,
-                                                        const int* perm, const unsigned* colmax, _Float16* Vh,
-                                                        _Float16* Vl, int ldh, int ncp, float* inv_scale,
-                                                        CgGate gate) {
-  __shared__ int se[kSplitSlots];
+__global__ __launch_bounds__(256) void place_rhs_kernel(RhsJob J, CgGate gate) {
+  __shared__ int se[kPlaceSlots];
   if (gate.skip_all()) return;
-  const int j = blockIdx.x * 256 + threadIdx.x, slot0 = blockIdx.y * kSplitSlots, lane = threadIdx.x & 63;
-  bool packed[kSplitSlots];
-  int c[kSplitSlots];
-  float v[kSplitSlots];
-#pragma unroll
-  for (int k = 0; k < kSplitSlots; ++k) {
-    c[k] = slot_column(slot0 + k, nrhs, packed[k]);
-    v[k] = j < ldh ? gather_rhs(j, c[k], n, nrhs, perm, V, ldv) : 0.f;
-  }
-  {
-    bool pk;
-    const int w = threadIdx.x >> 6, cw = slot_column(slot0 + w, nrhs, pk);
-    unsigned mb = cw < nrhs && lane < kColmaxBlocks ? colmax[cw * kColmaxBlocks + lane] : 0u;
-    for (int off = 32; off > 0; off >>= 1) mb = max(mb, (unsigned)__shfl_xor((int)mb, off, 64));
-    if (lane == 0) se[w] = cw < nrhs ? column_exponent(__uint_as_float(mb)) : 0;
-  }
-  __syncthreads();
-  if (j >= ldh) return;
-#pragma unroll
-  for (int k = 0; k < kSplitSlots; ++k)
-    split_rhs_at(j, slot0 + k, c[k], packed[k], se[k], nrhs, v[k], Vh, Vl, ncp, inv_scale);
+  place_unit(J, blockIdx.x, blockIdx.y * kPlaceSlots, threadIdx.x, se);
 }
 
 // Both steps for a small product, one workgroup per slot (the column maximum is
 // formed by every workgroup that needs it): a launch less where launches are
 // what counts.
 constexpr int kSmallRhs = 4096;
-__global__ __launch_bounds__(1024) void small_rhs_kernel(int n, int nrhs, const float* __restrict__ V, int ldv,
-                                                         const int* perm, _Float16* Vh, _Float16* Vl, int ldh, int ncp,
-                                                         float* inv_scale, CgGate gate) {
+__global__ __launch_bounds__(1024) void small_rhs_kernel(RhsJob J, CgGate gate) {
   __shared__ float red[16];
   if (gate.skip_all()) return;
   bool packed;
-  const int slot = blockIdx.x, c = slot_column(slot, nrhs, packed);
+  const int slot = blockIdx.x, c = slot_column(slot, J.nrhs, packed);
   float m = 0.f;
-  if (c < nrhs)
-    for (int i = threadIdx.x; i < n; i += 1024) m = fmaxf(m, fabsf(V[(size_t)c * ldv + i]));
+  if (c < J.nrhs)
+    for (int i = threadIdx.x; i < J.n; i += 1024) m = fmaxf(m, fabsf(J.V[(size_t)c * J.ldv + i]));
   for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
   for (int k = 0; k < 16; ++k) m = fmaxf(m, red[k]);
-  const int e = c < nrhs ? column_exponent(m) : 0;
-  for (int j = threadIdx.x; j < ldh; j += 1024)
-    split_rhs_at(j, slot, c, packed, e, nrhs, gather_rhs(j, c, n, nrhs, perm, V, ldv), Vh, Vl, ncp, inv_scale);
-}
-
-// FP32 form: the RHS block in sorted order, zero padded.
-__device__ __forceinline__ void pack_rhs_body(int bx, int c, int n, int nrhs, const float* __restrict__ V, int ldv,
-                                              const int* perm, float* Vp, int ldh, int ncp) {
-  const int j = bx * blockDim.x + threadIdx.x;
-  if (j >= ldh) return;
-  Vp[rhs_at(c, j, ncp)] = gather_rhs(j, c, n, nrhs, perm, V, ldv);
-}
-
-__global__ void pack_rhs_kernel(int n, int nrhs, const float* __restrict__ V, int ldv, const int* perm, float* Vp,
-                                int ldh, int ncp, CgGate gate) {
-  if (gate.skip_all()) return;
-  pack_rhs_body(blockIdx.x, blockIdx.y, n, nrhs, V, ldv, perm, Vp, ldh, ncp);
+  const int e = c < J.nrhs ? column_exponent(m) : 0;
+  for (int j = threadIdx.x; j < J.b.ldh; j += 1024) split_rhs_at(J, j, slot, c, packed, e, gather_rhs(J, j, c));
 }
 
 // ---------------------------------------------------------------- work of one wave
@@ -666,19 +566,17 @@ int mfma_zero_rhs(const ProdBufs& b, int prec, hipStream_t stream) {
 
 int mfma_prep_rhs(const TilePlan& P, const ProdBufs& b, int prec, int nrhs, const float* V, int ldv, CgGate gate,
                   hipStream_t stream) {
-  const int n = P.n;
-  if (prec == GPL_PREC_F16X3 && n <= kSmallRhs) {
-    hipLaunchKernelGGL(small_rhs_kernel, dim3(b.ncp), dim3(1024), 0, stream, n, nrhs, V, ldv, P.perm, b.Vh, b.Vl, b.ldh,
-                       b.ncp, b.inv_scale, gate);
-  } else if (prec == GPL_PREC_F16X3) {
-    hipLaunchKernelGGL(colmax_kernel, dim3(kColmaxBlocks, nrhs), dim3(256), 0, stream, n, V, ldv, b.colmax, gate);
+  const RhsJob J{P.n, nrhs, ldv, prec == GPL_PREC_F16X3, V, P.perm, b};
+  if (J.f16 && J.n <= kSmallRhs) {
+    hipLaunchKernelGGL(small_rhs_kernel, dim3(b.ncp), dim3(1024), 0, stream, J, gate);
     GPL_LAUNCH_CHECK();
-    hipLaunchKernelGGL(split_rhs_kernel, dim3(cdiv(b.ldh, 256), b.ncp / kSplitSlots), dim3(256), 0, stream, n, nrhs, V, ldv, P.perm,
-                       b.colmax, b.Vh, b.Vl, b.ldh, b.ncp, b.inv_scale, gate);
-  } else {
-    hipLaunchKernelGGL(pack_rhs_kernel, dim3(cdiv(b.ldh, 256), b.ncp), dim3(256), 0, stream, n, nrhs, V, ldv, P.perm,
-                       b.Vp, b.ldh, b.ncp, gate);
+    return GPL_OK;
   }
+  if (J.f16) {
+    hipLaunchKernelGGL(colmax_kernel, dim3(kColmaxBlocks, nrhs), dim3(256), 0, stream, J, gate);
+    GPL_LAUNCH_CHECK();
+  }
+  hipLaunchKernelGGL(place_rhs_kernel, dim3(cdiv(b.ldh, 256), b.ncp / kPlaceSlots), dim3(256), 0, stream, J, gate);
   GPL_LAUNCH_CHECK();
   return GPL_OK;
 }

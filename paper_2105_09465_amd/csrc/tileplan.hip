@@ -11,6 +11,7 @@
 #include <cmath>
 #include <utility>
 
+#include "mvm_rhs.hpp"
 #include "tileplan.hpp"
 
 namespace gpl {
@@ -70,16 +71,37 @@ __device__ __forceinline__ float4 extent_square(const float4& e) {
 }
 
 // Partial extents, one per workgroup (at most 64: the key kernel folds them).
-__global__ __launch_bounds__(kSortThreads) void plan_extent_kernel(int n, const float* __restrict__ px,
-                                                                   const float* __restrict__ py, float4* part) {
+__device__ __forceinline__ void extent_part(int n, const float* __restrict__ px, const float* __restrict__ py,
+                                            int parts, float4* part) {
   __shared__ float4 red[kSortThreads / 64];
-  float4 e = wave_extent(thread_extent(n, px, py, blockIdx.x * kSortThreads + threadIdx.x,
-                                       (int)gridDim.x * kSortThreads));
+  float4 e = wave_extent(thread_extent(n, px, py, blockIdx.x * kSortThreads + threadIdx.x, parts * kSortThreads));
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = e;
   __syncthreads();
   if (threadIdx.x != 0) return;
   for (int k = 1; k < kSortThreads / 64; ++k) e = join_extent(e, red[k]);
   part[blockIdx.x] = e;
+}
+
+__global__ __launch_bounds__(kSortThreads) void plan_extent_kernel(int n, const float* __restrict__ px,
+                                                                   const float* __restrict__ py, float4* part) {
+  extent_part(n, px, py, gridDim.x, part);
+}
+
+// The right-hand sides of a product that follows the plan are prepared beside it: the
+// column maxima with the extent, their places in the sorted order with the last
+// kernel of the plan, a single workgroup. In launches of their own these took 4.0 and
+// 5.0 us at 40,000 points and 17 columns, 10 and 29 at 160,000 and 64; the product
+// takes 93.7 us for 102 with them there, and 281 for 299.
+__global__ __launch_bounds__(kSortThreads) void plan_extent_rhs_kernel(int n, const float* __restrict__ px,
+                                                                       const float* __restrict__ py, int parts,
+                                                                       float4* part, RhsJob J) {
+  __shared__ float red[kSortThreads / 64];
+  if ((int)blockIdx.x < parts) {
+    extent_part(n, px, py, parts, part);
+  } else {
+    const int g = threadIdx.x >> 8;
+    colmax_unit(J, ((int)blockIdx.x - parts) * (kSortThreads / 256) + g, threadIdx.x & 255, red + 4 * g);
+  }
 }
 
 // Index of cell (x, y) along the Hilbert curve of a 2^kHilbertBits square grid:
@@ -831,11 +853,10 @@ __device__ __forceinline__ void finish_waves(int nrt, int nw, const int* off, co
   for (int r = tid; r < nrt; r += 1024) rslot[r] = make_int2(first[r], past[r] - first[r]);
 }
 
-__global__ __launch_bounds__(1024) void plan_finish_kernel(int nrt, int nw, const int* __restrict__ unit_off,
-                                                           const int* __restrict__ count_g,
-                                                           const int* __restrict__ wunit,
-                                                           const int2* __restrict__ wrows, int2* __restrict__ rslot,
-                                                           int4* __restrict__ wdesc, int* __restrict__ wrest) {
+__device__ __forceinline__ void plan_finish_body(int nrt, int nw, const int* __restrict__ unit_off,
+                                                 const int* __restrict__ count_g, const int* __restrict__ wunit,
+                                                 const int2* __restrict__ wrows, int2* __restrict__ rslot,
+                                                 int4* __restrict__ wdesc, int* __restrict__ wrest) {
   __shared__ int off[kFoldRows], wslot[kMaxPlanWaves];
   __shared__ unsigned short count[kFoldRows], first[kFoldRows], past[kFoldRows];
   for (int r = threadIdx.x; r < nrt; r += 1024) {
@@ -843,6 +864,30 @@ __global__ __launch_bounds__(1024) void plan_finish_kernel(int nrt, int nw, cons
     count[r] = (unsigned short)count_g[r];
   }
   finish_waves(nrt, nw, off, count, wunit, wrows, wslot, first, past, rslot, wdesc, wrest);
+}
+
+__global__ __launch_bounds__(1024) void plan_finish_kernel(int nrt, int nw, const int* __restrict__ unit_off,
+                                                           const int* __restrict__ count,
+                                                           const int* __restrict__ wunit,
+                                                           const int2* __restrict__ wrows, int2* __restrict__ rslot,
+                                                           int4* __restrict__ wdesc, int* __restrict__ wrest) {
+  plan_finish_body(nrt, nw, unit_off, count, wunit, wrows, rslot, wdesc, wrest);
+}
+
+// And the right-hand sides by the workgroups after the first.
+__global__ __launch_bounds__(1024) void plan_finish_rhs_kernel(int nrt, int nw, const int* __restrict__ unit_off,
+                                                               const int* __restrict__ count,
+                                                               const int* __restrict__ wunit,
+                                                               const int2* __restrict__ wrows,
+                                                               int2* __restrict__ rslot, int4* __restrict__ wdesc,
+                                                               int* __restrict__ wrest, RhsJob J) {
+  __shared__ int se[1024 / 256][kPlaceSlots];
+  if (blockIdx.x == 0) {
+    plan_finish_body(nrt, nw, unit_off, count, wunit, wrows, rslot, wdesc, wrest);
+  } else {
+    const int g = threadIdx.x >> 8, per = cdiv(J.b.ldh, 1024), u = blockIdx.x - 1;
+    place_unit(J, (u % per) * (1024 / 256) + g, u / per * kPlaceSlots, threadIdx.x & 255, se[g]);
+  }
 }
 
 // ---- small point sets: the whole plan by one workgroup ----
@@ -1042,10 +1087,11 @@ static int compute_units() {
 }
 
 // Sort of more than kSmallPoints points, and (kScaled) the scaled coordinates;
-// side (nullable): a small set sorted in the same launches.
+// side (nullable): a small set sorted in the same launches; job (nullable): the column
+// maxima of its right-hand sides too.
 template <bool kScaled>
 static int sort_points(TilePlan& p, int n, const float* px, const float* py, float s2, const SmallSort* side,
-                       hipStream_t stream) {
+                       const RhsJob* job, hipStream_t stream) {
   int* perm = const_cast<int*>(p.perm);
   int* irank = const_cast<int*>(p.irank);
   const int span = sort_span(n), nb = cdiv(n, span);
@@ -1054,7 +1100,11 @@ static int sort_points(TilePlan& p, int n, const float* px, const float* py, flo
   float4* ext = p.cbox;
   uint32_t *k0 = reinterpret_cast<uint32_t*>(p.xc), *k1 = reinterpret_cast<uint32_t*>(p.yc);
   const int parts = nb < 64 ? nb : 64;  // of the extent, one per workgroup: a wave folds them
-  hipLaunchKernelGGL(plan_extent_kernel, dim3(parts), dim3(kSortThreads), 0, stream, n, px, py, ext);
+  if (job && job->f16)
+    hipLaunchKernelGGL(plan_extent_rhs_kernel, dim3(parts + cdiv(job->nrhs * kColmaxBlocks, kSortThreads / 256)),
+                       dim3(kSortThreads), 0, stream, n, px, py, parts, ext, *job);
+  else
+    hipLaunchKernelGGL(plan_extent_kernel, dim3(parts), dim3(kSortThreads), 0, stream, n, px, py, ext);
   GPL_LAUNCH_CHECK();
   hipLaunchKernelGGL(plan_keys_kernel, dim3(nb), dim3(kSortThreads), 0, stream, n, span, px, py, ext, parts, k0,
                      p.shist);
@@ -1090,7 +1140,7 @@ static int small_plan(TilePlan& p, int n, const float* px, const float* py, floa
 int plan_sort(TilePlan& p, int n, const float* px, const float* py, hipStream_t stream) {
   GPL_REQUIRE(n >= 1, "plan needs at least one point");
   if (n <= kSmallPoints) return small_plan<false>(p, n, px, py, 1.f, 0.f, 0.f, stream);
-  return sort_points<false>(p, n, px, py, 1.f, nullptr, stream);
+  return sort_points<false>(p, n, px, py, 1.f, nullptr, nullptr, stream);
 }
 
 int plan_sort_pair(TilePlan& a, int na, const float* ax, const float* ay, TilePlan& b, int nb, const float* bx,
@@ -1101,14 +1151,15 @@ int plan_sort_pair(TilePlan& a, int na, const float* ax, const float* ay, TilePl
     return plan_sort(b, nb, bx, by, stream);
   }
   const SmallSort side = small_sort(b, nb, bx, by);
-  if (na > kSmallPoints) return sort_points<false>(a, na, ax, ay, 1.f, &side, stream);
+  if (na > kSmallPoints) return sort_points<false>(a, na, ax, ay, 1.f, &side, nullptr, stream);
   hipLaunchKernelGGL(sort_small_pair_kernel, dim3(2), dim3(kSortThreads), 0, stream, small_sort(a, na, ax, ay), side);
   GPL_LAUNCH_CHECK();
   return GPL_OK;
 }
 
 int plan_build(TilePlan& p, int n, const float* px, const float* py, const gpl_grid* grid, float s2, float threshold,
-               float lo_threshold, hipStream_t stream) {
+               float lo_threshold, hipStream_t stream, const RhsJob* job, bool* placed) {
+  if (placed) *placed = false;
   if (grid) {
     const int m = grid->n * grid->ss;
     GPL_REQUIRE(m > 0 && (long)m * m == n, "grid does not match n=%d", n);
@@ -1117,7 +1168,8 @@ int plan_build(TilePlan& p, int n, const float* px, const float* py, const gpl_g
   GPL_REQUIRE(p.nch <= kMaxPlanChunks, "n=%d exceeds the product's limit of %d points", n, kMaxPlanChunks * kChunk);
   p.wround = 4 * compute_units();
   if (n <= kSmallPoints) return small_plan<true>(p, n, px, py, s2, threshold, lo_threshold, stream);
-  GPL_TRY(sort_points<true>(p, n, px, py, s2, nullptr, stream));
+  if (p.nrt > kFoldRows) job = nullptr;
+  GPL_TRY(sort_points<true>(p, n, px, py, s2, nullptr, job, stream));
   hipLaunchKernelGGL(plan_lists_kernel, dim3(p.nrt), dim3(256), 0, stream, p.nch, p.cbox, p.sbox, s2, threshold,
                      lo_threshold, p.count, p.list, p.roww);
   GPL_LAUNCH_CHECK();
@@ -1125,9 +1177,15 @@ int plan_build(TilePlan& p, int n, const float* px, const float* py, const gpl_g
     hipLaunchKernelGGL(plan_wunit_fold_kernel, dim3(cdiv(p.nw + 1, 4)), dim3(256), 0, stream, p.nrt, p.nch, p.nw,
                        p.wround, p.count, p.list, p.roww, p.unit_off, p.wunit, reinterpret_cast<int2*>(p.wrow));
     GPL_LAUNCH_CHECK();
-    hipLaunchKernelGGL(plan_finish_kernel, dim3(1), dim3(1024), 0, stream, p.nrt, p.nw, p.unit_off, p.count, p.wunit,
-                       reinterpret_cast<int2*>(p.wrow), p.rslot, p.wdesc, p.wrest);
+    if (job)
+      hipLaunchKernelGGL(plan_finish_rhs_kernel, dim3(1 + cdiv(job->b.ldh, 1024) * (job->b.ncp / kPlaceSlots)),
+                         dim3(1024), 0, stream, p.nrt, p.nw, p.unit_off, p.count, p.wunit,
+                         reinterpret_cast<int2*>(p.wrow), p.rslot, p.wdesc, p.wrest, *job);
+    else
+      hipLaunchKernelGGL(plan_finish_kernel, dim3(1), dim3(1024), 0, stream, p.nrt, p.nw, p.unit_off, p.count, p.wunit,
+                         reinterpret_cast<int2*>(p.wrow), p.rslot, p.wdesc, p.wrest);
     GPL_LAUNCH_CHECK();
+    if (placed) *placed = job != nullptr;
     return GPL_OK;
   }
   hipLaunchKernelGGL(plan_scan_kernel<int>, dim3(1), dim3(1024), 0, stream, p.nrt, p.count, p.unit_off, p.total);

@@ -222,9 +222,11 @@ void sort_carve(C& cv, int n, TilePlan& p) {
 // fine grid in row-major order, which is what irank is indexed by in the fused
 // PSF adjoint. `s2` is the exp2 scale, `threshold` the skip threshold of the
 // form and `lo_threshold` that of the lo masks (kLoF16x3 in the precision form;
-// equal to `threshold` where the form has no lo part).
+// equal to `threshold` where the form has no lo part). `job` (nullable): right-hand
+// sides to be prepared beside the plan; *placed says whether they were.
+struct RhsJob;
 int plan_build(TilePlan& p, int n, const float* px, const float* py, const gpl_grid* grid, float s2, float threshold,
-               float lo_threshold, hipStream_t stream);
+               float lo_threshold, hipStream_t stream, const RhsJob* job = nullptr, bool* placed = nullptr);
 // The first part of plan_build alone: the Hilbert sort (perm, irank, xs, ys)
 // and the chunk and subtile boxes.
 int plan_sort(TilePlan& p, int n, const float* px, const float* py, hipStream_t stream);
