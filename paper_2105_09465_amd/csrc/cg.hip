@@ -511,7 +511,7 @@ extern "C" int gpl_apply_A(const gpl_problem* prob, int nrhs, const float* X, in
   MvmCtx mv;
   GPL_TRY(mvm_prepare(mv, prob->kernel.lengthscale, prob->kernel.amplitude, N, prob->px, prob->py, &prob->grid, nrhs,
                       prec, false, mws, mb, stream, T1, ldf));
-  GPL_TRY(mvm_run_prepared(mv, nrhs, T2, ldf, 0.f, CgGate{}, stream));
+  GPL_TRY(mvm_run_prepared(mv, nrhs, T2, ldf, 0.f, CgGate{}, stream, true));
   return psf_forward_launch(n, ss, taps, nrhs, T2, ldf, Y, ldy, 1.f, 0.f, X, ldx,
                             (float)(prob->noise_sigma * prob->noise_sigma), nullptr, 0, nullptr, CgGate{}, stream);
 }

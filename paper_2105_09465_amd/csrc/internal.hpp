@@ -133,7 +133,9 @@ int mvm_prepare(MvmCtx& m, double lengthscale, double amplitude, int n, const fl
 int mvm_run(const MvmCtx& m, int nrhs, const float* V, int ldv, float* Y, int ldy, float beta, CgGate gate,
             hipStream_t stream);
 // The product from RHS buffers already written (by the fused PSF adjoint).
-int mvm_run_prepared(const MvmCtx& m, int nrhs, float* Y, int ldy, float beta, CgGate gate, hipStream_t stream);
+// tail_ok: see mfma_product (not for iterations whose bits are to stay).
+int mvm_run_prepared(const MvmCtx& m, int nrhs, float* Y, int ldy, float beta, CgGate gate, hipStream_t stream,
+                     bool tail_ok = false);
 
 // Where the fused PSF adjoint writes B^T P: the product's RHS buffers (fine point
 // (fx, fy) at its sorted position in the plan, the FP16 parts of column c at the

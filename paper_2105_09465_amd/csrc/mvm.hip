@@ -58,9 +58,10 @@ int mvm_prepare(MvmCtx& m, double lengthscale, double amplitude, int n, const fl
   return V && !placed ? mfma_prep_rhs(m.plan, m.bufs, prec, nrhs, V, ldv, CgGate{}, stream) : GPL_OK;
 }
 
-int mvm_run_prepared(const MvmCtx& m, int nrhs, float* Y, int ldy, float beta, CgGate gate, hipStream_t stream) {
+int mvm_run_prepared(const MvmCtx& m, int nrhs, float* Y, int ldy, float beta, CgGate gate, hipStream_t stream,
+                     bool tail_ok) {
   GPL_REQUIRE(nrhs <= m.nrhs_max, "product prepared for %d columns, %d given", m.nrhs_max, nrhs);
-  return mfma_product(m.plan, m.bufs, m.prec, m.s2, m.amp2, nrhs, Y, ldy, beta, gate, stream);
+  return mfma_product(m.plan, m.bufs, m.prec, m.s2, m.amp2, nrhs, Y, ldy, beta, tail_ok, gate, stream);
 }
 
 int mvm_run(const MvmCtx& m, int nrhs, const float* V, int ldv, float* Y, int ldy, float beta, CgGate gate,
@@ -75,7 +76,7 @@ int mvm_launch(double lengthscale, double amplitude, int n, const float* px, con
                CgGate gate, hipStream_t stream) {
   MvmCtx m;
   GPL_TRY(mvm_prepare(m, lengthscale, amplitude, n, px, py, grid, nrhs, prec, false, ws, ws_bytes, stream, V, ldv));
-  return mvm_run_prepared(m, nrhs, Y, ldy, beta, gate, stream);
+  return mvm_run_prepared(m, nrhs, Y, ldy, beta, gate, stream, true);
 }
 
 // out[0] = listed (row tile, chunk) pairs, out[1] = listed (subtile, chunk) pairs.

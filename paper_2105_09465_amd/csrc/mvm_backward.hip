@@ -411,6 +411,6 @@ extern "C" int gpl_gp_kernel_mvm_vjp(const gpl_kernel* kern, int n, const float*
   MvmCtx m;
   GPL_TRY(mvm_prepare(m, kern->lengthscale, kern->amplitude, n, px, py, nullptr, ncols, prec, false, mws, mb, stream,
                       G, ldg));
-  GPL_TRY(mvm_run_prepared(m, ncols, gV, ldgv, 0.f, CgGate{}, stream));  // K is symmetric
+  GPL_TRY(mvm_run_prepared(m, ncols, gV, ldgv, 0.f, CgGate{}, stream, true));  // K is symmetric
   return bwd_run(m.plan, b, kern, ncols, G, ldg, V, ldv, nullptr, false, gpx, gpy, g_hyp, stream);
 }

@@ -165,13 +165,14 @@ __device__ __forceinline__ void for_chunks_pf(const uint32_t* lst, int kb, int k
 // One wave's share of a product: for each row tile its units touch, load the
 // tile's 64 row coordinates (from rx, ry), accumulate over the tile's chunks in
 // the range, and write the partial rows. `chunk_fn(acc, xi, yi, r, lst, kb, ke,
-// lane)` accumulates list positions [kb, ke) of row tile r. The wave's range comes from one
+// lane)` accumulates list positions [kb, ke) of row tile r, `store_fn(slot)` writes what
+// it holds besides. The wave's range comes from one
 // descriptor load, issued together with the gate flag; `skip()` is evaluated
 // once both are in.
-template <int CB, bool PK, class S, class F>
+template <int CB, bool PK, class S, class F, class T>
 __device__ __forceinline__ void wave_product(int w, const TilePlan& P, const float* __restrict__ rx,
                                              const float* __restrict__ ry, float* __restrict__ part, int pcols, int c0,
-                                             int ncols, S&& skip, F&& chunk_fn) {
+                                             int ncols, S&& skip, F&& chunk_fn, T&& store_fn) {
   const int4 d = P.wdesc[w];
   int rest = P.wrest[w];
   if (skip() || d.x < 0) return;
@@ -193,6 +194,7 @@ __device__ __forceinline__ void wave_product(int w, const TilePlan& P, const flo
       for (int cb = 0; cb < CB; ++cb) acc[rt][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
     chunk_fn(acc, xi, yi, r, P.list + (size_t)r * P.nch, kb, ke, lane);
     store_partial<CB, PK>(acc, slot, part, pcols, c0, ncols, ri, g);
+    store_fn(slot);
     if (rest <= 0) break;
     ++r;
     ++slot;
@@ -324,7 +326,8 @@ __device__ __forceinline__ void mvm_f16x3_wave(Skip&& skip, int w, const TilePla
                            f16_load<CB, PK, FILT>(c, P, Vh, Vl, ncp, e, ri, g, cgen, gen);
                          },
                          [&](const F16Chunk<CB, PK>& c) { f16_compute(acc, c, xi, yi, rcen); });
-                   });
+                   },
+                   [](int) {});
 }
 
 // One wave per share of the plan's units; 4 independent waves per workgroup.
@@ -340,10 +343,17 @@ __global__ __launch_bounds__(256) void mvm_f16x3_kernel(const TilePlan P, const 
 
 // ---------------------------------------------------------------- FP32 form
 
-template <int CB>
-__device__ __forceinline__ void f32_chunk(f32x4 (&acc)[kRT][CB], const float (&xi)[kRT], const float (&yi)[kRT],
-                                          const TilePlan& P, float s2, const float* __restrict__ Vp, int ncp,
-                                          uint32_t entry, int ri, int g) {
+// Sums of up to TL columns past the last whole block, by FMAs: per lane one row of
+// each 16-row tile and the 8 points of a chunk that its lane group holds.
+template <int TL>
+struct Tail {
+  float sum[kRT][TL > 0 ? TL : 1];
+};
+
+template <int CB, int TL>
+__device__ __forceinline__ void f32_chunk(f32x4 (&acc)[kRT][CB], Tail<TL>& tail, const float (&xi)[kRT],
+                                          const float (&yi)[kRT], const TilePlan& P, float s2,
+                                          const float* __restrict__ Vp, int ncp, uint32_t entry, int ri, int g) {
   // two groups of 16 points; in each, this lane's 4 consecutive points
   const unsigned mask = entry_mask(entry);
   const int jc = entry_chunk(entry) * kChunk + g * 4;
@@ -354,11 +364,15 @@ __device__ __forceinline__ void f32_chunk(f32x4 (&acc)[kRT][CB], const float (&x
   *reinterpret_cast<f32x4*>(&yj[4]) = *reinterpret_cast<const f32x4*>(&P.ys[jc + 16]);
   const float* vp = Vp + (size_t)entry_chunk(entry) * ncp * kChunk;  // uniform chunk base
   const unsigned lo = ri * kChunk + g * 4;
-  f32x4 b[CB][2];
+  f32x4 b[CB][2], tv[TL > 0 ? TL : 1][2];
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
     for (int h = 0; h < 2; ++h) b[cb][h] = *reinterpret_cast<const f32x4*>(vp + cb * 16 * kChunk + 16 * h + lo);
+#pragma unroll
+  for (int l = 0; l < TL; ++l)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) tv[l][h] = *reinterpret_cast<const f32x4*>(vp + (CB * 16 + l) * kChunk + 16 * h + g * 4);
 #pragma unroll
   for (int rt = 0; rt < kRT; ++rt) {
     if (!((mask >> rt) & 1u)) continue;  // every exp of this 16 x 32 tile is exactly zero
@@ -374,28 +388,50 @@ __device__ __forceinline__ void f32_chunk(f32x4 (&acc)[kRT][CB], const float (&x
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb)
         acc[rt][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], b[cb][e >> 2][e & 3], acc[rt][cb], 0, 0, 0);
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int l = 0; l < TL; ++l) tail.sum[rt][l] = fmaf(kv[e], tv[l][e >> 2][e & 3], tail.sum[rt][l]);
   }
 }
 
-template <int CB, class Skip>
+template <int CB, int TL, class Skip>
 __device__ __forceinline__ void mvm_f32_wave(Skip&& skip, int w, const TilePlan& P, float s2, const float* __restrict__ Vp,
                                              int ncp, int ncols, float* __restrict__ part, int pcols, int c0) {
   const int lane = threadIdx.x & 63, ri = lane & 15, g = lane >> 4;
-  wave_product<CB, false>(w, P, P.xs, P.ys, part, pcols, c0, ncols, skip,
-                   [&](f32x4 (&acc)[kRT][CB], const float (&xi)[kRT], const float (&yi)[kRT], int,
-                       const uint32_t* lst, int kb, int ke, int lane) {
-                     for_chunks(lst, kb, ke, lane,
-                                [&](uint32_t e) { f32_chunk<CB>(acc, xi, yi, P, s2, Vp, ncp, e, ri, g); });
-                   });
+  Tail<TL> tail;
+  wave_product<CB, false>(
+      w, P, P.xs, P.ys, part, pcols, c0, min(ncols, TL > 0 ? CB * 16 : ncols), skip,
+      [&](f32x4 (&acc)[kRT][CB], const float (&xi)[kRT], const float (&yi)[kRT], int, const uint32_t* lst, int kb,
+          int ke, int lane) {
+#pragma unroll
+        for (int rt = 0; rt < kRT; ++rt)
+#pragma unroll
+          for (int l = 0; l < TL; ++l) tail.sum[rt][l] = 0.f;
+        for_chunks(lst, kb, ke, lane,
+                   [&](uint32_t e) { f32_chunk<CB, TL>(acc, tail, xi, yi, P, s2, Vp, ncp, e, ri, g); });
+      },
+      [&](int slot) {
+#pragma unroll
+        for (int l = 0; l < TL; ++l)
+#pragma unroll
+          for (int rt = 0; rt < kRT; ++rt) {
+            float v = tail.sum[rt][l];
+            v += __shfl_xor(v, 16, 64);
+            v += __shfl_xor(v, 32, 64);
+            const int c = CB * 16 + l;
+            if (g == 0 && c < ncols) part[((size_t)slot * pcols + c0 + c) * kRowTile + rt * 16 + ri] = v;
+          }
+      });
 }
 
-template <int CB>
+template <int CB, int TL>
 __global__ __launch_bounds__(256) void mvm_f32_kernel(const TilePlan P, float s2, const float* __restrict__ Vp,
                                                       int ncp, int ncols, float* __restrict__ part, int pcols, int c0,
                                                       CgGate gate) {
   const int w = plan_block(blockIdx.x, P.nw, P.wround) * kWaves +
                 __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  mvm_f32_wave<CB>([&] { return gate.skip_all(); }, w, P, s2, Vp, ncp, ncols, part, pcols, c0);
+  mvm_f32_wave<CB, TL>([&] { return gate.skip_all(); }, w, P, s2, Vp, ncp, ncols, part, pcols, c0);
 }
 
 // ---------------------------------------------------------------- reduction
@@ -529,10 +565,13 @@ static void launch_f16x3(bool packed, const TilePlan& P, const _Float16* Vh, con
 }
 
 template <int CB>
-static void launch_f32(const TilePlan& P, float s2, const float* Vp, int ncp, int ncols, float* part, int pcols,
-                       int c0, CgGate gate, hipStream_t stream) {
-  hipLaunchKernelGGL((mvm_f32_kernel<CB>), dim3(P.nw / kWaves), dim3(256), 0, stream, P, s2, Vp, ncp, ncols, part,
-                     pcols, c0, gate);
+static void launch_f32(int tail, const TilePlan& P, float s2, const float* Vp, int ncp, int ncols, float* part,
+                       int pcols, int c0, CgGate gate, hipStream_t stream) {
+  const auto kern = tail == 0   ? mvm_f32_kernel<CB, 0>
+                    : tail == 1 ? mvm_f32_kernel<CB, 1>
+                    : tail == 2 ? mvm_f32_kernel<CB, 2>
+                                : mvm_f32_kernel<CB, 4>;
+  hipLaunchKernelGGL(kern, dim3(P.nw / kWaves), dim3(256), 0, stream, P, s2, Vp, ncp, ncols, part, pcols, c0, gate);
 }
 
 int mfma_carve(const TilePlan& P, int prec, int nrhs, void* ws, size_t ws_bytes, ProdBufs& b) {
@@ -582,12 +621,18 @@ int mfma_prep_rhs(const TilePlan& P, const ProdBufs& b, int prec, int nrhs, cons
 }
 
 int mfma_product(const TilePlan& P, const ProdBufs& b, int prec, float s2, float amp2, int nrhs, float* Y, int ldy,
-                 float beta, CgGate gate, hipStream_t stream) {
+                 float beta, bool tail_ok, CgGate gate, hipStream_t stream) {
   const bool f16 = prec == GPL_PREC_F16X3;
+  // A last block of at most four columns of the FP32 form goes to the vector units
+  // beside the blocks before it (@@TAIL@@). Its sums
+  // run in another order, so the caller says whether it may.
+  const int left = nrhs % 16, tail = tail_ok && !f16 && nrhs > 16 && left <= 4 ? left : 0;
+  const int nb = cdiv(nrhs - tail, 16);  // blocks on the matrix cores
   // column blocks of up to 64 columns per pass; each pass writes its own columns
-  for (int c0 = 0; c0 < b.ncp; c0 += kMaxCB * 16) {
-    const int cb = std::min(kMaxCB, (b.ncp - c0) / 16);
-    const int ncols = std::min(nrhs - c0, cb * 16);
+  for (int c0 = 0; c0 < nb * 16; c0 += kMaxCB * 16) {
+    const int cb = std::min(kMaxCB, nb - c0 / 16);
+    const int tl = c0 / 16 + cb == nb ? tail : 0;
+    const int ncols = std::min(nrhs - c0, cb * 16 + tl);
     hipEvent_t t0 = timing_begin(stream);
     if (f16) {
       // columns c0.. of each chunk (rhs_at layout); the pass with the last block
@@ -604,10 +649,10 @@ int mfma_product(const TilePlan& P, const ProdBufs& b, int prec, float s2, float
     } else {
       const float* vp = b.Vp + (size_t)c0 * kChunk;
       switch (cb) {
-        case 4: launch_f32<4>(P, s2, vp, b.ncp, ncols, b.part, nrhs, c0, gate, stream); break;
-        case 3: launch_f32<3>(P, s2, vp, b.ncp, ncols, b.part, nrhs, c0, gate, stream); break;
-        case 2: launch_f32<2>(P, s2, vp, b.ncp, ncols, b.part, nrhs, c0, gate, stream); break;
-        default: launch_f32<1>(P, s2, vp, b.ncp, ncols, b.part, nrhs, c0, gate, stream); break;
+        case 4: launch_f32<4>(tl, P, s2, vp, b.ncp, ncols, b.part, nrhs, c0, gate, stream); break;
+        case 3: launch_f32<3>(tl, P, s2, vp, b.ncp, ncols, b.part, nrhs, c0, gate, stream); break;
+        case 2: launch_f32<2>(tl, P, s2, vp, b.ncp, ncols, b.part, nrhs, c0, gate, stream); break;
+        default: launch_f32<1>(tl, P, s2, vp, b.ncp, ncols, b.part, nrhs, c0, gate, stream); break;
       }
     }
     GPL_LAUNCH_CHECK();
@@ -649,9 +694,9 @@ __global__ __launch_bounds__(256, 3) void mvm_grouped_kernel(SlotBatch B, int p)
     }
   } else {
     if (S.nrhs > 16)
-      mvm_f32_wave<2>(skip, w, S.plan, S.s2, S.Vp, S.ncp, S.nrhs, S.part, S.nrhs, 0);
+      mvm_f32_wave<2, 0>(skip, w, S.plan, S.s2, S.Vp, S.ncp, S.nrhs, S.part, S.nrhs, 0);
     else
-      mvm_f32_wave<1>(skip, w, S.plan, S.s2, S.Vp, S.ncp, S.nrhs, S.part, S.nrhs, 0);
+      mvm_f32_wave<1, 0>(skip, w, S.plan, S.s2, S.Vp, S.ncp, S.nrhs, S.part, S.nrhs, 0);
   }
 }
 
