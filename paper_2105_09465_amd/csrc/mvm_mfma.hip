@@ -624,7 +624,9 @@ int mfma_product(const TilePlan& P, const ProdBufs& b, int prec, float s2, float
                  float beta, bool tail_ok, CgGate gate, hipStream_t stream) {
   const bool f16 = prec == GPL_PREC_F16X3;
   // A last block of at most four columns of the FP32 form goes to the vector units
-  // beside the blocks before it (@@TAIL@@). Its sums
+  // beside the blocks before it: a block keeps the matrix units busy for as long as the
+  // kernel values do the vector units, whatever it holds (40,000 points, 17 columns: two
+  // blocks 70 us, one and a column 54). Its sums
   // run in another order, so the caller says whether it may.
   const int left = nrhs % 16, tail = tail_ok && !f16 && nrhs > 16 && left <= 4 ? left : 0;
   const int nb = cdiv(nrhs - tail, 16);  // blocks on the matrix cores
