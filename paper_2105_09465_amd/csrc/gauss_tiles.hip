@@ -5,14 +5,17 @@
 // "transmission"), the windowed kernel of Sec. 3.2 (eq. "covariance") and the
 // variational step built on them.
 //
-// Both sides are taken along a Hilbert curve of their positions (plan_sort). A
-// pair of boxes with gap g has d^T C^{-1} d >= g^2 / lambda for every pair in
-// it, lambda the largest eigenvalue of C there (base plus the largest
-// eigenvalues of the shapes of both boxes). v_exp_f32 returns zero below an
-// argument of -126.5, so a 16-target x 32-source pair of boxes with
-// (log2(e)/2) g^2 / lambda >= 127 holds exact zeros only and is not evaluated:
-// the sum over the rest is the sum over all pairs up to its order. A chunk with
-// a non-finite position, shape, weight or column value, or a shape whose
+// Both sides are taken along a Hilbert curve of their positions (plan_sort). For any
+// direction e, d^T C^{-1} d >= (e.d)^2 / (e^T C e), so a pair of boxes with gap g along
+// e has at least g^2 / (base + the largest e^T Z e of both boxes' shapes) for every
+// pair in it, and g^2 / lambda for its gap in the plane, lambda the largest eigenvalue.
+// v_exp_f32 returns zero below an argument of -126.5, so a 16-target x 32-source pair
+// of boxes where (log2(e)/2) times one of these reaches 127 holds exact zeros only and
+// is not evaluated: the sum over the rest is the sum over all pairs up to its order.
+// Directions: the axes and the diagonals (traced pixels are long and thin where the
+// image is magnified; with the eigenvalue alone, 15% of the pairs of 40,000 traced
+// points were evaluated for 12.9 at l = 0.04 and 5.6 for 3.4 at l = 0.01). A chunk
+// with a non-finite position, shape, weight or column value, or a shape whose
 // covariance is not positive definite, is never left out.
 //
 // Work: a workgroup of four waves takes 64 targets and every kslices-th chunk of
@@ -24,10 +27,12 @@
 // not vary between runs. Slices keep the tiles whose shapes reach far (next to
 // the lens centre one sees every chunk) from being the launch's tail.
 //
-// Bound by FP32 issue (8 to 19 VALU instructions and one exp a pair). At 40,000
-// traced points, shapes on one side: l = 0.01 evaluates 4% of the pairs, 45 us, and
-// l = 0.04 10%, 88 us, with three sums; the all-pairs kernels take 636 us for one
-// sum and 678 us for three.
+// Bound by FP32 issue (8 to 19 VALU instructions and one or two transcendentals a
+// pair). At 40,000 traced points and l = 0.04 one sum with shapes on one side takes
+// 70 us (84 with the eigenvalue's test alone, 636 in the all-pairs kernel); three sums
+// of two such layers (l = 0.01 and 0.04) and one of a 40 x 40 grid's 103 us together
+// (123). Shapes on both sides, three columns, 16,384 points, l = 0.04: 120 us (178 with
+// that test, four columns held and the exponent's factor outside the shapes).
 #include <algorithm>
 #include <cmath>
 
@@ -39,7 +44,7 @@
 namespace gpl {
 
 constexpr int kTWaves = 4;                     // waves per workgroup
-constexpr int kTBatch = 4;                     // box tests of a lane in flight
+constexpr int kTBatch = 4;                     // box tests of a lane in a round
 constexpr int kTList = kTWaves * kTBatch * 64; // chunks tested per round
 constexpr float kZeroArg = 127.f;              // exp2(-kZeroArg) is exactly zero, with margin for rounding
 
@@ -63,53 +68,148 @@ __device__ __forceinline__ float shape_reach(float zxx, float zxy, float zyy, fl
   return finite_or_inf(fmaxf(0.f, (0.5f * (zxx + zyy) + sqrtf(h * h + zxy * zxy)) * 1.00001f));
 }
 
+// The same along the axes and the diagonals: upper bounds of e^T Z e for e = x, y,
+// (x + y)/sqrt 2 and (x - y)/sqrt 2, with lam the largest eigenvalue's.
+struct Reach {
+  float4 dir;
+  float lam;
+};
+__device__ __forceinline__ Reach all_reach(float v) { return Reach{make_float4(v, v, v, v), v}; }
+__device__ __forceinline__ Reach shape_reaches(float zxx, float zxy, float zyy, float base_min) {
+  const float lam = shape_reach(zxx, zxy, zyy, base_min);
+  if (!(lam < INFINITY)) return all_reach(INFINITY);
+  const float e = 1e-5f * (fabsf(zxx) + fabsf(zyy) + fabsf(zxy)), h = 0.5f * (zxx + zyy);
+  return Reach{make_float4(fmaxf(0.f, zxx) + e, fmaxf(0.f, zyy) + e, fmaxf(0.f, h + zxy) + e, fmaxf(0.f, h - zxy) + e),
+               lam};
+}
+template <int W>  // over each W lanes
+__device__ __forceinline__ Reach join_reach(Reach r) {
+  for (int off = W / 2; off > 0; off >>= 1) {
+    r.dir.x = fmaxf(r.dir.x, __shfl_xor(r.dir.x, off, W));
+    r.dir.y = fmaxf(r.dir.y, __shfl_xor(r.dir.y, off, W));
+    r.dir.z = fmaxf(r.dir.z, __shfl_xor(r.dir.z, off, W));
+    r.dir.w = fmaxf(r.dir.w, __shfl_xor(r.dir.w, off, W));
+    r.lam = fmaxf(r.lam, __shfl_xor(r.lam, off, W));
+  }
+  return r;
+}
+
+// Box along the diagonals, (x + y)/sqrt 2 and (x - y)/sqrt 2, of the live points of
+// each W lanes, widened by the rounding of these sums; infinite when one is not finite.
+template <int W>
+__device__ __forceinline__ float4 diagonal_box(float x, float y, bool live) {
+  constexpr float kHalfRoot = 0.70710678f, kRound = 4e-7f;
+  const float u = (x + y) * kHalfRoot, v = (x - y) * kHalfRoot, eu = kRound * fabsf(u), ev = kRound * fabsf(v);
+  float4 q = make_float4(u - eu, u + eu, v - ev, v + ev);
+  if (!(isfinite(u) && isfinite(v))) q = make_float4(-INFINITY, INFINITY, -INFINITY, INFINITY);
+  if (!live) q = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
+  for (int off = W / 2; off > 0; off >>= 1) {
+    q.x = fminf(q.x, __shfl_xor(q.x, off, W));
+    q.y = fmaxf(q.y, __shfl_xor(q.y, off, W));
+    q.z = fminf(q.z, __shfl_xor(q.z, off, W));
+    q.w = fmaxf(q.w, __shfl_xor(q.w, off, W));
+  }
+  return q;
+}
+
+// Are all pairs of two boxes exact zeros? a, b: the boxes, da, db: along the
+// diagonals; r: base plus the reaches of both (kAxes 0: r.lam alone is looked at).
+template <bool kAxes>
+__device__ __forceinline__ bool boxes_zero(const float4& a, const float4& da, const float4& b, const float4& db,
+                                           const Reach& r) {
+  const float gx = fmaxf(0.f, fmaxf(b.x - a.y, a.x - b.y)), gy = fmaxf(0.f, fmaxf(b.z - a.w, a.z - b.w));
+  const float x2 = -kFormScale * (gx * gx), y2 = -kFormScale * (gy * gy);
+  bool zero = x2 + y2 >= kZeroArg * r.lam;
+  if (kAxes) {
+    const float gu = fmaxf(0.f, fmaxf(db.x - da.y, da.x - db.y)), gv = fmaxf(0.f, fmaxf(db.z - da.w, da.z - db.w));
+    zero = zero || x2 >= kZeroArg * r.dir.x || y2 >= kZeroArg * r.dir.y ||
+           -kFormScale * (gu * gu) >= kZeroArg * r.dir.z || -kFormScale * (gv * gv) >= kZeroArg * r.dir.w;
+  }
+  return zero;
+}
+__device__ __forceinline__ Reach add_reach(float base, const float4& d0, float l0, const float4& d1, float l1) {
+  return Reach{make_float4(base + d0.x + d1.x, base + d0.y + d1.y, base + d0.z + d1.z, base + d0.w + d1.w),
+               base + l0 + l1};
+}
+
+// In the both-sided form shapes and base are held times kBothScale, which makes
+// d^T C^{-1} d the exponent; the determinant's root is smaller by it.
+constexpr float kBothScale = -1.f / kFormScale;
+
 // Source side in sorted order: columns ws_j V_j (times |C_j|^{-1/2} when the
-// shapes are the sources' alone), the forms or shapes, and per chunk the reach
-// of its shapes. Thread j handles sorted source j < npad; the padding has zero
-// columns.
+// shapes are the sources' alone), the forms or shapes, and per chunk its diagonal box
+// and the reach of its shapes. Thread j handles sorted source j < npad; the padding
+// has zero columns.
 template <int MODE>
-__device__ __forceinline__ void gauss_prep_body(const GSorted& S, const float* __restrict__ z,
-                                                const float* __restrict__ w, const float* __restrict__ V, int ldv,
-                                                int nc, float base, float* __restrict__ wv, float* __restrict__ form,
-                                                float* __restrict__ reach) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void gauss_prep_source(int j, const GSorted& S, const float* __restrict__ z,
+                                                  const float* __restrict__ w, const float* __restrict__ V, int ldv,
+                                                  int nc, float base, const GTileBufs& b) {
   const int npad = S.nch * kChunk;
   if (j >= npad) return;  // whole waves: npad is a multiple of 64
   const bool live = j < S.n;
   const int jj = live ? S.perm[j] : 0;
-  float scale = live ? (w ? w[jj] : 1.f) : 0.f, lam = 0.f;
+  float scale = live ? (w ? w[jj] : 1.f) : 0.f;
+  Reach r = all_reach(0.f);
   if (MODE == kShapesSource || MODE == kShapesBoth) {
     const float zxx = live && z ? z[jj] : 0.f, zxy = live && z ? z[S.n + jj] : 0.f,
                 zyy = live && z ? z[2 * (size_t)S.n + jj] : 0.f;
     if (MODE == kShapesSource) {
       const Form f = gauss_form(zxx + base, zxy, zyy + base);
-      form[j] = f.xx;
-      form[npad + j] = f.xy;
-      form[2 * npad + j] = f.yy;
+      b.form[j] = f.xx;
+      b.form[npad + j] = f.xy;
+      b.form[2 * npad + j] = f.yy;
       scale *= f.rdet;
-      lam = shape_reach(zxx, zxy, zyy, base);
+      r = shape_reaches(zxx, zxy, zyy, base);
     } else {
-      form[j] = zxx;
-      form[npad + j] = zxy;
-      form[2 * npad + j] = zyy;
-      lam = shape_reach(zxx, zxy, zyy, 0.5f * base);
+      b.form[j] = kBothScale * zxx;
+      b.form[npad + j] = kBothScale * zxy;
+      b.form[2 * npad + j] = kBothScale * zyy;
+      r = shape_reaches(zxx, zxy, zyy, 0.5f * base);
     }
   }
   for (int c = 0; c < nc; ++c) {
     const float v = live ? scale * V[(size_t)c * ldv + jj] : 0.f;
-    wv[(size_t)c * npad + j] = v;
-    if (!isfinite(v)) lam = INFINITY;
+    b.wv[(size_t)c * npad + j] = v;
+    if (!isfinite(v)) r = all_reach(INFINITY);
   }
-  for (int off = 16; off > 0; off >>= 1) lam = fmaxf(lam, __shfl_xor(lam, off, 32));
-  if ((j & (kChunk - 1)) == 0) reach[j / kChunk] = lam;
+  r = join_reach<kChunk>(r);
+  const float4 q = diagonal_box<kChunk>(S.x[j], S.y[j], live);
+  if ((j & (kChunk - 1)) == 0) {
+    b.reach[j / kChunk] = r.lam;
+    b.cdir[j / kChunk] = r.dir;
+    b.cdiag[j / kChunk] = q;
+  }
 }
 
+// Target side: per 16-target subtile its diagonal box and the reach of its shapes.
 template <int MODE>
-__global__ __launch_bounds__(256) void gauss_prep_kernel(GSorted S, const float* __restrict__ z,
-                                                         const float* __restrict__ w, const float* __restrict__ V,
-                                                         int ldv, int nc, float base, float* __restrict__ wv,
-                                                         float* __restrict__ form, float* __restrict__ reach) {
-  gauss_prep_body<MODE>(S, z, w, V, ldv, nc, base, wv, form, reach);
+__device__ __forceinline__ void gauss_prep_target(int i, const GSorted& T, const float* __restrict__ z, float base,
+                                                  const GTileBufs& b) {
+  if (i >= T.nch * kChunk) return;
+  const bool live = i < T.n;
+  Reach r = all_reach(0.f);
+  if ((MODE == kShapesTarget || MODE == kShapesBoth) && live) {
+    const int ii = T.perm[i];
+    r = shape_reaches(z[ii], z[T.n + ii], z[2 * (size_t)T.n + ii], MODE == kShapesTarget ? base : 0.5f * base);
+  }
+  r = join_reach<kSubTile>(r);
+  const float4 q = diagonal_box<kSubTile>(T.x[i], T.y[i], live);
+  if ((i & (kSubTile - 1)) == 0) {
+    b.slam[i / kSubTile] = r.lam;
+    b.sdir[i / kSubTile] = r.dir;
+    b.sdiag[i / kSubTile] = q;
+  }
+}
+
+// Both, the second half of the launch (blockIdx.y 1) the targets.
+template <int MODE>
+__global__ __launch_bounds__(256) void gauss_prep_kernel(GSorted T, const float* __restrict__ tz, GSorted S,
+                                                         const float* __restrict__ z, const float* __restrict__ w,
+                                                         const float* __restrict__ V, int ldv, int nc, float base,
+                                                         GTileBufs b) {
+  const int j = blockIdx.x * 256 + threadIdx.x;
+  if (blockIdx.y == 0) gauss_prep_source<MODE>(j, S, z, w, V, ldv, nc, base, b);
+  else gauss_prep_target<MODE>(j, T, tz, base, b);
 }
 
 // Sums held per target: NC columns, or (MOM) the sum and its first moments in
@@ -119,10 +219,11 @@ constexpr int kSums = MOM ? 3 : NC;
 
 template <int MODE, bool MOM, int NC>
 __device__ __forceinline__ void gauss_tiles_body(int tile, int slice, int nslices, const GSorted& T,
-                                                 const float* __restrict__ tz, const GSorted& S,
-                                                 const float* __restrict__ wv, const float* __restrict__ form,
-                                                 const float* __restrict__ reach, float base,
-                                                 float* __restrict__ part) {
+                                                 const float* __restrict__ tz, const GSorted& S, float base,
+                                                 const GTileBufs& b) {
+  constexpr bool kAxes = MODE != kShapesNone;
+  const float *__restrict__ wv = b.wv, *__restrict__ form = b.form;
+  float* __restrict__ part = b.part;
   constexpr int K = kSums<MOM, NC>;
   __shared__ uint32_t list[kTList];
   __shared__ int cnt_s[kTWaves * kTBatch];
@@ -130,26 +231,20 @@ __device__ __forceinline__ void gauss_tiles_body(int tile, int slice, int nslice
   const int tid = threadIdx.x, lane = tid & 63, wvi = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ri = lane & 15, g = lane >> 4;
   const int npt = T.nch * kChunk, nps = S.nch * kChunk;
-  // this lane's target of each subtile, and the subtiles' boxes and reaches
+  // this lane's target of each subtile
   float xi[kSubsPerTile], yi[kSubsPerTile];
   Form F[kSubsPerTile];  // the target's form (shapes of the targets alone) or its shape (both sides)
-  float4 sb[kSubsPerTile];
-  float lam[kSubsPerTile];
 #pragma unroll
   for (int t = 0; t < kSubsPerTile; ++t) {
     const int i = tile * kRowTile + t * kSubTile + ri;
     xi[t] = T.x[i];
     yi[t] = T.y[i];
-    sb[t] = T.sbox[tile * kSubsPerTile + t];
-    lam[t] = base;
     F[t] = Form{0.f, 0.f, 0.f, 1.f};
     if (MODE == kShapesTarget || MODE == kShapesBoth) {
       const int ii = T.perm[min(i, T.n - 1)];
       const float zxx = tz[ii], zxy = tz[T.n + ii], zyy = tz[2 * (size_t)T.n + ii];
-      float l = shape_reach(zxx, zxy, zyy, MODE == kShapesTarget ? base : 0.5f * base);
-      for (int off = 8; off > 0; off >>= 1) l = fmaxf(l, __shfl_xor(l, off, 16));
-      lam[t] += l;
-      F[t] = MODE == kShapesTarget ? gauss_form(zxx + base, zxy, zyy + base) : Form{zxx + base, zxy, zyy + base, 1.f};
+      F[t] = MODE == kShapesTarget ? gauss_form(zxx + base, zxy, zyy + base)
+                                   : Form{kBothScale * (zxx + base), kBothScale * zxy, kBothScale * (zyy + base), 1.f};
     }
   }
   const float iso = kFormScale / base;
@@ -163,43 +258,38 @@ __device__ __forceinline__ void gauss_tiles_body(int tile, int slice, int nslice
   for (int k0 = 0; k0 < mine; k0 += kTList) {
     // the live chunks of this round, in order
     uint32_t e[kTBatch];
-    float4 q[kTBatch];
-    float ls[kTBatch];
-#pragma unroll
-    for (int u = 0; u < kTBatch; ++u) {
-      const int k = k0 + (wvi * kTBatch + u) * 64 + lane;
-      const int c = min(slice + k * nslices, S.nch - 1);
-      e[u] = (uint32_t)c;
-      q[u] = S.cbox[c];
-      ls[u] = reach[c];
-    }
     unsigned long long bal[kTBatch];
 #pragma unroll
     for (int u = 0; u < kTBatch; ++u) {
-      const int k = k0 + (wvi * kTBatch + u) * 64 + lane;
+      const int kw = k0 + (u * kTWaves + wvi) * 64, k = kw + lane;  // the wave's first and the lane's
       uint32_t mask = 0u;
+      e[u] = 0u;
+      if (kw < mine) {  // few chunks a slice: one batch
+        const int c = min(slice + k * nslices, S.nch - 1);
+        const float4 q = S.cbox[c], qd = kAxes ? b.cdiag[c] : q, qr = kAxes ? b.cdir[c] : q;
+        const float ls = b.reach[c];
 #pragma unroll
-      for (int t = 0; t < kSubsPerTile; ++t) {
-        const float gx = fmaxf(0.f, fmaxf(q[u].x - sb[t].y, sb[t].x - q[u].y));
-        const float gy = fmaxf(0.f, fmaxf(q[u].z - sb[t].w, sb[t].z - q[u].w));
-        const bool zero = -kFormScale * fmaf(gx, gx, gy * gy) >= kZeroArg * (lam[t] + ls[u]);
-        mask |= (zero ? 0u : 1u) << t;
+        for (int t = 0; t < kSubsPerTile; ++t) {
+          const int st = tile * kSubsPerTile + t;  // uniform: the subtile's records come by scalar loads
+          const float4 sb = T.sbox[st], sd = kAxes ? b.sdiag[st] : sb, sr = kAxes ? b.sdir[st] : sb;
+          const bool zero = boxes_zero<kAxes>(sb, sd, q, qd, add_reach(base, sr, b.slam[st], qr, ls));
+          mask |= (zero ? 0u : 1u) << t;
+        }
+        if (k >= mine) mask = 0u;
+        e[u] = (uint32_t)c | (mask << kEntryShift);
       }
-      if (k >= mine) mask = 0u;
-      e[u] |= mask << kEntryShift;
       bal[u] = __ballot(mask != 0u);
-      if (lane == 0) cnt_s[wvi * kTBatch + u] = __popcll(bal[u]);
+      if (lane == 0) cnt_s[u * kTWaves + wvi] = __popcll(bal[u]);
     }
     __syncthreads();
     int total = 0, before[kTBatch];
 #pragma unroll
-    for (int b = 0; b < kTWaves * kTBatch; ++b) {
-      const int u = b - wvi * kTBatch;
+    for (int u = 0; u < kTBatch; ++u)
 #pragma unroll
-      for (int uu = 0; uu < kTBatch; ++uu)
-        if (u == uu) before[uu] = total;
-      total += cnt_s[b];
-    }
+      for (int w = 0; w < kTWaves; ++w) {
+        if (w == wvi) before[u] = total;
+        total += cnt_s[u * kTWaves + w];
+      }
 #pragma unroll
     for (int u = 0; u < kTBatch; ++u)
       if (e[u] >> kEntryShift) list[before[u] + __popcll(bal[u] & ((1ull << lane) - 1ull))] = e[u];
@@ -232,10 +322,9 @@ __device__ __forceinline__ void gauss_tiles_body(int tile, int slice, int nslice
             val = exp2_fast(iso * fmaf(dx, dx, dy * dy));
           } else if (MODE == kShapesBoth) {
             const float cxx = F[t].xx + fxx[v], cxy = F[t].xy + fxy[v], cyy = F[t].yy + fyy[v];
-            const float det = fmaf(cxx, cyy, -cxy * cxy);
-            const float qd = fmaf(cyy * dx, dx, fmaf(-2.f * cxy * dx, dy, cxx * dy * dy));
-            const float rd = rsqrtf(det);
-            val = rd * exp2_fast(kFormScale * (qd * (rd * rd)));
+            const float rd = rsqrtf(fmaf(cxx, cyy, -cxy * cxy));
+            const float vx = fmaf(-cxy, dy, cyy * dx), vy = fmaf(-cxy, dx, cxx * dy);
+            val = rd * exp2_fast(-(fmaf(dx, vx, dy * vy) * (rd * rd)));
           } else {
             const float a = MODE == kShapesTarget ? F[t].xx : fxx[v], b = MODE == kShapesTarget ? F[t].xy : fxy[v],
                         d = MODE == kShapesTarget ? F[t].yy : fyy[v];
@@ -279,11 +368,8 @@ __device__ __forceinline__ void gauss_tiles_body(int tile, int slice, int nslice
 
 template <int MODE, bool MOM, int NC>
 __global__ __launch_bounds__(64 * kTWaves) void gauss_tiles_kernel(GSorted T, const float* __restrict__ tz, GSorted S,
-                                                                   const float* __restrict__ wv,
-                                                                   const float* __restrict__ form,
-                                                                   const float* __restrict__ reach, float base,
-                                                                   float* __restrict__ part) {
-  gauss_tiles_body<MODE, MOM, NC>(blockIdx.x, blockIdx.y, gridDim.y, T, tz, S, wv, form, reach, base, part);
+                                                                   float base, GTileBufs b) {
+  gauss_tiles_body<MODE, MOM, NC>(blockIdx.x, blockIdx.y, gridDim.y, T, tz, S, base, b);
 }
 
 // Y[c][i] = norm wt_i |C_i|^{-1/2} sum + beta Y[c][i] (the determinant when the
@@ -300,6 +386,7 @@ __global__ __launch_bounds__(256) void gauss_finish_kernel(GSorted T, const floa
   if (MODE == kShapesTarget)
     f *= gauss_form(tz[ii] + base, tz[T.n + ii], tz[2 * (size_t)T.n + ii] + base).rdet;
   if (MODE == kShapesNone) f *= rsqrtf(base * base);
+  if (MODE == kShapesBoth) f *= kBothScale;
   const float s = f * fold_slices(part, nslices, K, T.nch * kChunk, c, i);
   float* y = Y + (size_t)c * ldy + ii;
   *y = beta != 0.f ? s + beta * *y : s;
@@ -310,8 +397,8 @@ static int tile_slices(const GSorted& T, const GSorted& S) {
   return std::max(1, std::min({32, 4096 / cdiv(T.n, kRowTile), S.nch}));
 }
 
-// Columns a kernel holds for nc columns: the next of 1, 2, 4 and 8.
-static int held_columns(int nc) { return nc > 4 ? 8 : nc > 2 ? 4 : nc; }
+// Columns a kernel holds for nc columns: nc up to four, and eight.
+static int held_columns(int nc) { return nc > 4 ? 8 : nc; }
 
 template <class C>
 static void carve_tiles(C& cv, const GSorted& T, const GSorted& S, int cols, GTileBufs& b) {
@@ -320,6 +407,12 @@ static void carve_tiles(C& cv, const GSorted& T, const GSorted& S, int cols, GTi
   b.wv = cv.template take<float>(held * nps);
   b.form = cv.template take<float>(3 * nps);
   b.reach = cv.template take<float>(S.nch);
+  b.cdiag = cv.template take<float4>(S.nch);
+  b.cdir = cv.template take<float4>(S.nch);
+  const size_t subs = (size_t)T.nch * kChunk / kSubTile;
+  b.sdiag = cv.template take<float4>(subs);
+  b.sdir = cv.template take<float4>(subs);
+  b.slam = cv.template take<float>(subs);
   b.part = cv.template take<float>((size_t)tile_slices(T, S) * std::max(held, 3) * npt);
 }
 
@@ -346,20 +439,11 @@ int gauss_tiles_carve(int nt, int ns, int cols, void* ws, size_t ws_bytes, GTile
   return cv.ok() ? GPL_OK : check_ws(nullptr, 0, 1);
 }
 
-template <int MODE>
-static int prep_launch(const GSorted& S, const float* z, const float* w, const float* V, int ldv, int nc, float base,
-                       const GTileBufs& b, hipStream_t stream) {
-  hipLaunchKernelGGL(gauss_prep_kernel<MODE>, dim3(cdiv(S.nch * kChunk, 256)), dim3(256), 0, stream, S, z, w, V, ldv,
-                     nc, base, b.wv, b.form, b.reach);
-  GPL_LAUNCH_CHECK();
-  return GPL_OK;
-}
-
 template <int MODE, bool MOM, int NC>
 static int tiles_launch(const GSorted& T, const float* tz, const GSorted& S, float base, const GTileBufs& b,
                         int nslices, hipStream_t stream) {
   hipLaunchKernelGGL((gauss_tiles_kernel<MODE, MOM, NC>), dim3(cdiv(T.n, kRowTile), nslices), dim3(64 * kTWaves), 0,
-                     stream, T, tz, S, b.wv, b.form, b.reach, base, b.part);
+                     stream, T, tz, S, base, b);
   GPL_LAUNCH_CHECK();
   return GPL_OK;
 }
@@ -372,10 +456,13 @@ static int product_cols(const GSorted& T, const float* tz, const float* tw, cons
   for (int c0 = 0; c0 < nrhs;) {
     const int nc = std::min(8, nrhs - c0);
     const int held = held_columns(nc);  // those past nc hold anything and are not stored
-    GPL_TRY(prep_launch<MODE>(S, sz, sw, V + (size_t)c0 * ldv, ldv, nc, base, b, stream));
+    hipLaunchKernelGGL(gauss_prep_kernel<MODE>, dim3(cdiv(std::max(S.nch, T.nch) * kChunk, 256), 2), dim3(256), 0,
+                       stream, T, tz, S, sz, sw, V + (size_t)c0 * ldv, ldv, nc, base, b);
+    GPL_LAUNCH_CHECK();
     switch (held) {
       case 1: GPL_TRY((tiles_launch<MODE, false, 1>(T, tz, S, base, b, ns, stream))); break;
       case 2: GPL_TRY((tiles_launch<MODE, false, 2>(T, tz, S, base, b, ns, stream))); break;
+      case 3: GPL_TRY((tiles_launch<MODE, false, 3>(T, tz, S, base, b, ns, stream))); break;
       case 4: GPL_TRY((tiles_launch<MODE, false, 4>(T, tz, S, base, b, ns, stream))); break;
       default: GPL_TRY((tiles_launch<MODE, false, 8>(T, tz, S, base, b, ns, stream))); break;
     }
@@ -416,24 +503,25 @@ struct SumsArgs {
   } l[kGaussLayers];
 };
 
+// blockIdx.y: layer, then the sources (0) or the targets.
 __global__ __launch_bounds__(256) void gauss_layers_prep_kernel(SumsArgs A) {
-  const auto& L = A.l[blockIdx.y];
-  if (L.shapes)
-    gauss_prep_body<kShapesSource>(A.S, A.sz, nullptr, A.V, 0, 1, L.base, L.b.wv, L.b.form, L.b.reach);
-  else
-    gauss_prep_body<kShapesNone>(A.S, nullptr, nullptr, A.V, 0, 1, L.base, L.b.wv, L.b.form, L.b.reach);
+  const auto& L = A.l[blockIdx.y >> 1];
+  const int j = blockIdx.x * 256 + threadIdx.x;
+  if (blockIdx.y & 1) {
+    gauss_prep_target<kShapesNone>(j, L.T, nullptr, L.base, L.b);
+  } else if (L.shapes) {
+    gauss_prep_source<kShapesSource>(j, A.S, A.sz, nullptr, A.V, 0, 1, L.base, L.b);
+  } else {
+    gauss_prep_source<kShapesNone>(j, A.S, nullptr, nullptr, A.V, 0, 1, L.base, L.b);
+  }
 }
 
 __global__ __launch_bounds__(64 * kTWaves) void gauss_layers_kernel(SumsArgs A) {
   const auto& L = A.l[blockIdx.y];
   const int slice = blockIdx.x / L.tiles, tile = blockIdx.x - slice * L.tiles;
   if (slice >= L.slices) return;
-  if (L.shapes)
-    gauss_tiles_body<kShapesSource, true, 1>(tile, slice, L.slices, L.T, nullptr, A.S, L.b.wv, L.b.form, L.b.reach,
-                                             L.base, L.b.part);
-  else
-    gauss_tiles_body<kShapesNone, false, 1>(tile, slice, L.slices, L.T, nullptr, A.S, L.b.wv, L.b.form, L.b.reach,
-                                            L.base, L.b.part);
+  if (L.shapes) gauss_tiles_body<kShapesSource, true, 1>(tile, slice, L.slices, L.T, nullptr, A.S, L.base, L.b);
+  else gauss_tiles_body<kShapesNone, false, 1>(tile, slice, L.slices, L.T, nullptr, A.S, L.base, L.b);
 }
 
 template <class C>
@@ -466,15 +554,16 @@ int gauss_layers_sums(GaussLayerSums* layers, int nl, const GSorted& S, const fl
   A.V = V;
   A.sz = sz;
   A.nl = nl;
-  int blocks = 0;
+  int blocks = 0, npad = S.nch * kChunk;
   for (int q = 0; q < nl; ++q) {
     GaussLayerSums& L = layers[turn[q]];
     L.part = b[turn[q]].part;
     L.nslices = tile_slices(L.T, S);
     A.l[q] = {L.T, cdiv(L.T.n, kRowTile), L.nslices, L.shapes, (float)L.base, b[turn[q]]};
     blocks = std::max(blocks, A.l[q].tiles * L.nslices);
+    npad = std::max(npad, L.T.nch * kChunk);
   }
-  hipLaunchKernelGGL(gauss_layers_prep_kernel, dim3(cdiv(S.nch * kChunk, 256), nl), dim3(256), 0, stream, A);
+  hipLaunchKernelGGL(gauss_layers_prep_kernel, dim3(cdiv(npad, 256), 2 * nl), dim3(256), 0, stream, A);
   GPL_LAUNCH_CHECK();
   hipLaunchKernelGGL(gauss_layers_kernel, dim3(blocks, nl), dim3(64 * kTWaves), 0, stream, A);
   GPL_LAUNCH_CHECK();
@@ -500,9 +589,10 @@ int gauss_layers_sums(GaussLayerSums* layers, int nl, const GSorted& S, const fl
 // 430 us at l = 0.04 of a launch whose work is worth 150. For the same reason each
 // wave is a workgroup of its own, and a second kernel adds the shares: waves that
 // wait for the longest share of their targets keep others from being started.
-// Bound by issue, about 27 VALU instructions and one exp for 64 pairs: 71 us at
-// l = 0.01 and 200 us at 0.04 (40,000 points); the all-pairs product took 580 us and
-// its adjoint towards the targets, formed here with it, another 767 us.
+// Bound by issue, about 27 VALU instructions and one exp for 64 pairs: 204 us for two
+// layers of 40,000 points (l = 0.01 and 0.04) and one of a 40 x 40 grid together, 231 us
+// with the eigenvalue's test alone; the all-pairs product took 580 us a layer and its
+// adjoint towards the targets, formed here with it, another 767 us.
 //
 // Targets whose shapes reach far (next to the lens centre) would have their
 // neighbours evaluate every source too. Those with a shape beyond kFarReach base
@@ -520,7 +610,9 @@ static_assert(64 % kOChunk == 0 && kOChunk % 4 == 0 && kOTargets == kSubTile, "w
 static __host__ __device__ int ordered_share(int n) { return cdiv(cdiv(n, 64), kOWaves) * (64 / kOChunk); }
 
 struct OrderedBufs {
-  float4 *src, *box;
+  float4 *src, *box, *cdiag;  // sources, and the boxes of their chunks
+  float4 *sdiag, *sdir;       // per 16 targets: diagonal box and reach of their shapes
+  float* slam;
   int* far;
   float* part;
 };
@@ -547,29 +639,46 @@ __global__ __launch_bounds__(256) void ordered_prep_kernel(OrderedArgs A) {
   const int n = L.ns;
   const float *__restrict__ x = L.x, *__restrict__ y = L.y, *__restrict__ w = L.w, *__restrict__ V = L.V;
   const float* __restrict__ tz = A.tz;
-  float4 *__restrict__ src = L.b.src, *__restrict__ box = L.b.box;
   const int j = blockIdx.x * 256 + threadIdx.x, npad = round_up(n, kOChunk);
-  if (L.shapes && j < A.T.n) {
-    const int jj = A.T.perm[j];
-    if (shape_reach(tz[jj], tz[A.T.n + jj], tz[2 * (size_t)A.T.n + jj], L.base) > kFarReach * L.base)
-      L.b.far[atomicAdd(L.far_count, 1)] = j;
+  if (L.shapes && j < A.T.nch * kChunk) {
+    Reach r = all_reach(0.f);
+    bool live = j < A.T.n;
+    if (live) {
+      const int jj = A.T.perm[j];
+      r = shape_reaches(tz[jj], tz[A.T.n + jj], tz[2 * (size_t)A.T.n + jj], L.base);
+      if (r.lam > kFarReach * L.base) {
+        L.b.far[atomicAdd(L.far_count, 1)] = j;
+        r = all_reach(0.f);
+        live = false;
+      }
+    }
+    r = join_reach<kSubTile>(r);
+    const float4 q = diagonal_box<kSubTile>(A.T.x[j], A.T.y[j], live);
+    if ((j & (kSubTile - 1)) == 0) {
+      L.b.slam[j / kSubTile] = r.lam;
+      L.b.sdir[j / kSubTile] = r.dir;
+      L.b.sdiag[j / kSubTile] = q;
+    }
   }
-  float4 q = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
+  float4 q = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY), s = make_float4(0.f, 0.f, 0.f, 0.f);
+  bool ok = false;
   if (j < n) {
-    const float4 s = make_float4(x[j], y[j], w[j], V[j]);
-    src[j] = s;
-    const bool ok = isfinite(s.x) && isfinite(s.y) && isfinite(s.z) && isfinite(s.w);
+    s = make_float4(x[j], y[j], w[j], V[j]);
+    ok = isfinite(s.x) && isfinite(s.y) && isfinite(s.z) && isfinite(s.w);
     q = ok ? make_float4(s.x, s.x, s.y, s.y) : make_float4(-INFINITY, INFINITY, -INFINITY, INFINITY);
-  } else if (j < npad) {
-    src[j] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
+  if (j < npad) L.b.src[j] = s;
   for (int off = kOChunk / 2; off > 0; off >>= 1) {
     q.x = fminf(q.x, __shfl_xor(q.x, off, kOChunk));
     q.y = fmaxf(q.y, __shfl_xor(q.y, off, kOChunk));
     q.z = fminf(q.z, __shfl_xor(q.z, off, kOChunk));
     q.w = fmaxf(q.w, __shfl_xor(q.w, off, kOChunk));
   }
-  if (j < npad && (j & (kOChunk - 1)) == 0) box[j / kOChunk] = q;
+  const float4 d = diagonal_box<kOChunk>(ok ? s.x : INFINITY, s.y, j < n);
+  if (j < npad && (j & (kOChunk - 1)) == 0) {
+    L.b.box[j / kOChunk] = q;
+    L.b.cdiag[j / kOChunk] = d;
+  }
 }
 
 // One target of the ordered product: its form, and the terms of one source.
@@ -633,9 +742,11 @@ __device__ __forceinline__ float quad_next(float v) {
 // shapes): wave q takes eighth q % 8 of the sources of listed target q / 8.
 template <bool kShapes>
 __device__ __forceinline__ void gauss_ordered_body(const GSorted& T, int tiles, const float* __restrict__ tz, int ns,
-                                                   const float4* __restrict__ src, const float4* __restrict__ box,
-                                                   float base, const int* __restrict__ far_count,
-                                                   const int* __restrict__ far, float* __restrict__ part) {
+                                                   const OrderedBufs& b, float base,
+                                                   const int* __restrict__ far_count) {
+  const float4* __restrict__ src = b.src;
+  const int* __restrict__ far = b.far;
+  float* __restrict__ part = b.part;
   using Target = OrderedTarget<kShapes>;
   constexpr int K = Target::K;
   const int lane = threadIdx.x, wv = blockIdx.x / tiles, tile = blockIdx.x % tiles, npt = T.nch * kChunk;
@@ -661,28 +772,25 @@ __device__ __forceinline__ void gauss_ordered_body(const GSorted& T, int tiles, 
   const int i = tile * kOTargets + (lane >> 2);
   bool live = i < T.n;
   const int ii = T.perm[min(i, T.n - 1)];
-  float txx = 0.f, txy = 0.f, tyy = 0.f, lam = 0.f;
+  float txx = 0.f, txy = 0.f, tyy = 0.f;
+  Reach r = all_reach(base);
+  const float4 rb = T.sbox[tile];
+  float4 rd = rb;
   if (kShapes) {
     txx = tz[ii];
     txy = tz[T.n + ii];
     tyy = tz[2 * (size_t)T.n + ii];
-    lam = shape_reach(txx, txy, tyy, base);
-    if (lam > kFarReach * base) {  // listed
-      lam = 0.f;
-      live = false;
-    }
-    for (int off = 32; off > 2; off >>= 1) lam = fmaxf(lam, __shfl_xor(lam, off, 64));
+    if (shape_reach(txx, txy, tyy, base) > kFarReach * base) live = false;  // listed
+    rd = b.sdiag[tile];
+    r = add_reach(base, b.sdir[tile], b.slam[tile], make_float4(0.f, 0.f, 0.f, 0.f), 0.f);
   }
   t.init(T.x[i], T.y[i], txx, txy, tyy, base);
-  const float4 rb = T.sbox[tile];
-  const float limit = kZeroArg * (base + lam);
   const int nch = cdiv(ns, kOChunk), share = ordered_share(ns);
   const int cend = min(nch, (wv + 1) * share);
   for (int c0 = wv * share; c0 < cend; c0 += 64) {
-    const float4 q = box[min(c0 + lane, nch - 1)];
-    const float gx = fmaxf(0.f, fmaxf(q.x - rb.y, rb.x - q.y));
-    const float gy = fmaxf(0.f, fmaxf(q.z - rb.w, rb.z - q.w));
-    const bool zero = -kFormScale * fmaf(gx, gx, gy * gy) >= limit;
+    const int c = min(c0 + lane, nch - 1);
+    const float4 q = b.box[c], qd = kShapes ? b.cdiag[c] : q;
+    const bool zero = boxes_zero<kShapes>(rb, rd, q, qd, r);
     unsigned long long m = __ballot(c0 + lane < cend && !zero);
     while (m != 0ull) {
       const int j0 = (c0 + __ffsll((long long)m) - 1) * kOChunk;
@@ -712,9 +820,9 @@ __device__ __forceinline__ void gauss_ordered_body(const GSorted& T, int tiles, 
 __global__ __launch_bounds__(64) void gauss_ordered_kernel(OrderedArgs A) {
   const auto& L = A.l[A.turn[blockIdx.y]];
   if (L.shapes) {
-    gauss_ordered_body<true>(A.T, A.tiles, A.tz, L.ns, L.b.src, L.b.box, L.base, L.far_count, L.b.far, L.b.part);
+    gauss_ordered_body<true>(A.T, A.tiles, A.tz, L.ns, L.b, L.base, L.far_count);
   } else if ((int)blockIdx.x < A.tiles * kOWaves) {
-    gauss_ordered_body<false>(A.T, A.tiles, nullptr, L.ns, L.b.src, L.b.box, L.base, nullptr, nullptr, L.b.part);
+    gauss_ordered_body<false>(A.T, A.tiles, nullptr, L.ns, L.b, L.base, nullptr);
   }
 }
 
@@ -764,6 +872,11 @@ static void carve_ordered(C& cv, int nt, const int* ns, int nl, OrderedBufs* b) 
   for (int k = 0; k < nl; ++k) {
     b[k].src = cv.template take<float4>(round_up(ns[k], kOChunk));
     b[k].box = cv.template take<float4>(cdiv(ns[k], kOChunk));
+    b[k].cdiag = cv.template take<float4>(cdiv(ns[k], kOChunk));
+    const size_t subs = (size_t)round_up(nt, kRowTile) / kSubTile;
+    b[k].sdiag = cv.template take<float4>(subs);
+    b[k].sdir = cv.template take<float4>(subs);
+    b[k].slam = cv.template take<float>(subs);
     b[k].far = cv.template take<int>(nt);
     b[k].part = cv.template take<float>((size_t)kOWaves * 6 * round_up(nt, kRowTile));
   }
@@ -790,7 +903,7 @@ int gauss_ordered_launch(const GSorted& T, const float* tz, const GaussLayer* la
   for (int k = 0; k < nl; ++k) {
     ns[k] = layers[k].S.n;
     A.turn[k] = k;
-    prep = std::max({prep, round_up(ns[k], kOChunk), layers[k].shapes ? T.n : 0});
+    prep = std::max({prep, round_up(ns[k], kOChunk), layers[k].shapes ? round_up(T.n, kRowTile) : 0});
     shapes = shapes || layers[k].shapes;
   }
   Carver cv(scratch, bytes);

@@ -24,6 +24,9 @@ struct GTileBufs {
   float* wv;     // [columns][32 nch] source columns with their weights, sorted
   float* form;   // [3][32 nch] forms or shapes of the sources, sorted
   float* reach;  // [nch] largest eigenvalue of a chunk's shapes
+  float4 *cdiag, *cdir;  // [nch] its box along the diagonals, reach of its shapes along axes and diagonals
+  float4 *sdiag, *sdir;  // the same per 16-target subtile of the targets,
+  float* slam;           // and the largest eigenvalue
   float* part;   // [slices][sums][32 nch of the targets] partial sums
 };
 
