@@ -885,8 +885,11 @@ __global__ __launch_bounds__(1024) void plan_finish_rhs_kernel(int nrt, int nw, 
   if (blockIdx.x == 0) {
     plan_finish_body(nrt, nw, unit_off, count, wunit, wrows, rslot, wdesc, wrest);
   } else {
-    const int g = threadIdx.x >> 8, per = cdiv(J.b.ldh, 1024), u = blockIdx.x - 1;
-    place_unit(J, (u % per) * (1024 / 256) + g, u / per * kPlaceSlots, threadIdx.x & 255, se[g]);
+    // past what the L2s hold (40 MB at 160,000 points and 64 columns) an XCD takes
+    // neighbouring points: their rows of V share cache lines
+    const int g = threadIdx.x >> 8, per = round_up(cdiv(J.b.ldh, 1024), kXcds), u = blockIdx.x - 1;
+    const int bx = per > 64 ? xcd_block(u % per, per) : u % per;
+    place_unit(J, bx * (1024 / 256) + g, u / per * kPlaceSlots, threadIdx.x & 255, se[g]);
   }
 }
 
@@ -1178,8 +1181,8 @@ int plan_build(TilePlan& p, int n, const float* px, const float* py, const gpl_g
                        p.wround, p.count, p.list, p.roww, p.unit_off, p.wunit, reinterpret_cast<int2*>(p.wrow));
     GPL_LAUNCH_CHECK();
     if (job)
-      hipLaunchKernelGGL(plan_finish_rhs_kernel, dim3(1 + cdiv(job->b.ldh, 1024) * (job->b.ncp / kPlaceSlots)),
-                         dim3(1024), 0, stream, p.nrt, p.nw, p.unit_off, p.count, p.wunit,
+      hipLaunchKernelGGL(plan_finish_rhs_kernel,
+                         dim3(1 + round_up(cdiv(job->b.ldh, 1024), kXcds) * (job->b.ncp / kPlaceSlots)), dim3(1024), 0, stream, p.nrt, p.nw, p.unit_off, p.count, p.wunit,
                          reinterpret_cast<int2*>(p.wrow), p.rslot, p.wdesc, p.wrest, *job);
     else
       hipLaunchKernelGGL(plan_finish_kernel, dim3(1), dim3(1024), 0, stream, p.nrt, p.nw, p.unit_off, p.count, p.wunit,

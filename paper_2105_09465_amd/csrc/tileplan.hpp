@@ -239,6 +239,9 @@ constexpr int kRounds = 3;
 constexpr int kRoundWeight[kRounds] = {16, 9, 4};
 constexpr int kPlanWaves = 4;  // waves per workgroup of a product launch
 constexpr int kXcds = 8;       // workgroup b of a launch runs on XCD b % kXcds
+// Block b of nb (a multiple of kXcds) for workgroup b so that an XCD's blocks are
+// neighbours, for kernels whose neighbouring blocks share cache lines.
+__host__ __device__ inline int xcd_block(int b, int nb) { return (b % kXcds) * (nb / kXcds) + b / kXcds; }
 
 // Order of a launch's waves along the unit sequence. Workgroups are dispatched
 // in order, wround / kPlanWaves per round, round-robin over the XCDs. Within
