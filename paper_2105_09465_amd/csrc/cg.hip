@@ -10,6 +10,8 @@
 //   -> update1 (alpha; X += alpha P; R -= alpha AP; r.r partials)
 //   -> update2 (beta; P = R + beta P; bookkeeping; partial max |P| for the
 //      column scales of the precision form).
+// On a small image two: the product, and the rest by a workgroup per column
+// (cg_small.hip).
 // Per-column state is double-buffered by iteration parity so that every block
 // of a kernel reads the same old values. Kernels return at once when no column
 // is active. Either every iteration up to the cap is enqueued at once (fully
@@ -21,6 +23,7 @@
 #include <cmath>
 #include <mutex>
 
+#include "cg_step.hpp"
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -35,7 +38,7 @@ struct CgBuffers {
   int ntiles, nb_upd;
   ColState* st[2];
   double* bb;
-  int* n_active;  // [2]
+  int* n_active;  // [3]
   unsigned* pmax;  // [nrhs][nb_upd] partial max |P| (float bits)
 };
 
@@ -54,7 +57,7 @@ static void carve_cg(C& c, int npix, int N, int nrhs, int prec, CgBuffers* b, si
   ColState* s0 = c.template take<ColState>(nrhs);
   ColState* s1 = c.template take<ColState>(nrhs);
   double* bb = c.template take<double>(nrhs);
-  int* na = c.template take<int>(2);
+  int* na = c.template take<int>(3);
   unsigned* pm = c.template take<unsigned>((size_t)nb_upd * nrhs);
   if (b) {
     *b = CgBuffers{R, P, AP, T2, ldv, ldf, mws, mvm_bytes, pap, rrp, ntiles, nb_upd, {s0, s1}, bb, na, pm};
@@ -104,8 +107,9 @@ __global__ __launch_bounds__(256) void cg_init_kernel(int npix, const float* __r
 }
 
 __global__ void cg_init_state_kernel(int nrhs, const double* part, int nb, ColState* st0, ColState* st1, double* bb,
-                                     int* n_active, int limit) {
-  // one thread per column; thread 0 of the block also writes the active count
+                                     int* n_active, int limit, bool ring) {
+  // one thread per column; thread 0 of the block also writes the active count (of a
+  // ring of three the others are those of later iterations)
   __shared__ int count;
   if (threadIdx.x == 0) count = 0;
   __syncthreads();
@@ -135,7 +139,8 @@ __global__ void cg_init_state_kernel(int nrhs, const double* part, int nb, ColSt
   __syncthreads();
   if (threadIdx.x == 0) {
     n_active[0] = count;
-    n_active[1] = count;
+    n_active[1] = ring ? 0 : count;
+    if (ring) n_active[2] = 0;
   }
 }
 
@@ -169,13 +174,12 @@ __device__ __forceinline__ void cg_update1_body(int bx, int c, int npix, float* 
   const ColState st = sin[c];
   if (!st.active) return;
   if (threadIdx.x == 0) {
-    const double a = st.rr / pap;
-    const int ok = (pap > 0.0) && isfinite(a);
-    s_alpha = ok ? a : 0.0;
-    s_ok = ok;
+    const ColumnAlpha a = cg_alpha(st.rr, pap);
+    s_alpha = a.alpha;
+    s_ok = a.bad == 0;
     if (bx == 0) {
-      sout[c].alpha = s_alpha;
-      sout[c].bad = ok ? 0 : (isfinite(pap) ? 1 : 2);
+      sout[c].alpha = a.alpha;
+      sout[c].bad = a.bad;
     }
   }
   __syncthreads();
@@ -234,44 +238,13 @@ __device__ __forceinline__ void cg_update2_body(int bx, int c, int npix, const f
   }
   if (threadIdx.x == 0) {
     const ColState half = sout[c];  // alpha and bad written by update1
-    const double beta = rr_new / st.rr;
-    ColState nx;
-    nx.alpha = half.alpha;
-    nx.bad = 0;
-    nx.iters = st.iters;
-    nx.rr = st.rr;
-    nx.status = GPL_CG_CONVERGED;
-    nx.active = 0;
-    int go = 0;
-    if (half.bad) {
-      nx.status = half.bad == 1 ? GPL_CG_BREAKDOWN : GPL_CG_NONFINITE;
-    } else if (!isfinite(rr_new) || !isfinite(beta)) {
-      nx.status = GPL_CG_NONFINITE;
-      nx.iters = st.iters + 1;
-    } else {
-      go = 1;
-      nx.rr = rr_new;
-      nx.iters = st.iters + 1;
-      if (bx == 0 && st.iters < n_lanczos) {
-        double* e = ab + ((size_t)c * n_lanczos + st.iters) * 2;
-        e[0] = half.alpha;
-        e[1] = beta;
-      }
-      if (fixed_iters > 0) {
-        nx.active = nx.iters < fixed_iters;
-      } else if (sqrt(rr_new) <= tol * sqrt(bb[c])) {
-        nx.active = 0;
-      } else if (nx.iters >= max_iter) {
-        nx.status = GPL_CG_MAXITER;
-      } else {
-        nx.active = 1;
-      }
-    }
-    s_beta = beta;
-    s_go = go;
+    const ColumnStep k =
+        cg_step(st, half.alpha, half.bad, rr_new, c, bb, tol, max_iter, fixed_iters, n_lanczos, ab, bx == 0);
+    s_beta = k.beta;
+    s_go = k.go;
     if (bx == 0) {
-      sout[c] = nx;
-      if (nx.active) atomicAdd(n_active_out, 1);
+      sout[c] = k.next;
+      if (k.next.active) atomicAdd(n_active_out, 1);
     }
   }
   __syncthreads();
@@ -410,7 +383,7 @@ int cg_init_launch(int npix, int nrhs, const float* Bm, int ldb, float* X, int l
                      pmax);
   GPL_LAUNCH_CHECK();
   hipLaunchKernelGGL(cg_init_state_kernel, dim3(1), dim3(256), 0, stream, nrhs, part, nb, st0, st1, bb, n_active,
-                     limit);
+                     limit, false);
   GPL_LAUNCH_CHECK();
   return GPL_OK;
 }
@@ -553,12 +526,17 @@ extern "C" int gpl_cg_solve(const gpl_problem* prob, int nrhs, const float* Bm, 
   const float sigma2 = (float)(prob->noise_sigma * prob->noise_sigma);
 
   const int nb = b.nb_upd;
+  // a small image: one workgroup a column for all that lies between two products
+  const bool column = cg_column_fits(n, ss, taps.r);
+  const int ring = column ? 3 : 2;  // places of the active counts
+  const CgColumn col{n, ss, nrhs, b.ntiles, sigma2, mv.amp2, taps, mv.plan, mv.bufs, rhs_out, X, b.R, b.P, ldx, b.ldv,
+                     b.bb, tol, max_iter, fixed_iters, n_lanczos, lanczos_ab};
   const int limit = fixed_iters > 0 ? fixed_iters : max_iter;
   hipLaunchKernelGGL(cg_init_kernel, dim3(nb, nrhs), dim3(256), 0, stream, npix, Bm, ldb, X, ldx, b.R, b.P, b.ldv,
                      b.rr_part, nb, b.pmax);
   GPL_LAUNCH_CHECK();
   hipLaunchKernelGGL(cg_init_state_kernel, dim3(1), dim3(256), 0, stream, nrhs, b.rr_part, nb, b.st[0], b.st[1], b.bb,
-                     b.n_active, limit);
+                     b.n_active, limit, column);
   GPL_LAUNCH_CHECK();
 
   // check_every = 0: every iteration up to the limit is enqueued at once, and
@@ -571,7 +549,14 @@ extern "C" int gpl_cg_solve(const gpl_problem* prob, int nrhs, const float* Bm, 
     for (int it = k * chunk; it < end; ++it) {
       const int p = it & 1;
       CgGate gate;
-      gate.n_active = b.n_active + p;
+      gate.n_active = b.n_active + it % ring;
+      if (column) {
+        if (it == 0) GPL_TRY(psf_adjoint_rhs_launch(n, ss, taps, nrhs, b.P, b.ldv, rhs_out, gate, stream));
+        GPL_TRY(mvm_run_partials(mv, nrhs, gate, stream));
+        GPL_TRY(cg_column_launch(col, b.st[p], b.st[1 - p], b.n_active + it % 3, b.n_active + (it + 1) % 3,
+                                 b.n_active + (it + 2) % 3, stream));
+        continue;
+      }
       // AP = B K B^T P + sigma^2 P with p.Ap partials; B^T P goes straight into
       // the product's RHS buffers
       GPL_TRY(psf_adjoint_rhs_launch(n, ss, taps, nrhs, b.P, b.ldv, rhs_out, gate, stream));
@@ -589,7 +574,7 @@ extern "C" int gpl_cg_solve(const gpl_problem* prob, int nrhs, const float* Bm, 
     }
     last_end = end;
     if (!poll) return GPL_OK;
-    hipLaunchKernelGGL(cg_snapshot_kernel, dim3(1), dim3(64), 0, stream, b.n_active + (end & 1),
+    hipLaunchKernelGGL(cg_snapshot_kernel, dim3(1), dim3(64), 0, stream, b.n_active + end % ring,
                        poll->flags + (k & 1));
     GPL_LAUNCH_CHECK();
     GPL_HIP(hipEventRecord(poll->ev[k & 1], stream));

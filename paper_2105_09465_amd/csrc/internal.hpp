@@ -137,6 +137,9 @@ int mvm_run(const MvmCtx& m, int nrhs, const float* V, int ldv, float* Y, int ld
 int mvm_run_prepared(const MvmCtx& m, int nrhs, float* Y, int ldy, float beta, CgGate gate, hipStream_t stream,
                      bool tail_ok = false);
 
+// Its partial rows alone (not added up, not scaled).
+int mvm_run_partials(const MvmCtx& m, int nrhs, CgGate gate, hipStream_t stream);
+
 // Where the fused PSF adjoint writes B^T P: the product's RHS buffers (fine point
 // (fx, fy) at its sorted position in the plan, the FP16 parts of column c at the
 // slots hi_slot gives), with per-column scales of the precision form taken from

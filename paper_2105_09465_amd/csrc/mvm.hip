@@ -64,6 +64,11 @@ int mvm_run_prepared(const MvmCtx& m, int nrhs, float* Y, int ldy, float beta, C
   return mfma_product(m.plan, m.bufs, m.prec, m.s2, m.amp2, nrhs, Y, ldy, beta, tail_ok, gate, stream);
 }
 
+int mvm_run_partials(const MvmCtx& m, int nrhs, CgGate gate, hipStream_t stream) {
+  GPL_REQUIRE(nrhs <= m.nrhs_max, "product prepared for %d columns, %d given", m.nrhs_max, nrhs);
+  return mfma_partials(m.plan, m.bufs, m.prec, m.s2, nrhs, false, gate, stream);
+}
+
 int mvm_run(const MvmCtx& m, int nrhs, const float* V, int ldv, float* Y, int ldy, float beta, CgGate gate,
             hipStream_t stream) {
   GPL_REQUIRE(nrhs <= m.nrhs_max, "product prepared for %d columns, %d given", m.nrhs_max, nrhs);

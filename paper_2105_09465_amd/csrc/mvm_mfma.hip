@@ -623,8 +623,8 @@ int mfma_prep_rhs(const TilePlan& P, const ProdBufs& b, int prec, int nrhs, cons
   return GPL_OK;
 }
 
-int mfma_product(const TilePlan& P, const ProdBufs& b, int prec, float s2, float amp2, int nrhs, float* Y, int ldy,
-                 float beta, bool tail_ok, CgGate gate, hipStream_t stream) {
+int mfma_partials(const TilePlan& P, const ProdBufs& b, int prec, float s2, int nrhs, bool tail_ok, CgGate gate,
+                  hipStream_t stream) {
   const bool f16 = prec == GPL_PREC_F16X3;
   // A last block of at most four columns of the FP32 form goes to the vector units
   // beside the blocks before it: a block keeps the matrix units busy for as long as the
@@ -663,6 +663,13 @@ int mfma_product(const TilePlan& P, const ProdBufs& b, int prec, float s2, float
     GPL_LAUNCH_CHECK();
     timing_end(t0, stream);
   }
+  return GPL_OK;
+}
+
+int mfma_product(const TilePlan& P, const ProdBufs& b, int prec, float s2, float amp2, int nrhs, float* Y, int ldy,
+                 float beta, bool tail_ok, CgGate gate, hipStream_t stream) {
+  GPL_TRY(mfma_partials(P, b, prec, s2, nrhs, tail_ok, gate, stream));
+  const bool f16 = prec == GPL_PREC_F16X3;
   // four columns a thread when that still leaves sixteen workgroups per compute
   // unit (measured: 64 columns at N = 160k 33.6 against 38.8 us with one column
   // a thread; at N = 40k, where that gives ten, 24.5 against 22.9 us)

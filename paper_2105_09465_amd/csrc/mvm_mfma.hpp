@@ -20,6 +20,9 @@ int mfma_zero_rhs(const ProdBufs& b, int prec, hipStream_t stream);
 // RHS block V (caller order) into the product buffers (sorted order, split or packed).
 int mfma_prep_rhs(const TilePlan& P, const ProdBufs& b, int prec, int nrhs, const float* V, int ldv, CgGate gate,
                   hipStream_t stream);
+// The partial rows of the product alone, in b.part over the plan's slots.
+int mfma_partials(const TilePlan& P, const ProdBufs& b, int prec, float s2, int nrhs, bool tail_ok, CgGate gate,
+                  hipStream_t stream);
 // Y = amp2 K V + beta Y (caller order) from the prepared RHS buffers. tail_ok: the sums
 // of a few columns past whole blocks of 16 may run in another order (FP32 form).
 int mfma_product(const TilePlan& P, const ProdBufs& b, int prec, float s2, float amp2, int nrhs, float* Y, int ldy,
