@@ -97,10 +97,44 @@ inline int check_ws(void* ws, size_t have, size_t need) {
 
 __device__ inline float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// v of the lane whose index differs in bit OFF (32 ... 1), where OFF = 4 asks that lanes
+// differing in bit 3 hold the same value: DPP moves within rows of 16 lanes, permlane
+// swaps across them, no trip through LDS.
+template <int OFF>
+__device__ __forceinline__ unsigned lane_xor(unsigned v) {
+  if constexpr (OFF == 32) {
+    const auto s = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return (threadIdx.x & 32) ? s[0] : s[1];
+  } else if constexpr (OFF == 16) {
+    const auto s = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return (threadIdx.x & 16) ? s[0] : s[1];
+  } else {
+    constexpr int ctrl = OFF == 8 ? 0x128 : OFF == 4 ? 0x124 : OFF == 2 ? 0x4e : 0xb1;  // row_ror:8, :4, quad_perm
+    return (unsigned)__builtin_amdgcn_mov_dpp((int)v, ctrl, 0xf, 0xf, true);
+  }
+}
+template <int OFF, class T>
+__device__ __forceinline__ T add_lane_xor(T v) {
+  static_assert(sizeof(T) == 4 || sizeof(T) == 8, "a register or two");
+  if constexpr (sizeof(T) == 4) {
+    return v + __builtin_bit_cast(T, lane_xor<OFF>(__builtin_bit_cast(unsigned, v)));
+  } else {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned long long o =
+        ((unsigned long long)lane_xor<OFF>((unsigned)(b >> 32)) << 32) | lane_xor<OFF>((unsigned)b);
+    return v + __builtin_bit_cast(T, o);
+  }
+}
+
+// Sum over the wave, the same in every lane (a butterfly from the widest step down).
 template <class T>
-__device__ inline T warp_sum(T v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+__device__ __forceinline__ T warp_sum(T v) {
+  v = add_lane_xor<32>(v);
+  v = add_lane_xor<16>(v);
+  v = add_lane_xor<8>(v);
+  v = add_lane_xor<4>(v);
+  v = add_lane_xor<2>(v);
+  return add_lane_xor<1>(v);
 }
 
 // Sum of p[0, cnt) over the 64 lanes of one wave in a fixed order (lane-strided
