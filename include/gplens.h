@@ -196,7 +196,7 @@ int gpl_gauss_product(const gpl_gauss* g, int nt, const float* tx, const float* 
 /* The same product with a workspace, which large products use to sort both sides
  * along a Hilbert curve and leave out the pairs whose Gaussian is exactly zero
  * in FP32 (the result equals the all-pairs product up to FP32 summation order).
- * gpl_gauss_product_workspace is 0 where the all-pairs product is used; with
+ * gpl_gauss_product_workspace is 0 where no product of that size is sorted; with
  * ws = NULL this is gpl_gauss_product. */
 size_t gpl_gauss_product_workspace(int nt, int ns, int nrhs);
 int gpl_gauss_product_ws(const gpl_gauss* g, int nt, const float* tx, const float* ty, const float* tz,

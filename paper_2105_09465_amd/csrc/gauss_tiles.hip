@@ -48,10 +48,13 @@ constexpr int kTBatch = 4;                     // box tests of a lane in a round
 constexpr int kTList = kTWaves * kTBatch * 64; // chunks tested per round
 constexpr float kZeroArg = 127.f;              // exp2(-kZeroArg) is exactly zero, with margin for rounding
 
-// Pairs from which a product of points in the caller's order is sorted first: the
-// all-pairs kernel takes some 0.4 us a million pairs, the sorts of both sides and
-// the three launches after them 100 us and more.
-constexpr long long kSortedPairs = 1LL << 25;
+// Pairs from which a product of points in the caller's order is sorted first. One
+// column with shapes on one side: all pairs take 25 us for 4,096 traced points, 41 for
+// 6,400, 58 for 10,000 and 74 for 12,544, sorted 52, 55, 59 and 71. With shapes on both
+// sides a pair costs more and a sorted product does less of it: A on the windowed
+// kernel and three columns takes 50 us for 1,296 points either way, for 2,304 67 all
+// pairs and 58 sorted, for 5,184 139 and 79.
+constexpr long long kSortedPairs = 3LL << 25, kSortedPairsBoth = 1LL << 22;
 constexpr int kEntryShift = 28;                // list entries: chunk below, subtile mask above
 constexpr uint32_t kEntryChunk = (1u << kEntryShift) - 1u;
 
@@ -574,12 +577,12 @@ int gauss_layers_sums(GaussLayerSums* layers, int nl, const GSorted& S, const fl
 //
 // The transmission T y of the variational step with the sums its adjoint towards
 // the targets needs. The targets are sorted, the sources stay in the caller's
-// order, and the sum over them has the order of the dense kernel: eight shares of
-// whole 64-point steps, each added up source by source, then the shares in order.
-// Chunks of 16 consecutive sources whose terms are exact zeros are left out, so
-// the flux keeps the dense product's bits. (The log-likelihood is a sum of squares
-// of small differences of these fluxes in FP64: another order of the sum moves it
-// by some 1e-9, within its own error but visible.)
+// order, and the sum over them has a fixed one: eight shares of whole 64-point steps,
+// each added up source by source, then the shares in order. Chunks of eight
+// consecutive sources whose terms are exact zeros are left out, which changes no bit.
+// (The log-likelihood is a sum of squares of small differences of these fluxes in
+// FP64: another order of the sum moves it by some 1e-9, within its own error but
+// visible from one version to the next.)
 //
 // A wave takes 16 targets and one share: lane 4 t + q forms the terms of target t
 // and source q of every four, and the sum goes round the four lanes of a target,
@@ -933,10 +936,12 @@ static void carve_pair(C& cv, int nt, int ns, bool same, int cols, TilePlan& pt,
   rest = cv.template take<char>(bytes);
 }
 
-bool gauss_pair_sorted(int nt, int ns) { return (long long)nt * ns >= kSortedPairs; }
+bool gauss_pair_sorted(int nt, int ns, bool both) {
+  return (long long)nt * ns >= (both ? kSortedPairsBoth : kSortedPairs);
+}
 
 size_t gauss_pair_workspace(int nt, int ns, bool same, int nrhs) {
-  if (nt <= 0 || ns <= 0 || nrhs <= 0 || !gauss_pair_sorted(nt, ns)) return 0;
+  if (nt <= 0 || ns <= 0 || nrhs <= 0 || !gauss_pair_sorted(nt, ns, true)) return 0;
   Sizer s;
   TilePlan pt, ps;
   char* rest;
