@@ -9,6 +9,7 @@
 // itself (no scan launches between), boxes and scaled coordinates in one kernel,
 // and the split over the waves in two.
 #include <cmath>
+#include <type_traits>
 #include <utility>
 
 #include "mvm_rhs.hpp"
@@ -606,20 +607,30 @@ __device__ __forceinline__ int wave_of_unit(int u, const int* wunit, int nw) {
 }
 
 // Units of a row tile's list L (cnt of them) whose cost before them, the row
-// tile's own included, is below rem: by one wave, 64 units at a time.
+// tile's own included, is below rem: by one wave, 64 units at a time, the loads of
+// four such groups in flight together (a wave that waited for each group on its own
+// spent most of its time there).
 __device__ __forceinline__ int units_before(const uint32_t* L, int cnt, long long rem, int lane) {
+  constexpr int kGroups = 4;
   long long before = kCostRowTile;  // cost up to the current group of 64 units
   int k = 0;
-  for (int k0 = 0; k0 < cnt && before < rem; k0 += 64) {
-    const int kk = k0 + lane;
-    const int c = kk < cnt ? unit_cost(L[kk]) : 0;
-    int x = c;  // inclusive prefix within the group
-    for (int off = 1; off < 64; off <<= 1) {
-      const int y = __shfl_up(x, off, 64);
-      if (lane >= off) x += y;
+  for (int k0 = 0; k0 < cnt && before < rem; k0 += 64 * kGroups) {
+    uint32_t e[kGroups];
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) e[g] = L[min(k0 + 64 * g + lane, cnt - 1)];
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+      if (k0 + 64 * g >= cnt) break;
+      const int kk = k0 + 64 * g + lane;
+      const int c = kk < cnt ? unit_cost(e[g]) : 0;
+      int x = c;  // inclusive prefix within the group
+      for (int off = 1; off < 64; off <<= 1) {
+        const int y = __shfl_up(x, off, 64);
+        if (lane >= off) x += y;
+      }
+      k += __popcll(__ballot(kk < cnt && before + (x - c) < rem));
+      before += __shfl(x, 63, 64);
     }
-    k += __popcll(__ballot(kk < cnt && before + (x - c) < rem));
-    before += __shfl(x, 63, 64);
   }
   return k;
 }
@@ -771,6 +782,19 @@ __device__ __forceinline__ int last_at_most(const T* v, int n, T u) {
   return lo;
 }
 
+// The same by one wave, all its lanes with the same arguments: 64 entries a look.
+template <class T>
+__device__ __forceinline__ int wave_last_at_most(const T* v, int n, T u, int lane) {
+  int lo = 0, len = n;
+  while (len > 1) {
+    const int step = cdiv(len, 64), at = lane * step;
+    const int j = __popcll(__ballot(at < len && v[lo + min(at, len - 1)] <= u)) - 1;
+    lo += j * step;
+    len = min(step, len - j * step);
+  }
+  return lo;
+}
+
 // The row tiles of the units on both sides of a boundary at unit u: (of u - 1, of u).
 __device__ __forceinline__ int2 boundary_rows(const int* off, int nrt, int u) {
   const int r = last_at_most(off, nrt, u);
@@ -778,23 +802,32 @@ __device__ __forceinline__ int2 boundary_rows(const int* off, int nrt, int u) {
 }
 
 // plan_wunit_kernel with the prefixes of the row tiles formed by every workgroup
-// itself; the first one writes unit_off.
-__global__ __launch_bounds__(256) void plan_wunit_fold_kernel(int nrt, int nch, int nw, int wround, const int* count,
-                                                              const uint32_t* __restrict__ list, const int* roww,
-                                                              int* unit_off, int* wunit, int2* wrows) {
+// itself; the first one writes unit_off. Bound by latency, so few row tiles are left
+// to a thread (512 threads past kFewRows row tiles; below, the larger workgroups take
+// longer to start: 5.8 us instead of 5.3 at 88 row tiles), and the searches look at 64
+// entries at a time. 4.5 us at 88 row tiles, 7.6 at 625 and 8.6 at 2500, where 256
+// threads, binary searches and lists read 64 units at a time took 5.0, 9.6 and 14.1.
+constexpr int kFewRows = 256;
+template <int NT>
+__global__ __launch_bounds__(NT) void plan_wunit_fold_kernel(int nrt, int nch, int nw, int wround, const int* count,
+                                                             const uint32_t* __restrict__ list, const int* roww,
+                                                             int* unit_off, int* wunit, int2* wrows) {
   __shared__ int off[kFoldRows];
   __shared__ long long woff[kFoldRows];
-  const long long wtot = fold_rows<256>(nrt, count, roww, off, woff);
+  const long long wtot = fold_rows<NT>(nrt, count, roww, off, woff);
   if (blockIdx.x == 0)
-    for (int r = threadIdx.x; r < nrt; r += 256) unit_off[r] = off[r];
-  const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    for (int r = threadIdx.x; r < nrt; r += NT) unit_off[r] = off[r];
+  const int b = blockIdx.x * (NT / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
   if (b > nw) return;
   const long long t = wtot * wave_weight_below(b, wround) / wave_weight_below(nw, wround);
-  const int r = last_at_most(woff, nrt, t), cnt = count[r];
+  const int r = wave_last_at_most(woff, nrt, t, lane), cnt = count[r];
   const int u = off[r] + units_before(list + (size_t)r * nch, cnt, t - woff[r], lane);
+  const int ru = wave_last_at_most(off, nrt, u, lane);
+  const int rb = u > 0 && off[ru] == u ? wave_last_at_most(off, nrt, u - 1, lane) : ru;
   if (lane == 0) {
     wunit[b] = u;
-    wrows[b] = boundary_rows(off, nrt, u);
+    wrows[b] = make_int2(rb, ru);
   }
 }
 
@@ -1177,8 +1210,13 @@ int plan_build(TilePlan& p, int n, const float* px, const float* py, const gpl_g
                      lo_threshold, p.count, p.list, p.roww);
   GPL_LAUNCH_CHECK();
   if (p.nrt <= kFoldRows) {
-    hipLaunchKernelGGL(plan_wunit_fold_kernel, dim3(cdiv(p.nw + 1, 4)), dim3(256), 0, stream, p.nrt, p.nch, p.nw,
-                       p.wround, p.count, p.list, p.roww, p.unit_off, p.wunit, reinterpret_cast<int2*>(p.wrow));
+    const auto split = [&](auto ntc) {
+      constexpr int NT = decltype(ntc)::value;
+      hipLaunchKernelGGL(plan_wunit_fold_kernel<NT>, dim3(cdiv(p.nw + 1, NT / 64)), dim3(NT), 0, stream, p.nrt, p.nch,
+                         p.nw, p.wround, p.count, p.list, p.roww, p.unit_off, p.wunit,
+                         reinterpret_cast<int2*>(p.wrow));
+    };
+    if (p.nrt <= kFewRows) split(std::integral_constant<int, 256>{}); else split(std::integral_constant<int, 512>{});
     GPL_LAUNCH_CHECK();
     if (job)
       hipLaunchKernelGGL(plan_finish_rhs_kernel,
