@@ -47,43 +47,40 @@ constexpr double kPcRelTol = 1e-5;
 // d[I] = sum_{f, g in fp(I)} b_f b_g K(p_f, p_g) with b = B^T e_I: the fine
 // points within the composite filter's reach of pixel I (weights
 // g[ty] g[tx] / ss^2, zero outside the grid). One workgroup per pixel; the
-// footprint is staged in LDS and the pair sum is reduced in a fixed order.
+// footprint, a rectangle of the grid, is staged in LDS (row-major, as large as
+// the filter) and the pair sum is reduced in a fixed order. Bound by VALU issue:
+// a thread's next pair comes by additions, a point of it in one LDS read. 305 us
+// at 10,000 pixels and 196 points each (666 with a division a pair, six LDS reads
+// and one thread staging).
 constexpr int kMaxFoot = (2 * GPL_PSF_MAX_RADIUS + 8) * (2 * GPL_PSF_MAX_RADIUS + 8);
-__global__ __launch_bounds__(256) void bkb_diag_kernel(int n, int ss, const Taps taps, float s2, double amp2,
-                                                       const float* __restrict__ px, const float* __restrict__ py,
-                                                       double* d) {
-  __shared__ float fx[kMaxFoot], fy[kMaxFoot], fw[kMaxFoot];
-  __shared__ double red[4];
-  __shared__ int s_cnt;
+constexpr int kDiagThreads = 256;
+__global__ __launch_bounds__(kDiagThreads) void bkb_diag_kernel(int n, int ss, const Taps taps, float s2, double amp2,
+                                                                const float* __restrict__ px,
+                                                                const float* __restrict__ py, double* d) {
+  extern __shared__ float4 foot[];  // x, y, weight
+  __shared__ double red[kDiagThreads / 64];
   const int I = blockIdx.x, iy = I / n, ix = I - iy * n, M = n * ss, L = taps.L, r = taps.r;
-  if (threadIdx.x == 0) s_cnt = 0;
-  __syncthreads();
-  // compact the in-grid footprint in a fixed (row-major) order
-  if (threadIdx.x == 0) {
-    int c = 0;
-    const float inv = 1.f / (float)(ss * ss);
-    for (int ty = 0; ty < L; ++ty) {
-      const int gy = iy * ss + ty - r;
-      if (gy < 0 || gy >= M) continue;
-      for (int tx = 0; tx < L; ++tx) {
-        const int gx = ix * ss + tx - r;
-        if (gx < 0 || gx >= M) continue;
-        const int j = gy * M + gx;
-        fx[c] = px[j];
-        fy[c] = py[j];
-        fw[c] = taps.g[ty] * taps.g[tx] * inv;
-        ++c;
-      }
-    }
-    s_cnt = c;
+  const int gx0 = max(ix * ss - r, 0), gy0 = max(iy * ss - r, 0);
+  const int w = min(ix * ss - r + L, M) - gx0, c = w * (min(iy * ss - r + L, M) - gy0);
+  const float inv = 1.f / (float)(ss * ss);
+  for (int e = threadIdx.x; e < c; e += kDiagThreads) {
+    const int gy = gy0 + e / w, gx = gx0 + e % w, j = gy * M + gx;
+    foot[e] = make_float4(px[j], py[j], taps.g[gy - iy * ss + r] * taps.g[gx - ix * ss + r] * inv, 0.f);
   }
   __syncthreads();
-  const int c = s_cnt;
   double s = 0.0;
-  for (int e = threadIdx.x; e < c * c; e += blockDim.x) {
-    const int a = e / c, b = e - a * c;
-    const float dx = fx[a] - fx[b], dy = fy[a] - fy[b];
-    s += (double)fw[a] * (double)fw[b] * (double)exp2_fast(-(fmaf(dx, dx, dy * dy) * s2));
+  const int da = kDiagThreads / c, db = kDiagThreads % c;
+  int a = threadIdx.x / c, b = threadIdx.x % c;
+  for (int e = threadIdx.x; e < c * c; e += kDiagThreads) {
+    const float4 pa = foot[a], pb = foot[b];
+    const float dx = pa.x - pb.x, dy = pa.y - pb.y;
+    s += (double)pa.z * (double)pb.z * (double)exp2_fast(-(fmaf(dx, dx, dy * dy) * s2));
+    a += da;
+    b += db;
+    if (b >= c) {
+      b -= c;
+      ++a;
+    }
   }
   s = block_sum_double(s, red);
   if (threadIdx.x == 0) d[I] = amp2 * s;
@@ -1119,8 +1116,8 @@ extern "C" int gpl_pchol(const gpl_problem* prob, int k, int prec, double* L, in
   GPL_HIP(hipStreamWaitEvent(s2, ev[1], 0));
   const int rc = [&]() -> int {
     GPL_TRY(border_begin(info, s2));
-    hipLaunchKernelGGL(bkb_diag_kernel, dim3(npix), dim3(256), 0, stream, n, ss, taps, s2s, amp2, prob->px, prob->py,
-                       b.d);
+    hipLaunchKernelGGL(bkb_diag_kernel, dim3(npix), dim3(kDiagThreads), taps.L * taps.L * sizeof(float4), stream, n,
+                       ss, taps, s2s, amp2, prob->px, prob->py, b.d);
     GPL_LAUNCH_CHECK();
     hipLaunchKernelGGL(dmax_kernel, dim3(1), dim3(1024), 0, stream, npix, b.d, b.dmax);
     GPL_LAUNCH_CHECK();
