@@ -472,18 +472,21 @@ extern "C" int gpl_apply_A(const gpl_problem* prob, int nrhs, const float* X, in
     }
     const int n = prob->grid.n, ss = prob->grid.ss;
     const float s2 = (float)(prob->noise_sigma * prob->noise_sigma);
-    GPL_TRY(psf_adjoint_launch(n, ss, taps, nrhs, X, ldx, T1, ldf, 1.f, 0.f, CgGate{}, stream));
+    PlanSide adj;
+    GPL_TRY(psf_adjoint_side(adj, n, ss, taps, nrhs, X, ldx, T1, ldf));
     GPL_TRY(windowed_mvm(&prob->kernel, &prob->grid, N, prob->px, prob->py, nrhs, T1, ldf, T2, ldf, 0.f, mws, mb,
-                         stream));
+                         stream, &adj));
     return psf_forward_launch(n, ss, taps, nrhs, T2, ldf, Y, ldy, 1.f, 0.f, X, ldx, s2, nullptr, 0, nullptr,
                               CgGate{}, stream);
   }
-  // B^T X first: it is placed in the product's buffers beside the plan
+  // B^T X is formed beside the first half of the plan and placed in the product's
+  // buffers beside the second
   const int n = prob->grid.n, ss = prob->grid.ss;
-  GPL_TRY(psf_adjoint_launch(n, ss, taps, nrhs, X, ldx, T1, ldf, 1.f, 0.f, CgGate{}, stream));
+  PlanSide adj;
+  GPL_TRY(psf_adjoint_side(adj, n, ss, taps, nrhs, X, ldx, T1, ldf));
   MvmCtx mv;
   GPL_TRY(mvm_prepare(mv, prob->kernel.lengthscale, prob->kernel.amplitude, N, prob->px, prob->py, &prob->grid, nrhs,
-                      prec, false, mws, mb, stream, T1, ldf));
+                      prec, false, mws, mb, stream, T1, ldf, &adj));
   GPL_TRY(mvm_run_prepared(mv, nrhs, T2, ldf, 0.f, CgGate{}, stream, true));
   return psf_forward_launch(n, ss, taps, nrhs, T2, ldf, Y, ldy, 1.f, 0.f, X, ldx,
                             (float)(prob->noise_sigma * prob->noise_sigma), nullptr, 0, nullptr, CgGate{}, stream);

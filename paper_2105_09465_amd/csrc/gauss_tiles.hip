@@ -951,7 +951,8 @@ size_t gauss_pair_workspace(int nt, int ns, bool same, int nrhs) {
 }
 
 int gauss_pair_product(const GSide& T, const GSide& S, double base, double norm, int nrhs, const float* V, int ldv,
-                       float* Y, int ldy, float beta, void* ws, size_t ws_bytes, hipStream_t stream) {
+                       float* Y, int ldy, float beta, void* ws, size_t ws_bytes, hipStream_t stream,
+                       const PlanSide* side) {
   const bool same = T.n == S.n && T.x == S.x && T.y == S.y;  // one set of points: one sort
   Carver cv(ws, ws_bytes);
   TilePlan pt, ps;
@@ -961,7 +962,7 @@ int gauss_pair_product(const GSide& T, const GSide& S, double base, double norm,
   if (!cv.ok()) return check_ws(ws, ws_bytes, gauss_pair_workspace(T.n, S.n, same, nrhs));
   GTileBufs b;
   GPL_TRY(gauss_tiles_carve(T.n, S.n, std::min(nrhs, 8), rest, bytes, b));
-  GPL_TRY(plan_sort(pt, T.n, T.x, T.y, stream));
+  GPL_TRY(plan_sort(pt, T.n, T.x, T.y, stream, side));
   if (!same) GPL_TRY(plan_sort(ps, S.n, S.x, S.y, stream));
   return gauss_tiles_product(sorted_view(pt), T.z, T.w, sorted_view(same ? pt : ps), S.z, S.w, base, norm, nrhs, V,
                              ldv, Y, ldy, beta, b, stream);

@@ -101,6 +101,7 @@ int gauss_ordered_launch(const GSorted& T, const float* tz, const GaussLayer* la
 bool gauss_pair_sorted(int nt, int ns, bool both);
 size_t gauss_pair_workspace(int nt, int ns, bool same, int nrhs);
 int gauss_pair_product(const GSide& T, const GSide& S, double base, double norm, int nrhs, const float* V, int ldv,
-                       float* Y, int ldy, float beta, void* ws, size_t ws_bytes, hipStream_t stream);
+                       float* Y, int ldy, float beta, void* ws, size_t ws_bytes, hipStream_t stream,
+                       const PlanSide* side = nullptr);
 
 }  // namespace gpl

@@ -102,6 +102,22 @@ int psf_forward_launch(int n, int ss, const Taps& taps, int nrhs, const float* i
 int psf_adjoint_launch(int n, int ss, const Taps& taps, int nrhs, const float* in, int ld_in, float* out, int ld_out,
                        float alpha, float beta, CgGate gate, hipStream_t stream);
 
+// Work of a call that needs the caller's order alone, done beside the plan's boxes:
+// B^T of nrhs columns, and the pixel shapes z of the fine points px, py (nullable).
+struct PlanSide {
+  int n, ss, nrhs, ld_in, ld_out;
+  Taps taps;
+  const float* in;
+  float* out;
+  const float *px, *py;
+  float* z;
+};
+// B^T of nrhs >= 1 columns, not launched yet.
+int psf_adjoint_side(PlanSide& s, int n, int ss, const Taps& taps, int nrhs, const float* in, int ld_in, float* out,
+                     int ld_out);
+int plan_side_launch(const PlanSide& s, hipStream_t stream);  // in launches of its own
+int plan_tiles_side_launch(const TilePlan& p, int n, float s2, bool scaled, const PlanSide& s, hipStream_t stream);
+
 // Kernel product Y = K V + beta Y (internal form with the CG gate). A product
 // is prepared once per point set (tile plan) and run for any RHS block of at
 // most nrhs_max columns. `grid` (nullable) says the points are that grid's fine
@@ -126,10 +142,11 @@ struct MvmCtx {
 size_t mvm_workspace(int n, int nrhs, int prec);
 // zero_rhs: clear the RHS buffers (needed unless every product is an mvm_run,
 // which writes them whole, the padding included). V (nullable): the columns of the
-// first product, put into the buffers beside the plan for mvm_run_prepared.
+// first product, put into the buffers beside the plan for mvm_run_prepared; side
+// (nullable): see plan_build.
 int mvm_prepare(MvmCtx& m, double lengthscale, double amplitude, int n, const float* px, const float* py,
                 const gpl_grid* grid, int nrhs, int prec, bool zero_rhs, void* ws, size_t ws_bytes,
-                hipStream_t stream, const float* V = nullptr, int ldv = 0);
+                hipStream_t stream, const float* V = nullptr, int ldv = 0, const PlanSide* side = nullptr);
 int mvm_run(const MvmCtx& m, int nrhs, const float* V, int ldv, float* Y, int ldy, float beta, CgGate gate,
             hipStream_t stream);
 // The product from RHS buffers already written (by the fused PSF adjoint).
@@ -199,7 +216,7 @@ int check_kernel_any(const gpl_kernel* k);  // RBF or windowed (kind 1)
 size_t windowed_workspace(int n, int nrhs);
 int windowed_mvm(const gpl_kernel* kern, const gpl_grid* grid, int n, const float* px, const float* py, int nrhs,
                  const float* V, int ldv, float* Y, int ldy, float beta, void* ws, size_t ws_bytes,
-                 hipStream_t stream);
+                 hipStream_t stream, const PlanSide* before = nullptr);
 
 // Grouped launches of one CG iteration's kernels over the slots of a batch
 // (parity p selects the state buffers). Each returns GPL_OK or GPL_EHIP.

@@ -38,7 +38,7 @@ size_t mvm_workspace(int n, int nrhs, int prec) {
 
 int mvm_prepare(MvmCtx& m, double lengthscale, double amplitude, int n, const float* px, const float* py,
                 const gpl_grid* grid, int nrhs, int prec, bool zero_rhs, void* ws, size_t ws_bytes,
-                hipStream_t stream, const float* V, int ldv) {
+                hipStream_t stream, const float* V, int ldv, const PlanSide* side) {
   GPL_TRY(check_ws(ws, ws_bytes, mvm_workspace(n, nrhs, prec)));
   Carver cv(ws, ws_bytes);
   void* scratch;
@@ -54,7 +54,7 @@ int mvm_prepare(MvmCtx& m, double lengthscale, double amplitude, int n, const fl
   const RhsJob job{n, nrhs, ldv, prec == GPL_PREC_F16X3, V, m.plan.perm, m.bufs};
   bool placed;
   GPL_TRY(plan_build(m.plan, n, px, py, grid, m.s2, plan_threshold(prec), plan_lo_threshold(prec), stream,
-                     V ? &job : nullptr, &placed));
+                     V ? &job : nullptr, &placed, side));
   return V && !placed ? mfma_prep_rhs(m.plan, m.bufs, prec, nrhs, V, ldv, CgGate{}, stream) : GPL_OK;
 }
 
@@ -140,19 +140,26 @@ size_t windowed_workspace(int n, int nrhs) {
 // with their pixel shapes, Z staged at the start of the workspace.
 int windowed_mvm(const gpl_kernel* kern, const gpl_grid* grid, int n, const float* px, const float* py, int nrhs,
                  const float* V, int ldv, float* Y, int ldy, float beta, void* ws, size_t ws_bytes,
-                 hipStream_t stream) {
+                 hipStream_t stream, const PlanSide* before) {
   GPL_REQUIRE(grid != nullptr, "the windowed kernel (kind 1) needs the grid of the points");
   GPL_REQUIRE((long)grid->n * grid->ss * grid->n * grid->ss == n, "grid does not match n=%d", n);
   GPL_TRY(check_ws(ws, ws_bytes, (size_t)3 * n * sizeof(float)));
   float* z = static_cast<float*>(ws);
-  GPL_TRY(pixel_shapes_launch(grid->n * grid->ss, px, py, z, stream));
+  PlanSide s{};  // the shapes, and what the caller needs done before
+  if (before) s = *before;
+  s.n = grid->n;
+  s.ss = grid->ss;
+  s.px = px;
+  s.py = py;
+  s.z = z;
   const double l2 = kern->lengthscale * kern->lengthscale;
   const GSide side{px, py, z, nullptr, n};
   // the sorted product where it is the faster one and the workspace holds it
   const size_t used = align_up((size_t)3 * n * sizeof(float));
   if (gauss_pair_sorted(n, n, true) && ws_bytes >= windowed_workspace(n, nrhs))
     return gauss_pair_product(side, side, l2, kern->amplitude * kern->amplitude * l2, nrhs, V, ldv, Y, ldy, beta,
-                              static_cast<char*>(ws) + used, ws_bytes - used, stream);
+                              static_cast<char*>(ws) + used, ws_bytes - used, stream, &s);
+  GPL_TRY(plan_side_launch(s, stream));
   return gauss_product_launch(side, side, l2, kern->amplitude * kern->amplitude * l2, nrhs, V, ldv, Y, ldy, beta,
                               stream);
 }

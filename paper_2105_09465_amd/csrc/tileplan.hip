@@ -13,6 +13,7 @@
 #include <utility>
 
 #include "mvm_rhs.hpp"
+#include "tile_boxes.hpp"
 #include "tileplan.hpp"
 
 namespace gpl {
@@ -37,11 +38,6 @@ __device__ __forceinline__ float4 wave_extent(float4 e) {
   }
   return e;
 }
-__device__ __forceinline__ float4 join_extent(const float4& a, const float4& b) {
-  return make_float4(fminf(a.x, b.x), fmaxf(a.y, b.y), fminf(a.z, b.z), fmaxf(a.w, b.w));
-}
-constexpr float kInf = INFINITY;
-
 // Extent of the finite points among first, first + step, ... below n for this
 // thread; 4 points a round, their loads issued together (an index past n reads
 // point 0 and is not used).
@@ -393,63 +389,12 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(int n, int s
   sort_scatter_body<kLast>(lds, gridDim.x, n, span, pass, kin, vin, hist, kout, vout, px, py, irank, xs, ys);
 }
 
-// Boxes of one 64-point tile by a wave, lane = sorted point (x, y, live or
-// padding): of every 16-point subtile and 32-point chunk, and (kScaled) the block
-// centre and the scaled, block-centred coordinates (TilePlan::xc, yc, cen). A
-// non-finite coordinate gives an infinite box (never dropped), no valid point an
-// empty one (always dropped). The centre is the middle of the block's box, scaled
-// and rounded to a multiple of 2^-12 (a float); xc = sqrt(s2) x - centre is formed
-// in FP64 and rounded once.
-template <bool kScaled>
-__device__ __forceinline__ void tile_boxes(int tile, float x, float y, bool live, float s2, float4* cbox, float4* sbox,
-                                           float* __restrict__ xc, float* __restrict__ yc, float2* __restrict__ cen) {
-  const int lane = threadIdx.x & 63;
-  const unsigned long long bad = __ballot(live && !(isfinite(x) && isfinite(y)));
-  float4 e = live && isfinite(x) && isfinite(y) ? make_float4(x, x, y, y) : make_float4(kInf, -kInf, kInf, -kInf);
-  for (int off = kSubTile / 2; off > 0; off >>= 1) {
-    e.x = fminf(e.x, __shfl_xor(e.x, off, 64));
-    e.y = fmaxf(e.y, __shfl_xor(e.y, off, 64));
-    e.z = fminf(e.z, __shfl_xor(e.z, off, 64));
-    e.w = fmaxf(e.w, __shfl_xor(e.w, off, 64));
-  }
-  if ((bad >> (lane & ~(kSubTile - 1))) & ((1ull << kSubTile) - 1ull)) e = make_float4(-kInf, kInf, -kInf, kInf);
-  if (lane % kSubTile == 0) sbox[tile * kSubsPerTile + lane / kSubTile] = e;
-  static_assert(kChunk == 2 * kSubTile && kRowTile == 2 * kChunk, "pairs of boxes");
-  auto pair = [](const float4& a, int off) {
-    return join_extent(a, make_float4(__shfl_xor(a.x, off, 64), __shfl_xor(a.y, off, 64), __shfl_xor(a.z, off, 64),
-                                      __shfl_xor(a.w, off, 64)));
-  };
-  e = pair(e, kSubTile);
-  if (lane % kChunk == 0) cbox[tile * kChunksPerTile + lane / kChunk] = e;
-  if (kScaled) {
-    e = pair(e, kChunk);
-    const double sg = sqrt((double)s2);
-    const double mx = 0.5 * ((double)e.x + (double)e.y), my = 0.5 * ((double)e.z + (double)e.w);
-    const float cx = isfinite(mx) ? (float)(rint(mx * sg * 4096.0) / 4096.0) : 0.f;
-    const float cy = isfinite(my) ? (float)(rint(my * sg * 4096.0) / 4096.0) : 0.f;
-    const int r = tile * kRowTile + lane;
-    xc[r] = (float)((double)(live ? x : 0.f) * sg - (double)cx);
-    yc[r] = (float)((double)(live ? y : 0.f) * sg - (double)cy);
-    if (lane == 0) cen[tile] = make_float2(cx, cy);
-  }
-}
-
 template <bool kScaled>
 __global__ __launch_bounds__(256) void plan_tiles_kernel(int n, int nrt, float s2, int* perm, float* __restrict__ xs,
                                                          float* __restrict__ ys, float4* cbox, float4* sbox,
                                                          float* __restrict__ xc, float* __restrict__ yc,
                                                          float2* __restrict__ cen) {
-  const int tile = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (tile >= nrt) return;
-  const int r = tile * kRowTile + (threadIdx.x & 63);
-  const bool live = r < n;
-  const float x = live ? xs[r] : 0.f, y = live ? ys[r] : 0.f;
-  if (!live) {
-    xs[r] = 0.f;
-    ys[r] = 0.f;
-    perm[r] = -1;
-  }
-  tile_boxes<kScaled>(tile, x, y, live, s2, cbox, sbox, xc, yc, cen);
+  plan_tiles_block<kScaled>(blockIdx.x, n, nrt, s2, perm, xs, ys, cbox, sbox, xc, yc, cen);
 }
 
 // ---- lists of live chunks ----
@@ -479,12 +424,12 @@ __device__ __forceinline__ float4 row_box(const float4* cbox, int r) {
 // chunks, 1024 chunks a round (four box loads of a lane in flight), compacted by
 // ballots; the row tile's cost.
 constexpr int kListBatch = 4;
-__global__ __launch_bounds__(256) void plan_lists_kernel(int nch, const float4* __restrict__ cbox,
-                                                         const float4* __restrict__ sbox, float s2, float threshold,
-                                                         float lo_threshold, int* count, uint32_t* list, int* roww) {
+__device__ __forceinline__ void row_list(int r, int nch, const float4* __restrict__ cbox,
+                                         const float4* __restrict__ sbox, float s2, float threshold,
+                                         float lo_threshold, int* count, uint32_t* list, int* roww) {
   __shared__ int cnt_s[4 * kListBatch];
   __shared__ int cost_s[4];
-  const int r = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   float4 sb[kSubsPerTile];
 #pragma unroll
   for (int t = 0; t < kSubsPerTile; ++t) sb[t] = sbox[kSubsPerTile * r + t];
@@ -529,6 +474,23 @@ __global__ __launch_bounds__(256) void plan_lists_kernel(int nch, const float4* 
     count[r] = base;
     roww[r] = kCostRowTile + cost_s[0] + cost_s[1] + cost_s[2] + cost_s[3];
   }
+}
+
+__global__ __launch_bounds__(256) void plan_lists_kernel(int nch, const float4* __restrict__ cbox,
+                                                         const float4* __restrict__ sbox, float s2, float threshold,
+                                                         float lo_threshold, int* count, uint32_t* list, int* roww) {
+  row_list(blockIdx.x, nch, cbox, sbox, s2, threshold, lo_threshold, count, list, roww);
+}
+
+// And by the workgroups after the row tiles' the column maxima of right-hand sides
+// that were formed beside the boxes, too late for plan_extent_rhs_kernel.
+__global__ __launch_bounds__(256) void plan_lists_rhs_kernel(int nrt, int nch, const float4* __restrict__ cbox,
+                                                             const float4* __restrict__ sbox, float s2,
+                                                             float threshold, float lo_threshold, int* count,
+                                                             uint32_t* list, int* roww, RhsJob J) {
+  __shared__ float red[4];
+  if ((int)blockIdx.x < nrt) row_list(blockIdx.x, nch, cbox, sbox, s2, threshold, lo_threshold, count, list, roww);
+  else colmax_unit(J, blockIdx.x - nrt, threadIdx.x, red);
 }
 
 // Exclusive prefix sum of n ints in one workgroup of 1024 threads (in place
@@ -1123,11 +1085,11 @@ static int compute_units() {
 }
 
 // Sort of more than kSmallPoints points, and (kScaled) the scaled coordinates;
-// side (nullable): a small set sorted in the same launches; job (nullable): the column
-// maxima of its right-hand sides too.
+// pair (nullable): a small set sorted in the same launches; job (nullable): the column
+// maxima of its right-hand sides too; side (nullable): work without need of the order.
 template <bool kScaled>
-static int sort_points(TilePlan& p, int n, const float* px, const float* py, float s2, const SmallSort* side,
-                       const RhsJob* job, hipStream_t stream) {
+static int sort_points(TilePlan& p, int n, const float* px, const float* py, float s2, const SmallSort* pair,
+                       const RhsJob* job, const PlanSide* side, hipStream_t stream) {
   int* perm = const_cast<int*>(p.perm);
   int* irank = const_cast<int*>(p.irank);
   const int span = sort_span(n), nb = cdiv(n, span);
@@ -1146,9 +1108,9 @@ static int sort_points(TilePlan& p, int n, const float* px, const float* py, flo
                      p.shist);
   GPL_LAUNCH_CHECK();
   static_assert(kSortPasses == 2, "a first and a last pass");
-  if (side)
+  if (pair)
     hipLaunchKernelGGL(sort_scatter_side_kernel, dim3(nb + 1), dim3(kSortThreads), 0, stream, n, span, k0, p.shist, k1,
-                       p.sval, *side);
+                       p.sval, *pair);
   else
     hipLaunchKernelGGL(sort_scatter_kernel<false>, dim3(nb), dim3(kSortThreads), 0, stream, n, span, 0, k0, nullptr,
                        p.shist, k1, p.sval, px, py, irank, p.xs, p.ys);
@@ -1158,6 +1120,7 @@ static int sort_points(TilePlan& p, int n, const float* px, const float* py, flo
   hipLaunchKernelGGL(sort_scatter_kernel<true>, dim3(nb), dim3(kSortThreads), 0, stream, n, span, 1, k1, p.sval,
                      p.shist, nullptr, perm, px, py, irank, p.xs, p.ys);
   GPL_LAUNCH_CHECK();
+  if (side) return plan_tiles_side_launch(p, n, s2, kScaled, *side, stream);
   hipLaunchKernelGGL(plan_tiles_kernel<kScaled>, dim3(cdiv(p.nrt, 4)), dim3(256), 0, stream, n, p.nrt, s2, perm, p.xs,
                      p.ys, p.cbox, p.sbox, p.xc, p.yc, p.cen);
   GPL_LAUNCH_CHECK();
@@ -1173,10 +1136,11 @@ static int small_plan(TilePlan& p, int n, const float* px, const float* py, floa
   return GPL_OK;
 }
 
-int plan_sort(TilePlan& p, int n, const float* px, const float* py, hipStream_t stream) {
+int plan_sort(TilePlan& p, int n, const float* px, const float* py, hipStream_t stream, const PlanSide* side) {
   GPL_REQUIRE(n >= 1, "plan needs at least one point");
-  if (n <= kSmallPoints) return small_plan<false>(p, n, px, py, 1.f, 0.f, 0.f, stream);
-  return sort_points<false>(p, n, px, py, 1.f, nullptr, nullptr, stream);
+  if (n > kSmallPoints) return sort_points<false>(p, n, px, py, 1.f, nullptr, nullptr, side, stream);
+  if (side) GPL_TRY(plan_side_launch(*side, stream));
+  return small_plan<false>(p, n, px, py, 1.f, 0.f, 0.f, stream);
 }
 
 int plan_sort_pair(TilePlan& a, int na, const float* ax, const float* ay, TilePlan& b, int nb, const float* bx,
@@ -1187,14 +1151,14 @@ int plan_sort_pair(TilePlan& a, int na, const float* ax, const float* ay, TilePl
     return plan_sort(b, nb, bx, by, stream);
   }
   const SmallSort side = small_sort(b, nb, bx, by);
-  if (na > kSmallPoints) return sort_points<false>(a, na, ax, ay, 1.f, &side, nullptr, stream);
+  if (na > kSmallPoints) return sort_points<false>(a, na, ax, ay, 1.f, &side, nullptr, nullptr, stream);
   hipLaunchKernelGGL(sort_small_pair_kernel, dim3(2), dim3(kSortThreads), 0, stream, small_sort(a, na, ax, ay), side);
   GPL_LAUNCH_CHECK();
   return GPL_OK;
 }
 
 int plan_build(TilePlan& p, int n, const float* px, const float* py, const gpl_grid* grid, float s2, float threshold,
-               float lo_threshold, hipStream_t stream, const RhsJob* job, bool* placed) {
+               float lo_threshold, hipStream_t stream, const RhsJob* job, bool* placed, const PlanSide* side) {
   if (placed) *placed = false;
   if (grid) {
     const int m = grid->n * grid->ss;
@@ -1203,11 +1167,18 @@ int plan_build(TilePlan& p, int n, const float* px, const float* py, const gpl_g
   GPL_REQUIRE(n >= 1, "plan needs at least one point");
   GPL_REQUIRE(p.nch <= kMaxPlanChunks, "n=%d exceeds the product's limit of %d points", n, kMaxPlanChunks * kChunk);
   p.wround = 4 * compute_units();
-  if (n <= kSmallPoints) return small_plan<true>(p, n, px, py, s2, threshold, lo_threshold, stream);
+  if (n <= kSmallPoints) {
+    if (side) GPL_TRY(plan_side_launch(*side, stream));
+    return small_plan<true>(p, n, px, py, s2, threshold, lo_threshold, stream);
+  }
   if (p.nrt > kFoldRows) job = nullptr;
-  GPL_TRY(sort_points<true>(p, n, px, py, s2, nullptr, job, stream));
-  hipLaunchKernelGGL(plan_lists_kernel, dim3(p.nrt), dim3(256), 0, stream, p.nch, p.cbox, p.sbox, s2, threshold,
-                     lo_threshold, p.count, p.list, p.roww);
+  GPL_TRY(sort_points<true>(p, n, px, py, s2, nullptr, side ? nullptr : job, side, stream));
+  if (side && job && job->f16)  // the columns are there since the launch before
+    hipLaunchKernelGGL(plan_lists_rhs_kernel, dim3(p.nrt + job->nrhs * kColmaxBlocks), dim3(256), 0, stream, p.nrt,
+                       p.nch, p.cbox, p.sbox, s2, threshold, lo_threshold, p.count, p.list, p.roww, *job);
+  else
+    hipLaunchKernelGGL(plan_lists_kernel, dim3(p.nrt), dim3(256), 0, stream, p.nch, p.cbox, p.sbox, s2, threshold,
+                       lo_threshold, p.count, p.list, p.roww);
   GPL_LAUNCH_CHECK();
   if (p.nrt <= kFoldRows) {
     const auto split = [&](auto ntc) {

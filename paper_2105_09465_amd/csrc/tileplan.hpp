@@ -223,13 +223,18 @@ void sort_carve(C& cv, int n, TilePlan& p) {
 // PSF adjoint. `s2` is the exp2 scale, `threshold` the skip threshold of the
 // form and `lo_threshold` that of the lo masks (kLoF16x3 in the precision form;
 // equal to `threshold` where the form has no lo part). `job` (nullable): right-hand
-// sides to be prepared beside the plan; *placed says whether they were.
+// sides to be prepared beside the plan; *placed says whether they were. `side`
+// (nullable): work that the caller needs done by then, the columns of `job` included,
+// launched with the boxes (before the plan for a small set).
 struct RhsJob;
+struct PlanSide;
 int plan_build(TilePlan& p, int n, const float* px, const float* py, const gpl_grid* grid, float s2, float threshold,
-               float lo_threshold, hipStream_t stream, const RhsJob* job = nullptr, bool* placed = nullptr);
+               float lo_threshold, hipStream_t stream, const RhsJob* job = nullptr, bool* placed = nullptr,
+               const PlanSide* side = nullptr);
 // The first part of plan_build alone: the Hilbert sort (perm, irank, xs, ys)
 // and the chunk and subtile boxes.
-int plan_sort(TilePlan& p, int n, const float* px, const float* py, hipStream_t stream);
+int plan_sort(TilePlan& p, int n, const float* px, const float* py, hipStream_t stream,
+              const PlanSide* side = nullptr);
 // The sort of two sets; a small one b shares the launches of a.
 int plan_sort_pair(TilePlan& a, int na, const float* ax, const float* ay, TilePlan& b, int nb, const float* bx,
                    const float* by, hipStream_t stream);
