@@ -12,6 +12,12 @@ namespace gpl {
 __device__ __forceinline__ float4 join_extent(const float4& a, const float4& b) {
   return make_float4(fminf(a.x, b.x), fmaxf(a.y, b.y), fminf(a.z, b.z), fmaxf(a.w, b.w));
 }
+// An extent joined with that of the lane whose index differs in bit OFF (lane_xor).
+template <int OFF>
+__device__ __forceinline__ float4 join_lane_xor(const float4& e) {
+  auto other = [](float v) { return __builtin_bit_cast(float, lane_xor<OFF>(__builtin_bit_cast(unsigned, v))); };
+  return join_extent(e, make_float4(other(e.x), other(e.y), other(e.z), other(e.w)));
+}
 constexpr float kInf = INFINITY;
 
 // Boxes of one 64-point tile by a wave, lane = sorted point (x, y, live or
@@ -27,23 +33,17 @@ __device__ __forceinline__ void tile_boxes(int tile, float x, float y, bool live
   const int lane = threadIdx.x & 63;
   const unsigned long long bad = __ballot(live && !(isfinite(x) && isfinite(y)));
   float4 e = live && isfinite(x) && isfinite(y) ? make_float4(x, x, y, y) : make_float4(kInf, -kInf, kInf, -kInf);
-  for (int off = kSubTile / 2; off > 0; off >>= 1) {
-    e.x = fminf(e.x, __shfl_xor(e.x, off, 64));
-    e.y = fmaxf(e.y, __shfl_xor(e.y, off, 64));
-    e.z = fminf(e.z, __shfl_xor(e.z, off, 64));
-    e.w = fmaxf(e.w, __shfl_xor(e.w, off, 64));
-  }
+  static_assert(kSubTile == 16 && kChunk == 32 && kRowTile == 64, "steps of lane_xor");
+  e = join_lane_xor<8>(e);
+  e = join_lane_xor<4>(e);
+  e = join_lane_xor<2>(e);
+  e = join_lane_xor<1>(e);
   if ((bad >> (lane & ~(kSubTile - 1))) & ((1ull << kSubTile) - 1ull)) e = make_float4(-kInf, kInf, -kInf, kInf);
   if (lane % kSubTile == 0) sbox[tile * kSubsPerTile + lane / kSubTile] = e;
-  static_assert(kChunk == 2 * kSubTile && kRowTile == 2 * kChunk, "pairs of boxes");
-  auto pair = [](const float4& a, int off) {
-    return join_extent(a, make_float4(__shfl_xor(a.x, off, 64), __shfl_xor(a.y, off, 64), __shfl_xor(a.z, off, 64),
-                                      __shfl_xor(a.w, off, 64)));
-  };
-  e = pair(e, kSubTile);
+  e = join_lane_xor<16>(e);
   if (lane % kChunk == 0) cbox[tile * kChunksPerTile + lane / kChunk] = e;
   if (kScaled) {
-    e = pair(e, kChunk);
+    e = join_lane_xor<32>(e);
     const double sg = sqrt((double)s2);
     const double mx = 0.5 * ((double)e.x + (double)e.y), my = 0.5 * ((double)e.z + (double)e.w);
     const float cx = isfinite(mx) ? (float)(rint(mx * sg * 4096.0) / 4096.0) : 0.f;

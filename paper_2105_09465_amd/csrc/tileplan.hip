@@ -30,14 +30,14 @@ size_t plan_workspace(int n) {
 
 // Four-way extent (xmin, xmax, ymin, ymax) over the lanes of a wave.
 __device__ __forceinline__ float4 wave_extent(float4 e) {
-  for (int off = 32; off > 0; off >>= 1) {
-    e.x = fminf(e.x, __shfl_xor(e.x, off, 64));
-    e.y = fmaxf(e.y, __shfl_xor(e.y, off, 64));
-    e.z = fminf(e.z, __shfl_xor(e.z, off, 64));
-    e.w = fmaxf(e.w, __shfl_xor(e.w, off, 64));
-  }
-  return e;
+  e = join_lane_xor<8>(e);
+  e = join_lane_xor<4>(e);
+  e = join_lane_xor<2>(e);
+  e = join_lane_xor<1>(e);
+  e = join_lane_xor<16>(e);
+  return join_lane_xor<32>(e);
 }
+
 // Extent of the finite points among first, first + step, ... below n for this
 // thread; 4 points a round, their loads issued together (an index past n reads
 // point 0 and is not used).
@@ -897,10 +897,15 @@ constexpr int kSmallPoints = 4096;
 constexpr int kSmallTiles = kSmallPoints / kRowTile, kSmallChunks = kSmallTiles * kChunksPerTile;
 static_assert(kSortThreads == 1024, "one workgroup size for the sort and the small plan");
 
+constexpr int kSmallRounds = kSmallPoints / kSortThreads;  // items a thread
+constexpr int kSmallBits = 6, kSmallPasses = 2 * kHilbertBits / kSmallBits;
+static_assert(1 << kSmallBits == 64 && kSmallPasses * kSmallBits == 2 * kHilbertBits, "a lane per digit");
+
 union SmallLds {
+  ScatterLds rank;  // of the large set sorted beside (sort_scatter_side_kernel)
   struct {
-    uint32_t key[kSmallPoints];
-    ScatterLds rank;
+    uint32_t key[2][kSmallPoints];
+    int cnt[64 * (kSmallRounds * kSortThreads / 64 + 1)];
   } sort;
   struct {
     unsigned short cost[kSmallTiles][kSmallChunks];  // cost of a row tile before each of its units
@@ -908,10 +913,77 @@ union SmallLds {
     int2 wrows[8 * kSmallTiles + 1];
     int off[kSmallTiles], count[kSmallTiles], roww[kSmallTiles];
     unsigned short first[kSmallTiles], past[kSmallTiles];
-    long long woff[kSmallTiles];
+    int woff[kSmallTiles];
     float4 cbox[kSmallChunks], sbox[kSmallTiles * kSubsPerTile];
   } plan;
 };
+
+// Stable order of the keys in L.sort.key[0], six bits a pass. A group of 64 items (wave
+// w in round k) counts its digits in a column of cnt, lane by lane; the prefix of cnt
+// along the digits, the groups of each in turn, gives every group's first position of a
+// digit. Bound by the issue of one compute unit: two sets of 4,096 and 576 points take
+// 26.4 us (28.9 with 12 bits a pass, 80 KB of counters cleared for each and the rounds
+// ranked in turn), 576 points 16 us either way.
+__device__ __forceinline__ const unsigned short* small_order(SmallLds& L, int n,
+                                                             unsigned short (&val)[2][kSmallPoints], int* ws) {
+  constexpr int kWaves = kSortThreads / 64;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int R = cdiv(n, kSortThreads), row = R * kWaves + 1;  // one more: lanes fall on distinct banks
+  int* const cnt = L.sort.cnt;
+  for (int pass = 0; pass < kSmallPasses; ++pass) {
+    const uint32_t* kin = L.sort.key[pass & 1];
+    const unsigned short* vin = val[~pass & 1];
+    uint32_t key[kSmallRounds];
+    int v[kSmallRounds], at[kSmallRounds], lower[kSmallRounds];
+#pragma unroll
+    for (int k = 0; k < kSmallRounds; ++k) {
+      if (k >= R) break;
+      const int i = k * kSortThreads + tid, g = k * kWaves + w;
+      const bool valid = i < n;
+      cnt[lane * row + g] = 0;
+      if (k * kSortThreads + w * 64 >= n) continue;  // no item in the group
+      __builtin_amdgcn_wave_barrier();  // a wave's own LDS stores stay in order
+      key[k] = valid ? kin[i] : 0u;
+      v[k] = valid && pass > 0 ? (int)vin[i] : i;
+      const int d = (int)(key[k] >> (kSmallBits * pass)) & 63;
+      unsigned long long m = __ballot(valid);
+#pragma unroll
+      for (int b = 0; b < kSmallBits; ++b) {
+        const bool bit = (d >> b) & 1;
+        const unsigned long long bb = __ballot(bit);
+        m &= bit ? bb : ~bb;
+      }
+      lower[k] = __popcll(m & ((1ull << lane) - 1ull));
+      at[k] = d * row + g;
+      if (valid && lower[k] == 0) cnt[at[k]] = __popcll(m);
+    }
+    __syncthreads();
+    int* const mine = cnt + (tid / kWaves) * row + tid % kWaves * R;  // R entries of digit tid / kWaves
+    int c[kSmallRounds], sum = 0;
+#pragma unroll
+    for (int k = 0; k < kSmallRounds; ++k) {
+      c[k] = k < R ? mine[k] : 0;
+      sum += c[k];
+    }
+    int run = block_exclusive(sum, ws);
+#pragma unroll
+    for (int k = 0; k < kSmallRounds; ++k) {
+      if (k >= R) break;
+      mine[k] = run;
+      run += c[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSmallRounds; ++k) {
+      if (k >= R || k * kSortThreads + tid >= n) break;
+      const int r = cnt[at[k]] + lower[k];
+      L.sort.key[~pass & 1][r] = key[k];
+      val[pass & 1][r] = (unsigned short)v[k];
+    }
+    __syncthreads();
+  }
+  return val[(kSmallPasses - 1) & 1];
+}
 
 template <bool kPlan>
 __device__ __forceinline__ void plan_small_body(SmallLds& L, int n, const float* __restrict__ px,
@@ -930,39 +1002,8 @@ __device__ __forceinline__ void plan_small_body(SmallLds& L, int n, const float*
   float4 ext = red[0];
   for (int k = 1; k < kWaves; ++k) ext = join_extent(ext, red[k]);
   ext = extent_square(ext);
-  for (int i = tid; i < n; i += kSortThreads) L.sort.key[i] = point_key(px[i], py[i], ext);
-  for (int pass = 0; pass < kSortPasses; ++pass) {
-    for (int d = tid; d < kSortDigits; d += kSortThreads) {
-      L.sort.rank.pos[d] = 0;
-      L.sort.rank.wcnt[d] = make_uint4(0u, 0u, 0u, 0u);
-    }
-    __syncthreads();
-    for (int i = tid; i < n; i += kSortThreads) atomicAdd(&L.sort.rank.pos[key_digit(L.sort.key[i], pass)], 1);
-    __syncthreads();
-    constexpr int kPer = kSortDigits / kSortThreads;
-    int c[kPer], sum = 0;
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      c[k] = L.sort.rank.pos[kPer * tid + k];
-      sum += c[k];
-    }
-    int run = block_exclusive(sum, ws);
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      L.sort.rank.pos[kPer * tid + k] = run;
-      run += c[k];
-    }
-    __syncthreads();
-    for (int i0 = 0; i0 < n; i0 += kSortThreads) {
-      const int i = i0 + tid;
-      const bool valid = i < n;
-      const int v = valid ? (pass == 0 ? i : (int)val[(pass - 1) & 1][i]) : 0;
-      const int r = rank_items(key_digit(L.sort.key[v], pass), valid, i0 + kSortThreads < n, L.sort.rank.pos, L.sort.rank.wcnt);
-      if (valid) val[pass & 1][r] = (unsigned short)v;
-    }
-    __syncthreads();
-  }
-  const unsigned short* order = val[(kSortPasses - 1) & 1];
+  for (int i = tid; i < n; i += kSortThreads) L.sort.key[0][i] = point_key(px[i], py[i], ext);
+  const unsigned short* order = small_order(L, n, val, ws);
   for (int tile = w; tile < P.nrt; tile += kWaves) {
     const int r = tile * kRowTile + lane;
     const bool live = r < n;
@@ -1011,15 +1052,38 @@ __device__ __forceinline__ void plan_small_body(SmallLds& L, int n, const float*
   }
   __syncthreads();
   const int nrt = P.nrt, nw = P.nw;
-  const long long wtot = fold_rows<kSortThreads>(nrt, L.plan.count, L.plan.roww, L.plan.off, L.plan.woff);
+  // prefixes of the row tiles' unit counts and costs, a lane per row tile
+  static_assert(kSmallTiles <= 64, "a wave holds the row tiles");
+  int wtot;
+  {
+    const int c = lane < nrt ? L.plan.count[lane] : 0, v = lane < nrt ? L.plan.roww[lane] : 0;
+    int xc = c, xv = v;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int yc = __shfl_up(xc, o, 64), yv = __shfl_up(xv, o, 64);
+      if (lane >= o) {
+        xc += yc;
+        xv += yv;
+      }
+    }
+    wtot = __shfl(xv, 63, 64);
+    if (w == 0 && lane < nrt) {
+      L.plan.off[lane] = xc - c;
+      L.plan.woff[lane] = xv - v;
+    }
+  }
+  __syncthreads();
+  // cost and weight fit 32 bits, and so does their product
+  constexpr long long kMostCost = kSmallTiles * (kCostRowTile + (long long)kSmallChunks * kMostUnitCost);
+  static_assert(kMostCost * 8 * kSmallTiles * kRoundWeight[0] < 1ll << 32, "32-bit targets");
+  const unsigned wall = (unsigned)wave_weight_below(nw, P.wround);
   for (int b = tid; b <= nw; b += kSortThreads) {
-    const long long t = wtot * wave_weight_below(b, P.wround) / wave_weight_below(nw, P.wround);
+    const int t = (int)((unsigned)wtot * (unsigned)wave_weight_below(b, P.wround) / wall);
     const int r = last_at_most(L.plan.woff, nrt, t);
-    const long long rem = t - L.plan.woff[r];
+    const int rem = t - L.plan.woff[r];
     int lo = 0, hi = L.plan.count[r];  // units whose cost before them is below rem
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
-      if ((long long)L.plan.cost[r][mid] < rem) lo = mid + 1; else hi = mid;
+      if ((int)L.plan.cost[r][mid] < rem) lo = mid + 1; else hi = mid;
     }
     const int u = L.plan.off[r] + lo;
     L.plan.wunit[b] = u;
@@ -1067,7 +1131,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter_side_kernel(int n, 
                                                                          int* vout, SmallSort side) {
   __shared__ SmallLds lds;
   if (blockIdx.x + 1 == gridDim.x) sort_small(lds, side);
-  else sort_scatter_body<false>(lds.sort.rank, gridDim.x - 1, n, span, 0, kin, nullptr, hist, kout, vout, nullptr, nullptr, nullptr,
+  else sort_scatter_body<false>(lds.rank, gridDim.x - 1, n, span, 0, kin, nullptr, hist, kout, vout, nullptr, nullptr, nullptr,
                                 nullptr, nullptr);
 }
 

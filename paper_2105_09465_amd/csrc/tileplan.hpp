@@ -283,6 +283,7 @@ constexpr int kCostSubtile = 3;
 constexpr int kCostSubtileLo = 2;
 constexpr int kCostUnit = 5;
 constexpr int kCostRowTile = 36;
+constexpr int kMostUnitCost = kSubsPerTile * (kCostSubtile + kCostSubtileLo) + kCostUnit;
 __host__ __device__ inline int unit_cost(uint32_t e) {
   return kCostSubtile * __builtin_popcount(entry_mask(e)) + kCostSubtileLo * __builtin_popcount(entry_lomask(e)) +
          kCostUnit;
