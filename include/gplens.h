@@ -491,8 +491,9 @@ int gpl_sersic_backward(const gpl_source* src, int n, const float* px, const flo
  * through the traced points, their pixel shapes and the k-NN weights of
  * image-plane inducing points (each point's k-th neighbour held at its current
  * index; its share is added with FP64 atomics, so the last FP32 bit of a
- * gradient may vary between runs). All products are dense Gaussian products
- * (every pair in FP32), FP64 sums for the scalars. */
+ * gradient may vary between runs). All products are Gaussian products in FP32
+ * over the points sorted once per call (pairs that are exactly zero are left
+ * out), with FP64 sums for the scalars. */
 #define GPL_VIGP_IMAGE_PLANE 0
 #define GPL_VIGP_SOURCE_PLANE 1
 typedef struct {
