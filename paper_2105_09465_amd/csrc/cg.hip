@@ -67,7 +67,7 @@ static void carve_cg(C& c, int npix, int N, int nrhs, int prec, CgBuffers* b, si
 
 // Block maximum of v >= 0 (result in thread 0).
 __device__ __forceinline__ float block_max(float v, float* smem) {
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
+  v = warp_max(v);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) smem[threadIdx.x >> 6] = v;
   __syncthreads();

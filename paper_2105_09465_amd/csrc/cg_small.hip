@@ -320,7 +320,7 @@ __global__ __launch_bounds__(kColThreads) void cg_column_kernel(CgColumn C, cons
         win[y * dim.width + dim.lo + i[e] - y * n] = pn;
         m = fmaxf(m, fabsf(pn));
       }
-    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    m = warp_max(m);
     if (lane == 0) redm[q][wv] = m;
   }
   __syncthreads();

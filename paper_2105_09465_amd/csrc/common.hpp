@@ -137,6 +137,17 @@ __device__ __forceinline__ T warp_sum(T v) {
   return add_lane_xor<1>(v);
 }
 
+// Largest of the wave's values, the same in every lane.
+__device__ __forceinline__ float warp_max(float v) {
+  auto step = [](float a, unsigned b) { return fmaxf(a, __builtin_bit_cast(float, b)); };
+  v = step(v, lane_xor<32>(__builtin_bit_cast(unsigned, v)));
+  v = step(v, lane_xor<16>(__builtin_bit_cast(unsigned, v)));
+  v = step(v, lane_xor<8>(__builtin_bit_cast(unsigned, v)));
+  v = step(v, lane_xor<4>(__builtin_bit_cast(unsigned, v)));
+  v = step(v, lane_xor<2>(__builtin_bit_cast(unsigned, v)));
+  return step(v, lane_xor<1>(__builtin_bit_cast(unsigned, v)));
+}
+
 // Sum of p[0, cnt) over the 64 lanes of one wave in a fixed order (lane-strided
 // partial sums, then a butterfly); the result is the same in every lane.
 __device__ inline double wave_fold_sum(const double* __restrict__ p, int cnt) {

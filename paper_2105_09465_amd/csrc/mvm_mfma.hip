@@ -78,7 +78,7 @@ __global__ __launch_bounds__(1024) void small_rhs_kernel(RhsJob J, CgGate gate) 
   float m = 0.f;
   if (c < J.nrhs)
     for (int i = threadIdx.x; i < J.n; i += 1024) m = fmaxf(m, fabsf(J.V[(size_t)c * J.ldv + i]));
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  m = warp_max(m);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
   for (int k = 0; k < 16; ++k) m = fmaxf(m, red[k]);

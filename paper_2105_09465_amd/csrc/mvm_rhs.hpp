@@ -37,7 +37,7 @@ __device__ __forceinline__ void colmax_unit(const RhsJob& J, int u, int t, float
       for (int q = 0; q < kU; ++q) m = fmaxf(m, fabsf(x[q]));
     }
   }
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  m = warp_max(m);
   if ((t & 63) == 0) red[t >> 6] = m;
   __syncthreads();
   if (t == 0 && c < J.nrhs) J.b.colmax[u] = __float_as_uint(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));

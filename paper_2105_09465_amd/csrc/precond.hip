@@ -794,7 +794,7 @@ __global__ __launch_bounds__(256) void pcg_init_p_kernel(int npix, const float* 
     P[(size_t)c * ldv + i] = z;
     m = fabsf(z);
   }
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  m = warp_max(m);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) redm[threadIdx.x >> 6] = m;
   __syncthreads();
@@ -973,7 +973,7 @@ __global__ __launch_bounds__(256) void pcg_update2_kernel(int npix, const float*
     P[iv] = pn;
     m = fabsf(pn);
   }
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  m = warp_max(m);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) redm[threadIdx.x >> 6] = m;
   __syncthreads();
@@ -1033,7 +1033,7 @@ __global__ __launch_bounds__(256) void pcg_absmax_kernel(int npix, const float* 
   const int c = blockIdx.y;
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   float m = i < npix ? fabsf(X[(size_t)c * ldx + i]) : 0.f;
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  m = warp_max(m);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) redm[threadIdx.x >> 6] = m;
   __syncthreads();
