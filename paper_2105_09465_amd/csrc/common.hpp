@@ -137,6 +137,18 @@ __device__ __forceinline__ T warp_sum(T v) {
   return add_lane_xor<1>(v);
 }
 
+// Inclusive prefix sum over the wave in lane order, every lane active: shifts within rows
+// of 16 lanes, then the rows' last lanes broadcast onwards.
+__device__ __forceinline__ int warp_prefix(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1, 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2, 3
+  return v;
+}
+
 // Largest of the wave's values, the same in every lane.
 __device__ __forceinline__ float warp_max(float v) {
   auto step = [](float a, unsigned b) { return fmaxf(a, __builtin_bit_cast(float, b)); };

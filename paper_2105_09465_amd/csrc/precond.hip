@@ -89,16 +89,11 @@ __global__ __launch_bounds__(kDiagThreads) void bkb_diag_kernel(int n, int ss, c
 // ---------------------------------------------------------------- candidate selection
 
 // Exclusive prefix sum of v over the workgroup in thread order (wave scans by
-// lane shuffles, then one combine of the wave totals through LDS); *total gets
+// DPP moves, then one combine of the wave totals through LDS); *total gets
 // the sum. Every thread of the workgroup must call it.
 __device__ __forceinline__ int block_excl_scan(int v, int* wsum, int* total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  int x = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int y = __shfl_up(x, off, 64);
-    if (lane >= off) x += y;
-  }
+  const int x = warp_prefix(v);
   if (lane == 63) wsum[w] = x;
   __syncthreads();
   int before = 0, tot = 0;

@@ -187,11 +187,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(int n, int spa
 // Exclusive prefix of one int per thread of the workgroup; ws: a wave's sums.
 __device__ __forceinline__ int block_exclusive(int v, int* ws) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int x = v;
-  for (int off = 1; off < 64; off <<= 1) {
-    const int y = __shfl_up(x, off, 64);
-    if (lane >= off) x += y;
-  }
+  const int x = warp_prefix(v);
   if (lane == 63) ws[w] = x;
   __syncthreads();
   int before = 0;
@@ -585,13 +581,9 @@ __device__ __forceinline__ int units_before(const uint32_t* L, int cnt, long lon
       if (k0 + 64 * g >= cnt) break;
       const int kk = k0 + 64 * g + lane;
       const int c = kk < cnt ? unit_cost(e[g]) : 0;
-      int x = c;  // inclusive prefix within the group
-      for (int off = 1; off < 64; off <<= 1) {
-        const int y = __shfl_up(x, off, 64);
-        if (lane >= off) x += y;
-      }
+      const int x = warp_prefix(c);  // within the group
       k += __popcll(__ballot(kk < cnt && before + (x - c) < rem));
-      before += __shfl(x, 63, 64);
+      before += __builtin_amdgcn_readlane(x, 63);
     }
   }
   return k;
@@ -678,11 +670,12 @@ constexpr int kFoldRows = 4096;
 
 // Exclusive prefixes of the row tiles' unit counts and costs, off and woff (LDS,
 // nrt <= kFoldRows), by a workgroup of NT threads; returns the total cost.
+static_assert(kFoldRows * (kCostRowTile + (long long)kChunksPerTile * kFoldRows * kMostUnitCost) < 1ll << 31,
+              "32-bit costs");
 template <int NT>
-__device__ __forceinline__ long long fold_rows(int nrt, const int* __restrict__ count, const int* __restrict__ roww,
-                                               int* off, long long* woff) {
-  __shared__ int cs[NT / 64];
-  __shared__ long long ws[NT / 64];
+__device__ __forceinline__ int fold_rows(int nrt, const int* __restrict__ count, const int* __restrict__ roww,
+                                         int* off, int* woff) {
+  __shared__ int cs[NT / 64], ws[NT / 64];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   for (int r = tid; r < nrt; r += NT) {
     off[r] = count[r];
@@ -690,22 +683,12 @@ __device__ __forceinline__ long long fold_rows(int nrt, const int* __restrict__ 
   }
   __syncthreads();
   const int per = cdiv(nrt, NT), r0 = min(tid * per, nrt), r1 = min(r0 + per, nrt);
-  int c = 0;
-  long long v = 0;
+  int c = 0, v = 0;
   for (int r = r0; r < r1; ++r) {
     c += off[r];
     v += woff[r];
   }
-  int xc = c;
-  long long xv = v;
-  for (int o = 1; o < 64; o <<= 1) {
-    const int yc = __shfl_up(xc, o, 64);
-    const long long yv = __shfl_up(xv, o, 64);
-    if (lane >= o) {
-      xc += yc;
-      xv += yv;
-    }
-  }
+  int xc = warp_prefix(c), xv = warp_prefix(v);
   if (lane == 63) {
     cs[w] = xc;
     ws[w] = xv;
@@ -713,7 +696,7 @@ __device__ __forceinline__ long long fold_rows(int nrt, const int* __restrict__ 
   __syncthreads();
   xc -= c;
   xv -= v;
-  long long total = 0;
+  int total = 0;
   for (int k = 0; k < NT / 64; ++k) {
     if (k < w) {
       xc += cs[k];
@@ -722,8 +705,7 @@ __device__ __forceinline__ long long fold_rows(int nrt, const int* __restrict__ 
     total += ws[k];
   }
   for (int r = r0; r < r1; ++r) {
-    const int cr = off[r];
-    const long long vr = woff[r];
+    const int cr = off[r], vr = woff[r];
     off[r] = xc;
     woff[r] = xv;
     xc += cr;
@@ -775,14 +757,14 @@ __global__ __launch_bounds__(NT) void plan_wunit_fold_kernel(int nrt, int nch, i
                                                              const uint32_t* __restrict__ list, const int* roww,
                                                              int* unit_off, int* wunit, int2* wrows) {
   __shared__ int off[kFoldRows];
-  __shared__ long long woff[kFoldRows];
+  __shared__ int woff[kFoldRows];
   const long long wtot = fold_rows<NT>(nrt, count, roww, off, woff);
   if (blockIdx.x == 0)
     for (int r = threadIdx.x; r < nrt; r += NT) unit_off[r] = off[r];
   const int b = blockIdx.x * (NT / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (b > nw) return;
-  const long long t = wtot * wave_weight_below(b, wround) / wave_weight_below(nw, wround);
+  const int t = (int)(wtot * wave_weight_below(b, wround) / wave_weight_below(nw, wround));
   const int r = wave_last_at_most(woff, nrt, t, lane), cnt = count[r];
   const int u = off[r] + units_before(list + (size_t)r * nch, cnt, t - woff[r], lane);
   const int ru = wave_last_at_most(off, nrt, u, lane);
@@ -1032,18 +1014,14 @@ __device__ __forceinline__ void plan_small_body(SmallLds& L, int n, const float*
       const unsigned long long bal = __ballot(mask != 0u);
       const uint32_t e = (uint32_t)c | (mask << 16);
       const int cost = mask ? unit_cost(e) : 0;
-      int x = cost;
-      for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
-      }
+      const int x = warp_prefix(cost);
       if (mask) {
         const int k = base + __popcll(bal & ((1ull << lane) - 1ull));
         out[k] = e;
         L.plan.cost[r][k] = (unsigned short)(before + x - cost);
       }
       base += __popcll(bal);
-      before += __shfl(x, 63, 64);
+      before += __builtin_amdgcn_readlane(x, 63);
     }
     if (lane == 0) {
       P.count[r] = L.plan.count[r] = base;
@@ -1057,15 +1035,8 @@ __device__ __forceinline__ void plan_small_body(SmallLds& L, int n, const float*
   int wtot;
   {
     const int c = lane < nrt ? L.plan.count[lane] : 0, v = lane < nrt ? L.plan.roww[lane] : 0;
-    int xc = c, xv = v;
-    for (int o = 1; o < 64; o <<= 1) {
-      const int yc = __shfl_up(xc, o, 64), yv = __shfl_up(xv, o, 64);
-      if (lane >= o) {
-        xc += yc;
-        xv += yv;
-      }
-    }
-    wtot = __shfl(xv, 63, 64);
+    const int xc = warp_prefix(c), xv = warp_prefix(v);
+    wtot = __builtin_amdgcn_readlane(xv, 63);
     if (w == 0 && lane < nrt) {
       L.plan.off[lane] = xc - c;
       L.plan.woff[lane] = xv - v;
