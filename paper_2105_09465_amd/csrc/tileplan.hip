@@ -750,7 +750,8 @@ __device__ __forceinline__ int2 boundary_rows(const int* off, int nrt, int u) {
 // to a thread (512 threads past kFewRows row tiles; below, the larger workgroups take
 // longer to start: 5.8 us instead of 5.3 at 88 row tiles), and the searches look at 64
 // entries at a time. 4.5 us at 88 row tiles, 7.6 at 625 and 8.6 at 2500, where 256
-// threads, binary searches and lists read 64 units at a time took 5.0, 9.6 and 14.1.
+// threads, binary searches and lists read 64 units at a time took 5.0, 9.6 and 14.1;
+// with the prefixes by DPP 6.5 at 625.
 constexpr int kFewRows = 256;
 template <int NT>
 __global__ __launch_bounds__(NT) void plan_wunit_fold_kernel(int nrt, int nch, int nw, int wround, const int* count,
@@ -905,7 +906,8 @@ union SmallLds {
 // along the digits, the groups of each in turn, gives every group's first position of a
 // digit. Bound by the issue of one compute unit: two sets of 4,096 and 576 points take
 // 26.4 us (28.9 with 12 bits a pass, 80 KB of counters cleared for each and the rounds
-// ranked in turn), 576 points 16 us either way.
+// ranked in turn). The whole plan of 576 points takes 14.2 us, 16.0 before the prefixes
+// were taken by DPP.
 __device__ __forceinline__ const unsigned short* small_order(SmallLds& L, int n,
                                                              unsigned short (&val)[2][kSmallPoints], int* ws) {
   constexpr int kWaves = kSortThreads / 64;

@@ -23,7 +23,7 @@
 // small steps is joined: every layer's launches are one, clears and per-point steps
 // ride on a launch that touches the same points, and partial sums are folded where
 // they are used: 23 launches for 57, 853 -> 579 us a step at 40,000 traced points, three
-// layers and a 40 x 40 grid, 18 for 44 and 222 -> 149 us at 4,096 points (480 and 139
+// layers and a 40 x 40 grid, 18 for 44 and 222 -> 149 us at 4,096 points (480 and 138
 // with what the products and the sorts have gained since).
 //
 // Each layer takes two passes over its pairs, not four. The adjoint of T_k y
