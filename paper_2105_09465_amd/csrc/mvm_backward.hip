@@ -19,9 +19,13 @@
 // stay in registers. They are FP64 moments of K s about the row tile's first
 // point, sum K s (1, x_j, y_j, x_j^2 + y_j^2), from which dF/dp_i, dF/dl and dF/da of
 // a row follow at the end: one conversion and four FP64 operations a pair (the
-// differences in FP64 would take three more conversions), with nothing lost (the
-// moments cancel by the ratio of the tile's extent to the pair distance, squared
-// at most: some 1e4 of FP64's 1e16).
+// differences in FP64 take three more conversions).
+//
+// The moments cancel: their sum of K s d^2 has an error of some 2^-53 E^2 sum |K s| for
+// a tile of extent E, against terms of l^2 sum |K s|. Up to E^2 s2 = kWideTile = 2^20
+// (E some 1,200 l) that is 2^-33 of the sum, below the terms' own FP32 rounding; a
+// wider tile (a point of its own far away, two clusters that share a tile, a
+// non-finite coordinate, whose box is infinite) adds up the differences.
 //
 // Bound by VALU issue (six FP32, one exp, one conversion and four FP64
 // instructions a pair) beside 9 MFMAs for 256 pairs at 17 columns: 91 us at 40,000
@@ -40,6 +44,7 @@ namespace gpl {
 constexpr int kMaxPass = 18;  // column pairs per pass
 constexpr float kSkipBackward = kSkipFp32;
 constexpr int kBwdSums = 4;   // sums of a row: gx, gy (without -1/l^2), K s d^2, K s
+constexpr double kWideTile = 1 << 20;  // extent^2 s2 of a row tile from which differences are summed
 
 // MFMA steps of a pass of nc column pairs: step s of lane group g takes entry
 // g S + s of the 2 nc entries of P and Q (zero padded to 4 S).
@@ -111,6 +116,70 @@ __global__ __launch_bounds__(256) void bwd_gather_kernel(int n, int npad, int nc
   }
 }
 
+// A row tile's sums over the list positions [kb, ke): of K s, and its moments about
+// (cx, cy) or (kWide) its products with the differences.
+template <int S, bool kWide>
+__device__ __forceinline__ void bwd_accumulate(const TilePlan& T, float s2, const float* __restrict__ Q,
+                                               const uint32_t* __restrict__ lst, int kb, int ke,
+                                               const float (&xi)[kSubsPerTile], const float (&yi)[kSubsPerTile],
+                                               const float (&pf)[kSubsPerTile][S], double cx, double cy,
+                                               double (&s0)[kSubsPerTile], double (&sx)[kSubsPerTile],
+                                               double (&sy)[kSubsPerTile], double (&sr)[kSubsPerTile]) {
+  constexpr int stride = bwd_stride(S);
+  const int lane = threadIdx.x & 63, ri = lane & 15, g = lane >> 4;
+#pragma unroll 1
+  for (int k0 = kb; k0 < ke; k0 += 64) {
+    const int m = min(64, ke - k0);
+    const int vidx = lane < m ? (int)lst[k0 + lane] : 0;
+#pragma unroll 1
+    for (int q = 0; q < m; ++q) {
+      const uint32_t e = (uint32_t)__builtin_amdgcn_readlane(vidx, q);
+      const unsigned mask = entry_mask(e);
+#pragma unroll
+      for (int h = 0; h < kChunk / 16; ++h) {
+        const int j0 = entry_chunk(e) * kChunk + h * 16;
+        float qf[S];
+        bwd_load<S>(qf, Q + bwd_at(j0 + ri, g, stride));
+        const bwd_f4 xj = *reinterpret_cast<const bwd_f4*>(&T.xs[j0 + 4 * g]);
+        const bwd_f4 yj = *reinterpret_cast<const bwd_f4*>(&T.ys[j0 + 4 * g]);
+        double X[4], Y[4], R[4];
+        if (!kWide) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            X[v] = (double)xj[v] - cx;
+            Y[v] = (double)yj[v] - cy;
+            R[v] = fma(X[v], X[v], Y[v] * Y[v]);
+          }
+        }
+#pragma unroll
+        for (int t = 0; t < kSubsPerTile; ++t) {
+          if (!((mask >> t) & 1u)) continue;
+          bwd_f4 sd = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int s = 0; s < S; ++s) sd = __builtin_amdgcn_mfma_f32_16x16x4f32(qf[s], pf[t][s], sd, 0, 0, 0);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const float dx = xi[t] - xj[v], dy = yi[t] - yj[v];
+            const float d2 = fmaf(dx, dx, dy * dy);
+            const double kt = (double)(exp2_fast(-(d2 * s2)) * sd[v]);
+            s0[t] += kt;
+            if (kWide) {
+              const double DX = dx, DY = dy;
+              sx[t] = fma(kt, DX, sx[t]);
+              sy[t] = fma(kt, DY, sy[t]);
+              sr[t] = fma(kt, fma(DX, DX, DY * DY), sr[t]);
+            } else {
+              sx[t] = fma(kt, X[v], sx[t]);
+              sy[t] = fma(kt, Y[v], sy[t]);
+              sr[t] = fma(kt, R[v], sr[t]);
+            }
+          }
+        }
+      }
+    }
+  }
+}
+
 // One wave's share of the plan (as the product's waves): per row tile it touches,
 // part[slot][kBwdSums][64 rows].
 template <int S>
@@ -133,53 +202,14 @@ __global__ __launch_bounds__(256, 3) void mvm_bwd_kernel(const TilePlan T, float
       yi[t] = T.ys[i];
       bwd_load<S>(pf[t], P + bwd_at(i, g, stride));
     }
-    // (a non-finite first point must not reach the other rows through the centre)
-    const float fx = T.xs[r * kRowTile], fy = T.ys[r * kRowTile];
-    const double cx = isfinite(fx) ? (double)fx : 0.0, cy = isfinite(fy) ? (double)fy : 0.0;
+    const float4 q0 = T.cbox[kChunksPerTile * r], q1 = T.cbox[kChunksPerTile * r + 1];
+    const double ex = (double)fmaxf(q0.y, q1.y) - fminf(q0.x, q1.x), ey = (double)fmaxf(q0.w, q1.w) - fminf(q0.z, q1.z);
+    const bool wide = __builtin_amdgcn_readfirstlane(fma(ex, ex, ey * ey) * s2 <= kWideTile ? 0 : 1);
+    const double cx = wide ? 0.0 : (double)T.xs[r * kRowTile], cy = wide ? 0.0 : (double)T.ys[r * kRowTile];
     double s0[kSubsPerTile] = {}, sx[kSubsPerTile] = {}, sy[kSubsPerTile] = {}, sr[kSubsPerTile] = {};
     const uint32_t* lst = T.list + (size_t)r * T.nch;
-#pragma unroll 1
-    for (int k0 = kb; k0 < ke; k0 += 64) {
-      const int m = min(64, ke - k0);
-      const int vidx = lane < m ? (int)lst[k0 + lane] : 0;
-#pragma unroll 1
-      for (int q = 0; q < m; ++q) {
-        const uint32_t e = (uint32_t)__builtin_amdgcn_readlane(vidx, q);
-        const unsigned mask = entry_mask(e);
-#pragma unroll
-        for (int h = 0; h < kChunk / 16; ++h) {
-          const int j0 = entry_chunk(e) * kChunk + h * 16;
-          float qf[S];
-          bwd_load<S>(qf, Q + bwd_at(j0 + ri, g, stride));
-          const bwd_f4 xj = *reinterpret_cast<const bwd_f4*>(&T.xs[j0 + 4 * g]);
-          const bwd_f4 yj = *reinterpret_cast<const bwd_f4*>(&T.ys[j0 + 4 * g]);
-          double X[4], Y[4], R[4];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            X[v] = (double)xj[v] - cx;
-            Y[v] = (double)yj[v] - cy;
-            R[v] = fma(X[v], X[v], Y[v] * Y[v]);
-          }
-#pragma unroll
-          for (int t = 0; t < kSubsPerTile; ++t) {
-            if (!((mask >> t) & 1u)) continue;
-            bwd_f4 sd = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int s = 0; s < S; ++s) sd = __builtin_amdgcn_mfma_f32_16x16x4f32(qf[s], pf[t][s], sd, 0, 0, 0);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              const float dx = xi[t] - xj[v], dy = yi[t] - yj[v];
-              const float d2 = fmaf(dx, dx, dy * dy);
-              const double kt = (double)(exp2_fast(-(d2 * s2)) * sd[v]);
-              s0[t] += kt;
-              sx[t] = fma(kt, X[v], sx[t]);
-              sy[t] = fma(kt, Y[v], sy[t]);
-              sr[t] = fma(kt, R[v], sr[t]);
-            }
-          }
-        }
-      }
-    }
+    if (wide) bwd_accumulate<S, true>(T, s2, Q, lst, kb, ke, xi, yi, pf, cx, cy, s0, sx, sy, sr);
+    else bwd_accumulate<S, false>(T, s2, Q, lst, kb, ke, xi, yi, pf, cx, cy, s0, sx, sy, sr);
     // over the four lane groups; lane 16 t + ri then ends row 16 t + ri
     double m0 = 0.0, mx = 0.0, my = 0.0, mr = 0.0;
     auto fold = [](double v) {
@@ -197,9 +227,9 @@ __global__ __launch_bounds__(256, 3) void mvm_bwd_kernel(const TilePlan T, float
       if (g == t) xo = xi[t], yo = yi[t];
     const double x = (double)xo - cx, y = (double)yo - cy;
     double* out = part + (size_t)slot * kBwdSums * kRowTile + lane;
-    out[0] = x * m0 - mx;
-    out[kRowTile] = y * m0 - my;
-    out[2 * kRowTile] = fma(fma(x, x, y * y), m0, mr) - 2.0 * fma(x, mx, y * my);
+    out[0] = wide ? mx : x * m0 - mx;
+    out[kRowTile] = wide ? my : y * m0 - my;
+    out[2 * kRowTile] = wide ? mr : fma(fma(x, x, y * y), m0, mr) - 2.0 * fma(x, mx, y * my);
     out[3 * kRowTile] = m0;
     if (rest <= 0) break;
     ++r;
