@@ -129,7 +129,7 @@ class RayTrace(torch.autograd.Function):
 
 
 class KernelMVM(torch.autograd.Function):
-    """(px, py, V (ncols, N), hyper (2,) = (lengthscale, amplitude)) -> K V."""
+    """(px, py (N points, any shape), V (ncols, N), hyper (2,) = (lengthscale, amplitude)) -> K V."""
 
     @staticmethod
     def forward(ctx, px, py, V, hyper, prec="fp32"):
@@ -144,7 +144,7 @@ class KernelMVM(torch.autograd.Function):
         gY = gY.contiguous()
         gpx, gpy, gV, ghyp = ops.kernel_mvm_vjp(ctx.kern, px.contiguous(), py.contiguous(), V.contiguous(), gY,
                                                 prec=ctx.prec)
-        return gpx, gpy, gV, ghyp.to(ctx.hdtype), None
+        return gpx.view(px.shape), gpy.view(py.shape), gV, ghyp.to(ctx.hdtype), None
 
 
 class PSFConv(torch.autograd.Function):

@@ -392,21 +392,23 @@ def kernel_mvm_backward(kernel: Kernel, px, py, A, Bv, weights, gpx=None, gpy=No
 
 def kernel_mvm_vjp(kernel: Kernel, px, py, V, gY, prec="fp32"):
     """Backward pass of Y = K V for dF/dY = gY: (gpx, gpy, gV, (dF/d lengthscale,
-    dF/d amplitude) as float64), over one plan of the points."""
+    dF/d amplitude) as float64), over one plan of the points; gpx and gpy are
+    rows of n, as the points are read."""
     n = px.numel()
     ldv, ldg = _block(V, n, "V"), _block(gY, n, "gY")
     ncols = V.shape[0]
     if gY.shape[0] != ncols:
         raise ValueError("V and gY must have the same number of columns")
     gV = torch.empty(ncols, n, dtype=torch.float32, device=V.device)
-    gp = torch.empty(2, n, dtype=torch.float32, device=px.device)
+    gpx = torch.empty(n, dtype=torch.float32, device=px.device)
+    gpy = torch.empty(n, dtype=torch.float32, device=px.device)
     ghyp = torch.empty(2, dtype=torch.float64, device=px.device)
     pc = prec_code(prec)
     ws, wsb = workspace(_lib.lib.gpl_gp_kernel_mvm_vjp_workspace(n, ncols, pc), px.device)
     k = kernel.c()
     _lib.call("gpl_gp_kernel_mvm_vjp", C.byref(k), n, _ptr(px), _ptr(py), ncols, _ptr(V), ldv, _ptr(gY), ldg, _ptr(gV),
-              n, _ptr(gp[0]), _ptr(gp[1]), _ptr(ghyp), pc, _wsptr(ws), wsb, _stream())
-    return gp[0], gp[1], gV, ghyp
+              n, _ptr(gpx), _ptr(gpy), _ptr(ghyp), pc, _wsptr(ws), wsb, _stream())
+    return gpx, gpy, gV, ghyp
 
 
 def lens_raytrace_backward(grid: Grid, lens: Lens, gpx, gpy):
