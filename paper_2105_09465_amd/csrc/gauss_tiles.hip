@@ -10,7 +10,7 @@
 // e has at least g^2 / (base + the largest e^T Z e of both boxes' shapes) for every
 // pair in it, and g^2 / lambda for its gap in the plane, lambda the largest eigenvalue.
 // v_exp_f32 returns zero below an argument of -126.5, so a 16-target x 32-source pair
-// of boxes where (log2(e)/2) times one of these reaches 127 holds exact zeros only and
+// of boxes where (log2(e)/2) times one of these exceeds 127 holds exact zeros only and
 // is not evaluated: the sum over the rest is the sum over all pairs up to its order.
 // Directions: the axes and the diagonals (traced pixels are long and thin where the
 // image is magnified; with the eigenvalue alone, 15% of the pairs of 40,000 traced
@@ -116,17 +116,19 @@ __device__ __forceinline__ float4 diagonal_box(float x, float y, bool live) {
 }
 
 // Are all pairs of two boxes exact zeros? a, b: the boxes, da, db: along the
-// diagonals; r: base plus the reaches of both (kAxes 0: r.lam alone is looked at).
+// diagonals; r: base plus the reaches of both (kAxes 0: r.lam alone is looked at). An
+// infinite reach (something not finite) is never left out, also where a squared gap
+// overflows: so no pair at equality.
 template <bool kAxes>
 __device__ __forceinline__ bool boxes_zero(const float4& a, const float4& da, const float4& b, const float4& db,
                                            const Reach& r) {
   const float gx = fmaxf(0.f, fmaxf(b.x - a.y, a.x - b.y)), gy = fmaxf(0.f, fmaxf(b.z - a.w, a.z - b.w));
   const float x2 = -kFormScale * (gx * gx), y2 = -kFormScale * (gy * gy);
-  bool zero = x2 + y2 >= kZeroArg * r.lam;
+  bool zero = x2 + y2 > kZeroArg * r.lam;
   if (kAxes) {
     const float gu = fmaxf(0.f, fmaxf(db.x - da.y, da.x - db.y)), gv = fmaxf(0.f, fmaxf(db.z - da.w, da.z - db.w));
-    zero = zero || x2 >= kZeroArg * r.dir.x || y2 >= kZeroArg * r.dir.y ||
-           -kFormScale * (gu * gu) >= kZeroArg * r.dir.z || -kFormScale * (gv * gv) >= kZeroArg * r.dir.w;
+    zero = zero || x2 > kZeroArg * r.dir.x || y2 > kZeroArg * r.dir.y ||
+           -kFormScale * (gu * gu) > kZeroArg * r.dir.z || -kFormScale * (gv * gv) > kZeroArg * r.dir.w;
   }
   return zero;
 }
