@@ -266,9 +266,10 @@ __device__ __forceinline__ float adjoint_point(const VLayerAdj& L, int j, float 
 // sum G C^{-1} (t - q) to their positions (the sums hold kFormScale C^{-1} (q - t)), and
 // norm y_j sum G to the weights. Weights w_j = r_j sqrt(pi / k) (rho^{-1/2}, rho = k /
 // (pi r^2)), r_j = |q_j - q_nn(j)|: dF/dq_j += coef v, dF/dq_nn(j) -= coef v with
-// v = q_j - q_nn(j), coef = gw_j w_j / r_j^2; the neighbour's share is scattered with
-// FP64 atomic adds into gq (2n doubles: x then y). blockIdx.y 1: the source-plane layer,
-// dE/dC[:, b] = g_y e_l[b].
+// v = q_j - q_nn(j), coef = gw_j w_j / r_j^2; both shares are scattered with FP64 atomic
+// adds into gq (2n doubles: x then y), so that a point's shares, which may cancel, are
+// rounded to FP32 once, as their sum (its own rounded by itself saves 1 us a step).
+// blockIdx.y 1: the source-plane layer, dE/dC[:, b] = g_y e_l[b].
 __global__ __launch_bounds__(256) void vigp_adjoint_kernel(VAdj A, const double* __restrict__ e_l) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (blockIdx.y == 1) {
@@ -302,10 +303,10 @@ __global__ __launch_bounds__(256) void vigp_adjoint_kernel(VAdj A, const double*
   if (o >= 0 && r > 0.f) {
     const double coef = (double)gw * (double)wj / ((double)r * (double)r);
     const double vx = coef * (double)(A.px[j] - A.px[o]), vy = coef * (double)(A.py[j] - A.py[o]);
+    atomicAdd(A.gq + j, vx);
+    atomicAdd(A.gq + n + j, vy);
     atomicAdd(A.gq + o, -vx);
     atomicAdd(A.gq + n + o, -vy);
-    gx += (float)vx;
-    gy += (float)vy;
   }
   A.gpx[j] = gx;
   A.gpy[j] = gy;
