@@ -618,7 +618,8 @@ struct OrderedBufs {
   float4 *src, *box, *cdiag;  // sources, and the boxes of their chunks
   float4 *sdiag, *sdir;       // per 16 targets: diagonal box and reach of their shapes
   float* slam;
-  int* far;
+  int* far;                   // the listed targets
+  unsigned* sfar;             // per 16 targets: which of them are listed (the one decision on it)
   float* part;
 };
 struct OrderedArgs {
@@ -647,19 +648,22 @@ __global__ __launch_bounds__(256) void ordered_prep_kernel(OrderedArgs A) {
   const int j = blockIdx.x * 256 + threadIdx.x, npad = round_up(n, kOChunk);
   if (L.shapes && j < A.T.nch * kChunk) {
     Reach r = all_reach(0.f);
-    bool live = j < A.T.n;
+    bool live = j < A.T.n, listed = false;
     if (live) {
       const int jj = A.T.perm[j];
       r = shape_reaches(tz[jj], tz[A.T.n + jj], tz[2 * (size_t)A.T.n + jj], L.base);
-      if (r.lam > kFarReach * L.base) {
+      listed = r.lam > kFarReach * L.base;
+      if (listed) {
         L.b.far[atomicAdd(L.far_count, 1)] = j;
         r = all_reach(0.f);
         live = false;
       }
     }
+    const unsigned long long bal = __ballot(listed);
     r = join_reach<kSubTile>(r);
     const float4 q = diagonal_box<kSubTile>(A.T.x[j], A.T.y[j], live);
     if ((j & (kSubTile - 1)) == 0) {
+      L.b.sfar[j / kSubTile] = (unsigned)(bal >> (j & 63)) & ((1u << kSubTile) - 1u);
       L.b.slam[j / kSubTile] = r.lam;
       L.b.sdir[j / kSubTile] = r.dir;
       L.b.sdiag[j / kSubTile] = q;
@@ -785,7 +789,7 @@ __device__ __forceinline__ void gauss_ordered_body(const GSorted& T, int tiles, 
     txx = tz[ii];
     txy = tz[T.n + ii];
     tyy = tz[2 * (size_t)T.n + ii];
-    if (shape_reach(txx, txy, tyy, base) > kFarReach * base) live = false;  // listed
+    if ((b.sfar[tile] >> (lane >> 2)) & 1u) live = false;  // listed
     rd = b.sdiag[tile];
     r = add_reach(base, b.sdir[tile], b.slam[tile], make_float4(0.f, 0.f, 0.f, 0.f), 0.f);
   }
@@ -883,6 +887,7 @@ static void carve_ordered(C& cv, int nt, const int* ns, int nl, OrderedBufs* b) 
     b[k].sdir = cv.template take<float4>(subs);
     b[k].slam = cv.template take<float>(subs);
     b[k].far = cv.template take<int>(nt);
+    b[k].sfar = cv.template take<unsigned>(subs);
     b[k].part = cv.template take<float>((size_t)kOWaves * 6 * round_up(nt, kRowTile));
   }
 }
