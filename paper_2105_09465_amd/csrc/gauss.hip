@@ -6,12 +6,10 @@
 //   d = t_i - s_j,  C_ij = Zt_i + Zs_j + base_var I  (2 x 2),
 // over target points t and source points s, each optionally with a shape
 // covariance Z (three floats: xx, xy, yy) and a weight w. A workgroup owns 64
-// targets (one per lane) and runs 16 waves, each over its own sixteenth of the
+// targets (one per lane) and runs 8 or 16 waves, each over its own share of the
 // sources, staged 64 at a time in that wave's share of LDS with their
 // right-hand-side rows; the partial sums are added in wave order at the end
-// (deterministic). At the sizes these kernels serve the waves of a workgroup are the
-// parallelism there is: 4,096 targets are 64 workgroups (8 waves: 4,096 points 29.1 us
-// for 25.0 with 16, 5,184 38.9 for 35.5, 40,000 610 for 585). The Gaussian entries are evaluated in FP32 on the fly and never
+// (deterministic). The Gaussian entries are evaluated in FP32 on the fly and never
 // stored. Dense over all pairs (every pair is evaluated).
 #include <cmath>
 
@@ -23,7 +21,7 @@
 namespace gpl {
 
 constexpr int kGRows = 64;   // targets per workgroup (one per lane)
-constexpr int kGWaves = 16;  // waves per workgroup, each over its own share of the sources
+constexpr int kGWaves = 16;  // waves per workgroup of the adjoint, each over its own share of the points
 constexpr int kGThreads = kGRows * kGWaves;
 constexpr int kGCols = 8;    // right-hand-side columns per pass
 
@@ -37,22 +35,22 @@ __device__ inline float gauss_pair(float dx, float dy, float cxx, float cxy, flo
 // 64-point steps of each wave's share of n points: every wave runs the same
 // number of steps (so the workgroup barriers are uniform); steps past the end
 // are empty.
-__device__ inline int wave_steps(int n) { return cdiv(cdiv(n, 64), kGWaves); }
+__host__ __device__ inline int wave_steps(int n, int waves = kGWaves) { return cdiv(cdiv(n, 64), waves); }
 
 // Shapes on at most one side (kMode 1: targets, or none; kMode 2: sources)
 // make C_ij a per-point constant whose inverse and determinant are formed once
 // per point; kMode 0 (shapes on both sides, the windowed kernel) forms them per
 // pair. NC: right-hand-side columns held per pass (1 or kGCols).
-template <int kMode, int NC>
-__global__ __launch_bounds__(kGThreads) void gauss_product_kernel(GSide T, GSide S, float base, float norm, int nc,
+template <int kMode, int NC, int kWaves>
+__global__ __launch_bounds__(kGRows * kWaves) void gauss_product_kernel(GSide T, GSide S, float base, float norm, int nc,
                                                                   const float* __restrict__ V, int ldv, float* Y,
                                                                   int ldy, float beta) {
   // per source: x, y, then (kMode 0) zxx, zxy, zyy and w, or (kMode 2) the
   // inverse ixx, ixy, iyy and w |C|^{-1/2}, or (kMode 1) w
-  __shared__ float sx[kGWaves][64], sy[kGWaves][64], sa[kGWaves][64], sb[kGWaves][64], sc[kGWaves][64],
-      sw[kGWaves][64];
-  __shared__ float sv[kGWaves][NC][64];
-  __shared__ float red[kGWaves - 1][NC][64];
+  __shared__ float sx[kWaves][64], sy[kWaves][64], sa[kWaves][64], sb[kWaves][64], sc[kWaves][64],
+      sw[kWaves][64];
+  __shared__ float sv[kWaves][NC][64];
+  __shared__ float red[kWaves - 1][NC][64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int i = blockIdx.x * kGRows + lane;
   const bool live = i < T.n;
@@ -72,7 +70,7 @@ __global__ __launch_bounds__(kGThreads) void gauss_product_kernel(GSide T, GSide
   float acc[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) acc[c] = 0.f;
-  const int steps = wave_steps(S.n);
+  const int steps = wave_steps(S.n, kWaves);
   for (int st = 0; st < steps; ++st) {
     const int j0 = (wv * steps + st) * 64;
     __syncthreads();
@@ -120,7 +118,7 @@ __global__ __launch_bounds__(kGThreads) void gauss_product_kernel(GSide T, GSide
     for (int c = 0; c < NC; ++c) red[wv - 1][c][lane] = acc[c];
   __syncthreads();
   if (wv > 0 || !live) return;
-  for (int w = 0; w < kGWaves - 1; ++w)
+  for (int w = 0; w < kWaves - 1; ++w)
 #pragma unroll
     for (int c = 0; c < NC; ++c) acc[c] += red[w][c][lane];
   const float f = norm * (T.w ? T.w[i] : 1.f) * rdet;
@@ -344,27 +342,43 @@ int pixel_shapes_backward_launch(int M, const float* px, const float* py, const 
   return GPL_OK;
 }
 
+// Waves of a product's workgroups. A single round of workgroups leaves the waves of a
+// workgroup as the parallelism there is, so 16 of them where they run their steps of 64
+// sources in so many fewer that it pays: a step of 16 takes 1.65 times as long as one of 8,
+// with shapes of the sources and many columns 1.76, on both sides 1.88 (16,384 targets,
+// one column, shapes of the targets, us with 8 and 16: 1,024 sources 10.0 and 9.6, 2,500
+// 20.3 and 18.9, 10,000 70 and 57; three columns, shapes on both sides: 256 sources 11.8
+// and 13.6, 2,500 59 and 63, 10,000 215 and 203). Further rounds keep the chip busy with 8
+// waves, which leave room for more workgroups on a compute unit (three for one of 16 with
+// many columns): 40,000 targets and 2,500 sources 65 and 79 us with three columns. With
+// one column 16 are as good up to 40,960 targets (4,096 sources 64 and 59), and 400,000
+// targets and 256 sources take 37 and 53.
+static bool sixteen_waves(int mode, int nt, int ns, bool many) {
+  const double longer = !many || mode == 1 ? 1.65 : mode == 2 ? 1.76 : 1.88;
+  return nt <= (many ? 16384 : 40960) && wave_steps(ns, 16) * longer <= wave_steps(ns, 8);
+}
+
+template <int kMode, int NC>
+static void launch_product(bool wide, const GSide& T, const GSide& S, float base, float norm, int nc, const float* V,
+                           int ldv, float* Y, int ldy, float beta, hipStream_t stream) {
+  const auto kern = wide ? gauss_product_kernel<kMode, NC, 16> : gauss_product_kernel<kMode, NC, 8>;
+  hipLaunchKernelGGL(kern, dim3(cdiv(T.n, kGRows)), dim3(kGRows * (wide ? 16 : 8)), 0, stream, T, S, base, norm, nc, V,
+                     ldv, Y, ldy, beta);
+}
+
 int gauss_product_launch(const GSide& T, const GSide& S, double base_var, double norm, int nrhs, const float* V,
                          int ldv, float* Y, int ldy, float beta, hipStream_t stream) {
-  const dim3 grid(cdiv(T.n, kGRows));
   const int mode = S.z == nullptr ? 1 : (T.z == nullptr ? 2 : 0);
   for (int c0 = 0; c0 < nrhs; c0 += kGCols) {
     const int nc = std::min(kGCols, nrhs - c0);
-    const float *v = V + (size_t)c0 * ldv;
-    float* y = Y + (size_t)c0 * ldy;
+    const bool wide = sixteen_waves(mode, T.n, S.n, nc > 1);
     const float b = (float)base_var, nm = (float)norm;
-#define GPL_GAUSS_LAUNCH(M, C) \
-  hipLaunchKernelGGL((gauss_product_kernel<M, C>), grid, dim3(kGThreads), 0, stream, T, S, b, nm, nc, v, ldv, y, ldy, beta)
-    if (nc == 1) {
-      if (mode == 0) GPL_GAUSS_LAUNCH(0, 1);
-      else if (mode == 1) GPL_GAUSS_LAUNCH(1, 1);
-      else GPL_GAUSS_LAUNCH(2, 1);
-    } else {
-      if (mode == 0) GPL_GAUSS_LAUNCH(0, kGCols);
-      else if (mode == 1) GPL_GAUSS_LAUNCH(1, kGCols);
-      else GPL_GAUSS_LAUNCH(2, kGCols);
-    }
-#undef GPL_GAUSS_LAUNCH
+    const auto launch =
+        nc == 1 ? (mode == 0 ? launch_product<0, 1> : mode == 1 ? launch_product<1, 1> : launch_product<2, 1>)
+                : (mode == 0   ? launch_product<0, kGCols>
+                   : mode == 1 ? launch_product<1, kGCols>
+                               : launch_product<2, kGCols>);
+    launch(wide, T, S, b, nm, nc, V + (size_t)c0 * ldv, ldv, Y + (size_t)c0 * ldy, ldy, beta, stream);
     GPL_LAUNCH_CHECK();
   }
   return GPL_OK;
@@ -397,7 +411,7 @@ extern "C" int gpl_gauss_product_ws(const gpl_gauss* g, int nt, const float* tx,
   GPL_REQUIRE(ldv >= ns && ldy >= nt, "ldv=%d (>= %d) / ldy=%d (>= %d)", ldv, ns, ldy, nt);
   GPL_REQUIRE(V != Y, "V and Y must not overlap");
   const GSide T{tx, ty, tz, tw, nt}, S{sx, sy, sz, sw, ns};
-  if (ws != nullptr && gauss_pair_sorted(nt, ns, tz && sz))
+  if (ws != nullptr && gauss_pair_sorted(T, S, nrhs))
     return gauss_pair_product(T, S, g->base_var, g->norm, nrhs, V, ldv, Y, ldy, beta, ws, ws_bytes, stream);
   return gauss_product_launch(T, S, g->base_var, g->norm, nrhs, V, ldv, Y, ldy, beta, stream);
 }

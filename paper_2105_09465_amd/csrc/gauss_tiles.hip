@@ -48,12 +48,8 @@ constexpr int kTBatch = 4;                     // box tests of a lane in a round
 constexpr int kTList = kTWaves * kTBatch * 64; // chunks tested per round
 constexpr float kZeroArg = 127.f;              // exp2(-kZeroArg) is exactly zero, with margin for rounding
 
-// Pairs from which a product of points in the caller's order is sorted first. One
-// column with shapes on one side: all pairs take 25 us for 4,096 traced points, 41 for
-// 6,400, 58 for 10,000 and 74 for 12,544, sorted 52, 55, 59 and 71. With shapes on both
-// sides a pair costs more and a sorted product does less of it: A on the windowed
-// kernel and three columns takes 50 us for 1,296 points either way, for 2,304 67 all
-// pairs and 58 sorted, for 5,184 139 and 79.
+// Pairs below which a product of points in the caller's order is never sorted first
+// (shapes on one side or none, on both); above them gauss_pair_sorted weighs the two.
 constexpr long long kSortedPairs = 3LL << 25, kSortedPairsBoth = 1LL << 22;
 constexpr int kEntryShift = 28;                // list entries: chunk below, subtile mask above
 constexpr uint32_t kEntryChunk = (1u << kEntryShift) - 1u;
@@ -943,12 +939,37 @@ static void carve_pair(C& cv, int nt, int ns, bool same, int cols, TilePlan& pt,
   rest = cv.template take<char>(bytes);
 }
 
-bool gauss_pair_sorted(int nt, int ns, bool both) {
-  return (long long)nt * ns >= (both ? kSortedPairsBoth : kSortedPairs);
+// Whether a product is sorted first: whether the sorts of its points cost less than all
+// pairs do. In us, fitted to sizes of 64 to 400,000 points on either side at l = 0.04
+// over a field of 5: all pairs go by 1,024 sources (by steps of 512 in a single round of
+// workgroups) for each 16,384 targets, and a set's sort costs by its points up to some
+// 5,600 and is bound by launches beyond. The long side counts as much as the number of
+// pairs. One column with shapes of the targets takes, all pairs and sorted, 57 and 64 us
+// for 10,000 points (one set), 90 and 70 for 16,384; for 40,000 targets 17 and 72 with
+// 1,024 sources, 59 and 87 with 4,096, 142 and 109 with 10,000; 116 and 183 for 400,000
+// and 1,024. With shapes on both sides and three columns: 56 and 40 for 2,500 (one set), 24
+// and 61 for 4,096 targets and 1,024 sources, 82 and 55 for 1,024 and 4,096; with eight 134
+// and 145 for 40,000 and 2,500. Where the
+// lengthscale is not small against the field fewer terms are zero: at l = 1 the sorted
+// product takes up to 1.4 times as long as all pairs near the line.
+static double sort_us(int n) { return std::min(5.0 + n / 160.0, 40.0) + 3.5e-4 * n; }
+
+bool gauss_pair_sorted(int nt, int ns, bool tshapes, bool sshapes, bool same, int nrhs) {
+  const bool both = tshapes && sshapes, many = nrhs > 1;
+  if ((long long)nt * ns < (both ? kSortedPairsBoth : kSortedPairs)) return false;
+  const double step = both ? (many ? 20.0 : 17.0) : sshapes ? (many ? 13.0 : 6.05) : (many ? 8.5 : 5.6);
+  const double rounds = nt / 16384.0, steps = nt <= 16384 ? 0.5 * cdiv(ns, 512)
+                                                          : ns / 1024.0 * ((!both && many ? 0.95 : 0.8) * rounds + 0.7);
+  double sorting = (tshapes ? 17.0 : 12.0) + sort_us(nt) + (same ? 0.0 : sort_us(ns)) + 2.5e-5 * nt * nrhs;
+  if (both)  // the passes of eight columns keep few waves on a compute unit
+    sorting += 2.5e-3 * std::min(nt, 16384) * (nrhs / 8 + (nrhs % 8 > 4 ? 1 : 0));
+  return step * steps * cdiv(nrhs, 8) > sorting;
 }
 
+// For any of its shapes: those on both sides of one set ask for the most and are sorted
+// wherever others are.
 size_t gauss_pair_workspace(int nt, int ns, bool same, int nrhs) {
-  if (nt <= 0 || ns <= 0 || nrhs <= 0 || !gauss_pair_sorted(nt, ns, true)) return 0;
+  if (nt <= 0 || ns <= 0 || nrhs <= 0 || !gauss_pair_sorted(nt, ns, true, true, true, nrhs)) return 0;
   Sizer s;
   TilePlan pt, ps;
   char* rest;
@@ -957,10 +978,16 @@ size_t gauss_pair_workspace(int nt, int ns, bool same, int nrhs) {
   return s.used;
 }
 
+static bool same_points(const GSide& T, const GSide& S) { return T.n == S.n && T.x == S.x && T.y == S.y; }
+
+bool gauss_pair_sorted(const GSide& T, const GSide& S, int nrhs) {
+  return gauss_pair_sorted(T.n, S.n, T.z != nullptr, S.z != nullptr, same_points(T, S), nrhs);
+}
+
 int gauss_pair_product(const GSide& T, const GSide& S, double base, double norm, int nrhs, const float* V, int ldv,
                        float* Y, int ldy, float beta, void* ws, size_t ws_bytes, hipStream_t stream,
                        const PlanSide* side) {
-  const bool same = T.n == S.n && T.x == S.x && T.y == S.y;  // one set of points: one sort
+  const bool same = same_points(T, S);  // one set of points: one sort
   Carver cv(ws, ws_bytes);
   TilePlan pt, ps;
   char* rest;

@@ -96,9 +96,9 @@ size_t gauss_ordered_scratch(int nt, const int* ns, int nl);
 int gauss_ordered_launch(const GSorted& T, const float* tz, const GaussLayer* layers, int nl, float* f, float* tg,
                          int* far_count, void* scratch, size_t bytes, hipStream_t stream);
 // The product from the caller's order: sorts the points in the workspace (0 bytes
-// where the dense product is the faster one, gauss_pair_sorted false with shapes on
-// both sides, which asks for the least).
-bool gauss_pair_sorted(int nt, int ns, bool both);
+// where none of these sizes is sorted).
+bool gauss_pair_sorted(int nt, int ns, bool tshapes, bool sshapes, bool same, int nrhs);
+bool gauss_pair_sorted(const GSide& T, const GSide& S, int nrhs);
 size_t gauss_pair_workspace(int nt, int ns, bool same, int nrhs);
 int gauss_pair_product(const GSide& T, const GSide& S, double base, double norm, int nrhs, const float* V, int ldv,
                        float* Y, int ldy, float beta, void* ws, size_t ws_bytes, hipStream_t stream,

@@ -156,7 +156,7 @@ int windowed_mvm(const gpl_kernel* kern, const gpl_grid* grid, int n, const floa
   const GSide side{px, py, z, nullptr, n};
   // the sorted product where it is the faster one and the workspace holds it
   const size_t used = align_up((size_t)3 * n * sizeof(float));
-  if (gauss_pair_sorted(n, n, true) && ws_bytes >= windowed_workspace(n, nrhs))
+  if (gauss_pair_sorted(side, side, nrhs) && ws_bytes >= windowed_workspace(n, nrhs))
     return gauss_pair_product(side, side, l2, kern->amplitude * kern->amplitude * l2, nrhs, V, ldv, Y, ldy, beta,
                               static_cast<char*>(ws) + used, ws_bytes - used, stream, &s);
   GPL_TRY(plan_side_launch(s, stream));
