@@ -495,7 +495,6 @@ int gauss_tiles_product(const GSorted& T, const float* tz, const float* tw, cons
 struct SumsArgs {
   GSorted S;
   const float *V, *sz;
-  int nl;
   struct {
     GSorted T;
     int tiles, slices, shapes;
@@ -554,7 +553,6 @@ int gauss_layers_sums(GaussLayerSums* layers, int nl, const GSorted& S, const fl
   A.S = S;
   A.V = V;
   A.sz = sz;
-  A.nl = nl;
   int blocks = 0, npad = S.nch * kChunk;
   for (int q = 0; q < nl; ++q) {
     GaussLayerSums& L = layers[turn[q]];

@@ -140,16 +140,13 @@ struct MvmCtx {
   float s2, amp2;
 };
 size_t mvm_workspace(int n, int nrhs, int prec);
-// zero_rhs: clear the RHS buffers (needed unless every product is an mvm_run,
-// which writes them whole, the padding included). V (nullable): the columns of the
-// first product, put into the buffers beside the plan for mvm_run_prepared; side
-// (nullable): see plan_build.
+// V (nullable): the columns of a product, put into the buffers for mvm_run_prepared, which
+// writes them whole, the padding included. zero_rhs: clear the buffers (needed where
+// others write them, who leave the padding as it is). side (nullable): see plan_build.
 int mvm_prepare(MvmCtx& m, double lengthscale, double amplitude, int n, const float* px, const float* py,
                 const gpl_grid* grid, int nrhs, int prec, bool zero_rhs, void* ws, size_t ws_bytes,
                 hipStream_t stream, const float* V = nullptr, int ldv = 0, const PlanSide* side = nullptr);
-int mvm_run(const MvmCtx& m, int nrhs, const float* V, int ldv, float* Y, int ldy, float beta, CgGate gate,
-            hipStream_t stream);
-// The product from RHS buffers already written (by the fused PSF adjoint).
+// The product from RHS buffers already written (by mvm_prepare or the fused PSF adjoint).
 // tail_ok: see mfma_product (not for iterations whose bits are to stay).
 int mvm_run_prepared(const MvmCtx& m, int nrhs, float* Y, int ldy, float beta, CgGate gate, hipStream_t stream,
                      bool tail_ok = false);

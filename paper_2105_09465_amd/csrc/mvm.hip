@@ -55,7 +55,7 @@ int mvm_prepare(MvmCtx& m, double lengthscale, double amplitude, int n, const fl
   bool placed;
   GPL_TRY(plan_build(m.plan, n, px, py, grid, m.s2, plan_threshold(prec), plan_lo_threshold(prec), stream,
                      V ? &job : nullptr, &placed, side));
-  return V && !placed ? mfma_prep_rhs(m.plan, m.bufs, prec, nrhs, V, ldv, CgGate{}, stream) : GPL_OK;
+  return V && !placed ? mfma_prep_rhs(m.plan, m.bufs, prec, nrhs, V, ldv, stream) : GPL_OK;
 }
 
 int mvm_run_prepared(const MvmCtx& m, int nrhs, float* Y, int ldy, float beta, CgGate gate, hipStream_t stream,
@@ -67,13 +67,6 @@ int mvm_run_prepared(const MvmCtx& m, int nrhs, float* Y, int ldy, float beta, C
 int mvm_run_partials(const MvmCtx& m, int nrhs, CgGate gate, hipStream_t stream) {
   GPL_REQUIRE(nrhs <= m.nrhs_max, "product prepared for %d columns, %d given", m.nrhs_max, nrhs);
   return mfma_partials(m.plan, m.bufs, m.prec, m.s2, nrhs, false, gate, stream);
-}
-
-int mvm_run(const MvmCtx& m, int nrhs, const float* V, int ldv, float* Y, int ldy, float beta, CgGate gate,
-            hipStream_t stream) {
-  GPL_REQUIRE(nrhs <= m.nrhs_max, "product prepared for %d columns, %d given", m.nrhs_max, nrhs);
-  GPL_TRY(mfma_prep_rhs(m.plan, m.bufs, m.prec, nrhs, V, ldv, gate, stream));
-  return mvm_run_prepared(m, nrhs, Y, ldy, beta, gate, stream);
 }
 
 int mvm_launch(double lengthscale, double amplitude, int n, const float* px, const float* py, const gpl_grid* grid,

@@ -54,15 +54,13 @@ static_assert(kWaves == kPlanWaves, "the plan orders workgroups of kPlanWaves wa
 
 // ---------------------------------------------------------------- RHS preparation
 
-__global__ __launch_bounds__(256) void colmax_kernel(RhsJob J, CgGate gate) {
+__global__ __launch_bounds__(256) void colmax_kernel(RhsJob J) {
   __shared__ float red[4];
-  if (gate.skip_all()) return;
   colmax_unit(J, blockIdx.y * kColmaxBlocks + blockIdx.x, threadIdx.x, red);
 }
 
-__global__ __launch_bounds__(256) void place_rhs_kernel(RhsJob J, CgGate gate) {
+__global__ __launch_bounds__(256) void place_rhs_kernel(RhsJob J) {
   __shared__ int se[kPlaceSlots];
-  if (gate.skip_all()) return;
   place_unit(J, blockIdx.x, blockIdx.y * kPlaceSlots, threadIdx.x, se);
 }
 
@@ -70,9 +68,8 @@ __global__ __launch_bounds__(256) void place_rhs_kernel(RhsJob J, CgGate gate) {
 // formed by every workgroup that needs it): a launch less where launches are
 // what counts.
 constexpr int kSmallRhs = 4096;
-__global__ __launch_bounds__(1024) void small_rhs_kernel(RhsJob J, CgGate gate) {
+__global__ __launch_bounds__(1024) void small_rhs_kernel(RhsJob J) {
   __shared__ float red[16];
-  if (gate.skip_all()) return;
   bool packed;
   const int slot = blockIdx.x, c = slot_column(slot, J.nrhs, packed);
   float m = 0.f;
@@ -606,19 +603,19 @@ int mfma_zero_rhs(const ProdBufs& b, int prec, hipStream_t stream) {
   return zero_words(b.Vp, elems, stream);
 }
 
-int mfma_prep_rhs(const TilePlan& P, const ProdBufs& b, int prec, int nrhs, const float* V, int ldv, CgGate gate,
+int mfma_prep_rhs(const TilePlan& P, const ProdBufs& b, int prec, int nrhs, const float* V, int ldv,
                   hipStream_t stream) {
   const RhsJob J{P.n, nrhs, ldv, prec == GPL_PREC_F16X3, V, P.perm, b};
   if (J.f16 && J.n <= kSmallRhs) {
-    hipLaunchKernelGGL(small_rhs_kernel, dim3(b.ncp), dim3(1024), 0, stream, J, gate);
+    hipLaunchKernelGGL(small_rhs_kernel, dim3(b.ncp), dim3(1024), 0, stream, J);
     GPL_LAUNCH_CHECK();
     return GPL_OK;
   }
   if (J.f16) {
-    hipLaunchKernelGGL(colmax_kernel, dim3(kColmaxBlocks, nrhs), dim3(256), 0, stream, J, gate);
+    hipLaunchKernelGGL(colmax_kernel, dim3(kColmaxBlocks, nrhs), dim3(256), 0, stream, J);
     GPL_LAUNCH_CHECK();
   }
-  hipLaunchKernelGGL(place_rhs_kernel, dim3(cdiv(b.ldh, 256), b.ncp / kPlaceSlots), dim3(256), 0, stream, J, gate);
+  hipLaunchKernelGGL(place_rhs_kernel, dim3(cdiv(b.ldh, 256), b.ncp / kPlaceSlots), dim3(256), 0, stream, J);
   GPL_LAUNCH_CHECK();
   return GPL_OK;
 }

@@ -18,7 +18,7 @@ int mfma_carve(const TilePlan& P, int prec, int nrhs, void* ws, size_t ws_bytes,
 // Zero the RHS buffers (padding rows and columns must stay zero).
 int mfma_zero_rhs(const ProdBufs& b, int prec, hipStream_t stream);
 // RHS block V (caller order) into the product buffers (sorted order, split or packed).
-int mfma_prep_rhs(const TilePlan& P, const ProdBufs& b, int prec, int nrhs, const float* V, int ldv, CgGate gate,
+int mfma_prep_rhs(const TilePlan& P, const ProdBufs& b, int prec, int nrhs, const float* V, int ldv,
                   hipStream_t stream);
 // The partial rows of the product alone, in b.part over the plan's slots.
 int mfma_partials(const TilePlan& P, const ProdBufs& b, int prec, float s2, int nrhs, bool tail_ok, CgGate gate,

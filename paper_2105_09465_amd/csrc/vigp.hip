@@ -183,7 +183,7 @@ __global__ __launch_bounds__(256) void vigp_sums_kernel(VSeg seg, double* sums) 
 }
 
 struct VSample {
-  int nl, sp, ne, ngq;
+  int sp, ne, ngq;
   int e[kVMaxLayers], n[kVMaxLayers];  // noise offset and size of each layer
   const float *m[kVMaxLayers], *logs[kVMaxLayers], *cross;
 };
@@ -468,7 +468,6 @@ extern "C" int gpl_vigp_elbo(const gpl_vigp_model* model, const gpl_grid* grid, 
   // ---- samples
   const float* y[kVMaxLayers];
   VSample smp{};
-  smp.nl = L.nl;
   smp.sp = L.sp;
   smp.ne = (int)L.ne32;
   smp.ngq = L.nip > 0 ? 2 * N : 0;
