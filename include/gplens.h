@@ -196,8 +196,9 @@ int gpl_gauss_product(const gpl_gauss* g, int nt, const float* tx, const float* 
 /* The same product with a workspace, which large products use to sort both sides
  * along a Hilbert curve and leave out the pairs whose Gaussian is exactly zero
  * in FP32 (the result equals the all-pairs product up to FP32 summation order).
- * gpl_gauss_product_workspace is 0 where no product of that size is sorted; with
- * ws = NULL this is gpl_gauss_product. */
+ * gpl_gauss_product_workspace serves shapes on neither, one and both sides (the
+ * last are sorted first) and is 0 where none of them is; a product that all pairs
+ * serve better leaves it unused. With ws = NULL this is gpl_gauss_product. */
 size_t gpl_gauss_product_workspace(int nt, int ns, int nrhs);
 int gpl_gauss_product_ws(const gpl_gauss* g, int nt, const float* tx, const float* ty, const float* tz,
                          const float* tw, int ns, const float* sx, const float* sy, const float* sz, const float* sw,

@@ -8,13 +8,18 @@
 // cg_update1/2_kernel, psf_adjoint_rhs_kernel), so the iterates have the same bits on
 // either route: the taps of a composite filter in order, those outside the grid left
 // out (they add exact zeros there), and the FP64 sums over the same threads of the
-// same tiles and spans.
+// same tiles and spans. (The batch of the serving loop runs the separate kernels; a test
+// there asks for the same image bit for bit.)
 //
 // Bound by latency: six launches of some 4.5 us each do a microsecond's work apiece
 // on up to 64 x 64 pixels. An iteration on 31 x 31 pixels and 4 columns takes 15.9 us
 // instead of 30.9, 33 x 33 and 17 columns 20.2 for 32.2, 64 x 64 and 17 columns 30.6 for
 // 35.4. Beyond 4,096 fine points the column's one compute unit is the slower way (48 x 48
-// pixels twice supersampled, nine points a thread: 50.8 for 37.6).
+// pixels twice supersampled, nine points a thread: 50.8 for 37.6). Its LDS leaves room for
+// one workgroup on a compute unit, so more than 256 columns run in rounds: still no slower
+// (a solve of 12 iterations, us for the separate kernels': 32 x 32 pixels 291 for 504 with 17
+// columns, 594 for 836 with 256, 727 for 889 with 257, 1,965 for 2,087 with 1,024; 64 x 64
+// 434 for 540, 921 for 1,129 and 1,180 for 1,223 with 17, 256 and 257).
 #include <algorithm>
 #include <cmath>
 

@@ -42,9 +42,9 @@ __host__ __device__ inline int wave_steps(int n, int waves = kGWaves) { return c
 // per point; kMode 0 (shapes on both sides, the windowed kernel) forms them per
 // pair. NC: right-hand-side columns held per pass (1 or kGCols).
 template <int kMode, int NC, int kWaves>
-__global__ __launch_bounds__(kGRows * kWaves) void gauss_product_kernel(GSide T, GSide S, float base, float norm, int nc,
-                                                                  const float* __restrict__ V, int ldv, float* Y,
-                                                                  int ldy, float beta) {
+__global__ __launch_bounds__(kGRows * kWaves) void gauss_product_kernel(GSide T, GSide S, float base, float norm,
+                                                                        int nc, const float* __restrict__ V, int ldv,
+                                                                        float* Y, int ldy, float beta) {
   // per source: x, y, then (kMode 0) zxx, zxy, zyy and w, or (kMode 2) the
   // inverse ixx, ixy, iyy and w |C|^{-1/2}, or (kMode 1) w
   __shared__ float sx[kWaves][64], sy[kWaves][64], sa[kWaves][64], sb[kWaves][64], sc[kWaves][64],
@@ -420,7 +420,8 @@ extern "C" int gpl_gauss_product(const gpl_gauss* g, int nt, const float* tx, co
                                  const float* tw, int ns, const float* sx, const float* sy, const float* sz,
                                  const float* sw, int nrhs, const float* V, int ldv, float* Y, int ldy, float beta,
                                  hipStream_t stream) {
-  return gpl_gauss_product_ws(g, nt, tx, ty, tz, tw, ns, sx, sy, sz, sw, nrhs, V, ldv, Y, ldy, beta, nullptr, 0, stream);
+  return gpl_gauss_product_ws(g, nt, tx, ty, tz, tw, ns, sx, sy, sz, sw, nrhs, V, ldv, Y, ldy, beta, nullptr, 0,
+                              stream);
 }
 
 extern "C" int gpl_gauss_matrix(const gpl_gauss* g, int nt, const float* tx, const float* ty, const float* tz,

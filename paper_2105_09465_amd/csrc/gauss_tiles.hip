@@ -398,7 +398,8 @@ static int tile_slices(const GSorted& T, const GSorted& S) {
   return std::max(1, std::min({32, 4096 / cdiv(T.n, kRowTile), S.nch}));
 }
 
-// Columns a kernel holds for nc columns: nc up to four, and eight.
+// Columns a kernel holds for nc columns: nc up to four, and eight for five to seven (16,384
+// points, shapes of the targets: three columns take 76 us, five 106, eight 107).
 static int held_columns(int nc) { return nc > 4 ? 8 : nc; }
 
 template <class C>

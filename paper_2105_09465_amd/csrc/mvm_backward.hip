@@ -25,13 +25,16 @@
 // a tile of extent E, against terms of l^2 sum |K s|. Up to E^2 s2 = kWideTile = 2^20
 // (E some 1,200 l) that is 2^-33 of the sum, below the terms' own FP32 rounding; a
 // wider tile (a point of its own far away, two clusters that share a tile, a
-// non-finite coordinate, whose box is infinite) adds up the differences.
+// non-finite coordinate, whose box is infinite) adds up the differences. A point's own
+// term and those of its duplicates, which have no difference, leave some 2^-53 E |K s| in
+// the moments: a gradient below that (of a point whose neighbours' K are below 1e-10) is
+// rounding.
 //
 // Bound by VALU issue (six FP32, one exp, one conversion and four FP64
-// instructions a pair) beside 9 MFMAs for 256 pairs at 17 columns: 91 us at 40,000
-// traced points and 17 columns. The previous kernel (s_ij by FMAs from LDS-staged columns, 512-row blocks against 32-point
-// chunks) took 650-730 us for 16 columns of 40,000 points and another 260 us for
-// the seventeenth.
+// instructions a pair) beside 9 MFMAs for 256 pairs at 17 columns: 93 us at 40,000
+// traced points and 17 columns (91 without the look at the tile's box). The previous
+// kernel (s_ij by FMAs from LDS-staged columns, 512-row blocks against 32-point chunks)
+// took 650-730 us for 16 columns of 40,000 points and another 260 us for the seventeenth.
 #include <algorithm>
 #include <cmath>
 
@@ -242,8 +245,7 @@ __global__ __launch_bounds__(256, 3) void mvm_bwd_kernel(const TilePlan T, float
 
 // Sums of every row over its partial slots in order (and, gacc, over the passes);
 // the last pass ends them: gpx[perm[i]] = -(a^2/l^2) sum, added to what is there with
-// `add`, same for y. Per
-// workgroup, part_h = the sums of K s d^2 and K s of its rows.
+// `add`, same for y. Per workgroup, part_h = the sums of K s d^2 and K s of its rows.
 __global__ __launch_bounds__(256) void bwd_rows_kernel(const TilePlan T, const double* __restrict__ part, int first,
                                                        int last, int add, double scale, double* __restrict__ gacc,
                                                        float* gpx, float* gpy, double* __restrict__ part_h) {
@@ -324,8 +326,8 @@ static void carve_bwd(Cv& cv, int n, int npairs, BwdBufs& b) {
 }
 
 template <int S>
-static int launch_bwd(const TilePlan& plan, const BwdBufs& b, float s2, int nc, int c0, const float* A, int lda, const float* Bv, int ldb,
-                      const WChunk& w, hipStream_t stream) {
+static int launch_bwd(const TilePlan& plan, const BwdBufs& b, float s2, int nc, int c0, const float* A, int lda,
+                      const float* Bv, int ldb, const WChunk& w, hipStream_t stream) {
   hipLaunchKernelGGL(bwd_gather_kernel<S>, dim3(cdiv(4 * plan.npad, 256)), dim3(256), 0, stream, plan.n,
                      plan.npad, nc, c0, plan.perm, A, lda, Bv, ldb, w, b.P, b.Q);
   GPL_LAUNCH_CHECK();

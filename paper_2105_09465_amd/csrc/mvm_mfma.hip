@@ -369,7 +369,8 @@ __device__ __forceinline__ void f32_chunk(f32x4 (&acc)[kRT][CB], Tail<TL>& tail,
 #pragma unroll
   for (int l = 0; l < TL; ++l)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) tv[l][h] = *reinterpret_cast<const f32x4*>(vp + (CB * 16 + l) * kChunk + 16 * h + g * 4);
+    for (int h = 0; h < 2; ++h)
+      tv[l][h] = *reinterpret_cast<const f32x4*>(vp + (CB * 16 + l) * kChunk + 16 * h + g * 4);
 #pragma unroll
   for (int rt = 0; rt < kRT; ++rt) {
     if (!((mask >> rt) & 1u)) continue;  // every exp of this 16 x 32 tile is exactly zero
@@ -393,8 +394,9 @@ __device__ __forceinline__ void f32_chunk(f32x4 (&acc)[kRT][CB], Tail<TL>& tail,
 }
 
 template <int CB, int TL, class Skip>
-__device__ __forceinline__ void mvm_f32_wave(Skip&& skip, int w, const TilePlan& P, float s2, const float* __restrict__ Vp,
-                                             int ncp, int ncols, float* __restrict__ part, int pcols, int c0) {
+__device__ __forceinline__ void mvm_f32_wave(Skip&& skip, int w, const TilePlan& P, float s2,
+                                             const float* __restrict__ Vp, int ncp, int ncols,
+                                             float* __restrict__ part, int pcols, int c0) {
   const int lane = threadIdx.x & 63, ri = lane & 15, g = lane >> 4;
   Tail<TL> tail;
   wave_product<CB, false>(
@@ -626,8 +628,10 @@ int mfma_partials(const TilePlan& P, const ProdBufs& b, int prec, float s2, int 
   // A last block of at most four columns of the FP32 form goes to the vector units
   // beside the blocks before it: a block keeps the matrix units busy for as long as the
   // kernel values do the vector units, whatever it holds (40,000 points, 17 columns: two
-  // blocks 70 us, one and a column 54). Its sums
-  // run in another order, so the caller says whether it may.
+  // blocks 70 us, one and a column 54; a whole product of 17 to 20 columns 116 to 123 us,
+  // of 21 as two blocks 137; of 36 as two and four columns 153, of 52 as three and four 201,
+  // where four blocks, 64 columns, take 200 and the line lies). Its sums run in another
+  // order, so the caller says whether it may.
   const int left = nrhs % 16, tail = tail_ok && !f16 && nrhs > 16 && left <= 4 ? left : 0;
   const int nb = cdiv(nrhs - tail, 16);  // blocks on the matrix cores
   // column blocks of up to 64 columns per pass; each pass writes its own columns

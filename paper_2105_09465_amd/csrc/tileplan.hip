@@ -322,8 +322,9 @@ struct ScatterLds {
   uint4 wcnt[kSortDigits];
 };
 template <bool kLast>
-__device__ __forceinline__ void sort_scatter_body(ScatterLds& L, int nb, int n, int span, int pass, const uint32_t* __restrict__ kin,
-                                                  const int* __restrict__ vin, const SortCount* __restrict__ hist,
+__device__ __forceinline__ void sort_scatter_body(ScatterLds& L, int nb, int n, int span, int pass,
+                                                  const uint32_t* __restrict__ kin, const int* __restrict__ vin,
+                                                  const SortCount* __restrict__ hist,
                                                   uint32_t* __restrict__ kout, int* __restrict__ vout,
                                                   const float* __restrict__ px, const float* __restrict__ py,
                                                   int* __restrict__ irank, float* __restrict__ xs,
@@ -1104,8 +1105,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter_side_kernel(int n, 
                                                                          int* vout, SmallSort side) {
   __shared__ SmallLds lds;
   if (blockIdx.x + 1 == gridDim.x) sort_small(lds, side);
-  else sort_scatter_body<false>(lds.rank, gridDim.x - 1, n, span, 0, kin, nullptr, hist, kout, vout, nullptr, nullptr, nullptr,
-                                nullptr, nullptr);
+  else sort_scatter_body<false>(lds.rank, gridDim.x - 1, n, span, 0, kin, nullptr, hist, kout, vout, nullptr, nullptr,
+                                nullptr, nullptr, nullptr);
 }
 
 // Compute units of the current device (queried once per device).
@@ -1228,8 +1229,9 @@ int plan_build(TilePlan& p, int n, const float* px, const float* py, const gpl_g
     GPL_LAUNCH_CHECK();
     if (job)
       hipLaunchKernelGGL(plan_finish_rhs_kernel,
-                         dim3(1 + round_up(cdiv(job->b.ldh, 1024), kXcds) * (job->b.ncp / kPlaceSlots)), dim3(1024), 0, stream, p.nrt, p.nw, p.unit_off, p.count, p.wunit,
-                         reinterpret_cast<int2*>(p.wrow), p.rslot, p.wdesc, p.wrest, *job);
+                         dim3(1 + round_up(cdiv(job->b.ldh, 1024), kXcds) * (job->b.ncp / kPlaceSlots)), dim3(1024), 0,
+                         stream, p.nrt, p.nw, p.unit_off, p.count, p.wunit, reinterpret_cast<int2*>(p.wrow), p.rslot,
+                         p.wdesc, p.wrest, *job);
     else
       hipLaunchKernelGGL(plan_finish_kernel, dim3(1), dim3(1024), 0, stream, p.nrt, p.nw, p.unit_off, p.count, p.wunit,
                          reinterpret_cast<int2*>(p.wrow), p.rslot, p.wdesc, p.wrest);

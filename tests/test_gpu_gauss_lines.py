@@ -13,7 +13,8 @@ torch = pytest.importorskip("torch")
 @pytest.mark.parametrize("tshape,sshape", [(False, False), (True, False), (False, True), (True, True)])
 @pytest.mark.parametrize("nt,ns,cols", [
     (20011, 20011, 1), (13001, 16385, 3), (16385, 8193, 2), (100003, 4097, 9),  # sorted with any shapes or with both
-    (16384, 512, 3), (16384, 513, 3), (16385, 1024, 2), (40960, 700, 1), (40961, 700, 1), (70, 2561, 8), (33, 17000, 1)])
+    (16384, 512, 3), (16384, 513, 3), (16385, 1024, 2), (40960, 700, 1), (40961, 700, 1), (70, 2561, 8),
+    (33, 17000, 1)])
 def test_lines(tshape, sshape, nt, ns, cols):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
