@@ -21,8 +21,6 @@
 namespace gpl {
 
 constexpr int kGRows = 64;   // targets per workgroup (one per lane)
-constexpr int kGWaves = 16;  // waves per workgroup of the adjoint, each over its own share of the points
-constexpr int kGThreads = kGRows * kGWaves;
 constexpr int kGCols = 8;    // right-hand-side columns per pass
 
 // |C|^{-1/2} exp(-d^T C^{-1} d / 2) for the 2 x 2 covariance (cxx, cxy; cxy, cyy).
@@ -35,7 +33,16 @@ __device__ inline float gauss_pair(float dx, float dy, float cxx, float cxy, flo
 // 64-point steps of each wave's share of n points: every wave runs the same
 // number of steps (so the workgroup barriers are uniform); steps past the end
 // are empty.
-__host__ __device__ inline int wave_steps(int n, int waves = kGWaves) { return cdiv(cdiv(n, 64), waves); }
+__host__ __device__ inline int wave_steps(int n, int waves) { return cdiv(cdiv(n, 64), waves); }
+
+// Waves of the workgroups of `own` points that sum over `over` others. A single round of
+// workgroups leaves the waves of a workgroup as the parallelism there is, so 16 of them
+// where they run their steps in so many fewer that it pays, a step of 16 taking `longer`
+// times as long as one of 8. Further rounds (own > most) keep the chip busy with 8, which
+// leave room for more workgroups on a compute unit.
+static bool sixteen_waves(int own, int over, int most, double longer) {
+  return own <= most && wave_steps(over, 16) * longer <= wave_steps(over, 8);
+}
 
 // Shapes on at most one side (kMode 1: targets, or none; kMode 2: sources)
 // make C_ij a per-point constant whose inverse and determinant are formed once
@@ -157,14 +164,15 @@ __global__ void pixel_shapes_kernel(int M, const float* __restrict__ px, const f
 // as the symmetric matrix gradient (xx, xy, yy entries); the source pass
 // accumulates gsx/gsy += dF/ds_j and gsw += dF/dws_j. Sources without shapes
 // only (their shape gradient is not formed).
-template <bool kShapes>
-__global__ __launch_bounds__(kGThreads) void gauss_backward_target_kernel(GSide T, GSide S, float base, float norm,
-                                                                          const float* __restrict__ V,
-                                                                          const float* __restrict__ U, float* gtx,
-                                                                          float* gty, float* gtz) {
+template <bool kShapes, int kWaves>
+__global__ __launch_bounds__(kGRows * kWaves) void gauss_backward_target_kernel(GSide T, GSide S, float base,
+                                                                                float norm,
+                                                                                const float* __restrict__ V,
+                                                                                const float* __restrict__ U,
+                                                                                float* gtx, float* gty, float* gtz) {
   constexpr int kAcc = kShapes ? 6 : 2;
-  __shared__ float sx[kGWaves][64], sy[kGWaves][64], swv[kGWaves][64];
-  __shared__ float red[kGWaves - 1][kAcc][64];
+  __shared__ float sx[kWaves][64], sy[kWaves][64], swv[kWaves][64];
+  __shared__ float red[kWaves - 1][kAcc][64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int i = blockIdx.x * kGRows + lane;
   const bool live = i < T.n;
@@ -178,7 +186,7 @@ __global__ __launch_bounds__(kGThreads) void gauss_backward_target_kernel(GSide 
   float acc[kAcc];  // ax, ay, then (shapes) sum g, zxx, zxy, zyy
 #pragma unroll
   for (int a = 0; a < kAcc; ++a) acc[a] = 0.f;
-  const int steps = wave_steps(S.n);
+  const int steps = wave_steps(S.n, kWaves);
   for (int st = 0; st < steps; ++st) {
     const int j0 = (wv * steps + st) * 64;
     __syncthreads();
@@ -209,7 +217,7 @@ __global__ __launch_bounds__(kGThreads) void gauss_backward_target_kernel(GSide 
     for (int a = 0; a < kAcc; ++a) red[wv - 1][a][lane] = acc[a];
   __syncthreads();
   if (wv > 0 || !live) return;
-  for (int w = 0; w < kGWaves - 1; ++w)
+  for (int w = 0; w < kWaves - 1; ++w)
 #pragma unroll
     for (int a = 0; a < kAcc; ++a) acc[a] += red[w][a][lane];
   const float c = norm * (T.w ? T.w[i] : 1.f) * U[i] * rdet;
@@ -223,21 +231,23 @@ __global__ __launch_bounds__(kGThreads) void gauss_backward_target_kernel(GSide 
   }
 }
 
-__global__ __launch_bounds__(kGThreads) void gauss_backward_source_kernel(GSide T, GSide S, float base, float norm,
-                                                                          const float* __restrict__ V,
-                                                                          const float* __restrict__ U, float* gsx,
-                                                                          float* gsy, float* gsw) {
+template <int kWaves>
+__global__ __launch_bounds__(kGRows * kWaves) void gauss_backward_source_kernel(GSide T, GSide S, float base,
+                                                                                float norm,
+                                                                                const float* __restrict__ V,
+                                                                                const float* __restrict__ U,
+                                                                                float* gsx, float* gsy, float* gsw) {
   // per target: position, the inverse of C_i = Zt_i + base I, and wt_i U_i |C_i|^{-1/2}
-  __shared__ float tx[kGWaves][64], ty[kGWaves][64], ta[kGWaves][64], tb[kGWaves][64], tcc[kGWaves][64],
-      tc[kGWaves][64];
-  __shared__ float red[kGWaves - 1][3][64];
+  __shared__ float tx[kWaves][64], ty[kWaves][64], ta[kWaves][64], tb[kWaves][64], tcc[kWaves][64],
+      tc[kWaves][64];
+  __shared__ float red[kWaves - 1][3][64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int j = blockIdx.x * kGRows + lane;
   const bool live = j < S.n;
   const float xj = live ? S.x[j] : 0.f, yj = live ? S.y[j] : 0.f;
   const float kq = -0.5f * 1.4426950408889634f;
   float ax = 0.f, ay = 0.f, aw = 0.f;
-  const int steps = wave_steps(T.n);
+  const int steps = wave_steps(T.n, kWaves);
   for (int st = 0; st < steps; ++st) {
     const int i0 = (wv * steps + st) * 64;
     __syncthreads();
@@ -271,7 +281,7 @@ __global__ __launch_bounds__(kGThreads) void gauss_backward_source_kernel(GSide 
   }
   __syncthreads();
   if (wv > 0 || !live) return;
-  for (int w = 0; w < kGWaves - 1; ++w) {
+  for (int w = 0; w < kWaves - 1; ++w) {
     ax += red[w][0][lane];
     ay += red[w][1][lane];
     aw += red[w][2][lane];
@@ -311,22 +321,29 @@ __global__ void pixel_axes_gather_kernel(int M, const float* __restrict__ gab, f
   gpy[m] += s.y;
 }
 
+// The adjoint's step of 16 waves takes up to 1.85 times as long as one of 8 (the targets'
+// pass with shapes, us with 8 and 16: 16,384 targets and 4,096 sources 37.8 and 35.5, 2,500
+// sources 25.2 and 27.1; 40,000 and 2,500 58 and 73, 100,000 and 256 18 and 38; without
+// shapes 40,000 and 1,600 35 and 31).
 int gauss_backward_launch(const GSide& T, const GSide& S, double base_var, double norm, const float* V, const float* U,
                           float* gtx, float* gty, float* gtz, float* gsx, float* gsy, float* gsw, hipStream_t stream) {
   GPL_REQUIRE(S.z == nullptr, "the adjoint supports sources without shape covariances");
   if (T.n == 0 || S.n == 0) return GPL_OK;
+  const auto wide = [](int own, int over, int most) { return sixteen_waves(own, over, most, 1.85); };
+  const auto threads = [](bool w) { return dim3(kGRows * (w ? 16 : 8)); };
   if (gtx) {
-    if (gtz)
-      hipLaunchKernelGGL(gauss_backward_target_kernel<true>, dim3(cdiv(T.n, kGRows)), dim3(kGThreads), 0, stream, T, S,
-                         (float)base_var, (float)norm, V, U, gtx, gty, gtz);
-    else
-      hipLaunchKernelGGL(gauss_backward_target_kernel<false>, dim3(cdiv(T.n, kGRows)), dim3(kGThreads), 0, stream, T,
-                         S, (float)base_var, (float)norm, V, U, gtx, gty, gtz);
+    const bool w = wide(T.n, S.n, gtz ? 16384 : 40960);
+    const auto kern = gtz ? (w ? gauss_backward_target_kernel<true, 16> : gauss_backward_target_kernel<true, 8>)
+                          : (w ? gauss_backward_target_kernel<false, 16> : gauss_backward_target_kernel<false, 8>);
+    hipLaunchKernelGGL(kern, dim3(cdiv(T.n, kGRows)), threads(w), 0, stream, T, S, (float)base_var, (float)norm, V, U,
+                       gtx, gty, gtz);
     GPL_LAUNCH_CHECK();
   }
   if (gsx || gsw) {
-    hipLaunchKernelGGL(gauss_backward_source_kernel, dim3(cdiv(S.n, kGRows)), dim3(kGThreads), 0, stream, T, S,
-                       (float)base_var, (float)norm, V, U, gsx, gsy, gsw);
+    const bool w = wide(S.n, T.n, 40960);
+    hipLaunchKernelGGL(w ? gauss_backward_source_kernel<16> : gauss_backward_source_kernel<8>,
+                       dim3(cdiv(S.n, kGRows)), threads(w), 0, stream, T, S, (float)base_var, (float)norm, V, U, gsx,
+                       gsy, gsw);
     GPL_LAUNCH_CHECK();
   }
   return GPL_OK;
@@ -342,20 +359,16 @@ int pixel_shapes_backward_launch(int M, const float* px, const float* py, const 
   return GPL_OK;
 }
 
-// Waves of a product's workgroups. A single round of workgroups leaves the waves of a
-// workgroup as the parallelism there is, so 16 of them where they run their steps of 64
-// sources in so many fewer that it pays: a step of 16 takes 1.65 times as long as one of 8,
-// with shapes of the sources and many columns 1.76, on both sides 1.88 (16,384 targets,
-// one column, shapes of the targets, us with 8 and 16: 1,024 sources 10.0 and 9.6, 2,500
-// 20.3 and 18.9, 10,000 70 and 57; three columns, shapes on both sides: 256 sources 11.8
-// and 13.6, 2,500 59 and 63, 10,000 215 and 203). Further rounds keep the chip busy with 8
-// waves, which leave room for more workgroups on a compute unit (three for one of 16 with
-// many columns): 40,000 targets and 2,500 sources 65 and 79 us with three columns. With
+// A product's step of 16 waves takes 1.65 times as long as one of 8, with shapes of the
+// sources and many columns 1.76, on both sides 1.88 (16,384 targets, one column, shapes of
+// the targets, us with 8 and 16: 1,024 sources 10.0 and 9.6, 2,500 20.3 and 18.9, 10,000 70
+// and 57; three columns, shapes on both sides: 256 sources 11.8 and 13.6, 2,500 59 and 63,
+// 10,000 215 and 203). With many columns 8 waves leave room for three workgroups on a
+// compute unit, 16 for one: 40,000 targets and 2,500 sources 65 and 79 us with three. With
 // one column 16 are as good up to 40,960 targets (4,096 sources 64 and 59), and 400,000
 // targets and 256 sources take 37 and 53.
-static bool sixteen_waves(int mode, int nt, int ns, bool many) {
-  const double longer = !many || mode == 1 ? 1.65 : mode == 2 ? 1.76 : 1.88;
-  return nt <= (many ? 16384 : 40960) && wave_steps(ns, 16) * longer <= wave_steps(ns, 8);
+static bool product_waves(int mode, int nt, int ns, bool many) {
+  return sixteen_waves(nt, ns, many ? 16384 : 40960, !many || mode == 1 ? 1.65 : mode == 2 ? 1.76 : 1.88);
 }
 
 template <int kMode, int NC>
@@ -371,7 +384,7 @@ int gauss_product_launch(const GSide& T, const GSide& S, double base_var, double
   const int mode = S.z == nullptr ? 1 : (T.z == nullptr ? 2 : 0);
   for (int c0 = 0; c0 < nrhs; c0 += kGCols) {
     const int nc = std::min(kGCols, nrhs - c0);
-    const bool wide = sixteen_waves(mode, T.n, S.n, nc > 1);
+    const bool wide = product_waves(mode, T.n, S.n, nc > 1);
     const float b = (float)base_var, nm = (float)norm;
     const auto launch =
         nc == 1 ? (mode == 0 ? launch_product<0, 1> : mode == 1 ? launch_product<1, 1> : launch_product<2, 1>)
